@@ -1,0 +1,791 @@
+// Newton step and dual scan of the GRU at n = 16, 32 and 64 in fp32: chunks of the sequence are reduced to one affine map
+// each, the maps are folded, and sixteen chunks per wavefront are then walked side by side (Sec. 3.1 eq. 3 and 5, Sec. 3.1.1
+// eq. 7, Sec. 3.3 eq. 10).
+//
+// A sequence is cut into chunks of Lc positions, sixteen consecutive chunks form a group.
+//   1. chunk_totals_kernel: every chunk's map x -> M x + v (the composition of its pairs).  The only part that multiplies
+//      matrices by matrices; a wavefront streams through its positions with one running product in registers.  The maps
+//      of a group are then composed into the group's map.
+//   2. chunk_walk_kernel: a wavefront owns one group.  It folds the maps of the groups in front of it into the group's
+//      carry and the maps of its own chunks into sixteen carries, which are the columns of a 16 x 16 matrix-core tile; the
+//      sixteen chunks are then walked position by position, every step being a product of a constant weight matrix with
+//      the sixteen column vectors (J is never formed: J e = z e + p_z (U_z e) + s_r (U_c e) + s_t (U_r e)).
+// Nothing in a launch waits for another workgroup, the number of wavefronts does not depend on the length (the chunk does),
+// and the state that travels between the two launches is one map per chunk.
+//
+// Bound: issue.  The fp32 matrix instructions (32 cycles each) and the vector ALU of a SIMD do not overlap, so a position of
+// the reduction costs 32 x 32 + 72 x 4 cycles at n = 32 (4 x 32 + 20 x 4 at n = 16) beside its share of the gates; the tree over
+// wavefronts, the look-back and the second walk of the single-pass scan (a third of its tile's life at n = 32, with one to
+// four of eight wavefronts busy) are gone.  A Newton step, single-pass scan before / both launches now: n = 32, d = 8, 16 x 100,000
+// positions 2,650 / 1,400 us (1,090 + 300); n = 16, d = 6, 32 x 17,984 positions 240 / 130 us (88 + 42); the dual scan there 206 / 135.
+//
+// Everything is in correction form: with e = y_new - y the recurrence of a Newton step is e_i = J_i e_{i-1} + (f_i - y_i),
+// e_0 = 0, so neither J h nor a right-hand side is needed and rounding is relative to the correction.
+//
+// Matrix-core layout (16x16x4, lane (g = lane / 16, r = lane % 16)): operand A supplies A[r][4g + v] and operand B
+// B[4g + v][r] in the v-th of four instructions of a 16-wide contraction, the accumulator holds D[4g + v][r] in register v.  So an
+// accumulator is a valid B operand, four consecutive scalars of a row-major matrix are an A operand, and an accumulator of
+// X is the A operand of its transpose.
+#include "deer_common.h"
+
+namespace deer {
+
+namespace {
+
+using Acc = float __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ Acc mfma(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ Acc zero4() { return Acc{0.f, 0.f, 0.f, 0.f}; }
+
+__device__ __forceinline__ Acc load4(const float* __restrict__ p) { return *reinterpret_cast<const Acc*>(p); }
+
+__device__ __forceinline__ void store4(float* p, Acc v) { *reinterpret_cast<Acc*>(p) = v; }
+
+// sum over the four lane groups (lanes r, r + 16, r + 32, r + 48), in every lane
+__device__ __forceinline__ float sum_groups(float x) {
+    unsigned u = __float_as_uint(x);
+    const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const float s = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    u = __float_as_uint(s);
+    const auto w = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+// Four sums over the 16 lanes of a row, all four in every lane.  Lanes trade the values they do not keep (with the neighbour,
+// then with the other pair of the quad), two rotations add the quads, the quad then hands its four totals round.
+__device__ __forceinline__ Acc row_sums4(Acc q, int r) {
+    const bool odd = r & 1, upper = r & 2;
+    const float u0 = (odd ? q[1] : q[0]) + dpp<0xB1>(odd ? q[0] : q[1]);   // quad_perm 1,0,3,2
+    const float u1 = (odd ? q[3] : q[2]) + dpp<0xB1>(odd ? q[2] : q[3]);
+    float w = (upper ? u1 : u0) + dpp<0x4E>(upper ? u0 : u1);              // quad_perm 2,3,0,1
+    w += dpp<0x124>(w);                                                    // row_ror 4
+    w += dpp<0x128>(w);                                                    // row_ror 8
+    return Acc{dpp<0x00>(w), dpp<0x55>(w), dpp<0xAA>(w), dpp<0xFF>(w)};
+}
+
+// the LDS slice of a wavefront is written and read by its own lanes only: LDS operations of a wavefront complete in order,
+// the fence keeps the compiler from moving them
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+struct GruGates {
+    float f, pz, sr, st, z;
+};
+
+// gates of one row from the pre-activations ar, az, the candidate's input part ac and its hidden part q
+__device__ __forceinline__ GruGates gru_gates(float ar, float az, float ac, float q, float h) {
+    GruGates o;
+    const float rg = feed_sigmoid(ar);
+    o.z = feed_sigmoid(az);
+    const float c = feed_tanh(ac + rg * q);
+    const float zc = 1.0f - o.z;
+    const float dh = h - c;
+    o.f = c + o.z * dh;
+    o.pz = dh * o.z * zc;
+    const float sc = zc * (1.0f - c * c);
+    o.sr = sc * rg;
+    o.st = o.sr * q * (1.0f - rg);
+    return o;
+}
+
+// weights in LDS: rows of [U_gate | W_gate], W in the order the input operand takes its columns (step s of lane group g:
+// column DS g + s), zero beyond d; then the four bias vectors
+template <int N, int DS>
+struct Weights {
+    static constexpr int LD = N + 4 * DS + 4;
+    float row[3][N][LD];
+    float bias[4][N];
+};
+
+template <int N, int DS, int THREADS>
+__device__ __forceinline__ void fill_weights(Weights<N, DS>& w, const float* __restrict__ th, int d, int tid) {
+    const float* __restrict__ U = th + 3 * N * d;
+    const float* __restrict__ bias = U + 3 * N * N;
+    constexpr int NU = 3 * N * (N / 4), NW = 3 * N * 4 * DS, KU = (NU + THREADS - 1) / THREADS, KW = (NW + THREADS - 1) / THREADS;
+    Acc u[KU];
+    float v[KW];
+    // all requests first
+#pragma unroll
+    for (int k = 0; k < KU; ++k) u[k] = load4(U + 4 * min(tid + k * THREADS, NU - 1));
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+        const int i = min(tid + k * THREADS, NW - 1), c = i % (4 * DS);
+        v[k] = th[(i / (4 * DS)) * d + min(c, d - 1)];
+        v[k] = c < d ? v[k] : 0.f;
+    }
+    const float bv = bias[min(tid, 4 * N - 1)];
+#pragma unroll
+    for (int k = 0; k < KU; ++k) {
+        const int i = tid + k * THREADS, row = i / (N / 4);
+        if (i < NU) store4(&w.row[row / N][row % N][4 * (i % (N / 4))], u[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+        const int i = tid + k * THREADS, row = i / (4 * DS);
+        if (i < NW) w.row[row / N][row % N][N + i % (4 * DS)] = v[k];
+    }
+    static_assert(THREADS >= 4 * N, "one bias entry per thread");
+    if (tid < 4 * N) w.bias[tid / N][tid % N] = bv;
+}
+
+// Four scalars of row `row` of [U | W]: operand A of a product with that row block (lane (g, r): row r), and equally operand
+// B of the transposed product.
+template <int N, int DS>
+__device__ __forceinline__ Acc u_row(const Weights<N, DS>& w, int gate, int row, int K, int g) {
+    return load4(&w.row[gate][row][16 * K + 4 * g]);
+}
+template <int N, int DS>
+__device__ __forceinline__ void w_row(float* o, const Weights<N, DS>& w, int gate, int row, int g) {
+    vload<float, DS>(o, &w.row[gate][row][N + DS * g]);
+}
+
+// Input operand of one position: lane group g takes columns DS g .. DS g + DS - 1 (past d: a valid entry; its weight is zero)
+template <int DS>
+__device__ __forceinline__ void load_x(float* o, const float* __restrict__ xrow, int d, int g) {
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+        const int k = DS * g + s;
+        o[s] = xrow[k < d ? k : d - 1];
+    }
+}
+
+template <int N> constexpr int map_size() { return N * N + N; }
+
+// ------------------------------------------------------------------------------------------------------------------
+// Maps of the chunks.  Forward: the total of a chunk is P = J_L .. J_1, and Q = P^T is built from the last position to the
+// first, Q <- J_i^T Q, because the vector then needs no chain of its own: v = sum over i of (J_L .. J_{i+1}) r_i, four
+// multiply-adds per 16 rows with the running Q.  Dual: the map of the times [a, b) is N = J_{a+1}^T .. J_b^T, and S = N^T =
+// J_b .. J_{a+1} is built from the first to the last, S <- J_i S, with v = sum over j of (J_j .. J_{a+1})^T g_j.  In both
+// the accumulator of the running product is the map in the order of an A operand, so it leaves with 16-byte stores as M
+// row-major.
+// The gates of sixteen positions at a time are matrix products with the positions as columns (dual: as rows, which gives
+// the row factors to the lanes that assemble J instead of its transpose); the row factors reach the assembly through an
+// LDS slice of the wavefront.
+// ------------------------------------------------------------------------------------------------------------------
+template <int N, int DS, bool REV, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES / 4) void chunk_totals_kernel(ChunkParams p) {
+    constexpr int NB = N / 16, MS = map_size<N>(), CPW = 16 / WAVES;   // chunks of a wavefront
+    __shared__ __align__(16) Weights<N, DS> sW;
+    // forward: [kind: p_z, s_r, s_t, z, residual][position][row]; dual: [position][row][p_z, s_r, s_t, z], then [position][row] of g
+    __shared__ __align__(16) float sF[WAVES][5 * 16 * N];
+
+    if (gate_closed<float>(p.gate)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int b = (int)(blockIdx.x % (unsigned)p.B), grp = (int)(blockIdx.x / (unsigned)p.B);
+
+    const int T = p.T, d = p.d, Lc = p.Lc;
+    const int chunks = (T + Lc - 1) / Lc;
+    const float* __restrict__ yb = p.y + (long long)b * T * N;
+    const float* __restrict__ xb = p.x + (long long)b * T * d;
+    const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N : nullptr;
+    const float* __restrict__ gb = REV ? p.g + (long long)b * T * N : nullptr;
+    float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+    float* __restrict__ sFw = sF[wave];
+
+    const int q_lo = CPW * wave, q_hi = min(q_lo + CPW, chunks - 16 * grp);   // chunks of this wavefront (inside the group)
+    const int lo = (16 * grp + q_lo) * Lc;
+    const int hi = min(T, (16 * grp + q_hi) * Lc);
+    const int blocks = (hi - lo + 15) / 16;
+
+    // operands of one block: state in front of each position (16-byte pieces: operand of the products and the rows of
+    // this lane's accumulators), the vector the residual is taken against (forward: the iterate at the position; dual: g), x
+    Acc hB[NB], oB[NB];
+    float xB[DS];
+    auto request = [&](int blk) {
+        int pos = (REV ? lo + 16 * blk : hi - 16 * (blk + 1)) + r;
+        pos = min(max(pos, lo), hi - 1);
+        const float* hp = REV ? yb + (long long)pos * N : (pos > 0 ? yb + (long long)(pos - 1) * N : y0b);
+        const float* op = (REV ? gb : yb) + (long long)pos * N;
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            hB[K] = hp ? load4(hp + 16 * K + 4 * g) : zero4();
+            oB[K] = load4(op + 16 * K + 4 * g);
+        }
+        load_x<DS>(xB, xb + (long long)(REV ? min(pos + 1, T - 1) : pos) * d, d, g);
+    };
+    if (q_lo < q_hi) request(0);
+    fill_weights<N, DS, 64 * WAVES>(sW, p.theta, p.d, tid);
+    __syncthreads();
+
+    // weights of the assembly: ua[gate][X][Y][v] multiplies the factor of J's row
+    //   forward: J[16Y + 4g + v][16X + r] (operand A of J^T);  dual: J[16X + r][16Y + 4g + v] (operand A of J)
+    float ua[3][NB][NB][4];
+#pragma unroll
+    for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+        for (int X = 0; X < NB; ++X)
+#pragma unroll
+            for (int Y = 0; Y < NB; ++Y)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    ua[gate][X][Y][v] = REV ? sW.row[gate][16 * X + r][16 * Y + 4 * g + v] : sW.row[gate][16 * Y + 4 * g + v][16 * X + r];
+    float dsel[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dsel[v] = (4 * g + v == r) ? 1.f : 0.f;
+
+    if (q_lo < q_hi) {
+        Acc Q[NB][NB];
+        float vec[NB];
+        auto reset = [&]() {
+#pragma unroll
+            for (int X = 0; X < NB; ++X) {
+                vec[X] = 0.f;
+#pragma unroll
+                for (int C = 0; C < NB; ++C)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] : 0.f;
+            }
+        };
+        reset();
+
+        int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
+        int edge = REV ? min(T, (16 * grp + q + 1) * Lc) - 1 : (16 * grp + q) * Lc;   // its last position in traversal order
+
+        for (int blk = 0; blk < blocks; ++blk) {
+            const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            // ---- gates of the sixteen positions ----
+            if constexpr (!REV) {
+#pragma unroll
+                for (int I = 0; I < NB; ++I) {
+                    Acc ar = load4(&sW.bias[0][16 * I + 4 * g]), az = load4(&sW.bias[1][16 * I + 4 * g]);
+                    Acc ac = load4(&sW.bias[2][16 * I + 4 * g]), aq = load4(&sW.bias[3][16 * I + 4 * g]);
+#pragma unroll
+                    for (int K = 0; K < NB; ++K) {
+                        const Acc ur = u_row(sW, 0, 16 * I + r, K, g), uz = u_row(sW, 1, 16 * I + r, K, g), uc = u_row(sW, 2, 16 * I + r, K, g);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            ar = mfma(ur[v], hB[K][v], ar);
+                            az = mfma(uz[v], hB[K][v], az);
+                            aq = mfma(uc[v], hB[K][v], aq);
+                        }
+                    }
+                    float wr[DS], wz[DS], wc[DS];
+                    w_row(wr, sW, 0, 16 * I + r, g); w_row(wz, sW, 1, 16 * I + r, g); w_row(wc, sW, 2, 16 * I + r, g);
+#pragma unroll
+                    for (int s = 0; s < DS; ++s) {
+                        ar = mfma(wr[s], xB[s], ar);
+                        az = mfma(wz[s], xB[s], az);
+                        ac = mfma(wc[s], xB[s], ac);
+                    }
+                    Acc fpz, fsr, fst, fz, fr;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const GruGates o = gru_gates(ar[v], az[v], ac[v], aq[v], hB[I][v]);
+                        fpz[v] = o.pz; fsr[v] = o.sr; fst[v] = o.st; fz[v] = o.z; fr[v] = o.f - oB[I][v];
+                    }
+                    float* o = sFw + r * N + 16 * I + 4 * g;
+                    store4(o, fpz); store4(o + 16 * N, fsr); store4(o + 32 * N, fst); store4(o + 48 * N, fz); store4(o + 64 * N, fr);
+                }
+            } else {
+                // the state entries of the rows this lane evaluates (positions 4g + v, row 16 I + r) come through the slice too
+#pragma unroll
+                for (int K = 0; K < NB; ++K) {
+                    store4(sFw + 64 * N + r * N + 16 * K + 4 * g, oB[K]);
+                    store4(sFw + r * N + 16 * K + 4 * g, hB[K]);
+                }
+                wave_lds_fence();
+                float hr[NB][4];
+#pragma unroll
+                for (int I = 0; I < NB; ++I)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) hr[I][v] = sFw[(4 * g + v) * N + 16 * I + r];
+                wave_lds_fence();
+#pragma unroll
+                for (int I = 0; I < NB; ++I) {
+                    const float br = sW.bias[0][16 * I + r], bz = sW.bias[1][16 * I + r], bc = sW.bias[2][16 * I + r], bq = sW.bias[3][16 * I + r];
+                    Acc ar = {br, br, br, br}, az = {bz, bz, bz, bz}, ac = {bc, bc, bc, bc}, aq = {bq, bq, bq, bq};
+#pragma unroll
+                    for (int K = 0; K < NB; ++K) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            ar = mfma(hB[K][v], ua[0][I][K][v], ar);
+                            az = mfma(hB[K][v], ua[1][I][K][v], az);
+                            aq = mfma(hB[K][v], ua[2][I][K][v], aq);
+                        }
+                    }
+                    float wr[DS], wz[DS], wc[DS];
+                    w_row(wr, sW, 0, 16 * I + r, g); w_row(wz, sW, 1, 16 * I + r, g); w_row(wc, sW, 2, 16 * I + r, g);
+#pragma unroll
+                    for (int s = 0; s < DS; ++s) {
+                        ar = mfma(xB[s], wr[s], ar);
+                        az = mfma(xB[s], wz[s], az);
+                        ac = mfma(xB[s], wc[s], ac);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const GruGates o = gru_gates(ar[v], az[v], ac[v], aq[v], hr[I][v]);
+                        store4(sFw + ((4 * g + v) * N + 16 * I + r) * 4, Acc{o.pz, o.sr, o.st, o.z});
+                    }
+                }
+            }
+            wave_lds_fence();
+            if (blk + 1 < blocks) request(blk + 1);
+
+            // ---- the running product takes the positions of the block in one after the other ----
+            const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16;
+#pragma unroll 2
+            for (int k = 0; k < c_hi - c_lo; ++k) {
+                const int c = REV ? c_lo + k : c_hi - 1 - k;
+                float a[NB][NB][4];
+                Acc rv[NB];
+                if constexpr (!REV) {
+#pragma unroll
+                    for (int Y = 0; Y < NB; ++Y) {
+                        const float* o = sFw + c * N + 16 * Y + 4 * g;
+                        const Acc pz = load4(o), sr = load4(o + 16 * N), st = load4(o + 32 * N), z = load4(o + 48 * N);
+                        rv[Y] = load4(o + 64 * N);
+#pragma unroll
+                        for (int X = 0; X < NB; ++X)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                float j = pz[v] * ua[1][X][Y][v] + (sr[v] * ua[2][X][Y][v] + st[v] * ua[0][X][Y][v]);
+                                if (X == Y) j += dsel[v] * z[v];
+                                a[X][Y][v] = j;
+                            }
+                    }
+                } else {
+#pragma unroll
+                    for (int X = 0; X < NB; ++X) {
+                        rv[X] = load4(sFw + 64 * N + c * N + 16 * X + 4 * g);
+                        const Acc ff = load4(sFw + (c * N + 16 * X + r) * 4);
+#pragma unroll
+                        for (int Y = 0; Y < NB; ++Y)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                float j = ff[0] * ua[1][X][Y][v] + (ff[1] * ua[2][X][Y][v] + ff[2] * ua[0][X][Y][v]);
+                                if (X == Y) j += dsel[v] * ff[3];
+                                a[X][Y][v] = j;
+                            }
+                    }
+                }
+#pragma unroll
+                for (int C = 0; C < NB; ++C) {
+                    float s = vec[C];
+#pragma unroll
+                    for (int K = 0; K < NB; ++K)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) s += Q[K][C][v] * rv[K][v];
+                    vec[C] = s;
+                }
+                Acc Qn[NB][NB];
+#pragma unroll
+                for (int X = 0; X < NB; ++X)
+#pragma unroll
+                    for (int C = 0; C < NB; ++C) Qn[X][C] = zero4();
+#pragma unroll
+                for (int K = 0; K < NB; ++K)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int X = 0; X < NB; ++X)
+#pragma unroll
+                            for (int C = 0; C < NB; ++C) Qn[X][C] = mfma(a[X][K][v], Q[K][C][v], Qn[X][C]);
+#pragma unroll
+                for (int X = 0; X < NB; ++X)
+#pragma unroll
+                    for (int C = 0; C < NB; ++C) Q[X][C] = Qn[X][C];
+                if (base + c == edge) {
+                    // the chunk's map: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
+                    float* o = tot + (long long)q * MS;
+#pragma unroll
+                    for (int C = 0; C < NB; ++C) {
+#pragma unroll
+                        for (int X = 0; X < NB; ++X) store4(o + (16 * C + r) * N + 16 * X + 4 * g, Q[X][C]);
+                        const float s = sum_groups(vec[C]);
+                        if (g == 0) o[N * N + 16 * C + r] = s;
+                    }
+                    reset();
+                    q += REV ? 1 : -1;
+                    edge = REV ? min(T, (16 * grp + q + 1) * Lc) - 1 : (16 * grp + q) * Lc;
+                }
+            }
+            wave_lds_fence();
+        }
+    }
+    __syncthreads();
+
+    // ---- the group's map: the maps of its chunks composed in the order they apply (a wavefront per 16 columns, one more
+    // for the vector).  The group nothing follows needs none. ----
+    const bool last = REV ? grp == 0 : grp == p.groups - 1;
+    if (!last && wave <= NB) {
+        const int nq = min(16, chunks - 16 * grp);
+        const bool is_vec = wave == NB;
+        constexpr int PD = N == 16 ? 4 : 2;   // maps requested ahead
+        Acc X[NB], A[PD][NB][NB], V[PD][NB];
+        auto ask = [&](int j, int i) {
+            i = min(i, nq - 1);
+            const float* o = tot + (long long)(REV ? nq - 1 - i : i) * MS;
+#pragma unroll
+            for (int I = 0; I < NB; ++I) {
+                V[j][I] = is_vec ? load4(o + N * N + 16 * I + 4 * g) : zero4();
+#pragma unroll
+                for (int K = 0; K < NB; ++K) A[j][I][K] = load4(o + (16 * I + r) * N + 16 * K + 4 * g);
+            }
+        };
+        const float* m = tot + (long long)(REV ? nq - 1 : 0) * MS;
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            if (is_vec) X[K] = load4(m + N * N + 16 * K + 4 * g);
+            else
+#pragma unroll
+                for (int v = 0; v < 4; ++v) X[K][v] = m[(16 * K + 4 * g + v) * N + 16 * wave + r];
+        }
+#pragma unroll
+        for (int j = 0; j < PD; ++j) ask(j, 1 + j);
+        for (int i0 = 1; i0 < nq; i0 += PD) {
+#pragma unroll
+            for (int j = 0; j < PD; ++j) {
+                if (i0 + j < nq) {
+                    Acc Y[NB];
+#pragma unroll
+                    for (int I = 0; I < NB; ++I) Y[I] = V[j][I];
+#pragma unroll
+                    for (int K = 0; K < NB; ++K)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+#pragma unroll
+                            for (int I = 0; I < NB; ++I) Y[I] = mfma(A[j][I][K][v], X[K][v], Y[I]);
+#pragma unroll
+                    for (int I = 0; I < NB; ++I) X[I] = Y[I];
+                }
+                ask(j, i0 + j + PD);
+            }
+        }
+        float* o = p.sup + ((long long)b * p.groups + grp) * MS;
+#pragma unroll
+        for (int I = 0; I < NB; ++I) {
+            if (is_vec) {
+                if (r == 0) store4(o + N * N + 16 * I + 4 * g, X[I]);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[(16 * I + 4 * g + v) * N + 16 * wave + r] = X[I][v];
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// The walk: one wavefront per group, its sixteen chunks are the columns of every product.
+// ------------------------------------------------------------------------------------------------------------------
+// x <- M x + v over the maps of the groups in front, then over those of the group's own chunks, whose carries are the columns
+// of e.  A chain of small products with a vector: on the vector ALUs, because a matrix instruction would use one of its
+// sixteen columns (512 cycles a step at n = 32 against about 200).  Even steps take x as operand B holds it (16K + 4g + v) and
+// add over the lane groups, which leaves row 16I + r in lane r; odd steps start from there, multiply columns and add
+// over the lanes of a row, which leaves the operand order again: no step moves x between lanes.  The maps are requested PD
+// steps ahead (a step is shorter than a trip to the last-level cache).
+template <int N, bool REV>
+__device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int grp, int nq, int g, int r, Acc (&e)[N / 16]) {
+    constexpr int NB = N / 16, MS = map_size<N>(), PD = N == 16 ? 4 : 2;   // even
+    Acc A[PD][NB][NB], V[PD][NB];
+    Acc xk[NB];      // x[16K + 4g + v]
+    float xr[NB];    // x[16K + r]
+#pragma unroll
+    for (int K = 0; K < NB; ++K) {
+        xk[K] = e[K] = zero4();
+        xr[K] = 0.f;
+    }
+    const int before = REV ? p.groups - 1 - grp : grp, steps = before + nq - 1;
+    const float* __restrict__ sup = p.sup + (long long)b * p.groups * MS;
+    const float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+    auto request = [&](int j, int i) {
+        i = min(i, steps - 1);
+        const int k = i - before;
+        const float* m = i < before ? sup + (long long)(REV ? p.groups - 1 - i : i) * MS : tot + (long long)(REV ? nq - 1 - k : k) * MS;
+#pragma unroll
+        for (int I = 0; I < NB; ++I) {
+            if (j & 1) {
+                V[j][I] = load4(m + N * N + 16 * I + 4 * g);
+#pragma unroll
+                for (int K = 0; K < NB; ++K)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) A[j][I][K][v] = m[(16 * I + 4 * g + v) * N + 16 * K + r];
+            } else {
+                V[j][I][0] = m[N * N + 16 * I + r];
+#pragma unroll
+                for (int K = 0; K < NB; ++K) A[j][I][K] = load4(m + (16 * I + r) * N + 16 * K + 4 * g);
+            }
+        }
+    };
+    // the carry in front of step i belongs to chunk i - before
+    auto select = [&](int i, bool rows) {
+        const int k = i - before, q = REV ? nq - 1 - k : k;
+        if (k < 0) return;
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            Acc c = xk[K];
+            if (rows)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[v] = __shfl(xr[K], 4 * g + v);
+            e[K] = r == q ? c : e[K];
+        }
+    };
+    // in front of the sequence x is zero and M is not looked at (it may have overflowed)
+    auto step = [&](int j, int i) {
+        select(i, j & 1);
+        if (j & 1) {
+#pragma unroll
+            for (int I = 0; I < NB; ++I) {
+                Acc q = zero4();
+#pragma unroll
+                for (int K = 0; K < NB; ++K)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) q[v] += A[j][I][K][v] * xr[K];
+                xk[I] = V[j][I] + row_sums4(q, r);
+            }
+        } else {
+            float y[NB];
+#pragma unroll
+            for (int I = 0; I < NB; ++I) {
+                float q[2] = {0.f, 0.f};
+#pragma unroll
+                for (int K = 0; K < NB; ++K)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) q[v & 1] += A[j][I][K][v] * xk[K][v];
+                y[I] = V[j][I][0] + (i > 0 ? sum_groups(q[0] + q[1]) : 0.f);
+            }
+#pragma unroll
+            for (int I = 0; I < NB; ++I) xr[I] = y[I];
+        }
+    };
+    if (steps > 0) {
+#pragma unroll
+        for (int j = 0; j < PD; ++j) request(j, j);
+        int i = 0;
+        for (; i + PD <= steps; i += PD) {
+#pragma unroll
+            for (int j = 0; j < PD; ++j) {
+                step(j, i + j);
+                request(j, i + j + PD);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < PD - 1; ++j)
+            if (i + j < steps) step(j, i + j);
+    }
+    select(steps, steps & 1);
+}
+
+template <int N, int DS, bool REV>
+__global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkParams p) {
+    constexpr int NB = N / 16;
+    __shared__ unsigned s_max[4];
+    __shared__ __align__(16) float sB[4 * N];
+    if (gate_closed<float>(p.gate)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int T = p.T, d = p.d, Lc = p.Lc;
+    const float* __restrict__ th = p.theta;
+    const float* __restrict__ U = th + 3 * N * d;
+    if (tid < 4 * N) sB[tid] = U[3 * N * N + tid];
+    __syncthreads();
+
+    const unsigned id = blockIdx.x * 4u + (unsigned)wave;
+    const int b = (int)(id % (unsigned)p.B), grp = (int)(id / (unsigned)p.B);
+    unsigned emax = 0u;   // largest |y_new - y| as raw bits (a NaN compares above everything)
+    if (grp < p.groups) {
+        const int chunks = (T + Lc - 1) / Lc, nq = min(16, chunks - 16 * grp);
+        // addresses relative to the group's first position
+        const long long first = (long long)b * T + (long long)16 * grp * Lc;
+        const float* __restrict__ yb = p.y + first * N;
+        const float* __restrict__ xb = p.x + first * d;
+        const float* __restrict__ gb = REV ? p.g + first * N : nullptr;
+        float* __restrict__ ob = p.out + first * N;
+        const int a = r * Lc, end = T - 16 * grp * Lc;   // this column's first position, one past the last that exists
+        auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
+
+        // What step t reads: forward y at the position (the state in front of the next one), dual y and g at the position;
+        // both the input of the cell the step evaluates.  Requested R - 1 steps ahead: a step is shorter than a trip to the last-level
+        // cache.  Slots are named by t mod R, so nothing moves between registers.
+        constexpr int R = (REV && N == 32) ? 2 : 4;
+        Acc yr[R][NB], gr[REV ? R : 1][NB];
+        float xr[R][DS];
+        auto ask_y = [&](int j, int t) {
+            const unsigned o = row(REV ? a + Lc - 1 - t : a + t) * N + 4 * g;
+#pragma unroll
+            for (int K = 0; K < NB; ++K) {
+                yr[j][K] = load4(yb + o + 16 * K);
+                if constexpr (REV) gr[j][K] = load4(gb + o + 16 * K);
+            }
+        };
+        auto ask_x = [&](int j, int t) {
+            const unsigned o = row(REV ? a + Lc - t : a + t) * (unsigned)d;
+#pragma unroll
+            for (int s = 0; s < DS; ++s) xr[j][s] = xb[o + min(DS * g + s, d - 1)];
+        };
+        if constexpr (!REV) {
+            const bool start = a == 0 && grp == 0;
+            const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N : nullptr;
+            const float* hp = start ? y0b : yb + (long long)(min(a, end) - 1) * N;
+#pragma unroll
+            for (int K = 0; K < NB; ++K) yr[R - 1][K] = hp ? load4(hp + 16 * K + 4 * g) : zero4();
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (REV || j < R - 1) ask_y(j, j);
+            ask_x(j, j);
+        }
+
+        Acc u[3][NB][NB];      // U_gate as operand A
+        Acc ut[REV ? 3 : 1][REV ? NB : 1][REV ? NB : 1];   // dual: U_gate^T as operand A
+        float w[3][NB][DS];
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int I = 0; I < NB; ++I) {
+#pragma unroll
+                for (int K = 0; K < NB; ++K) {
+                    u[gate][I][K] = load4(U + (gate * N + 16 * I + r) * N + 16 * K + 4 * g);
+                    if constexpr (REV)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) ut[gate][I][K][v] = U[(gate * N + 16 * K + 4 * g + v) * N + 16 * I + r];
+                }
+#pragma unroll
+                for (int s = 0; s < DS; ++s) w[gate][I][s] = (DS * g + s < d) ? th[(gate * N + 16 * I + r) * d + DS * g + s] : 0.f;
+            }
+
+        Acc e[NB];   // forward: correction of the state in front of the position; dual: lambda at the time after it
+        fold_carries<N, REV>(p, b, grp, nq, g, r, e);
+
+        for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int t = t0 + j, rel = REV ? a + Lc - 1 - t : a + t;
+                const bool live = rel < end;
+                Acc (&h)[NB] = yr[REV ? j : (j + R - 1) % R];
+                // gates (forward: of the position, dual: of the one after it)
+                Acc y[NB];
+                Acc lr[NB], lz[NB], lc[NB];
+#pragma unroll
+                for (int I = 0; I < NB; ++I) {
+                    const float* bs = sB + 16 * I + 4 * g;
+                    Acc ar = load4(bs), az = load4(bs + N), ac = load4(bs + 2 * N), aq = load4(bs + 3 * N);
+                    Acc er = zero4(), ez = zero4(), ec = zero4();
+#pragma unroll
+                    for (int K = 0; K < NB; ++K)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            ar = mfma(u[0][I][K][v], h[K][v], ar);
+                            az = mfma(u[1][I][K][v], h[K][v], az);
+                            aq = mfma(u[2][I][K][v], h[K][v], aq);
+                            if constexpr (!REV) {
+                                er = mfma(u[0][I][K][v], e[K][v], er);
+                                ez = mfma(u[1][I][K][v], e[K][v], ez);
+                                ec = mfma(u[2][I][K][v], e[K][v], ec);
+                            }
+                        }
+#pragma unroll
+                    for (int s = 0; s < DS; ++s) {
+                        ar = mfma(w[0][I][s], xr[j][s], ar);
+                        az = mfma(w[1][I][s], xr[j][s], az);
+                        ac = mfma(w[2][I][s], xr[j][s], ac);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const GruGates k = gru_gates(ar[v], az[v], ac[v], aq[v], h[I][v]);
+                        if constexpr (!REV) {
+                            y[I][v] = k.f + (k.z * e[I][v] + (k.pz * ez[v] + (k.sr * ec[v] + k.st * er[v])));
+                        } else {
+                            const float l = e[I][v];
+                            lz[I][v] = k.pz * l;
+                            lc[I][v] = k.sr * l;
+                            lr[I][v] = k.st * l;
+                            y[I][v] = gr[REV ? j : 0][I][v] + k.z * l;
+                        }
+                    }
+                }
+                if constexpr (REV) {
+                    // lambda_pos = g_pos + J_{pos+1}^T lambda_{pos+1}
+#pragma unroll
+                    for (int I = 0; I < NB; ++I) {
+                        Acc s1 = zero4(), s2 = zero4();
+#pragma unroll
+                        for (int K = 0; K < NB; ++K)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                y[I] = mfma(ut[1][I][K][v], lz[K][v], y[I]);
+                                s1 = mfma(ut[2][I][K][v], lc[K][v], s1);
+                                s2 = mfma(ut[0][I][K][v], lr[K][v], s2);
+                            }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) y[I][v] += s1[v] + s2[v];
+                    }
+                }
+                const unsigned o = (unsigned)(rel * N + 4 * g);
+                if (live) {
+#pragma unroll
+                    for (int I = 0; I < NB; ++I) store4(ob + o + 16 * I, y[I]);
+                }
+                const unsigned mask = live ? 0x7fffffffu : 0u;
+#pragma unroll
+                for (int I = 0; I < NB; ++I)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if constexpr (!REV) {
+                            e[I][v] = y[I][v] - yr[j][I][v];
+                            emax = max(emax, __float_as_uint(e[I][v]) & mask);
+                        } else {
+                            e[I][v] = live ? y[I][v] : 0.f;   // nothing follows the last time
+                        }
+                    }
+                if constexpr (!REV) ask_y((j + R - 1) % R, t - 1 + R);
+                else ask_y(j, t + R);
+                ask_x(j, t + R);
+            }
+        }
+    }
+    if (!REV && p.err) {
+        // one read-modify-write per workgroup: all wavefronts end at about the same time and queue on one address
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) emax = max(emax, (unsigned)__shfl_xor((int)emax, o));
+        if (lane == 0) s_max[wave] = emax;
+        __syncthreads();
+        if (tid == 0) {
+            emax = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+            err_atomic_max(p.err, __uint_as_float(min(emax, 0x7f800000u)));
+        }
+    }
+}
+
+template <int N, int DS, bool REV>
+hipError_t launch_nd(const ChunkParams& p, hipStream_t s) {
+    const unsigned groups = (unsigned)((long long)p.B * p.groups);
+    constexpr int WIDE = N == 16 ? 16 : 8;
+    if (p.wide)
+        hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV, WIDE>), dim3(groups), dim3(64 * WIDE), 0, s, p);
+    else
+        hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV, 4>), dim3(groups), dim3(256), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((chunk_walk_kernel<N, DS, REV>), dim3((groups + 3) / 4), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+template <int N, bool REV>
+hipError_t launch_n(const ChunkParams& p, hipStream_t s) {
+    if (p.d <= 4) return launch_nd<N, 1, REV>(p, s);
+    if (p.d <= 8) return launch_nd<N, 2, REV>(p, s);
+    return launch_nd<N, 4, REV>(p, s);
+}
+
+}  // namespace
+
+bool chunk_gru_supported(int dtype, int n, int d) { return dtype == 0 && (n == 16 || n == 32) && d >= 1 && d <= 16; }
+
+size_t chunk_map_bytes(int n) { return ((size_t)n * n + n) * sizeof(float); }
+
+hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s) {
+    if (!chunk_gru_supported(0, n, p.d) || p.Lc < 4 || p.Lc % 4 != 0 || p.groups != (int)((p.T + 16LL * p.Lc - 1) / (16LL * p.Lc))) return hipErrorInvalidValue;
+    const bool rev = p.g != nullptr;
+    if (n == 16) return rev ? launch_n<16, true>(p, s) : launch_n<16, false>(p, s);
+    return rev ? launch_n<32, true>(p, s) : launch_n<32, false>(p, s);
+}
+
+}  // namespace deer

@@ -55,6 +55,9 @@ struct Plan {
     bool mh;             // multi-head GRU with strides: the scan's sequences are the heads' strided recurrences
     int mh_H, mh_K;      // heads, stride levels
     size_t off_dy0parts, off_mhtable;
+    bool chunk;          // GRU, n >= 16, fp32: Newton steps and the dual scan run by chunks (chunk_gru.hip)
+    int chunk_L, chunk_groups;
+    size_t off_tot, off_sup;
     bool grad_fused;     // deer_grad computes the transposed Jacobians inside the reverse scan
     bool need_J;         // some kernel of this plan reads or writes the Jacobian stream [B,T,n,n] and the right-hand side
     int vjp_blocks;
@@ -184,6 +187,35 @@ std::vector<unsigned> mh_table(const deer_config* c, int tile) {
         }
     }
     return v;
+}
+
+// Positions per chunk, a multiple of four.  Estimate in microseconds of one step (measured on MI355X): the reduction of a group of
+// sixteen chunks takes a compute unit per_total a position, all its groups one after the other, the walk a SIMD per_walk a
+// position of a chunk; each has a fixed part, and the walk folds the maps in front of it first.
+int chunk_length(const deer_config* c) {
+    const int forced = env_int("DEER_CHUNK_L", 0);
+    if (forced >= 4) return forced / 4 * 4;
+    const double per_total = c->n == 16 ? 0.041 * 16 : 0.155 * 16, per_walk = c->n == 16 ? 0.95 : 2.5, per_fold = c->n == 16 ? 0.04 : 0.1;
+    const double per_group = c->n == 16 ? 3.0 : 7.0;
+    int best_L = 4;
+    double best = 1e300;
+    for (int L = 4; L <= 2048; L += L < 64 ? 4 : (L < 256 ? 8 : 32)) {
+        const long long per_seq = ((long long)c->T + 16LL * L - 1) / (16LL * L), groups = per_seq * c->B;
+        const double est = (double)((groups + 255) / 256) * (per_total * L + per_group) + (double)((groups + 1023) / 1024) * per_walk * L +
+                           per_fold * (double)per_seq;
+        if (est < best) { best = est; best_L = L; }
+    }
+    return best_L;
+}
+
+// Where a step by chunks is faster than the single-pass scan with the cell inside.  The scan's tiles (64 to 96 positions) spread a
+// small problem over more compute units than the chunks' groups (64 positions and more, two launches); its chain of tiles
+// grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 143 / 209 at 1 x 500, 293 / 299 at 1 x 5,000, 347 / 339 at
+// 4 x 5,000, 858 / 643 at 64 x 2,000; n = 16 130 / 142 at 20 x 783, 188 / 158 at 1 x 5,000, 192 / 169 at 4 x 5,000.
+bool chunk_pays(const deer_config* c) {
+    if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
+    const long long total = (long long)c->B * c->T;
+    return total >= 20000 || (c->n == 16 && c->T >= 1536);
 }
 
 Plan make_plan(const deer_config* c) {
@@ -321,6 +353,12 @@ Plan make_plan(const deer_config* c) {
         p.fused_tiles = (p.scan_T + ft - 1) / ft;
         if (p.fused_tiles < 1) p.fused_tiles = 1;
     }
+    if (gru && p.fused && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c)) {
+        p.chunk = true;
+        p.fused_tiles = 0;
+        p.chunk_L = chunk_length(c);
+        p.chunk_groups = (int)((T + 16 * (size_t)p.chunk_L - 1) / (16 * (size_t)p.chunk_L));
+    }
     p.vjp_blocks = c->cell == DEER_CELL_GRU    ? gru_vjp_blocks(c->n, (long long)B * T)
                    : two_part_cell(c->cell) ? lstm_vjp_blocks(c->reserved, (long long)B * T)
                    : mlp_fast_path(c)       ? mlp_vjp_blocks(c->dtype, c->n, c->mlp_width, (long long)B * T)
@@ -347,6 +385,8 @@ Plan make_plan(const deer_config* c) {
     // slots of the one-launch solve's grid barrier (two banks, one tagged scalar per workgroup)
     p.off_barrier = take(p.fused ? 2 * (B * (size_t)p.fused_tiles + 4) * (p.esz / 4) * 8 : 0);   // (+4: test hook)
     p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);   // tickets, err bits, status
+    p.off_tot = take(p.chunk ? B * (size_t)p.chunk_groups * 16 * chunk_map_bytes(c->n) : 0);
+    p.off_sup = take(p.chunk ? B * (size_t)p.chunk_groups * chunk_map_bytes(c->n) : 0);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
     p.off_partial = take((size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
@@ -485,7 +525,19 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
     p.timing = reinterpret_cast<unsigned long long*>(c->ws + c->plan.off_timing) + (size_t)(p.epoch & 7u) * ((size_t)1 << 20);
 #endif
     hipError_t e;
-    if (fused_theta && c->plan.mh) {
+    if (fused_theta && c->plan.chunk) {
+        ChunkParams q{};
+        q.theta = reinterpret_cast<const float*>(fused_theta); q.x = reinterpret_cast<const float*>(fused_x);
+        q.y0 = reinterpret_cast<const float*>(y0); q.y = reinterpret_cast<const float*>(yold);
+        q.g = reverse ? reinterpret_cast<const float*>(bv) : nullptr;
+        q.out = reinterpret_cast<float*>(out);
+        q.tot = reinterpret_cast<float*>(c->ws + c->plan.off_tot);
+        q.sup = reinterpret_cast<float*>(c->ws + c->plan.off_sup);
+        q.err = p.err; q.gate = gate;
+        q.B = g.B; q.T = g.T; q.d = g.d; q.Lc = c->plan.chunk_L; q.groups = c->plan.chunk_groups; q.wide = (long long)g.B * c->plan.chunk_groups <= 256;
+        prof_begin(c, KIND_FUSED, iter);
+        e = launch_chunk_gru(g.n, q, c->stream);
+    } else if (fused_theta && c->plan.mh) {
         p.L = c->plan.fused_L;
         p.W = 8;
         p.tiles = c->plan.fused_tiles;

@@ -1,0 +1,39 @@
+"""GPU parity of the GRU step and dual scan by chunks (fp32, n = 16, 32, 64) at the edges of chunks, groups of sixteen chunks and blocks
+of sixteen positions: trajectory, iteration count and gradients against the fp64 oracle, plain max-abs at 1e-4."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2309_12252_amd import deer, inputs
+from helpers import DEV, dev, host, gpu_eval, oracle_cell, oracle_eval
+
+pytestmark = pytest.mark.gpu
+
+# (chunk length, B, T): one position, a single ragged chunk, group boundaries (16 chunks) minus / plus one position, several
+# groups with the last one ragged, chunks that are no multiple of the sixteen-position block, few and many groups
+SHAPES = [(4, 1, 1), (4, 2, 3), (4, 1, 64), (4, 3, 65), (8, 2, 127), (8, 1, 129), (20, 2, 1000), (12, 3, 1543), (36, 1, 2049), (100, 2, 3300)]
+
+
+@pytest.mark.parametrize("n,d", [(16, 1), (16, 6), (16, 16), (32, 4), (32, 8), (32, 13), (24, 3)])
+def test_step_and_dual_by_chunks(n, d, monkeypatch):
+    for k, (L, B, T) in enumerate(SHAPES):
+        monkeypatch.setenv("DEER_CHUNK_L", str(L))
+        w = inputs.gru_workload("chunk_n%d_L%d_T%d" % (n, L, T), 1300 + 20 * n + k, B=B, T=T, n=n, d=d)
+        w.y0 = np.random.default_rng(k).standard_normal((B, n)).astype(np.float32)
+        print(w.name, B, d, flush=True)
+        yo, ito, _, _ = oracle_eval(w)
+        yg, itg, _, conv, st = gpu_eval(w)
+        assert st == deer.DEER_OK and conv and abs(itg - ito) <= 1, (w.name, itg, ito)
+        assert np.abs(yg - yo).max() <= 1e-4, (w.name, np.abs(yg - yo).max())
+        y2, _, _, _, _ = gpu_eval(w, max_iter=2)   # an iterate far from the solution
+        assert np.abs(y2 - oracle_eval(w, max_iter=2)[0]).max() <= 1e-4, w.name
+        g = (np.random.default_rng(k + 1).standard_normal((B, T, n)) / np.sqrt(T)).astype(np.float32).astype(np.float64)
+        y = oracle.seq_eval(oracle_cell(w), w.theta, w.x, w.y0, nthreads=8)
+        want = oracle.gru_grad(w.n, w.d, w.theta, w.x, w.y0, y, g)
+        ctx = deer.context_for(w, device=DEV)
+        try:
+            got = ctx.grad(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), dev(y, 0), dev(g, 0))
+        finally:
+            ctx.close()
+        for name, a, b in zip(("dtheta", "dx", "dy0"), got, want):
+            assert np.abs(host(a) - b).max() <= 1e-4, (w.name, name, np.abs(host(a) - b).max())
