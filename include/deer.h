@@ -244,8 +244,10 @@ void deer_destroy(deer_ctx* ctx);
  *   DEER_FUSED_L, DEER_FUSED_W, DEER_SCAN_L
  *                       tile shapes of the n <= 8 kernels: positions per lane group (1, 2, 4, 8, 10, 12, 16; 24 for
  *                       the plain n = 4 scan) and wavefronts per tile (4 or 8); ignored when no such variant exists
- *   DEER_CHUNK_L        GRU, n = 16, 32 in fp32: positions per chunk of the step by chunks (a multiple of four, at least
- *                       four), which is then taken at every size; by default it is taken where it is faster
+ *   DEER_CHUNK_L, DEER_CHUNK_UNIT
+ *                       GRU, n = 16, 32, 64 in fp32: positions per chunk of the step by chunks (a multiple of four, at least
+ *                       four), which is then taken at every size (by default where it is faster), and chunks per
+ *                       workgroup of its first launch (4, 8 or 16)
  *   DEER_BATCH          Newton iterations enqueued per host round trip on a fresh context (1..8, default 4)
  *   DEER_VJP_MFMA=0     vector-ALU kernels for the vector-Jacobian products instead of the matrix-core ones
  *   DEER_MLP_MFMA=0     MLP fields outside the two-layer tanh shapes (fp32, n = 8, width 32 or 64): vector-ALU field

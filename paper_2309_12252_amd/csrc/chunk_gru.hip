@@ -1,12 +1,12 @@
-// Newton step and dual scan of the GRU at n = 16, 32 and 64 in fp32: chunks of the sequence are reduced to one affine map
+// Newton step and dual scan of the GRU at n = 16 and 32 in fp32 (n = 64: chunk_gru64.hip): chunks of the sequence are reduced to one affine map
 // each, the maps are folded, and sixteen chunks per wavefront are then walked side by side (Sec. 3.1 eq. 3 and 5, Sec. 3.1.1
 // eq. 7, Sec. 3.3 eq. 10).
 //
 // A sequence is cut into chunks of Lc positions, sixteen consecutive chunks form a group.
 //   1. chunk_totals_kernel: every chunk's map x -> M x + v (the composition of its pairs).  The only part that multiplies
 //      matrices by matrices; a wavefront streams through its positions with one running product in registers.  The maps
-//      of a group are then composed into the group's map.
-//   2. chunk_walk_kernel: a wavefront owns one group.  It folds the maps of the groups in front of it into the group's
+//      of a workgroup's 4, 8 or 16 chunks (a unit) are then composed into the unit's map.
+//   2. chunk_walk_kernel: a wavefront owns one group.  It folds the maps of the units in front of it into the group's
 //      carry and the maps of its own chunks into sixteen carries, which are the columns of a 16 x 16 matrix-core tile; the
 //      sixteen chunks are then walked position by position, every step being a product of a constant weight matrix with
 //      the sixteen column vectors (J is never formed: J e = z e + p_z (U_z e) + s_r (U_c e) + s_t (U_r e)).
@@ -26,76 +26,11 @@
 // B[4g + v][r] in the v-th of four instructions of a 16-wide contraction, the accumulator holds D[4g + v][r] in register v.  So an
 // accumulator is a valid B operand, four consecutive scalars of a row-major matrix are an A operand, and an accumulator of
 // X is the A operand of its transpose.
-#include "deer_common.h"
+#include "chunk_common.h"
 
 namespace deer {
 
 namespace {
-
-using Acc = float __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ Acc mfma(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
-__device__ __forceinline__ Acc zero4() { return Acc{0.f, 0.f, 0.f, 0.f}; }
-
-__device__ __forceinline__ Acc load4(const float* __restrict__ p) { return *reinterpret_cast<const Acc*>(p); }
-
-__device__ __forceinline__ void store4(float* p, Acc v) { *reinterpret_cast<Acc*>(p) = v; }
-
-// sum over the four lane groups (lanes r, r + 16, r + 32, r + 48), in every lane
-__device__ __forceinline__ float sum_groups(float x) {
-    unsigned u = __float_as_uint(x);
-    const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const float s = __uint_as_float(q[0]) + __uint_as_float(q[1]);
-    u = __float_as_uint(s);
-    const auto w = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-
-// Four sums over the 16 lanes of a row, all four in every lane.  Lanes trade the values they do not keep (with the neighbour,
-// then with the other pair of the quad), two rotations add the quads, the quad then hands its four totals round.
-__device__ __forceinline__ Acc row_sums4(Acc q, int r) {
-    const bool odd = r & 1, upper = r & 2;
-    const float u0 = (odd ? q[1] : q[0]) + dpp<0xB1>(odd ? q[0] : q[1]);   // quad_perm 1,0,3,2
-    const float u1 = (odd ? q[3] : q[2]) + dpp<0xB1>(odd ? q[2] : q[3]);
-    float w = (upper ? u1 : u0) + dpp<0x4E>(upper ? u0 : u1);              // quad_perm 2,3,0,1
-    w += dpp<0x124>(w);                                                    // row_ror 4
-    w += dpp<0x128>(w);                                                    // row_ror 8
-    return Acc{dpp<0x00>(w), dpp<0x55>(w), dpp<0xAA>(w), dpp<0xFF>(w)};
-}
-
-// the LDS slice of a wavefront is written and read by its own lanes only: LDS operations of a wavefront complete in order,
-// the fence keeps the compiler from moving them
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-struct GruGates {
-    float f, pz, sr, st, z;
-};
-
-// gates of one row from the pre-activations ar, az, the candidate's input part ac and its hidden part q
-__device__ __forceinline__ GruGates gru_gates(float ar, float az, float ac, float q, float h) {
-    GruGates o;
-    const float rg = feed_sigmoid(ar);
-    o.z = feed_sigmoid(az);
-    const float c = feed_tanh(ac + rg * q);
-    const float zc = 1.0f - o.z;
-    const float dh = h - c;
-    o.f = c + o.z * dh;
-    o.pz = dh * o.z * zc;
-    const float sc = zc * (1.0f - c * c);
-    o.sr = sc * rg;
-    o.st = o.sr * q * (1.0f - rg);
-    return o;
-}
 
 // weights in LDS: rows of [U_gate | W_gate], W in the order the input operand takes its columns (step s of lane group g:
 // column DS g + s), zero beyond d; then the four bias vectors
@@ -148,17 +83,6 @@ __device__ __forceinline__ void w_row(float* o, const Weights<N, DS>& w, int gat
     vload<float, DS>(o, &w.row[gate][row][N + DS * g]);
 }
 
-// Input operand of one position: lane group g takes columns DS g .. DS g + DS - 1 (past d: a valid entry; its weight is zero)
-template <int DS>
-__device__ __forceinline__ void load_x(float* o, const float* __restrict__ xrow, int d, int g) {
-#pragma unroll
-    for (int s = 0; s < DS; ++s) {
-        const int k = DS * g + s;
-        o[s] = xrow[k < d ? k : d - 1];
-    }
-}
-
-template <int N> constexpr int map_size() { return N * N + N; }
 
 // ------------------------------------------------------------------------------------------------------------------
 // Maps of the chunks.  Forward: the total of a chunk is P = J_L .. J_1, and Q = P^T is built from the last position to the
@@ -171,16 +95,16 @@ template <int N> constexpr int map_size() { return N * N + N; }
 // the row factors to the lanes that assemble J instead of its transpose); the row factors reach the assembly through an
 // LDS slice of the wavefront.
 // ------------------------------------------------------------------------------------------------------------------
-template <int N, int DS, bool REV, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES / 4) void chunk_totals_kernel(ChunkParams p) {
-    constexpr int NB = N / 16, MS = map_size<N>(), CPW = 16 / WAVES;   // chunks of a wavefront
+template <int N, int DS, bool REV>
+__global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(ChunkParams p) {
+    constexpr int NB = N / 16, MS = map_size<N>();
     __shared__ __align__(16) Weights<N, DS> sW;
     // forward: [kind: p_z, s_r, s_t, z, residual][position][row]; dual: [position][row][p_z, s_r, s_t, z], then [position][row] of g
-    __shared__ __align__(16) float sF[WAVES][5 * 16 * N];
+    __shared__ __align__(16) float sF[4][5 * 16 * N];
 
     if (gate_closed<float>(p.gate)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
-    const int b = (int)(blockIdx.x % (unsigned)p.B), grp = (int)(blockIdx.x / (unsigned)p.B);
+    const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
 
     const int T = p.T, d = p.d, Lc = p.Lc;
     const int chunks = (T + Lc - 1) / Lc;
@@ -188,12 +112,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES 
     const float* __restrict__ xb = p.x + (long long)b * T * d;
     const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N : nullptr;
     const float* __restrict__ gb = REV ? p.g + (long long)b * T * N : nullptr;
-    float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+    const int first = unit * p.per_unit, cpw = p.per_unit / 4;   // first chunk, chunks of a wavefront
+    float* __restrict__ tot = p.tot + ((long long)b * p.groups * 16 + first) * MS;
     float* __restrict__ sFw = sF[wave];
 
-    const int q_lo = CPW * wave, q_hi = min(q_lo + CPW, chunks - 16 * grp);   // chunks of this wavefront (inside the group)
-    const int lo = (16 * grp + q_lo) * Lc;
-    const int hi = min(T, (16 * grp + q_hi) * Lc);
+    const int q_lo = cpw * wave, q_hi = min(q_lo + cpw, chunks - first);   // chunks of this wavefront (inside the unit)
+    const int lo = (first + q_lo) * Lc;
+    const int hi = min(T, (first + q_hi) * Lc);
     const int blocks = (hi - lo + 15) / 16;
 
     // operands of one block: state in front of each position (16-byte pieces: operand of the products and the rows of
@@ -213,7 +138,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES 
         load_x<DS>(xB, xb + (long long)(REV ? min(pos + 1, T - 1) : pos) * d, d, g);
     };
     if (q_lo < q_hi) request(0);
-    fill_weights<N, DS, 64 * WAVES>(sW, p.theta, p.d, tid);
+    fill_weights<N, DS, 256>(sW, p.theta, p.d, tid);
     __syncthreads();
 
     // weights of the assembly: ua[gate][X][Y][v] multiplies the factor of J's row
@@ -248,7 +173,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES 
         reset();
 
         int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
-        int edge = REV ? min(T, (16 * grp + q + 1) * Lc) - 1 : (16 * grp + q) * Lc;   // its last position in traversal order
+        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
 
         for (int blk = 0; blk < blocks; ++blk) {
             const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
@@ -405,7 +330,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES 
                     }
                     reset();
                     q += REV ? 1 : -1;
-                    edge = REV ? min(T, (16 * grp + q + 1) * Lc) - 1 : (16 * grp + q) * Lc;
+                    edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
                 }
             }
             wave_lds_fence();
@@ -413,167 +338,16 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? (N == 16 ? 3 : 2) : WAVES 
     }
     __syncthreads();
 
-    // ---- the group's map: the maps of its chunks composed in the order they apply (a wavefront per 16 columns, one more
-    // for the vector).  The group nothing follows needs none. ----
-    const bool last = REV ? grp == 0 : grp == p.groups - 1;
-    if (!last && wave <= NB) {
-        const int nq = min(16, chunks - 16 * grp);
-        const bool is_vec = wave == NB;
-        constexpr int PD = N == 16 ? 4 : 2;   // maps requested ahead
-        Acc X[NB], A[PD][NB][NB], V[PD][NB];
-        auto ask = [&](int j, int i) {
-            i = min(i, nq - 1);
-            const float* o = tot + (long long)(REV ? nq - 1 - i : i) * MS;
-#pragma unroll
-            for (int I = 0; I < NB; ++I) {
-                V[j][I] = is_vec ? load4(o + N * N + 16 * I + 4 * g) : zero4();
-#pragma unroll
-                for (int K = 0; K < NB; ++K) A[j][I][K] = load4(o + (16 * I + r) * N + 16 * K + 4 * g);
-            }
-        };
-        const float* m = tot + (long long)(REV ? nq - 1 : 0) * MS;
-#pragma unroll
-        for (int K = 0; K < NB; ++K) {
-            if (is_vec) X[K] = load4(m + N * N + 16 * K + 4 * g);
-            else
-#pragma unroll
-                for (int v = 0; v < 4; ++v) X[K][v] = m[(16 * K + 4 * g + v) * N + 16 * wave + r];
-        }
-#pragma unroll
-        for (int j = 0; j < PD; ++j) ask(j, 1 + j);
-        for (int i0 = 1; i0 < nq; i0 += PD) {
-#pragma unroll
-            for (int j = 0; j < PD; ++j) {
-                if (i0 + j < nq) {
-                    Acc Y[NB];
-#pragma unroll
-                    for (int I = 0; I < NB; ++I) Y[I] = V[j][I];
-#pragma unroll
-                    for (int K = 0; K < NB; ++K)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-#pragma unroll
-                            for (int I = 0; I < NB; ++I) Y[I] = mfma(A[j][I][K][v], X[K][v], Y[I]);
-#pragma unroll
-                    for (int I = 0; I < NB; ++I) X[I] = Y[I];
-                }
-                ask(j, i0 + j + PD);
-            }
-        }
-        float* o = p.sup + ((long long)b * p.groups + grp) * MS;
-#pragma unroll
-        for (int I = 0; I < NB; ++I) {
-            if (is_vec) {
-                if (r == 0) store4(o + N * N + 16 * I + 4 * g, X[I]);
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) o[(16 * I + 4 * g + v) * N + 16 * wave + r] = X[I][v];
-            }
-        }
-    }
+    // the units of the group that nothing follows need no map
+    const int pu = 16 / p.per_unit;
+    const bool needed = REV ? unit >= pu : unit < (p.groups - 1) * pu;
+    if (needed && wave <= NB)
+        compose_unit<N, REV>(tot, p.sup + ((long long)b * p.units + unit) * MS, min(p.per_unit, chunks - first), wave, g, r);
 }
 
 // ------------------------------------------------------------------------------------------------------------------
 // The walk: one wavefront per group, its sixteen chunks are the columns of every product.
 // ------------------------------------------------------------------------------------------------------------------
-// x <- M x + v over the maps of the groups in front, then over those of the group's own chunks, whose carries are the columns
-// of e.  A chain of small products with a vector: on the vector ALUs, because a matrix instruction would use one of its
-// sixteen columns (512 cycles a step at n = 32 against about 200).  Even steps take x as operand B holds it (16K + 4g + v) and
-// add over the lane groups, which leaves row 16I + r in lane r; odd steps start from there, multiply columns and add
-// over the lanes of a row, which leaves the operand order again: no step moves x between lanes.  The maps are requested PD
-// steps ahead (a step is shorter than a trip to the last-level cache).
-template <int N, bool REV>
-__device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int grp, int nq, int g, int r, Acc (&e)[N / 16]) {
-    constexpr int NB = N / 16, MS = map_size<N>(), PD = N == 16 ? 4 : 2;   // even
-    Acc A[PD][NB][NB], V[PD][NB];
-    Acc xk[NB];      // x[16K + 4g + v]
-    float xr[NB];    // x[16K + r]
-#pragma unroll
-    for (int K = 0; K < NB; ++K) {
-        xk[K] = e[K] = zero4();
-        xr[K] = 0.f;
-    }
-    const int before = REV ? p.groups - 1 - grp : grp, steps = before + nq - 1;
-    const float* __restrict__ sup = p.sup + (long long)b * p.groups * MS;
-    const float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
-    auto request = [&](int j, int i) {
-        i = min(i, steps - 1);
-        const int k = i - before;
-        const float* m = i < before ? sup + (long long)(REV ? p.groups - 1 - i : i) * MS : tot + (long long)(REV ? nq - 1 - k : k) * MS;
-#pragma unroll
-        for (int I = 0; I < NB; ++I) {
-            if (j & 1) {
-                V[j][I] = load4(m + N * N + 16 * I + 4 * g);
-#pragma unroll
-                for (int K = 0; K < NB; ++K)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) A[j][I][K][v] = m[(16 * I + 4 * g + v) * N + 16 * K + r];
-            } else {
-                V[j][I][0] = m[N * N + 16 * I + r];
-#pragma unroll
-                for (int K = 0; K < NB; ++K) A[j][I][K] = load4(m + (16 * I + r) * N + 16 * K + 4 * g);
-            }
-        }
-    };
-    // the carry in front of step i belongs to chunk i - before
-    auto select = [&](int i, bool rows) {
-        const int k = i - before, q = REV ? nq - 1 - k : k;
-        if (k < 0) return;
-#pragma unroll
-        for (int K = 0; K < NB; ++K) {
-            Acc c = xk[K];
-            if (rows)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) c[v] = __shfl(xr[K], 4 * g + v);
-            e[K] = r == q ? c : e[K];
-        }
-    };
-    // in front of the sequence x is zero and M is not looked at (it may have overflowed)
-    auto step = [&](int j, int i) {
-        select(i, j & 1);
-        if (j & 1) {
-#pragma unroll
-            for (int I = 0; I < NB; ++I) {
-                Acc q = zero4();
-#pragma unroll
-                for (int K = 0; K < NB; ++K)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) q[v] += A[j][I][K][v] * xr[K];
-                xk[I] = V[j][I] + row_sums4(q, r);
-            }
-        } else {
-            float y[NB];
-#pragma unroll
-            for (int I = 0; I < NB; ++I) {
-                float q[2] = {0.f, 0.f};
-#pragma unroll
-                for (int K = 0; K < NB; ++K)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) q[v & 1] += A[j][I][K][v] * xk[K][v];
-                y[I] = V[j][I][0] + (i > 0 ? sum_groups(q[0] + q[1]) : 0.f);
-            }
-#pragma unroll
-            for (int I = 0; I < NB; ++I) xr[I] = y[I];
-        }
-    };
-    if (steps > 0) {
-#pragma unroll
-        for (int j = 0; j < PD; ++j) request(j, j);
-        int i = 0;
-        for (; i + PD <= steps; i += PD) {
-#pragma unroll
-            for (int j = 0; j < PD; ++j) {
-                step(j, i + j);
-                request(j, i + j + PD);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < PD - 1; ++j)
-            if (i + j < steps) step(j, i + j);
-    }
-    select(steps, steps & 1);
-}
-
 template <int N, int DS, bool REV>
 __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkParams p) {
     constexpr int NB = N / 16;
@@ -756,15 +530,10 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
 
 template <int N, int DS, bool REV>
 hipError_t launch_nd(const ChunkParams& p, hipStream_t s) {
-    const unsigned groups = (unsigned)((long long)p.B * p.groups);
-    constexpr int WIDE = N == 16 ? 16 : 8;
-    if (p.wide)
-        hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV, WIDE>), dim3(groups), dim3(64 * WIDE), 0, s, p);
-    else
-        hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV, 4>), dim3(groups), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((chunk_walk_kernel<N, DS, REV>), dim3((groups + 3) / 4), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((chunk_walk_kernel<N, DS, REV>), dim3((unsigned)(((long long)p.B * p.groups + 3) / 4)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
@@ -777,12 +546,14 @@ hipError_t launch_n(const ChunkParams& p, hipStream_t s) {
 
 }  // namespace
 
-bool chunk_gru_supported(int dtype, int n, int d) { return dtype == 0 && (n == 16 || n == 32) && d >= 1 && d <= 16; }
+bool chunk_gru_supported(int dtype, int n, int d) { return dtype == 0 && (n == 16 || n == 32 || n == 64) && d >= 1 && d <= 16; }
 
 size_t chunk_map_bytes(int n) { return ((size_t)n * n + n) * sizeof(float); }
 
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s) {
-    if (!chunk_gru_supported(0, n, p.d) || p.Lc < 4 || p.Lc % 4 != 0 || p.groups != (int)((p.T + 16LL * p.Lc - 1) / (16LL * p.Lc))) return hipErrorInvalidValue;
+    if (!chunk_gru_supported(0, n, p.d) || p.Lc < 4 || p.Lc % 4 != 0 || (p.per_unit != 4 && p.per_unit != 8 && p.per_unit != 16) ||
+        p.units != (int)((p.T + (long long)p.per_unit * p.Lc - 1) / ((long long)p.per_unit * p.Lc)) || p.groups != (int)((p.T + 16LL * p.Lc - 1) / (16LL * p.Lc))) return hipErrorInvalidValue;
+    if (n == 64) return launch_chunk_gru64(p, s);
     const bool rev = p.g != nullptr;
     if (n == 16) return rev ? launch_n<16, true>(p, s) : launch_n<16, false>(p, s);
     return rev ? launch_n<32, true>(p, s) : launch_n<32, false>(p, s);

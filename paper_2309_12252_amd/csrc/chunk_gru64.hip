@@ -1,0 +1,501 @@
+// The GRU step and dual scan by chunks (chunk_gru.hip) at n = 64 in fp32.  A 64 x 64 running product and its factor are 128
+// registers a lane for one wavefront, so four wavefronts share a position:
+//   reduction: wavefront w keeps columns 16 w .. 16 w + 15 of the running product (16 registers) and assembles a quarter of
+//     every factor (the rows of J whose gates it has evaluated) into LDS in operand order, double-buffered, one barrier a
+//     position; all four read the whole factor (64 KB of LDS reads against 4 x 2,048 matrix-core cycles).
+//   walk: wavefront w evaluates rows 16 w .. 16 w + 15 of all products; the column vectors cross LDS, one barrier a step.
+// Bound: issue of the matrix instructions, 64 x 32 cycles of about 2,450 a wavefront spends on a position.  Measured, a Newton
+// step at 16 x 10,000 positions, d = 8: 940 us; before (Jacobian kernel 1,220 us, then the scan of the stored matrices in tiles of eight
+// positions 3,570 us) 4,790 us.
+#include "chunk_common.h"
+
+namespace deer {
+
+namespace {
+
+constexpr int N = 64, NB = 4, MS = N * N + N;
+
+// Gate operands of a wavefront (rows 16 w .. 16 w + 15)
+template <int DS>
+struct GateRows {
+    Acc u[3][NB];
+    float w[3][DS];
+    Acc b[4];
+};
+
+template <int DS>
+__device__ __forceinline__ void load_gate_rows(GateRows<DS>& o, const float* __restrict__ th, int d, int wave, int g, int r) {
+    const float* __restrict__ U = th + 3 * N * d;
+    const float* __restrict__ bias = U + 3 * N * N;
+#pragma unroll
+    for (int gate = 0; gate < 3; ++gate) {
+        const int row = gate * N + 16 * wave + r;
+#pragma unroll
+        for (int K = 0; K < NB; ++K) o.u[gate][K] = load4(U + row * N + 16 * K + 4 * g);
+#pragma unroll
+        for (int s = 0; s < DS; ++s) {
+            const float v = th[row * d + min(DS * g + s, d - 1)];
+            o.w[gate][s] = DS * g + s < d ? v : 0.f;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o.b[j] = load4(bias + j * N + 16 * wave + 4 * g);
+}
+
+// gates of this wavefront's rows at sixteen positions (columns); h: rows 16K + 4g + v of the state, hw: this wavefront's rows
+template <int DS>
+__device__ __forceinline__ void gates16(GruGates (&o)[4], const GateRows<DS>& k, const Acc (&h)[NB], const float (&x)[DS], Acc hw) {
+    Acc ar = k.b[0], az = k.b[1], ac = k.b[2], aq = k.b[3];
+#pragma unroll
+    for (int K = 0; K < NB; ++K)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            ar = mfma(k.u[0][K][v], h[K][v], ar);
+            az = mfma(k.u[1][K][v], h[K][v], az);
+            aq = mfma(k.u[2][K][v], h[K][v], aq);
+        }
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+        ar = mfma(k.w[0][s], x[s], ar);
+        az = mfma(k.w[1][s], x[s], az);
+        ac = mfma(k.w[2][s], x[s], ac);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = gru_gates(ar[v], az[v], ac[v], aq[v], hw[v]);
+}
+
+template <int DS, bool REV>
+__global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
+    // row factors of this wavefront's 16 rows; forward [kind][position][row], dual [position][row][kind]
+    __shared__ __align__(16) float sF[4][4 * 16 * 16];
+    __shared__ __align__(16) float sR[16 * N];            // forward: residual, dual: cotangent, [position][row]
+    __shared__ __align__(16) Acc sJ[2][NB * NB][64];      // factor in operand order, [block][lane]
+    if (gate_closed<float>(p.gate)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
+    const int T = p.T, d = p.d, Lc = p.Lc, chunks = (T + Lc - 1) / Lc;
+    const int first = unit * p.per_unit, nq = min(p.per_unit, chunks - first);   // chunks of this unit
+    const float* __restrict__ yb = p.y + (long long)b * T * N;
+    const float* __restrict__ xb = p.x + (long long)b * T * d;
+    const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N : nullptr;
+    const float* __restrict__ gb = REV ? p.g + (long long)b * T * N : nullptr;
+    float* __restrict__ tot = p.tot + ((long long)b * p.groups * 16 + first) * MS;
+    float* __restrict__ sFw = sF[wave];
+
+    const int lo = first * Lc, hi = min(T, (first + nq) * Lc), blocks = (hi - lo + 15) / 16;
+    Acc h[NB], ow;   // state in front of each position, this wavefront's rows of the residual's other term
+    float x[DS];
+    auto request = [&](int blk) {
+        int pos = (REV ? lo + 16 * blk : hi - 16 * (blk + 1)) + r;
+        pos = min(max(pos, lo), hi - 1);
+        const float* hp = REV ? yb + (long long)pos * N : (pos > 0 ? yb + (long long)(pos - 1) * N : y0b);
+#pragma unroll
+        for (int K = 0; K < NB; ++K) h[K] = hp ? load4(hp + 16 * K + 4 * g) : zero4();
+        ow = load4((REV ? gb : yb) + (long long)pos * N + 16 * wave + 4 * g);
+        load_x<DS>(x, xb + (long long)(REV ? min(pos + 1, T - 1) : pos) * d, d, g);
+    };
+    request(0);
+    GateRows<DS> gr;
+    load_gate_rows<DS>(gr, p.theta, d, wave, g, r);
+    // weights of the quarter of the factor this wavefront assembles.  forward (J^T): J[16 w + 4g + v][16 X + r], block (X, w);
+    // dual (J): J[16 w + r][16 X + 4g + v], block (w, X) -- the gate operands themselves
+    Acc ua[REV ? 1 : 3][NB];
+    if constexpr (!REV) {
+        const float* __restrict__ U = p.theta + 3 * N * d;
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int X = 0; X < NB; ++X)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) ua[gate][X][v] = U[(gate * N + 16 * wave + 4 * g + v) * N + 16 * X + r];
+    }
+    float dsel[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dsel[v] = (4 * g + v == r) ? 1.f : 0.f;
+
+    Acc Q[NB];   // columns 16 w + r of the running product, rows 16 X + 4g + v
+    float vec = 0.f;
+    auto reset = [&]() {
+        vec = 0.f;
+#pragma unroll
+        for (int X = 0; X < NB; ++X)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Q[X][v] = X == wave ? dsel[v] : 0.f;
+    };
+    reset();
+
+    auto assemble = [&](int buf, int c) {
+        if constexpr (!REV) {
+            const float* o = sFw + c * 16 + 4 * g;
+            const Acc pz = load4(o), sr = load4(o + 256), st = load4(o + 512), z = load4(o + 768);
+#pragma unroll
+            for (int X = 0; X < NB; ++X) {
+                Acc a;
+                const float diag = X == wave ? 1.f : 0.f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    a[v] = pz[v] * ua[1][X][v] + (sr[v] * ua[2][X][v] + (st[v] * ua[0][X][v] + diag * dsel[v] * z[v]));
+                sJ[buf][X * NB + wave][lane] = a;
+            }
+        } else {
+            const Acc ff = load4(sFw + (c * 16 + r) * 4);
+#pragma unroll
+            for (int X = 0; X < NB; ++X) {
+                Acc a;
+                const float diag = X == wave ? 1.f : 0.f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    a[v] = ff[0] * gr.u[1][X][v] + (ff[1] * gr.u[2][X][v] + (ff[2] * gr.u[0][X][v] + diag * dsel[v] * ff[3]));
+                sJ[buf][wave * NB + X][lane] = a;
+            }
+        }
+    };
+
+    int q = REV ? 0 : nq - 1;   // chunk being reduced
+    int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+    for (int blk = 0; blk < blocks; ++blk) {
+        const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+        {
+            GruGates k[4];
+            gates16<DS>(k, gr, h, x, wave == 0 ? h[0] : wave == 1 ? h[1] : wave == 2 ? h[2] : h[3]);
+            Acc rv = ow;
+            if constexpr (!REV) {
+                Acc fpz, fsr, fst, fz;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) { fpz[v] = k[v].pz; fsr[v] = k[v].sr; fst[v] = k[v].st; fz[v] = k[v].z; rv[v] = k[v].f - ow[v]; }
+                float* o = sFw + r * 16 + 4 * g;
+                store4(o, fpz); store4(o + 256, fsr); store4(o + 512, fst); store4(o + 768, fz);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) store4(sFw + (r * 16 + 4 * g + v) * 4, Acc{k[v].pz, k[v].sr, k[v].st, k[v].z});
+            }
+            store4(sR + r * N + 16 * wave + 4 * g, rv);
+        }
+        wave_lds_fence();
+        const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16, cnt = c_hi - c_lo;
+        assemble(0, REV ? c_lo : c_hi - 1);
+        __syncthreads();
+        if (blk + 1 < blocks) request(blk + 1);
+#pragma unroll 1
+        for (int k = 0; k < cnt; ++k) {
+            const int c = REV ? c_lo + k : c_hi - 1 - k;
+            if (k + 1 < cnt) assemble((k + 1) & 1, REV ? c + 1 : c - 1);
+#pragma unroll
+            for (int K = 0; K < NB; ++K) {
+                const Acc rv = load4(sR + c * N + 16 * K + 4 * g);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) vec += Q[K][v] * rv[v];
+            }
+            Acc Qn[NB];
+#pragma unroll
+            for (int X = 0; X < NB; ++X) Qn[X] = zero4();
+#pragma unroll
+            for (int K = 0; K < NB; ++K) {
+                Acc a[NB];
+#pragma unroll
+                for (int X = 0; X < NB; ++X) a[X] = sJ[k & 1][X * NB + K][lane];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int X = 0; X < NB; ++X) Qn[X] = mfma(a[X][v], Q[K][v], Qn[X]);
+            }
+#pragma unroll
+            for (int X = 0; X < NB; ++X) Q[X] = Qn[X];
+            if (base + c == edge) {
+                // the chunk's map: M[16 w + r][16 X + 4g + v] = Q[X][v]
+                float* o = tot + (long long)q * MS;
+#pragma unroll
+                for (int X = 0; X < NB; ++X) store4(o + (16 * wave + r) * N + 16 * X + 4 * g, Q[X]);
+                const float s = sum_groups(vec);
+                if (g == 0) o[N * N + 16 * wave + r] = s;
+                reset();
+                q += REV ? 1 : -1;
+                edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
+            }
+            __syncthreads();   // the next factor is complete, this one and (at the end of a block) the residuals are free
+        }
+    }
+
+    // ---- the unit's map; none where no group follows ----
+    const int pu = 16 / p.per_unit;
+    if (REV ? unit < pu : unit >= (p.groups - 1) * pu) return;
+    float* sx = sR;   // running vector, two copies
+    Acc A[2][NB], Aw[NB];   // blocks of the next map: all rows of column block 0, this wavefront's rows
+    float mv;
+    auto map_at = [&](int i) { return tot + (long long)(REV ? nq - 1 - min(i, nq - 1) : min(i, nq - 1)) * MS; };
+    auto ask = [&](const float* m) {
+#pragma unroll
+        for (int I = 0; I < NB; ++I) A[0][I] = load4(m + (16 * I + r) * N + 4 * g);
+#pragma unroll
+        for (int K = 0; K < NB; ++K) Aw[K] = load4(m + (16 * wave + r) * N + 16 * K + 4 * g);
+        mv = m[N * N + 16 * wave + r];
+    };
+    ask(map_at(1));
+    {
+        const float* m = map_at(0);
+#pragma unroll
+        for (int K = 0; K < NB; ++K)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Q[K][v] = m[(16 * K + 4 * g + v) * N + 16 * wave + r];
+        if (tid < N) sx[tid] = m[N * N + tid];
+    }
+    __syncthreads();
+    for (int i = 1; i < nq; ++i) {
+        const float* m = map_at(i);
+        float s = 0.f;
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            const Acc xk = load4(sx + ((i + 1) & 1) * N + 16 * K + 4 * g);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s += Aw[K][v] * xk[v];
+        }
+        s = sum_groups(s) + mv;
+        if (g == 0) sx[(i & 1) * N + 16 * wave + r] = s;
+        Acc Y[NB];
+#pragma unroll
+        for (int I = 0; I < NB; ++I) Y[I] = zero4();
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            if (K + 1 < NB)
+#pragma unroll
+                for (int I = 0; I < NB; ++I) A[(K + 1) & 1][I] = load4(m + (16 * I + r) * N + 16 * (K + 1) + 4 * g);
+            else
+                ask(map_at(i + 1));
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int I = 0; I < NB; ++I) Y[I] = mfma(A[K & 1][I][v], Q[K][v], Y[I]);
+        }
+#pragma unroll
+        for (int I = 0; I < NB; ++I) Q[I] = Y[I];
+        __syncthreads();
+    }
+    float* o = p.sup + ((long long)b * p.units + unit) * MS;
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[(16 * I + 4 * g + v) * N + 16 * wave + r] = Q[I][v];
+    if (tid < N) o[N * N + tid] = sx[((nq - 1) & 1) * N + tid];
+}
+
+// Step t of a chunk needs all rows of the state and of the correction (dual: of the state and of the three weighted
+// cotangents) from the four wavefronts.
+template <int DS, bool REV>
+__global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
+    constexpr int KINDS = REV ? 4 : 2;
+    __shared__ __align__(16) Acc sX[2][KINDS][NB][64];   // [step parity][state, then correction or weighted cotangents][wavefront][lane]
+    __shared__ __align__(16) float sx[2][N];
+    __shared__ unsigned s_max[4];
+    if (gate_closed<float>(p.gate)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int b = (int)(blockIdx.x % (unsigned)p.B), grp = (int)(blockIdx.x / (unsigned)p.B);
+    const int T = p.T, d = p.d, Lc = p.Lc, chunks = (T + Lc - 1) / Lc, nq = min(16, chunks - 16 * grp);
+    // addresses relative to the group's first position, this wavefront's rows
+    const long long first = (long long)b * T + (long long)16 * grp * Lc;
+    const float* __restrict__ yb = p.y + first * N + 16 * wave + 4 * g;
+    const float* __restrict__ xb = p.x + first * d;
+    const float* __restrict__ gb = REV ? p.g + first * N + 16 * wave + 4 * g : nullptr;
+    float* __restrict__ ob = p.out + first * N + 16 * wave + 4 * g;
+    const int a = r * Lc, end = T - 16 * grp * Lc;
+    auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
+
+    // requested R - 1 (dual: R) steps ahead; slots named by t mod R
+    constexpr int R = 4;
+    Acc yr[R], go[REV ? R : 1];
+    float xr[R][DS];
+    auto ask_y = [&](int j, int t) {
+        const unsigned o = row(REV ? a + Lc - 1 - t : a + t) * N;
+        yr[j] = load4(yb + o);
+        if constexpr (REV) go[j] = load4(gb + o);
+    };
+    auto ask_x = [&](int j, int t) {
+        const unsigned o = row(REV ? a + Lc - t : a + t) * (unsigned)d;
+#pragma unroll
+        for (int s = 0; s < DS; ++s) xr[j][s] = xb[o + min(DS * g + s, d - 1)];
+    };
+    if constexpr (!REV) {
+        const bool start = a == 0 && grp == 0;
+        const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N + 16 * wave + 4 * g : nullptr;
+        const float* hp = start ? y0b : yb + (long long)(min(a, end) - 1) * N;
+        yr[R - 1] = hp ? load4(hp) : zero4();
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if (REV || j < R - 1) ask_y(j, j);
+        ask_x(j, j);
+    }
+    GateRows<DS> gr;
+    load_gate_rows<DS>(gr, p.theta, d, wave, g, r);
+    Acc ut[REV ? 3 : 1][NB];   // dual: rows 16 w + r of U_gate^T
+    if constexpr (REV) {
+        const float* __restrict__ U = p.theta + 3 * N * d;
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int K = 0; K < NB; ++K)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) ut[gate][K][v] = U[(gate * N + 16 * K + 4 * g + v) * N + 16 * wave + r];
+    }
+
+    // ---- carries: x <- M x + v over the units in front, then over the group's own chunks; a row of M per lane, a quarter
+    // of the rows per wavefront, x in LDS ----
+    Acc e = zero4();
+    {
+        constexpr int PD = REV ? 2 : 4;
+        const int pu = 16 / p.per_unit;   // units of a group
+        const int before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
+        const float* __restrict__ sup = p.sup + (long long)b * p.units * MS;
+        const float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+        Acc A[PD][NB];
+        float V[PD];
+        auto request = [&](int j, int i) {
+            i = min(i, steps - 1);
+            const int k = i - before;
+            const float* m = i < before ? sup + (long long)(REV ? p.units - 1 - i : i) * MS : tot + (long long)(REV ? nq - 1 - k : k) * MS;
+#pragma unroll
+            for (int K = 0; K < NB; ++K) A[j][K] = load4(m + (16 * wave + r) * N + 16 * K + 4 * g);
+            V[j] = m[N * N + 16 * wave + r];
+        };
+        if (steps > 0) {
+#pragma unroll
+            for (int j = 0; j < PD; ++j) request(j, j);
+        }
+        if (tid < N) sx[0][tid] = 0.f;
+        __syncthreads();
+        for (int i0 = 0; i0 <= steps; i0 += PD) {
+#pragma unroll
+            for (int j = 0; j < PD; ++j) {
+                const int i = i0 + j;
+                if (i <= steps) {
+                    const int k = i - before, qs = REV ? nq - 1 - k : k;
+                    const Acc mine = load4(&sx[i & 1][16 * wave + 4 * g]);
+                    e = (k >= 0 && r == qs) ? mine : e;
+                    if (i < steps) {
+                        float s = 0.f;
+                        if (i > 0) {   // in front of the sequence x is zero and M is not looked at (it may have overflowed)
+#pragma unroll
+                            for (int K = 0; K < NB; ++K) {
+                                const Acc xk = load4(&sx[i & 1][16 * K + 4 * g]);
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) s += A[j][K][v] * xk[v];
+                            }
+                            s = sum_groups(s);
+                        }
+                        if (g == 0) sx[(i + 1) & 1][16 * wave + r] = s + V[j];
+                        __syncthreads();
+                    }
+                }
+                if (steps > 0) request(j, i + PD);
+            }
+        }
+    }
+
+    unsigned emax = 0u;   // largest |y_new - y| as raw bits (a NaN compares above everything)
+    sX[0][0][wave][lane] = yr[REV ? 0 : R - 1];
+    if constexpr (!REV) sX[0][1][wave][lane] = e;
+    __syncthreads();
+    for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int t = t0 + j, rel = REV ? a + Lc - 1 - t : a + t;
+            const bool live = rel < end;
+            const int cur = j & 1, nxt = cur ^ 1;
+            Acc h[NB];
+#pragma unroll
+            for (int K = 0; K < NB; ++K) h[K] = sX[cur][0][K][lane];
+            GruGates k[4];
+            const Acc hw = yr[REV ? j : (j + R - 1) % R];
+            gates16<DS>(k, gr, h, xr[j], hw);
+            Acc y;
+            if constexpr (!REV) {
+                Acc er = zero4(), ez = zero4(), ec = zero4();
+#pragma unroll
+                for (int K = 0; K < NB; ++K) {
+                    const Acc ek = sX[cur][1][K][lane];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        er = mfma(gr.u[0][K][v], ek[v], er);
+                        ez = mfma(gr.u[1][K][v], ek[v], ez);
+                        ec = mfma(gr.u[2][K][v], ek[v], ec);
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y[v] = k[v].f + (k[v].z * e[v] + (k[v].pz * ez[v] + (k[v].sr * ec[v] + k[v].st * er[v])));
+                const unsigned mask = live ? 0x7fffffffu : 0u;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    e[v] = y[v] - yr[j][v];
+                    emax = max(emax, __float_as_uint(e[v]) & mask);
+                }
+                sX[nxt][0][wave][lane] = yr[j];
+                sX[nxt][1][wave][lane] = e;
+                __syncthreads();
+            } else {
+                // lambda_pos = g_pos + J_{pos+1}^T lambda_{pos+1}
+                Acc lz, lc, lr;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    lz[v] = k[v].pz * e[v];
+                    lc[v] = k[v].sr * e[v];
+                    lr[v] = k[v].st * e[v];
+                    y[v] = go[REV ? j : 0][v] + k[v].z * e[v];
+                }
+                sX[nxt][0][wave][lane] = yr[(j + 1) % R];
+                sX[cur][1][wave][lane] = lz;
+                sX[cur][2][wave][lane] = lc;
+                sX[cur][3][wave][lane] = lr;
+                __syncthreads();
+                Acc s1 = zero4(), s2 = zero4();
+#pragma unroll
+                for (int K = 0; K < NB; ++K) {
+                    const Acc kz = sX[cur][1][K][lane], kc = sX[cur][2][K][lane], kr = sX[cur][3][K][lane];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        y = mfma(ut[REV ? 1 : 0][K][v], kz[v], y);
+                        s1 = mfma(ut[REV ? 2 : 0][K][v], kc[v], s1);
+                        s2 = mfma(ut[0][K][v], kr[v], s2);
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    y[v] += s1[v] + s2[v];
+                    e[v] = live ? y[v] : 0.f;   // nothing follows the last time
+                }
+            }
+            if (live) store4(ob + (unsigned)(rel * N), y);
+            if constexpr (!REV) ask_y((j + R - 1) % R, t - 1 + R);
+            else ask_y(j, t + R);
+            ask_x(j, t + R);
+        }
+    }
+    if (!REV && p.err) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) emax = max(emax, (unsigned)__shfl_xor((int)emax, o));
+        if (lane == 0) s_max[wave] = emax;
+        __syncthreads();
+        if (tid == 0) {
+            emax = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+            err_atomic_max(p.err, __uint_as_float(min(emax, 0x7f800000u)));
+        }
+    }
+}
+
+template <int DS, bool REV>
+hipError_t launch_ds(const ChunkParams& p, hipStream_t s) {
+    hipLaunchKernelGGL((chunk_totals64_kernel<DS, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((chunk_walk64_kernel<DS, REV>), dim3((unsigned)((long long)p.B * p.groups)), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_chunk_gru64(const ChunkParams& p, hipStream_t s) {
+    const bool rev = p.g != nullptr;
+    if (p.d <= 4) return rev ? launch_ds<1, true>(p, s) : launch_ds<1, false>(p, s);
+    if (p.d <= 8) return rev ? launch_ds<2, true>(p, s) : launch_ds<2, false>(p, s);
+    return rev ? launch_ds<4, true>(p, s) : launch_ds<4, false>(p, s);
+}
+
+}  // namespace deer

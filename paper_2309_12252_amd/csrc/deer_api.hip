@@ -56,7 +56,7 @@ struct Plan {
     int mh_H, mh_K;      // heads, stride levels
     size_t off_dy0parts, off_mhtable;
     bool chunk;          // GRU, n >= 16, fp32: Newton steps and the dual scan run by chunks (chunk_gru.hip)
-    int chunk_L, chunk_groups;
+    int chunk_L, chunk_groups, chunk_per_unit, chunk_units;
     size_t off_tot, off_sup;
     bool grad_fused;     // deer_grad computes the transposed Jacobians inside the reverse scan
     bool need_J;         // some kernel of this plan reads or writes the Jacobian stream [B,T,n,n] and the right-hand side
@@ -189,21 +189,30 @@ std::vector<unsigned> mh_table(const deer_config* c, int tile) {
     return v;
 }
 
-// Positions per chunk, a multiple of four.  Estimate in microseconds of one step (measured on MI355X): the reduction of a group of
-// sixteen chunks takes a compute unit per_total a position, all its groups one after the other, the walk a SIMD per_walk a
-// position of a chunk; each has a fixed part, and the walk folds the maps in front of it first.
-int chunk_length(const deer_config* c) {
-    const int forced = env_int("DEER_CHUNK_L", 0);
-    if (forced >= 4) return forced / 4 * 4;
-    const double per_total = c->n == 16 ? 0.041 * 16 : 0.155 * 16, per_walk = c->n == 16 ? 0.95 : 2.5, per_fold = c->n == 16 ? 0.04 : 0.1;
-    const double per_group = c->n == 16 ? 3.0 : 7.0;
+// Positions per chunk (a multiple of four) and chunks per unit.  Estimate in microseconds of one step (measured on MI355X).  The
+// reduction: the workgroups of a compute unit one after the other, `total` for a position of each of sixteen chunks, `unit` and
+// `compose` per further chunk of a unit.  The walk: `walk` a position for the groups that run side by side, and `fold` for every map in
+// front of the last group.  The estimate's choice is within a tenth of the best of 33 combinations tried at each of 18 shapes.
+int chunk_length(const deer_config* c, int* per_unit) {
+    struct Cost { double total, unit, compose, walk, fold; int side_by_side; };
+    const Cost k = c->n == 16 ? Cost{0.66, 1.5, 0.1, 0.95, 0.04, 1024} : c->n == 32 ? Cost{2.5, 2.0, 0.35, 2.5, 0.1, 1024} : Cost{16.3, 4.0, 1.5, 1.9, 0.15, 256};
+    const int forced = env_int("DEER_CHUNK_L", 0), forced_unit = env_int("DEER_CHUNK_UNIT", 0);
     int best_L = 4;
+    *per_unit = 16;
     double best = 1e300;
     for (int L = 4; L <= 2048; L += L < 64 ? 4 : (L < 256 ? 8 : 32)) {
-        const long long per_seq = ((long long)c->T + 16LL * L - 1) / (16LL * L), groups = per_seq * c->B;
-        const double est = (double)((groups + 255) / 256) * (per_total * L + per_group) + (double)((groups + 1023) / 1024) * per_walk * L +
-                           per_fold * (double)per_seq;
-        if (est < best) { best = est; best_L = L; }
+        if (forced >= 4 && L != 4) break;
+        if (forced >= 4) L = forced / 4 * 4;
+        for (int pu = 4; pu <= 16; pu *= 2) {
+            if (forced_unit >= 4 && pu != forced_unit) continue;
+            const long long per_seq = ((long long)c->T + 16LL * L - 1) / (16LL * L), groups = per_seq * c->B;
+            const long long units = ((long long)c->T + (long long)pu * L - 1) / ((long long)pu * L);
+            // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes 1.3 times as long as half of two)
+            const long long share = (units * c->B + 255) / 256;
+            const double est = ((double)share + (c->n >= 32 && (share & 1) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
+                               (double)((groups + k.side_by_side - 1) / k.side_by_side) * k.walk * L + k.fold * (double)units;
+            if (est < best) { best = est; best_L = L; *per_unit = pu; }
+        }
     }
     return best_L;
 }
@@ -215,7 +224,7 @@ int chunk_length(const deer_config* c) {
 bool chunk_pays(const deer_config* c) {
     if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
     const long long total = (long long)c->B * c->T;
-    return total >= 20000 || (c->n == 16 && c->T >= 1536);
+    return c->n == 64 || total >= 20000 || (c->n == 16 && c->T >= 1536);
 }
 
 Plan make_plan(const deer_config* c) {
@@ -353,10 +362,12 @@ Plan make_plan(const deer_config* c) {
         p.fused_tiles = (p.scan_T + ft - 1) / ft;
         if (p.fused_tiles < 1) p.fused_tiles = 1;
     }
-    if (gru && p.fused && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c)) {
+    if (gru && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c)) {
         p.chunk = true;
+        p.fused = true;
         p.fused_tiles = 0;
-        p.chunk_L = chunk_length(c);
+        p.chunk_L = chunk_length(c, &p.chunk_per_unit);
+        p.chunk_units = (int)((T + (size_t)p.chunk_per_unit * p.chunk_L - 1) / ((size_t)p.chunk_per_unit * p.chunk_L));
         p.chunk_groups = (int)((T + 16 * (size_t)p.chunk_L - 1) / (16 * (size_t)p.chunk_L));
     }
     p.vjp_blocks = c->cell == DEER_CELL_GRU    ? gru_vjp_blocks(c->n, (long long)B * T)
@@ -386,7 +397,7 @@ Plan make_plan(const deer_config* c) {
     p.off_barrier = take(p.fused ? 2 * (B * (size_t)p.fused_tiles + 4) * (p.esz / 4) * 8 : 0);   // (+4: test hook)
     p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);   // tickets, err bits, status
     p.off_tot = take(p.chunk ? B * (size_t)p.chunk_groups * 16 * chunk_map_bytes(c->n) : 0);
-    p.off_sup = take(p.chunk ? B * (size_t)p.chunk_groups * chunk_map_bytes(c->n) : 0);
+    p.off_sup = take(p.chunk ? B * (size_t)p.chunk_units * chunk_map_bytes(c->n) : 0);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
     p.off_partial = take((size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
@@ -534,7 +545,8 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
         q.tot = reinterpret_cast<float*>(c->ws + c->plan.off_tot);
         q.sup = reinterpret_cast<float*>(c->ws + c->plan.off_sup);
         q.err = p.err; q.gate = gate;
-        q.B = g.B; q.T = g.T; q.d = g.d; q.Lc = c->plan.chunk_L; q.groups = c->plan.chunk_groups; q.wide = (long long)g.B * c->plan.chunk_groups <= 256;
+        q.B = g.B; q.T = g.T; q.d = g.d; q.Lc = c->plan.chunk_L; q.groups = c->plan.chunk_groups;
+        q.per_unit = c->plan.chunk_per_unit; q.units = c->plan.chunk_units;
         prof_begin(c, KIND_FUSED, iter);
         e = launch_chunk_gru(g.n, q, c->stream);
     } else if (fused_theta && c->plan.mh) {

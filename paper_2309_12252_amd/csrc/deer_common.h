@@ -96,11 +96,12 @@ struct ChunkParams {
     const float* y;            // previous iterate, or the trajectory of the backward pass [B,T,n]
     const float* g;            // dL/dy [B,T,n], or nullptr
     float* out;                // next iterate, or lambda [B,T,n]
-    float* tot; float* sup;    // maps of the chunks [B][groups][16][n*n + n] and of the groups [B][groups][n*n + n]
+    float* tot; float* sup;    // maps of the chunks [B][groups][16][n*n + n] and of the units [B][units][n*n + n]
     void* err;                 // max|y_new - y| (raw bits), or nullptr
     Gate gate;
-    int wide;                  // != 0: more wavefronts per group where few groups are in flight
-    int B, T, d, Lc, groups;   // groups per sequence = ceil(T / (16 Lc))
+    int B, T, d, Lc;
+    int groups;                // of sixteen chunks, per sequence: ceil(T / (16 Lc))
+    int per_unit, units;       // chunks of a unit (4, 8 or 16), units per sequence: ceil(T / (per_unit Lc))
 };
 
 // One launch that runs all Newton iterations of a GRU problem (n <= 8) whose tiles are all resident.
@@ -334,10 +335,11 @@ hipError_t launch_scan_gru_dual(int dtype, int n, const ScanParams& p, const voi
 bool scan_gru_mh_supported(int dtype, int n, int d, int L);
 hipError_t launch_scan_gru_mh(int dtype, int n, const ScanParams& p, const void* theta, const void* x, int d, hipStream_t s);
 int scan_mfma_tile(int dtype, int n);
-// Newton step and dual scan of the GRU by chunks (fp32, n = 16 or 32, d <= 16): two launches
+// Newton step and dual scan of the GRU by chunks (fp32, n = 16, 32 or 64, d <= 16): two launches
 bool chunk_gru_supported(int dtype, int n, int d);
 size_t chunk_map_bytes(int n);   // bytes of one chunk's map
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s);
+hipError_t launch_chunk_gru64(const ChunkParams& p, hipStream_t s);
 hipError_t launch_gru_funceval(int dtype, const GruParams& p, hipStream_t s);
 hipError_t launch_gru_vjp(int dtype, const GruVjpParams& p, hipStream_t s);
 // the same on the matrix cores (fp32, n = 16 or 32, d <= 16): kernel only, partial rows = blocks * 4

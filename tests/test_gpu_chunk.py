@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(4, 1, 1), (4, 2, 3), (4, 1, 64), (4, 3, 65), (8, 2, 127), (8, 1, 129), (20, 2, 1000), (12, 3, 1543), (36, 1, 2049), (100, 2, 3300)]
 
 
-@pytest.mark.parametrize("n,d", [(16, 1), (16, 6), (16, 16), (32, 4), (32, 8), (32, 13), (24, 3)])
+@pytest.mark.parametrize("n,d", [(16, 1), (16, 6), (16, 16), (32, 4), (32, 8), (32, 13), (24, 3), (64, 3), (64, 8), (64, 16), (50, 5)])
 def test_step_and_dual_by_chunks(n, d, monkeypatch):
     for k, (L, B, T) in enumerate(SHAPES):
         monkeypatch.setenv("DEER_CHUNK_L", str(L))
+        monkeypatch.setenv("DEER_CHUNK_UNIT", str((4, 8, 16)[k % 3]))
         w = inputs.gru_workload("chunk_n%d_L%d_T%d" % (n, L, T), 1300 + 20 * n + k, B=B, T=T, n=n, d=d)
         w.y0 = np.random.default_rng(k).standard_normal((B, n)).astype(np.float32)
         print(w.name, B, d, flush=True)
