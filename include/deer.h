@@ -236,7 +236,7 @@ void deer_destroy(deer_ctx* ctx);
 /* Environment.  Every variable the library reads; all are meant for tests and measurements, none changes a
  * result beyond rounding.  Read by deer_workspace_bytes() and deer_create() (the plan and the workspace size
  * depend on them), except DEER_VJP_MFMA and DEER_MLP_MFMA, which deer_grad() / deer_eval() read at each call.
- *   DEER_FUSED=0        GRU: run the cell kernel and the plain scan as two launches per iteration (needs the
+ *   DEER_FUSED=0        GRU, LSTM, LEM: run the cell kernel and the plain scan as two launches per iteration (needs the
  *                       Jacobian stream in the workspace) instead of the scan with the cell inside
  *   DEER_GRAD_FUSED=0   GRU deer_grad(): Jacobian kernel + plain reverse scan instead of the reverse scan with the
  *                       cell inside (needs the Jacobian stream in the workspace)
@@ -245,9 +245,9 @@ void deer_destroy(deer_ctx* ctx);
  *                       tile shapes of the n <= 8 kernels: positions per lane group (1, 2, 4, 8, 10, 12, 16; 24 for
  *                       the plain n = 4 scan) and wavefronts per tile (4 or 8); ignored when no such variant exists
  *   DEER_CHUNK_L, DEER_CHUNK_UNIT
- *                       GRU, n = 16, 32, 64 in fp32: positions per chunk of the step by chunks (a multiple of four, at least
- *                       four), which is then taken at every size (by default where it is faster), and chunks per
- *                       workgroup of its first launch (4, 8 or 16)
+ *                       GRU with n = 16, 32, 64, LSTM and LEM in fp32: positions per chunk of the step by chunks (a multiple of
+ *                       four, at least four), which is then taken at every size (by default where it is faster), and
+ *                       chunks per workgroup of its first launch (4, 8 or 16)
  *   DEER_BATCH          Newton iterations enqueued per host round trip on a fresh context (1..8, default 4)
  *   DEER_VJP_MFMA=0     vector-ALU kernels for the vector-Jacobian products instead of the matrix-core ones
  *   DEER_MLP_MFMA=0     MLP fields outside the two-layer tanh shapes (fp32, n = 8, width 32 or 64): vector-ALU field

@@ -1,0 +1,683 @@
+// Newton step and dual scan of the LSTM and the LEM by chunks in fp32 (the scheme of chunk_gru.hip: maps of chunks, then a walk of
+// sixteen chunks per wavefront), equations and factors of the cells in cell_lstm.hip.
+//
+// The state is two parts of u <= 16 units, (h | c) or (y | z); kernels hold UP = 8 or 16 units a part, the rest zero (zero
+// weights and zero state stay zero), and read and write the caller's rows of 2u scalars directly.  The Jacobian never exists
+// in memory, and the reduction uses its structure: a step of either cell is two triangular steps,
+//     LSTM   c' = f c + M h,             h' = D U_o h + a c'            M = sum of diag(factor) U over i, f, g
+//     LEM    z' = (1 - s1) z + M y,      y' = (1 - s2) y + F U_2 y + E U_y z'       M = C1 U_1 + C2 U_z
+// (in the differentials), so at UP = 16 the running product is multiplied by two or three u x u factors instead of one of
+// 2u x 2u.  At UP = 8 both parts share one 16 x 16 block: one dense factor (LSTM) or one per triangular step (LEM).
+//
+// Lane (g, r) of a wavefront evaluates units 4g .. 4g + 3 of position (column) r; at UP = 8 lanes g and g + 2 evaluate the same units
+// (the products with U then contract over 8 entries in two instructions: lane groups 0, 1 supply two of their four
+// units, groups 2, 3 the other two), groups 0, 1 answer for the rows of the first part, 2, 3 for those of the second.
+//
+// Bound: issue (matrix and vector instructions of a SIMD do not overlap).  Measured, a Newton step (Jacobian kernel and scan
+// before / both launches now): LSTM u = 8, d = 4, 16 x 50,000 positions 710 / 192 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 375 us.
+#include "chunk_common.h"
+
+namespace deer {
+
+namespace {
+
+enum { LSTM = 0, LEM = 1 };
+
+// Row factors of one unit.  LSTM: a = factor of U_i, b = of U_f, c = of U_g in dc', d = of U_o in dh', e = of dc' in dh', f = f.
+// LEM: a = factor of U_1, b = of U_z in dz', c = of U_2, d = of U_y in dy', e = 1 - s2, f = 1 - s1.
+struct Factors {
+    float n0, n1;   // new state, first and second part
+    float a, b, c, d, e, f;
+};
+
+template <int CELL, int UP, int DS>
+struct Cell {
+    static constexpr int KS = UP / 4;   // matrix instructions of a contraction over the units
+    float u[4][KS];    // operand A: row r (mod UP) of U_gate
+    float w[4][DS];
+    Acc b[4];
+
+    // entry of the contraction that lane group g supplies in instruction s
+    static __device__ __forceinline__ int kappa(int g, int s) { return UP == 16 ? 4 * g + s : 4 * (g & 1) + (g < 2 ? s : 2 + s); }
+    // operand B from the four units of a lane
+    static __device__ __forceinline__ float operand(const Acc& v, int g, int s) {
+        if constexpr (UP == 16) return v[s];
+        else {
+            const float lo = v[s], hi = v[s + 2];   // (both by constant index)
+            return g < 2 ? lo : hi;
+        }
+    }
+    __device__ __forceinline__ void load(const float* __restrict__ th, int n, int d, int g, int r) {
+        const float* __restrict__ U = th + 4 * n * d;
+        const float* __restrict__ bias = U + 4 * n * n;
+        const int row = min(r % UP, n - 1);
+        const bool in = r % UP < n;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const int k = kappa(g, s);
+                const float v = U[(q * n + row) * n + min(k, n - 1)];
+                u[q][s] = in && k < n ? v : 0.f;
+            }
+#pragma unroll
+            for (int s = 0; s < DS; ++s) {
+                const int k = DS * g + s;
+                const float v = th[(q * n + row) * d + min(k, d - 1)];
+                w[q][s] = in && k < d ? v : 0.f;
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int j = (4 * g + v) % UP;
+                const float t = bias[q * n + min(j, n - 1)];
+                b[q][v] = j < n ? t : 0.f;
+            }
+        }
+    }
+    // U_gate times a vector whose units the lanes hold, added to acc
+    __device__ __forceinline__ Acc times(int q, const Acc& x, Acc acc, int g) const {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) acc = mfma(u[q][s], operand(x, g, s), acc);
+        return acc;
+    }
+    // the cell at the lane's four units of sixteen positions
+    __device__ __forceinline__ void eval(Factors (&o)[4], const Acc& s0, const Acc& s1, const float (&x)[DS], float dt, int g) const {
+        Acc a[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            a[q] = b[q];
+#pragma unroll
+            for (int s = 0; s < DS; ++s) a[q] = mfma(w[q][s], x[s], a[q]);
+            if (CELL == LSTM || q < 3) a[q] = times(q, s0, a[q], g);
+        }
+        if constexpr (CELL == LSTM) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float i = feed_sigmoid(a[0][v]), f = feed_sigmoid(a[1][v]), gg = feed_tanh(a[2][v]), oo = feed_sigmoid(a[3][v]);
+                const float cn = f * s1[v] + i * gg, tc = feed_tanh(cn);
+                o[v].n0 = oo * tc;
+                o[v].n1 = cn;
+                o[v].a = gg * i * (1.f - i);
+                o[v].b = s1[v] * f * (1.f - f);
+                o[v].c = i * (1.f - gg * gg);
+                o[v].d = tc * oo * (1.f - oo);
+                o[v].e = oo * (1.f - tc * tc);
+                o[v].f = f;
+            }
+        } else {
+            Acc zn;
+            const float inv = 1.f / dt;
+            float s2[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float t1 = dt * feed_sigmoid(a[0][v]), gz = feed_tanh(a[2][v]);
+                s2[v] = dt * feed_sigmoid(a[1][v]);
+                zn[v] = (1.f - t1) * s1[v] + t1 * gz;
+                o[v].n1 = zn[v];
+                o[v].a = t1 * (1.f - t1 * inv) * (gz - s1[v]);
+                o[v].b = t1 * (1.f - gz * gz);
+                o[v].f = 1.f - t1;
+            }
+            a[3] = times(3, zn, a[3], g);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float gy = feed_tanh(a[3][v]);
+                o[v].n0 = (1.f - s2[v]) * s0[v] + s2[v] * gy;
+                o[v].c = s2[v] * (1.f - s2[v] * inv) * (gy - s0[v]);
+                o[v].d = s2[v] * (1.f - gy * gy);
+                o[v].e = 1.f - s2[v];
+            }
+        }
+    }
+};
+
+// four consecutive units of one part of a row of 2 n scalars (units past n: zero)
+template <bool VEC>
+__device__ __forceinline__ Acc load_units(const float* __restrict__ part, int j0, int n) {
+    Acc o = zero4();
+    if constexpr (VEC) {
+        const Acc t = load4(part + min(j0, n - 4));
+        if (j0 < n) o = t;
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float t = part[min(j0 + v, n - 1)];
+            o[v] = j0 + v < n ? t : 0.f;
+        }
+    }
+    return o;
+}
+template <bool VEC>
+__device__ __forceinline__ void store_units(float* __restrict__ part, int j0, int n, Acc x) {
+    if constexpr (VEC) {
+        if (j0 < n) store4(part + j0, x);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (j0 + v < n) part[j0 + v] = x[v];
+    }
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// Maps of the chunks.  Forward: Q <- J_i^T Q from the last position to the first (Q = P^T); dual: S <- J_i S from the first to the last; see
+// chunk_gru.hip.  The factors of sixteen positions sit in the wavefront's LDS slice, [kind][position][row].
+// ------------------------------------------------------------------------------------------------------------------
+template <int CELL, int UP> struct Slice;
+template <int CELL> struct Slice<CELL, 16> { static constexpr int kinds = 8; };   // a .. f, then the vector's two parts; row = unit
+template <> struct Slice<LSTM, 8> { static constexpr int kinds = 6; };            // factors of U_i, U_f, U_g, U_o, diagonal, vector; row of the state
+template <> struct Slice<LEM, 8> { static constexpr int kinds = 4; };             // two factors and the diagonal of the row's step, vector
+
+template <int CELL, int UP, int DS, bool VEC, bool REV>
+__global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
+    constexpr int N = 2 * UP, NB = N / 16, MS = map_size<N>(), KINDS = Slice<CELL, UP>::kinds;
+    __shared__ __align__(16) float sF[4][KINDS * 256];
+    if (gate_closed<float>(p.gate)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
+    const int T = p.T, d = p.d, Lc = p.Lc, n = p.cell_units, ld = 2 * n;
+    const float dt = p.dt;
+    const int chunks = (T + Lc - 1) / Lc, first = unit * p.per_unit, cpw = p.per_unit / 4;
+    const float* __restrict__ yb = p.y + (long long)b * T * ld;
+    const float* __restrict__ xb = p.x + (long long)b * T * d;
+    const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * ld : nullptr;
+    const float* __restrict__ gb = REV ? p.g + (long long)b * T * ld : nullptr;
+    float* __restrict__ tot = p.tot + ((long long)b * p.groups * 16 + first) * MS;
+    float* __restrict__ sFw = sF[wave];
+    const int q_lo = cpw * wave, q_hi = min(q_lo + cpw, chunks - first);   // chunks of this wavefront (inside the unit)
+    const int lo = (first + q_lo) * Lc, hi = min(T, (first + q_hi) * Lc), blocks = (hi - lo + 15) / 16;
+    const int j0 = (4 * g) % UP;   // this lane's units
+
+    Acc s0, s1, v0, v1;
+    float x[DS];
+    auto request = [&](int blk) {
+        int pos = (REV ? lo + 16 * blk : hi - 16 * (blk + 1)) + r;
+        pos = min(max(pos, lo), hi - 1);
+        const float* sp = REV ? yb + (long long)pos * ld : (pos > 0 ? yb + (long long)(pos - 1) * ld : y0b);
+        const float* vp = (REV ? gb : yb) + (long long)pos * ld;
+        s0 = sp ? load_units<VEC>(sp, j0, n) : zero4();
+        s1 = sp ? load_units<VEC>(sp + n, j0, n) : zero4();
+        v0 = load_units<VEC>(vp, j0, n);
+        v1 = load_units<VEC>(vp + n, j0, n);
+        load_x<DS>(x, xb + (long long)(REV ? min(pos + 1, T - 1) : pos) * d, d, g);
+    };
+    if (q_lo < q_hi) {
+        request(0);
+        Cell<CELL, UP, DS> cell;
+        cell.load(p.theta, n, d, g, r);
+        // weights of the assembly
+        //   UP = 16: forward U_gate[4g + v][r], dual U_gate[r][4g + v] (the gate operands)
+        //   UP = 8: the block of J (LSTM) or of its two steps (LEM) that entry (4g + v, r) of operand A^T (forward) or (r, 4g + v)
+        //   (dual) lies in
+        float wa[4][4], dm[4], im[4];
+        {
+            const float* __restrict__ U = p.theta + 4 * n * d;
+            auto at = [&](int q, int row, int col) {
+                const float t = U[(q * n + min(row, n - 1)) * n + min(col, n - 1)];
+                return row < n && col < n ? t : 0.f;
+            };
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = REV ? r : 4 * g + v, col = REV ? 4 * g + v : r;   // entry of J (UP = 8: rows 0..7 first part)
+                if constexpr (UP == 16) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) wa[q][v] = at(q, row, col);
+                    dm[v] = im[v] = 0.f;
+                } else if constexpr (CELL == LSTM) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) wa[q][v] = col < 8 ? at(q, row & 7, col) : 0.f;
+                    dm[v] = (col == 8 + (row & 7)) ? 1.f : 0.f;
+                    im[v] = 0.f;
+                } else {
+                    // second step (rows of y): U_2 in front of y, U_y in front of z; first step (rows of z): U_1, U_z in front of y
+                    wa[0][v] = row < 8 ? (col < 8 ? at(1, row, col) : at(3, row, col - 8)) : 0.f;
+                    wa[1][v] = row >= 8 && col < 8 ? at(0, row - 8, col) : 0.f;
+                    wa[2][v] = row >= 8 && col < 8 ? at(2, row - 8, col) : 0.f;
+                    wa[3][v] = 0.f;
+                    dm[v] = (row == col && row < 8) ? 1.f : 0.f;    // diagonal 1 - s2 in the second step, 1 in the first
+                    im[v] = (row == col && row >= 8) ? 1.f : 0.f;   // 1 in the second step, 1 - s1 in the first
+                }
+            }
+        }
+        float dsel[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dsel[v] = (4 * g + v == r) ? 1.f : 0.f;
+
+        Acc Q[NB][NB];
+        float vec[NB];
+        auto reset = [&]() {
+#pragma unroll
+            for (int X = 0; X < NB; ++X) {
+                vec[X] = 0.f;
+#pragma unroll
+                for (int C = 0; C < NB; ++C)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] : 0.f;
+            }
+        };
+        reset();
+        int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
+        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+
+        for (int blk = 0; blk < blocks; ++blk) {
+            const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            {
+                Factors k[4];
+                cell.eval(k, s0, s1, x, dt, g);
+                Acc r0 = v0, r1 = v1;
+                if constexpr (!REV)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) { r0[v] = k[v].n0 - v0[v]; r1[v] = k[v].n1 - v1[v]; }
+                Acc o[KINDS];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if constexpr (UP == 16) {
+                        o[0][v] = k[v].a; o[1][v] = k[v].b; o[2][v] = k[v].c; o[3][v] = k[v].d; o[4][v] = k[v].e; o[5][v] = k[v].f;
+                        o[6][v] = r0[v]; o[KINDS - 1][v] = r1[v];
+                    } else if constexpr (CELL == LSTM) {
+                        const float s = g < 2 ? k[v].e : 1.f;   // rows of h: dh' = d U_o h + e dc'
+                        o[0][v] = s * k[v].a; o[1][v] = s * k[v].b; o[2][v] = s * k[v].c;
+                        o[3][v] = g < 2 ? k[v].d : 0.f;
+                        o[4][v] = s * k[v].f;
+                        o[KINDS - 1][v] = g < 2 ? r0[v] : r1[v];
+                    } else {
+                        o[0][v] = g < 2 ? k[v].c : k[v].a;
+                        o[1][v] = g < 2 ? k[v].d : k[v].b;
+                        o[2][v] = g < 2 ? k[v].e : k[v].f;
+                        o[KINDS - 1][v] = g < 2 ? r0[v] : r1[v];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < KINDS; ++i) store4(sFw + i * 256 + r * 16 + 4 * g, o[i]);
+            }
+            wave_lds_fence();
+            if (blk + 1 < blocks) request(blk + 1);
+
+            const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16;
+#pragma unroll 2
+            for (int k = 0; k < c_hi - c_lo; ++k) {
+                const int c = REV ? c_lo + k : c_hi - 1 - k;
+                const float* fp = sFw + c * 16;   // factors of the position: of rows 4g + v, or of row r
+                auto rows = [&](int i) { return load4(fp + i * 256 + 4 * g); };
+                auto row_r = [&](int i) { return fp[i * 256 + r]; };
+                // a factor of operand A: forward it goes with the contraction index 4g + v, dual with the row r
+                auto fac = [&](int i) {
+                    if constexpr (!REV) return rows(i);
+                    else { const float t = row_r(i); return Acc{t, t, t, t}; }
+                };
+                if constexpr (UP == 16) {
+                    const Acc r0 = rows(6), r1 = rows(KINDS - 1);
+#pragma unroll
+                    for (int C = 0; C < NB; ++C)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) vec[C] += Q[0][C][v] * r0[v] + Q[NB - 1][C][v] * r1[v];
+                    const Acc fa = fac(0), fb = fac(1), fc = fac(2), fd = fac(3), fe = rows(4), ff = rows(5);
+                    Acc m, n2, n3;   // M; LSTM: D U_o; LEM: E U_y and F U_2
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if constexpr (CELL == LSTM) {
+                            m[v] = fa[v] * wa[0][v] + (fb[v] * wa[1][v] + fc[v] * wa[2][v]);
+                            n2[v] = fd[v] * wa[3][v];
+                        } else {
+                            m[v] = fa[v] * wa[0][v] + fb[v] * wa[2][v];
+                            n2[v] = fd[v] * wa[3][v];
+                            n3[v] = fc[v] * wa[1][v];
+                        }
+                    }
+#pragma unroll
+                    for (int C = 0; C < NB; ++C) {
+                        Acc &Q0 = Q[0][C], &Q1 = Q[NB - 1][C];
+                        if constexpr (CELL == LSTM && !REV) {
+                            // Z = Q1 + e Q0;  Q0 <- (D U_o)^T Q0 + M^T Z,  Q1 <- f Z
+                            Acc z, t = zero4();
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) z[v] = Q1[v] + fe[v] * Q0[v];
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t = mfma(n2[v], Q0[v], t);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t = mfma(m[v], z[v], t);
+                            Q0 = t;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) Q1[v] = ff[v] * z[v];
+                        } else if constexpr (CELL == LSTM) {
+                            // S1 <- f S1 + M S0,  S0 <- D U_o S0 + e S1
+                            Acc t, w;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t[v] = ff[v] * Q1[v];
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t = mfma(m[v], Q0[v], t);
+                            w = zero4();
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) w = mfma(n2[v], Q0[v], w);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) Q0[v] = w[v] + fe[v] * t[v];
+                            Q1 = t;
+                        } else if constexpr (!REV) {
+                            // Z = Q1 + (E U_y)^T Q0;  Q0 <- (1 - s2) Q0 + (F U_2)^T Q0 + M^T Z,  Q1 <- (1 - s1) Z
+                            Acc z = Q1, t;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t[v] = fe[v] * Q0[v];
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                z = mfma(n2[v], Q0[v], z);
+                                t = mfma(n3[v], Q0[v], t);
+                            }
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t = mfma(m[v], z[v], t);
+                            Q0 = t;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) Q1[v] = ff[v] * z[v];
+                        } else {
+                            // S1 <- (1 - s1) S1 + M S0,  S0 <- (1 - s2) S0 + F U_2 S0 + E U_y S1
+                            Acc t, w;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                t[v] = ff[v] * Q1[v];
+                                w[v] = fe[v] * Q0[v];
+                            }
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                t = mfma(m[v], Q0[v], t);
+                                w = mfma(n3[v], Q0[v], w);
+                            }
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) w = mfma(n2[v], t[v], w);
+                            Q0 = w;
+                            Q1 = t;
+                        }
+                    }
+                } else {
+                    const Acc rv = rows(KINDS - 1);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) vec[0] += Q[0][0][v] * rv[v];
+                    if constexpr (CELL == LSTM) {
+                        const Acc fi = fac(0), ff = fac(1), fg = fac(2), fo = fac(3), fd = fac(4);
+                        Acc t = zero4();
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const float a = fi[v] * wa[0][v] + (ff[v] * wa[1][v] + (fg[v] * wa[2][v] + (fo[v] * wa[3][v] + fd[v] * dm[v])));
+                            t = mfma(a, Q[0][0][v], t);
+                        }
+                        Q[0][0] = t;
+                    } else {
+                        const Acc f0 = fac(0), f1 = fac(1), fd = fac(2);
+                        // factor of the second step: F in front of y, E in front of z
+                        Acc a1, a2;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int col = REV ? 4 * g + v : r;
+                            a2[v] = (col < 8 ? f0[v] : f1[v]) * wa[0][v] + (fd[v] * dm[v] + im[v]);
+                            a1[v] = f0[v] * wa[1][v] + (f1[v] * wa[2][v] + (fd[v] * im[v] + dm[v]));
+                        }
+                        Acc t = zero4(), w = zero4();
+                        if constexpr (!REV) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t = mfma(a2[v], Q[0][0][v], t);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) w = mfma(a1[v], t[v], w);
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) t = mfma(a1[v], Q[0][0][v], t);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) w = mfma(a2[v], t[v], w);
+                        }
+                        Q[0][0] = w;
+                    }
+                }
+                if (base + c == edge) {
+                    // the chunk's map: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
+                    float* o = tot + (long long)q * MS;
+#pragma unroll
+                    for (int C = 0; C < NB; ++C) {
+#pragma unroll
+                        for (int X = 0; X < NB; ++X) store4(o + (16 * C + r) * N + 16 * X + 4 * g, Q[X][C]);
+                        const float s = sum_groups(vec[C]);
+                        if (g == 0) o[N * N + 16 * C + r] = s;
+                    }
+                    reset();
+                    q += REV ? 1 : -1;
+                    edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
+                }
+            }
+            wave_lds_fence();
+        }
+    }
+    __syncthreads();
+    // the units of the group that nothing follows need no map
+    const int pu = 16 / p.per_unit;
+    const bool needed = REV ? unit >= pu : unit < (p.groups - 1) * pu;
+    if (needed && wave <= NB) compose_unit<N, REV>(tot, p.sup + ((long long)b * p.units + unit) * MS, min(p.per_unit, chunks - first), wave, g, r);
+}
+
+// ------------------------------------------------------------------------------------------------------------------
+// The walk: one wavefront per group, its sixteen chunks are the columns of every product.
+// ------------------------------------------------------------------------------------------------------------------
+template <int CELL, int UP, int DS, bool VEC, bool REV>
+__global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
+    constexpr int N = 2 * UP, KS = UP / 4;
+    __shared__ unsigned s_max[4];
+    if (gate_closed<float>(p.gate)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int T = p.T, d = p.d, Lc = p.Lc, n = p.cell_units, ld = 2 * n;
+    const float dt = p.dt;
+    const unsigned id = blockIdx.x * 4u + (unsigned)wave;
+    const int b = (int)(id % (unsigned)p.B), grp = (int)(id / (unsigned)p.B);
+    unsigned emax = 0u;   // largest |y_new - y| as raw bits (a NaN compares above everything)
+    if (grp < p.groups) {
+        const int chunks = (T + Lc - 1) / Lc, nq = min(16, chunks - 16 * grp);
+        const long long first = (long long)b * T + (long long)16 * grp * Lc;
+        const int j0 = (4 * g) % UP;
+        const bool part0 = UP == 16 || g < 2, part1 = UP == 16 || g >= 2;   // parts this lane writes
+        const float* __restrict__ yb = p.y + first * ld;
+        const float* __restrict__ xb = p.x + first * d;
+        const float* __restrict__ gb = REV ? p.g + first * ld : nullptr;
+        float* __restrict__ ob = p.out + first * ld;
+        const int a = r * Lc, end = T - 16 * grp * Lc;
+        auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
+
+        // requested R - 1 (dual: R) steps ahead; slots named by t mod R
+        constexpr int R = 4;
+        Acc y0r[R], y1r[R], g0r[REV ? R : 1], g1r[REV ? R : 1];
+        float xr[R][DS];
+        auto ask_y = [&](int j, int t) {
+            const unsigned o = row(REV ? a + Lc - 1 - t : a + t) * (unsigned)ld;
+            y0r[j] = load_units<VEC>(yb + o, j0, n);
+            y1r[j] = load_units<VEC>(yb + o + n, j0, n);
+            if constexpr (REV) {
+                g0r[j] = load_units<VEC>(gb + o, j0, n);
+                g1r[j] = load_units<VEC>(gb + o + n, j0, n);
+            }
+        };
+        auto ask_x = [&](int j, int t) {
+            const unsigned o = row(REV ? a + Lc - t : a + t) * (unsigned)d;
+#pragma unroll
+            for (int s = 0; s < DS; ++s) xr[j][s] = xb[o + min(DS * g + s, d - 1)];
+        };
+        if constexpr (!REV) {
+            const bool start = a == 0 && grp == 0;
+            const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * ld : nullptr;
+            const float* hp = start ? y0b : yb + (long long)(min(a, end) - 1) * ld;
+            y0r[R - 1] = hp ? load_units<VEC>(hp, j0, n) : zero4();
+            y1r[R - 1] = hp ? load_units<VEC>(hp + n, j0, n) : zero4();
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (REV || j < R - 1) ask_y(j, j);
+            ask_x(j, j);
+        }
+        Cell<CELL, UP, DS> cell;
+        cell.load(p.theta, n, d, g, r);
+        float ut[REV ? 4 : 1][KS];   // dual: U_gate^T as operand A
+        if constexpr (REV) {
+            const float* __restrict__ U = p.theta + 4 * n * d;
+            const int col = min(r % UP, n - 1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const int k = Cell<CELL, UP, DS>::kappa(g, s);
+                    const float v = U[(q * n + min(k, n - 1)) * n + col];
+                    ut[q][s] = k < n && r % UP < n ? v : 0.f;
+                }
+        }
+        auto times_t = [&](int q, const Acc& x, Acc acc) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) acc = mfma(ut[REV ? q : 0][s], Cell<CELL, UP, DS>::operand(x, g, s), acc);
+            return acc;
+        };
+
+        // forward: correction of the state in front of the position; dual: lambda at the time after it
+        Acc e0, e1;
+        {
+            Acc e[N / 16];
+            fold_carries<N, REV>(p, b, grp, nq, g, r, e);
+            if constexpr (UP == 16) {
+                e0 = e[0];
+                e1 = e[N / 16 - 1];
+            } else {
+                Acc o;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] = __shfl_xor(e[0][v], 32);
+                e0 = g < 2 ? e[0] : o;
+                e1 = g < 2 ? o : e[0];
+            }
+        }
+
+        for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int t = t0 + j, rel = REV ? a + Lc - 1 - t : a + t;
+                const bool live = rel < end;
+                const int jh = REV ? j : (j + R - 1) % R;
+                Factors k[4];
+                cell.eval(k, y0r[jh], y1r[jh], xr[j], dt, g);
+                Acc n0, n1;
+                if constexpr (!REV) {
+                    if constexpr (CELL == LSTM) {
+                        const Acc ti = cell.times(0, e0, zero4(), g), tf = cell.times(1, e0, zero4(), g);
+                        const Acc tg = cell.times(2, e0, zero4(), g), to = cell.times(3, e0, zero4(), g);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const float dc = k[v].f * e1[v] + (k[v].a * ti[v] + (k[v].b * tf[v] + k[v].c * tg[v]));
+                            n1[v] = k[v].n1 + dc;
+                            n0[v] = k[v].n0 + (k[v].d * to[v] + k[v].e * dc);
+                        }
+                    } else {
+                        const Acc t1 = cell.times(0, e0, zero4(), g), t2 = cell.times(1, e0, zero4(), g), tz = cell.times(2, e0, zero4(), g);
+                        Acc dz;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            dz[v] = k[v].f * e1[v] + (k[v].a * t1[v] + k[v].b * tz[v]);
+                            n1[v] = k[v].n1 + dz[v];
+                        }
+                        const Acc ty = cell.times(3, dz, zero4(), g);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) n0[v] = k[v].n0 + (k[v].e * e0[v] + (k[v].c * t2[v] + k[v].d * ty[v]));
+                    }
+                } else {
+                    const Acc g0 = g0r[REV ? j : 0], g1 = g1r[REV ? j : 0];
+                    if constexpr (CELL == LSTM) {
+                        Acc di, df, dg, dd;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const float dc = e1[v] + k[v].e * e0[v];
+                            di[v] = k[v].a * dc;
+                            df[v] = k[v].b * dc;
+                            dg[v] = k[v].c * dc;
+                            dd[v] = k[v].d * e0[v];
+                            n1[v] = g1[v] + k[v].f * dc;
+                        }
+                        n0 = times_t(0, di, g0);
+                        const Acc s1 = times_t(1, df, zero4()), s2 = times_t(2, dg, zero4()), s3 = times_t(3, dd, zero4());
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) n0[v] += s1[v] + (s2[v] + s3[v]);
+                    } else {
+                        Acc dy, d2, d1, dz;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            dy[v] = k[v].d * e0[v];
+                            d2[v] = k[v].c * e0[v];
+                        }
+                        const Acc zn = times_t(3, dy, e1);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            d1[v] = k[v].a * zn[v];
+                            dz[v] = k[v].b * zn[v];
+                            n1[v] = g1[v] + k[v].f * zn[v];
+                            n0[v] = g0[v] + k[v].e * e0[v];
+                        }
+                        n0 = times_t(0, d1, n0);
+                        const Acc s1 = times_t(1, d2, zero4()), s2 = times_t(2, dz, zero4());
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) n0[v] += s1[v] + s2[v];
+                    }
+                }
+                if (live) {
+                    float* o = ob + (long long)rel * ld;
+                    if (part0) store_units<VEC>(o, j0, n, n0);
+                    if (part1) store_units<VEC>(o + n, j0, n, n1);
+                }
+                const unsigned mask = live ? 0x7fffffffu : 0u;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if constexpr (!REV) {
+                        e0[v] = n0[v] - y0r[j][v];
+                        e1[v] = n1[v] - y1r[j][v];
+                        emax = max(emax, max(__float_as_uint(e0[v]) & mask, __float_as_uint(e1[v]) & mask));
+                    } else {
+                        e0[v] = live ? n0[v] : 0.f;   // nothing follows the last time
+                        e1[v] = live ? n1[v] : 0.f;
+                    }
+                }
+                if constexpr (!REV) ask_y((j + R - 1) % R, t - 1 + R);
+                else ask_y(j, t + R);
+                ask_x(j, t + R);
+            }
+        }
+    }
+    if (!REV && p.err) {
+        // one read-modify-write per workgroup: all wavefronts end at about the same time and queue on one address
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) emax = max(emax, (unsigned)__shfl_xor((int)emax, o));
+        if (lane == 0) s_max[wave] = emax;
+        __syncthreads();
+        if (tid == 0) {
+            emax = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+            err_atomic_max(p.err, __uint_as_float(min(emax, 0x7f800000u)));
+        }
+    }
+}
+
+template <int CELL, int UP, int DS, bool VEC, bool REV>
+hipError_t launch_all(const ChunkParams& p, hipStream_t s) {
+    hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((cell_walk_kernel<CELL, UP, DS, VEC, REV>), dim3((unsigned)(((long long)p.B * p.groups + 3) / 4)), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+template <int CELL, int UP, int DS, bool VEC>
+hipError_t launch_v(const ChunkParams& p, hipStream_t s) {
+    return p.g ? launch_all<CELL, UP, DS, VEC, true>(p, s) : launch_all<CELL, UP, DS, VEC, false>(p, s);
+}
+template <int CELL, int UP, int DS>
+hipError_t launch_d(const ChunkParams& p, hipStream_t s) {
+    return p.cell_units % 4 == 0 ? launch_v<CELL, UP, DS, true>(p, s) : launch_v<CELL, UP, DS, false>(p, s);
+}
+template <int CELL>
+hipError_t launch_cell(const ChunkParams& p, hipStream_t s) {
+    if (p.cell_units <= 8) return p.d <= 4 ? launch_d<CELL, 8, 1>(p, s) : launch_d<CELL, 8, 2>(p, s);
+    return p.d <= 4 ? launch_d<CELL, 16, 1>(p, s) : launch_d<CELL, 16, 2>(p, s);
+}
+
+}  // namespace
+
+bool chunk_cells_supported(int dtype, int units, int d) { return dtype == 0 && units >= 1 && units <= 16 && d >= 1 && d <= 8; }
+
+size_t chunk_cells_map_bytes(int units) { return chunk_map_bytes(units <= 8 ? 16 : 32); }
+
+hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s) {
+    if (!chunk_cells_supported(0, p.cell_units, p.d) || !chunk_params_valid(p)) return hipErrorInvalidValue;
+    return lem ? launch_cell<LEM>(p, s) : launch_cell<LSTM>(p, s);
+}
+
+}  // namespace deer

@@ -550,9 +550,14 @@ bool chunk_gru_supported(int dtype, int n, int d) { return dtype == 0 && (n == 1
 
 size_t chunk_map_bytes(int n) { return ((size_t)n * n + n) * sizeof(float); }
 
+bool chunk_params_valid(const ChunkParams& p) {
+    return p.Lc >= 4 && p.Lc % 4 == 0 && (p.per_unit == 4 || p.per_unit == 8 || p.per_unit == 16) &&
+           p.groups == (int)((p.T + 16LL * p.Lc - 1) / (16LL * p.Lc)) &&
+           p.units == (int)((p.T + (long long)p.per_unit * p.Lc - 1) / ((long long)p.per_unit * p.Lc));
+}
+
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s) {
-    if (!chunk_gru_supported(0, n, p.d) || p.Lc < 4 || p.Lc % 4 != 0 || (p.per_unit != 4 && p.per_unit != 8 && p.per_unit != 16) ||
-        p.units != (int)((p.T + (long long)p.per_unit * p.Lc - 1) / ((long long)p.per_unit * p.Lc)) || p.groups != (int)((p.T + 16LL * p.Lc - 1) / (16LL * p.Lc))) return hipErrorInvalidValue;
+    if (!chunk_gru_supported(0, n, p.d) || !chunk_params_valid(p)) return hipErrorInvalidValue;
     if (n == 64) return launch_chunk_gru64(p, s);
     const bool rev = p.g != nullptr;
     if (n == 16) return rev ? launch_n<16, true>(p, s) : launch_n<16, false>(p, s);

@@ -113,6 +113,18 @@ int native_n(int n) {
 
 bool is_multihead(const deer_config* c);
 
+// LSTM and LEM in fp32 run by chunks (chunk_cells.hip) on the caller's rows of 2 units scalars where that is faster than the
+// Jacobian kernel and the scan.  Up to 4 units half of the 16 x 16 blocks would be padding and the stored Jacobians are small;
+// at 5 to 8 units a small problem is all latency.  Measured, microseconds a solve, Jacobian kernel and scan / chunks: LSTM of 4 units
+// 301 / 337 at 64 x 2,000 and 1,058 / 1,162 at 16 x 50,000; 8 units 119 / 132 at 1 x 500, 159 / 155 at 1 x 2,000, 303 / 210 at 4 x 5,000; 16 units
+// 184 / 165 at 1 x 500; LEM of 8 units 126 / 138 at 8 x 500, of 16 units 226 / 204 at 1 x 500.
+bool cell_by_chunks(const deer_config* user) {
+    if (!two_part_cell(user->cell) || !chunk_cells_supported(user->dtype, user->n, user->d)) return false;
+    if (env_int("DEER_FUSED", 1) == 0 || env_int("DEER_GRAD_FUSED", 1) == 0) return false;
+    if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
+    return user->n > 8 || (user->n > 4 && (user->T >= 1536 || (long long)user->B * user->T >= 8192));
+}
+
 // The configuration the kernels run: a plain GRU whose state size has no kernels of its own is embedded in the next
 // size that has (zero rows and columns in every weight: the extra channels stay at zero and the real ones never see
 // them, so iterates, iteration counts and gradients are those of the original cell).
@@ -121,7 +133,8 @@ deer_config internal_config(const deer_config* user) {
     if (c.cell == DEER_CELL_GRU && !is_multihead(user) && native_n(c.n) > 0) c.n = native_n(c.n);
     if (two_part_cell(c.cell)) {   // state (h | c) or (y | z) of 2 units entries in the next state size with a scan kernel
         c.reserved = user->n;
-        c.n = native_n(2 * user->n);
+        c.mlp_width = cell_by_chunks(user) ? 1 : 0;   // (a field these cells do not use: tells the plan)
+        c.n = c.mlp_width ? 2 * user->n : native_n(2 * user->n);
     }
     return c;
 }
@@ -195,7 +208,9 @@ std::vector<unsigned> mh_table(const deer_config* c, int tile) {
 // front of the last group.  The estimate's choice is within a tenth of the best of 33 combinations tried at each of 18 shapes.
 int chunk_length(const deer_config* c, int* per_unit) {
     struct Cost { double total, unit, compose, walk, fold; int side_by_side; };
-    const Cost k = c->n == 16 ? Cost{0.66, 1.5, 0.1, 0.95, 0.04, 1024} : c->n == 32 ? Cost{2.5, 2.0, 0.35, 2.5, 0.1, 1024} : Cost{16.3, 4.0, 1.5, 1.9, 0.15, 256};
+    const bool cell = two_part_cell(c->cell);
+    const Cost k = cell ? (c->reserved <= 8 ? Cost{0.75, 1.5, 0.1, 1.2, 0.04, 1024} : Cost{1.6, 2.0, 0.35, 1.8, 0.1, 1024})
+                 : c->n == 16 ? Cost{0.66, 1.5, 0.1, 0.95, 0.04, 1024} : c->n == 32 ? Cost{2.5, 2.0, 0.35, 2.5, 0.1, 1024} : Cost{16.3, 4.0, 1.5, 1.9, 0.15, 256};
     const int forced = env_int("DEER_CHUNK_L", 0), forced_unit = env_int("DEER_CHUNK_UNIT", 0);
     int best_L = 4;
     *per_unit = 16;
@@ -209,7 +224,7 @@ int chunk_length(const deer_config* c, int* per_unit) {
             const long long units = ((long long)c->T + (long long)pu * L - 1) / ((long long)pu * L);
             // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes 1.3 times as long as half of two)
             const long long share = (units * c->B + 255) / 256;
-            const double est = ((double)share + (c->n >= 32 && (share & 1) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
+            const double est = ((double)share + (!cell && c->n >= 32 && (share & 1) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
                                (double)((groups + k.side_by_side - 1) / k.side_by_side) * k.walk * L + k.fold * (double)units;
             if (est < best) { best = est; best_L = L; *per_unit = pu; }
         }
@@ -362,10 +377,12 @@ Plan make_plan(const deer_config* c) {
         p.fused_tiles = (p.scan_T + ft - 1) / ft;
         if (p.fused_tiles < 1) p.fused_tiles = 1;
     }
-    if (gru && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c)) {
+    const bool cell_chunk = two_part_cell(c->cell) && c->mlp_width == 1;
+    if (cell_chunk || (gru && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c))) {
         p.chunk = true;
         p.fused = true;
         p.fused_tiles = 0;
+        if (cell_chunk) p.tiles = 0;
         p.chunk_L = chunk_length(c, &p.chunk_per_unit);
         p.chunk_units = (int)((T + (size_t)p.chunk_per_unit * p.chunk_L - 1) / ((size_t)p.chunk_per_unit * p.chunk_L));
         p.chunk_groups = (int)((T + 16 * (size_t)p.chunk_L - 1) / (16 * (size_t)p.chunk_L));
@@ -376,7 +393,7 @@ Plan make_plan(const deer_config* c) {
                                             : mlp_general_vjp_blocks(c->dtype, c->n, c->mlp_width, c->mlp_hidden_layers, (long long)B * T);
 
     p.grad_fused = p.fused && env_int("DEER_GRAD_FUSED", 1) != 0 &&
-                   (p.mfma || scan_gru_dual_supported(c->dtype, c->n, c->d, p.fused_L, p.fused_W));
+                   (p.chunk || p.mfma || scan_gru_dual_supported(c->dtype, c->n, c->d, p.fused_L, p.fused_W));
     // The Jacobians exist in memory only where a kernel pair exchanges them: the ODE form, and the GRU sizes (or
     // knob settings) whose forward or backward pass runs the cell kernel followed by the plain scan.  With the
     // cell inside both scans the workspace is O(n T) instead of the O(n^2 T) of Sec. 3.5.
@@ -396,8 +413,9 @@ Plan make_plan(const deer_config* c) {
     // slots of the one-launch solve's grid barrier (two banks, one tagged scalar per workgroup)
     p.off_barrier = take(p.fused ? 2 * (B * (size_t)p.fused_tiles + 4) * (p.esz / 4) * 8 : 0);   // (+4: test hook)
     p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);   // tickets, err bits, status
-    p.off_tot = take(p.chunk ? B * (size_t)p.chunk_groups * 16 * chunk_map_bytes(c->n) : 0);
-    p.off_sup = take(p.chunk ? B * (size_t)p.chunk_units * chunk_map_bytes(c->n) : 0);
+    const size_t map = cell_chunk ? chunk_cells_map_bytes(c->reserved) : chunk_map_bytes(c->n);
+    p.off_tot = take(p.chunk ? B * (size_t)p.chunk_groups * 16 * map : 0);
+    p.off_sup = take(p.chunk ? B * (size_t)p.chunk_units * map : 0);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
     p.off_partial = take((size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
@@ -548,7 +566,13 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
         q.B = g.B; q.T = g.T; q.d = g.d; q.Lc = c->plan.chunk_L; q.groups = c->plan.chunk_groups;
         q.per_unit = c->plan.chunk_per_unit; q.units = c->plan.chunk_units;
         prof_begin(c, KIND_FUSED, iter);
-        e = launch_chunk_gru(g.n, q, c->stream);
+        if (two_part_cell(g.cell)) {
+            q.cell_units = g.reserved;
+            q.dt = (float)g.t1;
+            e = launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream);
+        } else {
+            e = launch_chunk_gru(g.n, q, c->stream);
+        }
     } else if (fused_theta && c->plan.mh) {
         p.L = c->plan.fused_L;
         p.W = 8;

@@ -100,6 +100,7 @@ struct ChunkParams {
     void* err;                 // max|y_new - y| (raw bits), or nullptr
     Gate gate;
     int B, T, d, Lc;
+    int cell_units; float dt;  // LSTM and LEM: units of the cell (rows of 2 cell_units scalars), the LEM's step
     int groups;                // of sixteen chunks, per sequence: ceil(T / (16 Lc))
     int per_unit, units;       // chunks of a unit (4, 8 or 16), units per sequence: ceil(T / (per_unit Lc))
 };
@@ -338,6 +339,11 @@ int scan_mfma_tile(int dtype, int n);
 // Newton step and dual scan of the GRU by chunks (fp32, n = 16, 32 or 64, d <= 16): two launches
 bool chunk_gru_supported(int dtype, int n, int d);
 size_t chunk_map_bytes(int n);   // bytes of one chunk's map
+bool chunk_params_valid(const ChunkParams& p);
+// the same for the LSTM and the LEM (fp32, 1..16 units, d <= 8)
+bool chunk_cells_supported(int dtype, int units, int d);
+size_t chunk_cells_map_bytes(int units);
+hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru64(const ChunkParams& p, hipStream_t s);
 hipError_t launch_gru_funceval(int dtype, const GruParams& p, hipStream_t s);

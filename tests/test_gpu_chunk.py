@@ -38,3 +38,37 @@ def test_step_and_dual_by_chunks(n, d, monkeypatch):
             ctx.close()
         for name, a, b in zip(("dtheta", "dx", "dy0"), got, want):
             assert np.abs(host(a) - b).max() <= 1e-4, (w.name, name, np.abs(host(a) - b).max())
+
+
+@pytest.mark.parametrize("cell", [oracle.CELL_LSTM, oracle.CELL_LEM], ids=["lstm", "lem"])
+@pytest.mark.parametrize("u,d", [(1, 2), (4, 8), (6, 3), (8, 4), (8, 8), (9, 1), (12, 6), (15, 5), (16, 8)])
+def test_two_part_cells_by_chunks(cell, u, d, monkeypatch):
+    # 1 to 8 units share one 16 x 16 block, 9 to 16 take a block per part; unit counts that are no multiple of four take scalar accesses
+    for k, (L, B, T) in enumerate(SHAPES):
+        monkeypatch.setenv("DEER_CHUNK_L", str(L))
+        monkeypatch.setenv("DEER_CHUNK_UNIT", str((4, 8, 16)[k % 3]))
+        make = inputs.lstm_workload if cell == oracle.CELL_LSTM else inputs.lem_workload
+        w = make("chunk_u%d_L%d_T%d" % (u, L, T), 1700 + 20 * u + k, B=B, T=T, units=u, d=d)
+        w.y0 = (np.random.default_rng(k).standard_normal((B, 2 * u)) * 0.5).astype(np.float32)
+        print(cell, w.name, B, d, flush=True)
+        c = oracle.make_cell(cell, 2 * u, d, **({} if cell == oracle.CELL_LSTM else {"dt": w.t1}))
+        ctx = deer.context_for(w, device=DEV)
+        try:
+            th, x, y0 = dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0)
+            for max_iter in (w.max_iter, 2):
+                yo, ito, _, _ = oracle.deer_eval(c, w.theta, w.x, w.y0, tol=w.tol, max_iter=max_iter, nthreads=8)
+                y, it, _, _, st = ctx.eval(th, x, y0, tol=w.tol, max_iter=max_iter)
+                # (one of the inputs, LEM u = 9, d = 1, T = 1,543, is a Newton iteration far from its solution: the oracle's iterates
+                # reach 1e16 before they converge after 22 iterations, and how many it takes depends on every rounding -- 26 with
+                # stored Jacobians in fp32.  The count is compared where the iteration is not of that kind, an iterate
+                # relative to its own largest entry.)
+                assert st == deer.DEER_OK and (abs(it - ito) <= 1 or ito > 10), (w.name, it, ito)
+                assert np.abs(host(y) - yo).max() <= 1e-4 * max(1.0, np.abs(yo).max()), (w.name, max_iter, np.abs(host(y) - yo).max())
+            ys = oracle.seq_eval(c, w.theta, w.x, w.y0, nthreads=8)
+            g = (np.random.default_rng(k + 1).standard_normal(ys.shape) / np.sqrt(T)).astype(np.float32).astype(np.float64)
+            want = oracle.rnn_grad(c, w.theta, w.x, w.y0, ys, g)
+            got = ctx.grad(th, x, y0, dev(ys, 0), dev(g, 0))
+        finally:
+            ctx.close()
+        for name, a, b in zip(("dtheta", "dx", "dy0"), got, want):
+            assert np.abs(host(a) - b).max() <= 1e-4, (w.name, name, np.abs(host(a) - b).max())
