@@ -245,7 +245,7 @@ void deer_destroy(deer_ctx* ctx);
  *                       tile shapes of the n <= 8 kernels: positions per lane group (1, 2, 4, 8, 10, 12, 16; 24 for
  *                       the plain n = 4 scan) and wavefronts per tile (4 or 8); ignored when no such variant exists
  *   DEER_CHUNK_L, DEER_CHUNK_UNIT
- *                       GRU with n = 16, 32, 64, LSTM and LEM in fp32: positions per chunk of the step by chunks (a multiple of
+ *                       GRU with n = 5..8, 16, 32, 64, multi-head GRU with n = 8, LSTM and LEM in fp32: positions per chunk of the step by chunks (a multiple of
  *                       four, at least four), which is then taken at every size (by default where it is faster), and
  *                       chunks per workgroup of its first launch (4, 8 or 16)
  *   DEER_BATCH          Newton iterations enqueued per host round trip on a fresh context (1..8, default 4)

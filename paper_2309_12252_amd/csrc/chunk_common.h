@@ -52,7 +52,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 struct GruGates {
-    float f, pz, sr, st, z;
+    float f, pz, sr, st, z, sc;
 };
 
 // gates of one row from the pre-activations ar, az, the candidate's input part ac and its hidden part q
@@ -65,8 +65,8 @@ __device__ __forceinline__ GruGates gru_gates(float ar, float az, float ac, floa
     const float dh = h - c;
     o.f = c + o.z * dh;
     o.pz = dh * o.z * zc;
-    const float sc = zc * (1.0f - c * c);
-    o.sr = sc * rg;
+    o.sc = zc * (1.0f - c * c);
+    o.sr = o.sc * rg;
     o.st = o.sr * q * (1.0f - rg);
     return o;
 }

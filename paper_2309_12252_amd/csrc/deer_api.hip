@@ -3,6 +3,7 @@
 // the right-hand side, a second trajectory buffer, scan tile descriptors and a few counters.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -57,6 +58,8 @@ struct Plan {
     size_t off_dy0parts, off_mhtable;
     bool chunk;          // GRU, n >= 16, fp32: Newton steps and the dual scan run by chunks (chunk_gru.hip)
     int chunk_L, chunk_groups, chunk_per_unit, chunk_units;
+    bool chunk8, chunk8_grad;   // GRU, 8 channels, fp32, plain or multi-head: the Newton steps, the gradient (chunk_gru8.hip)
+    Chunk8Params c8;     // their shapes and chunk lengths
     size_t off_tot, off_sup;
     bool grad_fused;     // deer_grad computes the transposed Jacobians inside the reverse scan
     bool need_J;         // some kernel of this plan reads or writes the Jacobian stream [B,T,n,n] and the right-hand side
@@ -242,6 +245,55 @@ bool chunk_pays(const deer_config* c) {
     return c->n == 64 || total >= 20000 || (c->n == 16 && c->T >= 1536);
 }
 
+// Steps by chunks at 8 channels: positions per chunk, and whether the Newton step and the gradient go this way.
+// Estimate in microseconds of one step (measured on MI355X, L = 4 .. 96 at 24 shapes; its choice is within a tenth of the best one's
+// time): two launches, a map of the fold, and a position of every chunk.  With one wavefront per SIMD a position costs the latency of its
+// chain of products; beyond that the wavefronts of equal length of a plain GRU take turns in pairs, those of the heads
+// (lengths differ by the level) fill in for each other and cost their positions and a start each.
+double chunk8_estimate(const Chunk8Params& q) {
+    const int chain = q.lv[0].C > 1 ? 15 + q.lv[0].Cc / 16 : 0, L = q.lv[0].Lc;
+    const double base = 15.0 + 0.13 * chain, waves = (double)q.groups / 1024.0;
+    if (q.levels == 1) return base + L * (waves <= 1.0 ? 1.45 : 2.3 * std::ceil(0.5 * waves));
+    double work = 0.0;
+    for (int k = 0; k < q.levels; ++k)
+        work += (double)((k + 1 < q.levels ? q.lv[k + 1].first : q.groups) - q.lv[k].first) * q.lv[k].Lc / 1024.0;
+    return base + std::max(1.45 * L, 1.15 * work) + 8.0 * std::max(0.0, waves - 1.0);
+}
+
+// The single-pass scan (all iterations in one launch up to about 260,000 positions) takes 20 us + 0.118 us per 1,000 positions a step.
+// Microseconds a solve, scan / chunks: plain 326 / 287 at 64 x 6,000, 502 / 466 at 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at
+// 4 x 100,000, where the fold is long; 123 / 207 at 16 x 10,000.  Heads (total positions of all heads): 118 / 135 at 9,600, 147 / 147 at
+// 42,000, 300 / 175 at 64,000, 3,898 / 1,112 at 2.1 million.  The gradient, whose walk takes the vector-Jacobian product in: plain
+// 64 / 60 at 4 x 3,000, 85 / 74 at 16 x 10,000, 87 / 92 at 2 x 30,000, 408 / 227 at 16 x 100,000; heads 83 / 63 at 42,000, 1,181 / 273 at 2.1 million.
+void chunk8_plan(const deer_config* c, Plan& p) {
+    const int H = c->heads > 1 ? c->heads : 1, forced = env_int("DEER_CHUNK_L", 0);
+    if (!chunk_gru8_supported(c->dtype, c->n, c->d, c->T, H)) return;
+    if (env_int("DEER_FUSED", 1) == 0 || env_int("DEER_GRAD_FUSED", 1) == 0 || env_int("DEER_FUSED_L", 0) > 0) return;
+    Chunk8Params q{};
+    q.B = c->B; q.T = c->T; q.d = c->d; q.H = H;
+    q.levels = c->stride_levels > 1 ? c->stride_levels : 1;
+    q.P = (long long)(theta_count(c) / (size_t)H);
+    double best = 1e300;
+    for (int L = forced >= 4 ? forced : 4; L <= (forced >= 4 ? forced : 64); L += 4) {
+        chunk_gru8_layout(q, L);
+        const double est = chunk8_estimate(q);
+        if (est < best) { best = est; p.c8 = q; }
+    }
+    const double total = (double)c->B * c->T * H;
+    if (forced >= 4) {
+        p.chunk8 = p.chunk8_grad = true;
+    } else if (is_multihead(c)) {
+        p.chunk8 = total >= 60000;
+        p.chunk8_grad = total >= 20000;
+    } else {
+        p.chunk8 = total >= 300000 && best < 20.0 + 1.18e-4 * total;
+        p.chunk8_grad = p.chunk8 || (total >= 30000 && c->T <= 16384);
+    }
+    if (!p.chunk8) return;
+    p.fused = true;
+    p.fused_L = p.fused_W = p.fused_tiles = 0;
+}
+
 Plan make_plan(const deer_config* c) {
     Plan p{};
     p.esz = c->dtype == DEER_F32 ? 4 : 8;
@@ -264,8 +316,9 @@ Plan make_plan(const deer_config* c) {
             if (forced == kLm[q]) est = -1.0;
             if (est < best) { best = est; p.fused_L = kLm[q]; }
         }
-        const int tile = scan_valu_tile(c->n, p.fused_L, 8);
-        p.fused_tiles = (int)mh_table(c, tile).size();   // tiles of one batch entry over all its recurrences
+        chunk8_plan(c, p);
+        const int tile = p.chunk8 ? 0 : scan_valu_tile(c->n, p.fused_L, 8);
+        if (!p.chunk8) p.fused_tiles = (int)mh_table(c, tile).size();   // tiles of one batch entry over all its recurrences
         p.tile = tile; p.tiles = p.fused_tiles;
         p.grad_fused = true; p.need_J = false;
         long long vb = ((long long)B * (long long)T + 31) / 32;
@@ -281,7 +334,9 @@ Plan make_plan(const deer_config* c) {
         p.off_inclW = take(nt * n * (p.esz / 4) * 8);
         p.off_barrier = take(0);
         p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);
-        p.off_partial = take((size_t)H * p.vjp_blocks * 4 * (theta_count(c) / H) * p.esz);
+        p.off_tot = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * chunk_map_bytes(8) : 0);
+        p.off_sup = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * chunk_map_bytes(8) : 0);
+        p.off_partial = take(p.chunk8_grad ? (size_t)(p.c8.groups / 4) * p.c8.P * p.esz : (size_t)H * p.vjp_blocks * 4 * (theta_count(c) / H) * p.esz);
         p.off_dy0parts = take(B * (size_t)H * ((size_t)1 << (K - 1)) * n * p.esz);
 #ifdef DEER_SCAN_TIMING
         p.off_timing = take(kTimingBytes);
@@ -377,6 +432,7 @@ Plan make_plan(const deer_config* c) {
         p.fused_tiles = (p.scan_T + ft - 1) / ft;
         if (p.fused_tiles < 1) p.fused_tiles = 1;
     }
+    if (gru) chunk8_plan(c, p);
     const bool cell_chunk = two_part_cell(c->cell) && c->mlp_width == 1;
     if (cell_chunk || (gru && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c))) {
         p.chunk = true;
@@ -393,7 +449,7 @@ Plan make_plan(const deer_config* c) {
                                             : mlp_general_vjp_blocks(c->dtype, c->n, c->mlp_width, c->mlp_hidden_layers, (long long)B * T);
 
     p.grad_fused = p.fused && env_int("DEER_GRAD_FUSED", 1) != 0 &&
-                   (p.chunk || p.mfma || scan_gru_dual_supported(c->dtype, c->n, c->d, p.fused_L, p.fused_W));
+                   (p.chunk || p.chunk8_grad || p.mfma || scan_gru_dual_supported(c->dtype, c->n, c->d, p.fused_L, p.fused_W));
     // The Jacobians exist in memory only where a kernel pair exchanges them: the ODE form, and the GRU sizes (or
     // knob settings) whose forward or backward pass runs the cell kernel followed by the plain scan.  With the
     // cell inside both scans the workspace is O(n T) instead of the O(n^2 T) of Sec. 3.5.
@@ -414,10 +470,10 @@ Plan make_plan(const deer_config* c) {
     p.off_barrier = take(p.fused ? 2 * (B * (size_t)p.fused_tiles + 4) * (p.esz / 4) * 8 : 0);   // (+4: test hook)
     p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);   // tickets, err bits, status
     const size_t map = cell_chunk ? chunk_cells_map_bytes(c->reserved) : chunk_map_bytes(c->n);
-    p.off_tot = take(p.chunk ? B * (size_t)p.chunk_groups * 16 * map : 0);
-    p.off_sup = take(p.chunk ? B * (size_t)p.chunk_units * map : 0);
+    p.off_tot = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * map : p.chunk ? B * (size_t)p.chunk_groups * 16 * map : 0);
+    p.off_sup = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * map : p.chunk ? B * (size_t)p.chunk_units * map : 0);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
-    p.off_partial = take((size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
+    p.off_partial = take(p.chunk8_grad ? (size_t)(p.c8.groups / 4) * p.c8.P * p.esz : (size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
     p.off_timing = take(kTimingBytes);
 #endif
@@ -531,6 +587,15 @@ void prof_collect(deer_ctx* c, int iters_done = 1 << 30) {
     c->ev_used = 0;
 }
 
+Chunk8Params chunk8_params(deer_ctx* c, const void* theta, const void* x, const void* y0, const void* y) {
+    Chunk8Params q = c->plan.c8;
+    q.theta = reinterpret_cast<const float*>(theta); q.x = reinterpret_cast<const float*>(x);
+    q.y0 = reinterpret_cast<const float*>(y0); q.y = reinterpret_cast<const float*>(y);
+    q.tot = reinterpret_cast<float*>(c->ws + c->plan.off_tot);
+    q.sup = reinterpret_cast<float*>(c->ws + c->plan.off_sup);
+    return q;
+}
+
 // One scan launch over the context's shapes.
 hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, void* out, const void* yold,
                     long long strideA, long long strideb, long long strideOut, int reverse, int slot, bool want_err,
@@ -573,6 +638,12 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
         } else {
             e = launch_chunk_gru(g.n, q, c->stream);
         }
+    } else if (fused_theta && c->plan.chunk8) {
+        Chunk8Params q = chunk8_params(c, fused_theta, fused_x, y0, yold);
+        q.out = reinterpret_cast<float*>(out);
+        q.err = p.err; q.gate = gate;
+        prof_begin(c, KIND_FUSED, iter);
+        e = launch_chunk_gru8(q, c->stream);
     } else if (fused_theta && c->plan.mh) {
         p.L = c->plan.fused_L;
         p.W = 8;
@@ -772,7 +843,7 @@ deer_status deer_create(const deer_config* cfg, void* d_workspace, size_t worksp
     if (c->batch < 1) c->batch = 1;
     if (c->batch > 8) c->batch = 8;
     std::vector<unsigned> table;   // (lives until the synchronisation below)
-    if (e == hipSuccess && plan.mh) {
+    if (e == hipSuccess && plan.mh && !plan.chunk8) {
         table = mh_table(cfg, plan.tile);
         e = hipMemcpyAsync(c->ws + plan.off_mhtable, table.data(), table.size() * 4, hipMemcpyHostToDevice, c->stream);
     }
@@ -1091,6 +1162,23 @@ static deer_status grad_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
 
     deer_status st = zero_ctl(c);
     if (st != DEER_OK) return st;
+    if (c->plan.chunk8_grad) {
+        // the dual recurrence and the vector-Jacobian product in one walk: lam never reaches memory
+        Chunk8Params q = chunk8_params(c, d_theta, d_x, d_y0, d_y);
+        q.g = reinterpret_cast<const float*>(d_dLdy);
+        q.dx = reinterpret_cast<float*>(d_dLdx);
+        const bool parts = c->plan.mh && d_dLdy0;   // dL/dy0 of a head: the sum over its recurrences
+        q.dy0 = parts ? reinterpret_cast<float*>(c->ws + c->plan.off_dy0parts) : reinterpret_cast<float*>(d_dLdy0);
+        q.dtheta = reinterpret_cast<float*>(d_dLdtheta);
+        q.partial = reinterpret_cast<float*>(c->ws + c->plan.off_partial);
+        prof_begin(c, KIND_FUSED);
+        HIPCHK(c, launch_chunk_gru8(q, c->stream));
+        if (parts) HIPCHK(c, launch_gru_dy0_mh(q.dy0, reinterpret_cast<float*>(d_dLdy0), g.B, g.T, c->plan.mh_H, c->plan.mh_K, g.n, c->stream));
+        prof_end(c);
+        st = check_status(c);
+        prof_collect(c);
+        return st;
+    }
     if (c->plan.grad_fused) {
         // lam = (dL/dy) L_G^{-1} with the transposed Jacobians computed inside the reverse scan (they never reach memory)
         HIPCHK(c, run_scan(c, nullptr, d_dLdy, nullptr, lam, d_y, 0, (long long)(T * n), (long long)(T * n), 1, 0, false, 0,

@@ -105,6 +105,28 @@ struct ChunkParams {
     int per_unit, units;       // chunks of a unit (4, 8 or 16), units per sequence: ceil(T / (per_unit Lc))
 };
 
+// The same for 8 channels, plain or multi-head (chunk_gru8.hip); with g the whole gradient.  Level k holds the heads k, k + levels, ..: stride 2^k.
+struct Chunk8Level {
+    int Lc, C, Cc;             // positions per chunk, chunks of the longest recurrence, columns a recurrence takes (1, 2, 4, 8 or a multiple of 16)
+    int groups, first;         // groups of sixteen columns per head, first group of the level
+};
+struct Chunk8Params {
+    const float* theta; const float* x; const float* y0;   // [heads][P], [B,T,heads,d], [B,heads,n] or nullptr (zeros)
+    const float* y;            // previous iterate, or the trajectory of the backward pass [B,T,heads,n]
+    const float* g;            // dL/dy [B,T,heads,n], or nullptr
+    float* out;                // next iterate (Newton step)
+    // gradient: dx [B,T,heads,d] or nullptr, dy0 one term per recurrence [B,heads,2^(levels - 1),n] or nullptr, dtheta [heads][P], one
+    // row of P scalars per workgroup
+    float* dx; float* dy0; float* dtheta; float* partial;
+    float* tot; float* sup;    // maps of the chunks [map_groups][16][72] and of the groups [map_groups][72]
+    void* err;
+    Gate gate;
+    long long P;               // parameters per head
+    int B, T, d, H, levels;    // levels <= 8
+    int groups, map_groups;    // groups in all, and of the levels whose recurrences have more than one chunk (these come first)
+    Chunk8Level lv[8];
+};
+
 // One launch that runs all Newton iterations of a GRU problem (n <= 8) whose tiles are all resident.
 struct NewtonParams {
     ScanParams scan;           // y0, out, yold = initial guess or nullptr (zeros), shapes, published-word regions,
@@ -346,6 +368,11 @@ size_t chunk_cells_map_bytes(int units);
 hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru64(const ChunkParams& p, hipStream_t s);
+bool chunk_gru8_supported(int dtype, int n, int d, int T, int H);
+// dL/dy0 of a multi-head GRU from the terms of its recurrences
+hipError_t launch_gru_dy0_mh(const float* parts, float* dy0, int B, int T, int H, int K, int n, hipStream_t s);
+void chunk_gru8_layout(Chunk8Params& p, int L);   // from B, T, H, levels: chunks of at most about L positions
+hipError_t launch_chunk_gru8(const Chunk8Params& p, hipStream_t s);
 hipError_t launch_gru_funceval(int dtype, const GruParams& p, hipStream_t s);
 hipError_t launch_gru_vjp(int dtype, const GruVjpParams& p, hipStream_t s);
 // the same on the matrix cores (fp32, n = 16 or 32, d <= 16): kernel only, partial rows = blocks * 4

@@ -471,6 +471,16 @@ __global__ __launch_bounds__(256) void gru_dy0_mh_kernel(const S* __restrict__ p
     dy0[q] = acc;
 }
 
+}  // namespace
+
+hipError_t launch_gru_dy0_mh(const float* parts, float* dy0, int B, int T, int H, int K, int n, hipStream_t s) {
+    const long long q = (long long)B * H * n;
+    hipLaunchKernelGGL((gru_dy0_mh_kernel<float>), dim3((unsigned)((q + 255) / 256)), dim3(256), 0, s, parts, dy0, B, T, H, K, n);
+    return hipGetLastError();
+}
+
+namespace {
+
 template <typename S, int N>
 hipError_t launch_vjp_mh(const GruVjpParams& p, hipStream_t s) {
     const size_t shmem = (size_t)3 * N * (p.d | 1) * sizeof(S);

@@ -72,3 +72,50 @@ def test_two_part_cells_by_chunks(cell, u, d, monkeypatch):
             ctx.close()
         for name, a, b in zip(("dtheta", "dx", "dy0"), got, want):
             assert np.abs(host(a) - b).max() <= 1e-4, (w.name, name, np.abs(host(a) - b).max())
+
+
+def _against_oracle(ctx, w, oracle_solve, oracle_sequential, oracle_gradient):
+    th, x, y0 = dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0)
+    for max_iter in (w.max_iter, 2):   # the solution and an iterate far from it
+        yo, ito, _, _ = oracle_solve(max_iter)
+        y, it, _, _, st = ctx.eval(th, x, y0, tol=w.tol, max_iter=max_iter)
+        assert st == deer.DEER_OK and abs(it - ito) <= 1, (w.name, it, ito)
+        assert np.abs(host(y) - yo).max() <= 1e-4, (w.name, max_iter, np.abs(host(y) - yo).max())
+    ys = oracle_sequential()
+    g = (np.random.default_rng(1).standard_normal(ys.shape) / np.sqrt(w.T)).astype(np.float32).astype(np.float64)
+    got = ctx.grad(th, x, y0, dev(ys, 0), dev(g, 0))
+    for name, a, b in zip(("dtheta", "dx", "dy0"), got, oracle_gradient(ys, g)):
+        assert np.abs(host(a).reshape(-1) - b.reshape(-1)).max() <= 1e-4, (w.name, name, np.abs(host(a).reshape(-1) - b.reshape(-1)).max())
+
+
+@pytest.mark.parametrize("n,d", [(8, 1), (8, 4), (8, 8), (5, 3), (7, 6)])
+def test_eight_channels_by_chunks(n, d, monkeypatch):
+    for k, (L, B, T) in enumerate(SHAPES):
+        monkeypatch.setenv("DEER_CHUNK_L", str(L))
+        w = inputs.gru_workload("chunk_n%d_L%d_T%d" % (n, L, T), 2100 + 20 * n + k, B=B, T=T, n=n, d=d)
+        w.y0 = np.random.default_rng(k).standard_normal((B, n)).astype(np.float32)
+        print(w.name, B, d, flush=True)
+        ctx = deer.context_for(w, device=DEV)
+        try:
+            _against_oracle(ctx, w, lambda m: oracle_eval(w, max_iter=m), lambda: oracle.seq_eval(oracle_cell(w), w.theta, w.x, w.y0, nthreads=8),
+                            lambda ys, g: oracle.gru_grad(w.n, w.d, w.theta, w.x, w.y0, ys, g))
+        finally:
+            ctx.close()
+
+
+# recurrences of 1, 2, 4, 8 and more than 16 chunks in one launch, fewer steps than the largest stride, groups of sixteen columns that
+# several batch entries share, one head, head counts that are no multiple of the levels
+@pytest.mark.parametrize("n,d", [(8, 1), (8, 4), (8, 7), (8, 8)])
+@pytest.mark.parametrize("L,B,T,H,K", [(4, 1, 1, 3, 2), (4, 2, 5, 6, 4), (8, 3, 300, 4, 3), (16, 1, 131, 8, 8), (12, 2, 1030, 11, 8), (32, 5, 333, 1, 4),
+                                       (64, 2, 700, 5, 2), (4, 1, 1543, 3, 3)])
+def test_heads_by_chunks(n, d, L, B, T, H, K, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", str(L))
+    w = inputs.mh_gru_workload("chunk_mh_n%d_H%d_K%d_T%d" % (n, H, K, T), 2500 + T + 40 * n + d, B=B, T=T, n=n, d=d, H=H, K=K)
+    w.y0 = np.random.default_rng(3).standard_normal((B, H, n)).astype(np.float32)
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        _against_oracle(ctx, w, lambda m: oracle.mh_deer_eval(n, d, H, K, w.theta, w.x, w.y0, tol=w.tol, max_iter=m, nthreads=8),
+                        lambda: oracle.mh_seq_eval(n, d, H, K, w.theta, w.x, w.y0, nthreads=8),
+                        lambda ys, g: oracle.mh_gru_grad(n, d, H, K, w.theta, w.x, w.y0, ys, g))
+    finally:
+        ctx.close()
