@@ -134,9 +134,10 @@ __global__ __launch_bounds__(kThreads) void mlp_funceval_kernel(MlpParams p) {
 //   Z1 = W1 Y + b1 (columns = the 16 points), A1 = tanh Z1, D1 = 1 - A1^2
 //   Z2 = W2 A1 + b2,                         A2 = tanh Z2, D2 = 1 - A2^2
 //   f  = W3 A2 + b3
-//   J y = W3 D2 W2 D1 (W1 y): the same chain applied to D1 * (Z1 - b1)        -> z = f - J y
-//   J   = W3 D2 W2 D1 W1 for every point: the columns of the right factor are (point, j) pairs, 16 at a
-//         time (two points x 8 columns); D1 and D2 of the right point reach a lane by one shuffle each.
+//   J   = W3 D2 W2 D1 W1, one column of the sixteen points' Jacobians at a time: the columns of the products stay
+//         the points, so D1 and D2 are already where they are needed;  z = f - J y from the columns
+// (two points x 8 columns in a product took a shuffle for every factor and a chain of its own for J y: width 32, 800,000 points
+// 234 us, now 211).
 // Rows 8..15 of the W3 products are padding (n = 8).
 typedef float mlp_acc __attribute__((ext_vector_type(4)));
 
@@ -165,7 +166,10 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
     float w2a[WB][WB][4];      // A operand: W2[16I + c][16K + 4g + v]
     float w3a[WB][4];          // A operand: W3[c][16K + 4g + v], rows >= 8 are zero
     mlp_acc b3c;
-    float w1b[WB][4];          // W1[16K + 4g + v][c & 7], the column factor of D1 W1
+    // W1 transposed: column k's factor of D1 W1 as 16-byte reads
+    __shared__ __align__(16) float sW1[N][W];
+    for (int q = threadIdx.x; q < W * N; q += kThreads) sW1[q % N][q / N] = W1[q];
+    __syncthreads();
 #pragma unroll
     for (int I = 0; I < WB; ++I) {
 #pragma unroll
@@ -174,7 +178,6 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
         for (int v = 0; v < 4; ++v) {
             b1c[I][v] = b1[16 * I + 4 * g + v];
             b2c[I][v] = b2[16 * I + 4 * g + v];
-            w1b[I][v] = W1[(16 * I + 4 * g + v) * N + (c & 7)];
             w3a[I][v] = (c < N) ? W3[c * W + 16 * I + 4 * g + v] : 0.0f;
         }
 #pragma unroll
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) yb[kk] = y[sc * N + 4 * kk + g];
 
-        mlp_acc a1[WB], d1[WB], q1[WB];
+        mlp_acc a1[WB], d1[WB];
 #pragma unroll
         for (int I = 0; I < WB; ++I) {
             mlp_acc acc = b1c[I];
@@ -207,78 +210,72 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
                 const float t = feed_tanh(acc[v]);
                 a1[I][v] = t;
                 d1[I][v] = 1.0f - t * t;
-                q1[I][v] = d1[I][v] * (acc[v] - b1c[I][v]);
             }
         }
-        mlp_acc a2[WB], d2[WB], q2[WB];
+        mlp_acc a2[WB], d2[WB];
 #pragma unroll
         for (int I = 0; I < WB; ++I) {
-            mlp_acc acc = b2c[I], accq = {0.f, 0.f, 0.f, 0.f};
+            mlp_acc acc = b2c[I];
 #pragma unroll
             for (int K = 0; K < WB; ++K)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], a1[K][v], acc, 0, 0, 0);
-                    if constexpr (!JONLY) accq = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], q1[K][v], accq, 0, 0, 0);
-                }
+                for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], a1[K][v], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const float t = feed_tanh(acc[v]);
                 a2[I][v] = t;
                 d2[I][v] = 1.0f - t * t;
-                q2[I][v] = d2[I][v] * accq[v];
             }
         }
-        {
-            mlp_acc f = b3c, jy = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (JONLY) {
-                f = mlp_acc{0.f, 0.f, 0.f, 0.f};
-            } else {
+        // f at point s0 + c, rows 4g + v < 8; J y is taken off column by column
+        mlp_acc f = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (!JONLY) {
+            f = b3c;
 #pragma unroll
-                for (int K = 0; K < WB; ++K)
+            for (int K = 0; K < WB; ++K)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        f = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], a2[K][v], f, 0, 0, 0);
-                        jy = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], q2[K][v], jy, 0, 0, 0);
-                    }
+                for (int v = 0; v < 4; ++v) f = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], a2[K][v], f, 0, 0, 0);
+        }
+        // columns k, k + 1 of the Jacobians
+#pragma unroll 1
+        for (int k = 0; k < N; k += 2) {
+            const float2 yk = *reinterpret_cast<const float2*>(y + sc * N + k);
+            mlp_acc u1[2][WB], u2[2][WB], jb[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                jb[j] = mlp_acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int K = 0; K < WB; ++K) {
+                    u2[j][K] = mlp_acc{0.f, 0.f, 0.f, 0.f};
+                    u1[j][K] = d1[K] * *reinterpret_cast<const mlp_acc*>(&sW1[k + j][16 * K + 4 * g]);
+                }
             }
-            // z = f + G y = f - J y at point s0 + c, rows 4g + v < 8
+#pragma unroll
+            for (int K = 0; K < WB; ++K)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int I = 0; I < WB; ++I)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) u2[j][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], u1[j][K][v], u2[j][I], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int I = 0; I < WB; ++I) u2[j][I] *= d2[I];
+#pragma unroll
+            for (int K = 0; K < WB; ++K)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) jb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], u2[j][K][v], jb[j], 0, 0, 0);
+            if constexpr (!JONLY) f -= jb[0] * yk.x + jb[1] * yk.y;
             if (g < 2 && s0 + c < total) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) z[(s0 + c) * N + 4 * g + v] = f[v] - jy[v];
+                for (int v = 0; v < 4; ++v)
+                    *reinterpret_cast<float2*>(G + ((s0 + c) * N + 4 * g + v) * N + k) = float2{-jb[0][v], -jb[1][v]};
             }
         }
-        // Jacobians, two points (16 columns) per round
-#pragma unroll 2
-        for (int cb = 0; cb < 8; ++cb) {
-            const int src = (lane & 48) + 2 * cb + ((lane >> 3) & 1);   // lane holding D of this column's point
-            float u1[WB][4];
-#pragma unroll
-            for (int K = 0; K < WB; ++K)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) u1[K][v] = __shfl(d1[K][v], src) * w1b[K][v];
-            float u2[WB][4];
-#pragma unroll
-            for (int I = 0; I < WB; ++I) {
-                mlp_acc t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int K = 0; K < WB; ++K)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) t = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], u1[K][v], t, 0, 0, 0);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) u2[I][v] = __shfl(d2[I][v], src) * t[v];
-            }
-            mlp_acc jb = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int K = 0; K < WB; ++K)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) jb = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], u2[K][v], jb, 0, 0, 0);
-            const long long sp = s0 + 2 * cb + (c >> 3);
-            if (g < 2 && sp < total) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) G[(sp * N + 4 * g + v) * N + (c & 7)] = -jb[v];
-            }
-        }
+        if (g < 2 && s0 + c < total) *reinterpret_cast<mlp_acc*>(z + (s0 + c) * N + 4 * g) = f;
     }
 }
 

@@ -76,12 +76,15 @@ __host__ __device__ inline long long gen_theta_len(int n, int w, int L) { return
 // The two-hidden-layer kernel's scheme for any depth: a wavefront handles 16 grid points as the columns of
 // 16 x 16 x 4 products whose results stay in accumulator layout (a valid B operand of the next product):
 //   values      A_1 = s(W_1 Y + b_1), A_l = s(W_l A_{l-1} + b_l), f = W_out A_L + b_out
-//   J y         Q_1 = D_1 (W_1 Y), Q_l = D_l (W_l Q_{l-1}), J y = W_out Q_L            (z = f - J y)
-//   Jacobians   16 columns (two points x 8 state entries) at a time: U_1 = D_1 W_1, U_l = D_l (W_l U_{l-1}),
-//               J = W_out U_L; the derivative factors D_l of a column's point come from that point's lane by
-//               one shuffle each.
+//   Jacobians   column k of the sixteen points' Jacobians at a time: U_1 = D_1 W_1[:, k], U_l = D_l (W_l U_{l-1}), J[:, k] =
+//               W_out U_L.  The columns stay the points, so the derivative factors D_l of a lane's rows and point are
+//               already in its registers; two columns k share every weight read and are independent chains.
+//               z = f - J y is added up from the columns.
 // The derivative factors of all layers stay in registers (L * WB * 4); the weights are A operands read from
 // LDS (rows padded to W + 4 words: 16-byte reads, lanes of a row group on different banks).
+// Bound: fp32 matrix instructions, 8 (L - 1) W^2 / 512 of 32 cycles for 16 points: 0.31 ms at five layers of 64 and 160,000 points.
+// With two points x 8 entries as the columns the factors crossed the lanes (640 shuffles a block) and J y took a second chain: 0.547 ms
+// there, now 0.461 ms.
 typedef float gacc __attribute__((ext_vector_type(4)));
 
 // softplus and its derivative (the logistic function) from one exp2, one log2 and one reciprocal of the hardware:
@@ -101,17 +104,17 @@ __device__ __forceinline__ void fast_act(int kind, float pre, float& a, float& d
 template <int WB, int L>
 __global__ __launch_bounds__(kThreads) void mlp_gen_funceval_mfma_kernel(MlpParams p) {
     if (gate_closed<float>(p.gate)) return;
-    constexpr int W = 16 * WB, N = 8, WS = W + 4, W1S = 12;
+    constexpr int W = 16 * WB, N = 8, WS = W + 4, W1S = W + 4;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    float* sW1 = reinterpret_cast<float*>(smem_raw);   // [W][W1S]: W_1, 8 columns used
-    float* sWh = sW1 + W * W1S;                        // [L - 1][W][WS]
+    float* sW1 = reinterpret_cast<float*>(smem_raw);   // [8][W1S]: W_1 transposed
+    float* sWh = sW1 + N * W1S;                        // [L - 1][W][WS]
     float* sWo = sWh + (L - 1) * W * WS;               // [16][WS]: W_out, rows 8..15 zero
     float* sb = sWo + 16 * WS;                         // [L][W] hidden biases, then [16] output bias (entries 8..15 zero)
     const int tid = threadIdx.x, lane = tid & 63;
     const int g = lane >> 4, c = lane & 15;
     const float* __restrict__ th = reinterpret_cast<const float*>(p.theta);
     const int kind = p.act;
-    for (int q = tid; q < W * N; q += kThreads) sW1[(q / N) * W1S + (q % N)] = th[q];
+    for (int q = tid; q < W * N; q += kThreads) sW1[(q % N) * W1S + q / N] = th[q];
     for (int q = tid; q < W; q += kThreads) sb[q] = th[W * N + q];
     for (int l = 1; l < L; ++l) {
         const float* src = th + layer_offset(N, W, l);
@@ -128,11 +131,6 @@ __global__ __launch_bounds__(kThreads) void mlp_gen_funceval_mfma_kernel(MlpPara
     const float* __restrict__ y = reinterpret_cast<const float*>(p.y);
     float* __restrict__ G = reinterpret_cast<float*>(p.G);
     float* __restrict__ z = reinterpret_cast<float*>(p.z);
-    float w1b[WB][4];   // W_1[16K + 4g + v][c & 7]: the column factor of D_1 W_1
-#pragma unroll
-    for (int K = 0; K < WB; ++K)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w1b[K][v] = sW1[(16 * K + 4 * g + v) * W1S + (c & 7)];
 
     const long long total = (long long)p.B * p.T;
     const long long nblk = (total + 15) / 16;
@@ -145,131 +143,130 @@ __global__ __launch_bounds__(kThreads) void mlp_gen_funceval_mfma_kernel(MlpPara
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) yb[kk] = y[sc * N + 4 * kk + g];
 
-        gacc a[WB], q[WB], d[L][WB];
+        gacc a[WB], d[L][WB];
         // layer 1
 #pragma unroll
         for (int I = 0; I < WB; ++I) {
-            gacc bias, acc;
+            gacc acc;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) bias[v] = sb[16 * I + 4 * g + v];
-            acc = bias;
+            for (int v = 0; v < 4; ++v) acc[v] = sb[16 * I + 4 * g + v];
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sW1[(16 * I + c) * W1S + 4 * kk + g], yb[kk], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sW1[(4 * kk + g) * W1S + 16 * I + c], yb[kk], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 float av, dv;
                 fast_act(kind, acc[v], av, dv);
                 a[I][v] = av;
                 d[0][I][v] = dv;
-                q[I][v] = dv * (acc[v] - bias[v]);
             }
         }
         // hidden layers 2..L
 #pragma unroll
         for (int l = 1; l < L; ++l) {
-            gacc an[WB], qn[WB];
+            gacc an[WB];
 #pragma unroll
             for (int I = 0; I < WB; ++I) {
-                gacc acc, accq = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[v] = sb[l * W + 16 * I + 4 * g + v];
+                for (int v = 0; v < 4; ++v) an[I][v] = sb[l * W + 16 * I + 4 * g + v];
 #pragma unroll
                 for (int K = 0; K < WB; ++K) {
                     float wa[4];
                     vload<float, 4>(wa, &sWh[((l - 1) * W + 16 * I + c) * WS + 16 * K + 4 * g]);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], acc, 0, 0, 0);
-                        if (!p.jac_only) accq = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], q[K][v], accq, 0, 0, 0);
-                    }
+                    for (int v = 0; v < 4; ++v) an[I] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], an[I], 0, 0, 0);
                 }
+            }
+#pragma unroll
+            for (int I = 0; I < WB; ++I)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     float av, dv;
-                    fast_act(kind, acc[v], av, dv);
-                    an[I][v] = av;
+                    fast_act(kind, an[I][v], av, dv);
+                    a[I][v] = av;
                     d[l][I][v] = dv;
-                    qn[I][v] = dv * accq[v];
                 }
-            }
-#pragma unroll
-            for (int I = 0; I < WB; ++I) { a[I] = an[I]; q[I] = qn[I]; }
         }
-        // output layer: z = f - J y at point s0 + c, rows 4g + v < 8
-        {
-            gacc f = {0.f, 0.f, 0.f, 0.f}, jy = {0.f, 0.f, 0.f, 0.f};
-            if (!p.jac_only) {
+        // output layer: f at point s0 + c, rows 4g + v < 8; J y is taken off column by column
+        gacc f = {0.f, 0.f, 0.f, 0.f};
+        if (!p.jac_only) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) f[v] = sb[L * W + 4 * g + v];
+            for (int v = 0; v < 4; ++v) f[v] = sb[L * W + 4 * g + v];
 #pragma unroll
-                for (int K = 0; K < WB; ++K) {
-                    float wa[4];
-                    vload<float, 4>(wa, &sWo[c * WS + 16 * K + 4 * g]);
+            for (int K = 0; K < WB; ++K) {
+                float wa[4];
+                vload<float, 4>(wa, &sWo[c * WS + 16 * K + 4 * g]);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        f = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], f, 0, 0, 0);
-                        jy = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], q[K][v], jy, 0, 0, 0);
-                    }
-                }
-            }
-            if (g < 2 && s0 + c < total) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) z[(s0 + c) * N + 4 * g + v] = f[v] - jy[v];
+                for (int v = 0; v < 4; ++v) f = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], f, 0, 0, 0);
             }
         }
-        // Jacobians, two points (16 columns) per round
+        // columns k, k + 1 of the Jacobians
 #pragma unroll 1
-        for (int cb = 0; cb < 8; ++cb) {
-            const int src = (lane & 48) + 2 * cb + ((lane >> 3) & 1);   // lane holding the factors of this column's point
+        for (int k = 0; k < N; k += 2) {
             // (an offset the compiler cannot see through: the weight reads of a round stay in the round instead of being
             // hoisted into hundreds of registers in front of the loop)
             int zoff = 0;
             asm volatile("" : "+v"(zoff));
-            float u[WB][4];
+            const float2 yk = *reinterpret_cast<const float2*>(y + sc * N + k);
+            gacc u[2][WB];
 #pragma unroll
-            for (int K = 0; K < WB; ++K)
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) u[K][v] = __shfl(d[0][K][v], src) * w1b[K][v];
+                for (int K = 0; K < WB; ++K) {
+                    float w1[4];
+                    vload<float, 4>(w1, &sW1[(k + j) * W1S + 16 * K + 4 * g + zoff]);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) u[j][K][v] = d[0][K][v] * w1[v];
+                }
 #pragma unroll
             for (int l = 1; l < L; ++l) {
-                float un[WB][4];
+                gacc un[2][WB];
 #pragma unroll
                 for (int I = 0; I < WB; ++I) {
-                    gacc t = {0.f, 0.f, 0.f, 0.f};
+                    un[0][I] = un[1][I] = gacc{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int K = 0; K < WB; ++K) {
                         float wa[4];
                         vload<float, 4>(wa, &sWh[((l - 1) * W + 16 * I + c) * WS + 16 * K + 4 * g + zoff]);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) t = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], u[K][v], t, 0, 0, 0);
-                    }
+                        for (int v = 0; v < 4; ++v)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) un[I][v] = __shfl(d[l][I][v], src) * t[v];
+                            for (int j = 0; j < 2; ++j) un[j][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], u[j][K][v], un[j][I], 0, 0, 0);
+                    }
                 }
 #pragma unroll
-                for (int I = 0; I < WB; ++I)
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) u[I][v] = un[I][v];
+                    for (int I = 0; I < WB; ++I)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) u[j][I][v] = d[l][I][v] * un[j][I][v];
             }
-            gacc jb = {0.f, 0.f, 0.f, 0.f};
+            gacc jb[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
             for (int K = 0; K < WB; ++K) {
                 float wa[4];
                 vload<float, 4>(wa, &sWo[c * WS + 16 * K + 4 * g + zoff]);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) jb = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], u[K][v], jb, 0, 0, 0);
-            }
-            const long long sp = s0 + 2 * cb + (c >> 3);
-            if (g < 2 && sp < total) {
+                for (int v = 0; v < 4; ++v)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) G[(sp * N + 4 * g + v) * N + (c & 7)] = -jb[v];
+                    for (int j = 0; j < 2; ++j) jb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], u[j][K][v], jb[j], 0, 0, 0);
             }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) f[v] -= jb[0][v] * yk.x + jb[1][v] * yk.y;
+            if (g < 2 && s0 + c < total) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    *reinterpret_cast<float2*>(G + ((s0 + c) * N + 4 * g + v) * N + k) = float2{-jb[0][v], -jb[1][v]};
+            }
+        }
+        if (!p.jac_only && g < 2 && s0 + c < total) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z[(s0 + c) * N + 4 * g + v] = f[v];
         }
     }
 }
 
-size_t fe_mfma_smem(int W, int L) { return ((size_t)W * 12 + (size_t)(L - 1) * W * (W + 4) + 16 * (size_t)(W + 4) + (size_t)L * W + 16) * 4; }
+size_t fe_mfma_smem(int W, int L) { return (8 * (size_t)(W + 4) + (size_t)(L - 1) * W * (W + 4) + 16 * (size_t)(W + 4) + (size_t)L * W + 16) * 4; }
 
 template <int WB, int L>
 hipError_t launch_fe_mfma_wl(const MlpParams& p, hipStream_t s) {
