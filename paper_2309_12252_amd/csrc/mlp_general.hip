@@ -306,65 +306,92 @@ bool fe_mfma_supported(int dtype, int n, int width, int nhid) {
 // vector-Jacobian product on the matrix cores (fp32, n = 8, hidden width 16 * WB, L hidden layers)
 // ---------------------------------------------------------------------------------------------------------
 // dL/dtheta = sum over grid points j of (df/dtheta)(y_j)^T w_j, w_j = (u_j + u_{j-1}) / 2 (Sec. 3.1.1 eq. 7, outer
-// bracket, ODE form).  The accumulators of all layers do not fit the registers of a wavefront (width 64: 64 per
-// hidden layer), so blockIdx.y names the layer a block accumulates: 0 = (W_1, b_1), l = (W_{l+1}, b_{l+1}),
-// L = (W_out, b_out).  Every block runs the forward pass of its 16-point tiles (it needs the derivative factors
-// of the layers above its own) and the reverse pass down to its layer, all as 16 x 16 x 4 products in accumulator
-// layout as in the field kernel (weights from LDS; for the reverse products they are read down a column, row
-// stride = 4 mod 64 words: no bank conflicts); its layer's cotangent and input then cross a wavefront-private LDS
-// tile so that the grid points land on the contraction index of the outer-product sum.  One partial row per
-// wavefront (each block fills its layer's slice of the row), the fixed-order reduction adds the rows.
+// bracket, ODE form).  The sums of all layers do not fit the registers of one wavefront (width 64: 64 per hidden layer
+// and block of rows), so the WB wavefronts of a team share sixteen points: wavefront w owns rows 16 w .. 16 w + 15 of every
+// hidden layer -- its rows of the activations, of the cotangents and of the sums (16 registers a layer) -- and the rows the others own come
+// through LDS, one barrier a layer each way.  Forward weights stay in registers, the transposed ones are read from LDS down
+// a column (row stride = 4 mod 64 words: no bank conflicts).  Two teams a workgroup; a partial row per team, the fixed-order reduction
+// adds the rows.
+// Bound: fp32 matrix instructions, 3 (L - 1) W^2 / 64 of 32 cycles for 16 points (0.11 ms at five layers of 64 and 160,000 points).  A
+// workgroup per layer that ran the forward and the reverse pass for its own layer alone took 0.841 ms there; now 0.231 ms.
 template <int WB, int L>
-__global__ __launch_bounds__(kThreads) void mlp_gen_vjp_mfma_kernel(MlpVjpParams p) {
-    constexpr int W = 16 * WB, N = 8, WS = W + 4, W1S = 12, LD = 17, kWaves = kThreads / 64;
+__global__ __launch_bounds__(128 * WB, 2) void mlp_gen_vjp_mfma_kernel(MlpVjpParams p) {
+    constexpr int W = 16 * WB, N = 8, WS = W + 4, THREADS = 128 * WB, TEAM = (L + 2) * 16 * WS + 256;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    float* sW1 = reinterpret_cast<float*>(smem_raw);   // [W][W1S]
-    float* sWh = sW1 + W * W1S;                        // [L - 1][W][WS]
-    float* sWo = sWh + (L - 1) * W * WS;               // [16][WS], rows 8..15 zero
-    float* sb = sWo + 16 * WS;                         // [L][W] (+ 16 unused)
-    float* sD = sb + L * W + 16;                       // [kWaves][2 W][LD]: cotangent rows | input rows of the block's layer
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = lane >> 4, c = lane & 15;
-    const int grp = blockIdx.y;
+    float* sWh = reinterpret_cast<float*>(smem_raw);   // [L - 1][W][WS]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c = lane & 15, w = wave % WB, team = wave / WB, row0 = 16 * w;
+    // per team: activations [L][point][WS], cotangents [2][point][WS], w [point][16] (entries 8..15 zero)
+    float* sA = sWh + (L - 1) * W * WS + team * TEAM;
+    float* sC = sA + L * 16 * WS;
+    float* sU = sC + 2 * 16 * WS;
     const int kind = p.act;
     const float* __restrict__ th = reinterpret_cast<const float*>(p.theta);
-    for (int q = tid; q < W * N; q += kThreads) sW1[(q / N) * W1S + (q % N)] = th[q];
-    for (int q = tid; q < W; q += kThreads) sb[q] = th[W * N + q];
+#pragma unroll 1
     for (int l = 1; l < L; ++l) {
         const float* src = th + layer_offset(N, W, l);
-        for (int q = tid; q < W * W; q += kThreads) sWh[((l - 1) * W + q / W) * WS + (q % W)] = src[q];
-        for (int q = tid; q < W; q += kThreads) sb[l * W + q] = src[W * W + q];
+        for (int q = tid; q < W * W; q += THREADS) sWh[((l - 1) * W + q / W) * WS + (q % W)] = src[q];
     }
+    // this wavefront's rows of the weights as A operands, its biases in accumulator layout
+    float w1[2], wf[L > 1 ? L - 1 : 1][WB][4], wo[4];
+    gacc bias[L];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) w1[m] = th[(row0 + c) * N + 4 * m + g];
+#pragma unroll
+    for (int l = 1; l < L; ++l) {
+        const float* src = th + layer_offset(N, W, l);
+#pragma unroll
+        for (int K = 0; K < WB; ++K)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) wf[l - 1][K][v] = src[(row0 + c) * W + 16 * K + 4 * g + v];
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bias[l][v] = th[layer_offset(N, W, l) + (l == 0 ? W * N : W * W) + row0 + 4 * g + v];
     {
+        // k-step v: lane group g supplies entry 4g + v of w (zero from g = 2 on); A[i = c][k = g] = W_out[4g + v][row0 + c]
         const float* src = th + layer_offset(N, W, L);
-        for (int q = tid; q < 16 * W; q += kThreads) sWo[(q / W) * WS + (q % W)] = (q / W < N) ? src[q] : 0.0f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float t = src[min(4 * g + v, N - 1) * W + row0 + c];
+            wo[v] = g < 2 ? t : 0.0f;
+        }
     }
-    float* myD = sD + (size_t)wave * 2 * W * LD;
-    for (int q = lane; q < 2 * W * LD; q += 64) myD[q] = 0.0f;   // (rows that a layer does not use stay zero)
-    __syncthreads();
+    if (w == 0) *reinterpret_cast<gacc*>(sU + c * 16 + 4 * g) = gacc{0.f, 0.f, 0.f, 0.f};
 
     const float* __restrict__ yg = reinterpret_cast<const float*>(p.y);
     const float* __restrict__ ug = reinterpret_cast<const float*>(p.u);
-    gacc acc[WB][WB], accB[WB];
+    const gacc zero = {0.f, 0.f, 0.f, 0.f};
+    gacc accH[L > 1 ? L - 1 : 1][WB], acc1 = zero, accO = zero, accB[L], accBo = zero;
 #pragma unroll
-    for (int I = 0; I < WB; ++I) {
-        accB[I] = gacc{0.f, 0.f, 0.f, 0.f};
+    for (int l = 0; l < L; ++l) {
+        accB[l] = zero;
+        if (l > 0)
 #pragma unroll
-        for (int J = 0; J < WB; ++J) acc[I][J] = gacc{0.f, 0.f, 0.f, 0.f};
+            for (int J = 0; J < WB; ++J) accH[l > 0 ? l - 1 : 0][J] = zero;
     }
     const long long total = (long long)p.B * p.T;
     const long long tiles = (total + 15) / 16;
-    const long long tstride = (long long)gridDim.x * kWaves;
-    for (long long tile = (long long)blockIdx.x * kWaves + wave; tile < tiles; tile += tstride) {
-        const long long s0 = tile * 16;
+    for (long long t0 = (long long)blockIdx.x * 2; t0 < tiles; t0 += (long long)gridDim.x * 2) {   // (the same for both teams)
+        const long long s0 = (t0 + team) * 16;   // (past the end for the second team of the last pair: no live point)
         const long long sc = s0 + c;
         const bool live = sc < total;
         const long long scl = live ? sc : 0;
-        float yB[2];
+        float yB[2], yK[4];
 #pragma unroll
-        for (int m = 0; m < 2; ++m) yB[m] = live ? yg[scl * N + 4 * m + g] : 0.0f;
+        for (int m = 0; m < 2; ++m) {
+            const float t = yg[scl * N + 4 * m + g];
+            yB[m] = live ? t : 0.0f;
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {   // entry c of point 4m + g
+            const long long sp = s0 + 4 * m + g;
+            const float t = yg[(sp < total ? sp : 0) * N + (c & 7)];
+            yK[m] = (c < N && sp < total) ? t : 0.0f;
+        }
         // w in accumulator layout: entries 4g .. 4g+3 of point c (zero for g >= 2 and past the end)
-        gacc wA = {0.f, 0.f, 0.f, 0.f};
+        gacc wA = zero;
         if (live && g < 2) {
             const long long b = sc / p.T, j = sc - b * p.T;
             float4 ua = {0.f, 0.f, 0.f, 0.f}, ub = {0.f, 0.f, 0.f, 0.f};
@@ -372,166 +399,120 @@ __global__ __launch_bounds__(kThreads) void mlp_gen_vjp_mfma_kernel(MlpVjpParams
             if (j > 0) ub = *reinterpret_cast<const float4*>(ug + (b * (p.T - 1) + j - 1) * N + 4 * g);
             wA = gacc{0.5f * (ua.x + ub.x), 0.5f * (ua.y + ub.y), 0.5f * (ua.z + ub.z), 0.5f * (ua.w + ub.w)};
         }
+        __syncthreads();   // (w and the activations of the previous tile have been read; the weights are there)
+        if (w == 0 && g < 2) *reinterpret_cast<gacc*>(sU + c * 16 + 4 * g) = wA;
 
-        // ---- forward: activations (the one entering the block's layer is kept) and derivative factors ----
-        gacc a[WB], ain[WB], dact[L][WB];
+        // ---- forward: this wavefront's rows of every layer ----
+        gacc dact[L];
+        float* mine = sA + c * WS + row0 + 4 * g;
 #pragma unroll
-        for (int I = 0; I < WB; ++I) {
-            gacc z;
+        for (int l = 0; l < L; ++l) {
+            gacc z = bias[l], z2 = zero;
+            if (l == 0) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) z[v] = sb[16 * I + 4 * g + v];
+                for (int m = 0; m < 2; ++m) z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[m], yB[m], z, 0, 0, 0);
+            } else {
+                const float* in = sA + (l - 1) * 16 * WS + c * WS + 4 * g;
 #pragma unroll
-            for (int m = 0; m < 2; ++m) z = __builtin_amdgcn_mfma_f32_16x16x4f32(sW1[(16 * I + c) * W1S + 4 * m + g], yB[m], z, 0, 0, 0);
+                for (int K = 0; K < WB; ++K) {
+                    const gacc a = *reinterpret_cast<const gacc*>(in + 16 * K);
+#pragma unroll
+                    for (int v = 0; v < 4; v += 2) {
+                        z = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[l > 0 ? l - 1 : 0][K][v], a[v], z, 0, 0, 0);
+                        z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[l > 0 ? l - 1 : 0][K][v + 1], a[v + 1], z2, 0, 0, 0);
+                    }
+                }
+            }
+            gacc a;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 float av, dv;
-                fast_act(kind, z[v], av, dv);
-                a[I][v] = live ? av : 0.0f;
-                dact[0][I][v] = dv;
+                fast_act(kind, z[v] + z2[v], av, dv);
+                a[v] = av;
+                dact[l][v] = dv;
             }
-            ain[I] = a[I];
+            *reinterpret_cast<gacc*>(mine + l * 16 * WS) = a;
+            if (l + 1 < L) __syncthreads();
         }
+
+        // ---- reverse: the cotangents of the pre-activations, the sums of a layer as soon as its cotangent is there ----
+        gacc dc = zero;
 #pragma unroll
-        for (int l = 1; l < L; ++l) {
-            gacc an[WB];
+        for (int v = 0; v < 4; ++v) dc = __builtin_amdgcn_mfma_f32_16x16x4f32(wo[v], wA[v], dc, 0, 0, 0);
+        dc *= dact[L - 1];
+        *reinterpret_cast<gacc*>(sC + ((L - 1) & 1) * 16 * WS + c * WS + row0 + 4 * g) = dc;
+        __syncthreads();
+        accBo += wA;
 #pragma unroll
-            for (int I = 0; I < WB; ++I) {
-                gacc z;
+        for (int m = 0; m < 4; ++m)
+            accO = __builtin_amdgcn_mfma_f32_16x16x4f32(sU[(4 * m + g) * 16 + c], sA[((L - 1) * 16 + 4 * m + g) * WS + row0 + c], accO, 0, 0, 0);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) z[v] = sb[l * W + 16 * I + 4 * g + v];
+        for (int l = L - 1; l >= 0; --l) {
+            const float* cur = sC + (l & 1) * 16 * WS;
+            accB[l] += dc;
+            if (l > 0) {
+                // the cotangent of the layer below first: the others wait for it
+                gacc z = zero, z2 = zero;
+                const float* wt = sWh + ((l - 1) * W + 4 * g) * WS + row0 + c;
 #pragma unroll
                 for (int K = 0; K < WB; ++K) {
-                    float wa[4];
-                    vload<float, 4>(wa, &sWh[((l - 1) * W + 16 * I + c) * WS + 16 * K + 4 * g]);
+                    const gacc in = *reinterpret_cast<const gacc*>(cur + c * WS + 16 * K + 4 * g);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) z = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], z, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float av, dv;
-                    fast_act(kind, z[v], av, dv);
-                    an[I][v] = live ? av : 0.0f;
-                    dact[l][I][v] = dv;
-                }
-            }
-#pragma unroll
-            for (int I = 0; I < WB; ++I) {
-                a[I] = an[I];
-                if (l < grp) ain[I] = an[I];   // ain = output of hidden layer min(grp, L) - 1 (grp >= 1)
-            }
-        }
-
-        // ---- reverse, down to the block's layer: dcur = cotangent of the pre-activation of hidden layer l ----
-        gacc dcur[WB];
-        if (grp < L) {
-#pragma unroll
-            for (int I = 0; I < WB; ++I) {
-                gacc z = {0.f, 0.f, 0.f, 0.f};
-                // k-step v: lane group g supplies entry 4g + v of w (zero from g = 2 on); A[i = c][k = g] = W_out[4g + v][16 I + c]
-#pragma unroll
-                for (int v = 0; v < 4; ++v) z = __builtin_amdgcn_mfma_f32_16x16x4f32(sWo[(4 * g + v) * WS + 16 * I + c], wA[v], z, 0, 0, 0);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) dcur[I][v] = z[v] * dact[L - 1][I][v];
-            }
-#pragma unroll
-            for (int l = L - 2; l >= 0; --l) {
-                if (l >= grp) {   // (uniform)
-                    gacc dn[WB];
-#pragma unroll
-                    for (int I = 0; I < WB; ++I) {
-                        gacc z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int K = 0; K < WB; ++K)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                z = __builtin_amdgcn_mfma_f32_16x16x4f32(sWh[(l * W + 16 * K + 4 * g + v) * WS + 16 * I + c], dcur[K][v], z, 0, 0, 0);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) dn[I][v] = z[v] * dact[l][I][v];
+                    for (int v = 0; v < 4; v += 2) {
+                        z = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[(16 * K + v) * WS], in[v], z, 0, 0, 0);
+                        z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[(16 * K + v + 1) * WS], in[v + 1], z2, 0, 0, 0);
                     }
+                }
+                dc = (z + z2) * dact[l > 0 ? l - 1 : 0];
+                *reinterpret_cast<gacc*>(sC + ((l - 1) & 1) * 16 * WS + c * WS + row0 + 4 * g) = dc;
+            }
 #pragma unroll
-                    for (int I = 0; I < WB; ++I) dcur[I] = dn[I];
+            for (int m = 0; m < 4; ++m) {
+                // A[i = c][k = g -> point 4m + g] from this wavefront's cotangent rows, B[k][j = c] from the layer's input
+                const float td = cur[(4 * m + g) * WS + row0 + c];
+                if (l == 0) {
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(td, yK[m], acc1, 0, 0, 0);
+                } else {
+                    const float* in = sA + ((l - 1) * 16 + 4 * m + g) * WS + c;
+#pragma unroll
+                    for (int J = 0; J < WB; ++J) accH[l > 0 ? l - 1 : 0][J] = __builtin_amdgcn_mfma_f32_16x16x4f32(td, in[16 * J], accH[l > 0 ? l - 1 : 0][J], 0, 0, 0);
                 }
             }
-        }
-
-        // ---- the layer's cotangent (rows 0 .. W-1 of the tile) and input (rows W .. 2W-1) with the points as columns ----
-        if (grp == L) {
-            if (g < 2) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) myD[(4 * g + v) * LD + c] = wA[v];
-            }
-            accB[0] += wA;
-        } else {
-#pragma unroll
-            for (int I = 0; I < WB; ++I) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) myD[(16 * I + 4 * g + v) * LD + c] = dcur[I][v];
-                accB[I] += dcur[I];
-            }
-        }
-        if (grp > 0) {
-#pragma unroll
-            for (int I = 0; I < WB; ++I)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) myD[(W + 16 * I + 4 * g + v) * LD + c] = ain[I][v];
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            // A[i = c][k = g -> point 4m + g] from the cotangent rows, B[k = g -> point 4m + g][j = c] from the input rows
-            const int at = c * LD + 4 * m + g;
-            float td[WB], tin[WB];
-#pragma unroll
-            for (int I = 0; I < WB; ++I) {
-                td[I] = myD[(16 * I) * LD + at];
-                tin[I] = myD[(W + 16 * I) * LD + at];
-            }
-            if (grp == 0) {
-                const long long sp = s0 + 4 * m + g;
-                const float yK = (c < N && sp < total) ? yg[sp * N + c] : 0.0f;   // entry c of point 4m + g
-#pragma unroll
-                for (int I = 0; I < WB; ++I) acc[I][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(td[I], yK, acc[I][0], 0, 0, 0);
-            } else if (grp == L) {
-#pragma unroll
-                for (int J = 0; J < WB; ++J) acc[0][J] = __builtin_amdgcn_mfma_f32_16x16x4f32(td[0], tin[J], acc[0][J], 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int I = 0; I < WB; ++I)
-#pragma unroll
-                    for (int J = 0; J < WB; ++J) acc[I][J] = __builtin_amdgcn_mfma_f32_16x16x4f32(td[I], tin[J], acc[I][J], 0, 0, 0);
-            }
+            if (l > 0) __syncthreads();
         }
     }
 
-    // ---- this layer's slice of the wavefront's partial row ----
+    // ---- the team's partial row ----
     const long long P = gen_theta_len(N, W, L);
-    float* __restrict__ prow = reinterpret_cast<float*>(p.partial) + ((long long)blockIdx.x * kWaves + wave) * P;
-    const long long base = layer_offset(N, W, grp);
+    float* __restrict__ prow = reinterpret_cast<float*>(p.partial) + ((long long)blockIdx.x * 2 + team) * P;
+    auto column_sum = [](float v) {
 #pragma unroll
-    for (int I = 0; I < WB; ++I)
+        for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
+        return v;
+    };
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = 16 * I + 4 * g + v;
-            float sbias = accB[I][v];
+    for (int v = 0; v < 4; ++v) {
+        const int row = row0 + 4 * g + v;
 #pragma unroll
-            for (int o = 1; o < 16; o <<= 1) sbias += __shfl_xor(sbias, o);
-            if (grp == 0) {
-                if (c < N) prow[base + row * N + c] = acc[I][0][v];
-                if (c == 0) prow[base + W * N + row] = sbias;
-            } else if (grp == L) {
-                if (I == 0 && g < 2) {
-#pragma unroll
-                    for (int J = 0; J < WB; ++J) prow[base + (4 * g + v) * W + 16 * J + c] = acc[0][J][v];
-                    if (c == 0) prow[base + N * W + 4 * g + v] = sbias;
-                }
+        for (int l = 0; l < L; ++l) {
+            const long long base = layer_offset(N, W, l);
+            if (l == 0) {
+                if (c < N) prow[row * N + c] = acc1[v];
             } else {
 #pragma unroll
-                for (int J = 0; J < WB; ++J) prow[base + row * W + 16 * J + c] = acc[I][J][v];
-                if (c == 0) prow[base + W * W + row] = sbias;
+                for (int J = 0; J < WB; ++J) prow[base + row * W + 16 * J + c] = accH[l > 0 ? l - 1 : 0][J][v];
             }
+            const float s = column_sum(accB[l][v]);
+            if (c == 0) prow[base + (l == 0 ? W * N : W * W) + row] = s;
         }
+        const long long base = layer_offset(N, W, L);
+        if (g < 2) prow[base + (4 * g + v) * W + row0 + c] = accO[v];
+        const float s = column_sum(accBo[v]);
+        if (w == 0 && g < 2 && c == 0) prow[base + N * W + 4 * g + v] = s;
+    }
 }
 
-size_t vj_mfma_smem(int W, int L) { return ((size_t)W * 12 + (size_t)(L - 1) * W * (W + 4) + 16 * (size_t)(W + 4) + (size_t)L * W + 16 + 4 * 2 * (size_t)W * 17) * 4; }
+size_t vj_mfma_smem(int W, int L) { return ((size_t)(L - 1) * W * (W + 4) + 2 * ((size_t)(L + 2) * 16 * (W + 4) + 256)) * 4; }
 
 template <int WB, int L>
 hipError_t launch_vj_mfma_wl(const MlpVjpParams& p, int blocks, hipStream_t s) {
@@ -539,7 +520,7 @@ hipError_t launch_vj_mfma_wl(const MlpVjpParams& p, int blocks, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_gen_vjp_mfma_kernel<WB, L>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((mlp_gen_vjp_mfma_kernel<WB, L>), dim3((unsigned)blocks, (unsigned)(L + 1)), dim3(kThreads), shmem, s, p);
+    hipLaunchKernelGGL((mlp_gen_vjp_mfma_kernel<WB, L>), dim3((unsigned)blocks), dim3(128 * WB), shmem, s, p);
     return hipGetLastError();
 }
 
@@ -973,11 +954,12 @@ hipError_t launch_mlp_general_vjp(int dtype, const MlpVjpParams& p, hipStream_t 
     if (!mlp_general_supported(p.n, p.width, p.nhid, p.act) || p.T < 2) return hipErrorInvalidValue;
     const char* e = getenv("DEER_MLP_MFMA");
     if (!(e && *e && atoi(e) == 0) && fe_mfma_supported(dtype, p.n, p.width, p.nhid) && p.blocks >= 1) {
-        // the partial region holds p.blocks * 4 rows: that many wavefront rows at most, and one block per CU by its LDS
-        const int blocks = p.blocks < 256 ? p.blocks : 256;
+        // two rows a workgroup (the partial region holds p.blocks * 4); one workgroup per compute unit by its LDS at width 64
+        const long long pairs = ((long long)p.B * p.T + 31) / 32;
+        const int most = p.blocks < 256 ? p.blocks : 256, blocks = pairs < most ? (int)pairs : most;
         hipError_t err = p.width == 32 ? launch_vj_mfma_w<2>(p, blocks, s) : launch_vj_mfma_w<4>(p, blocks, s);
         if (err != hipSuccess) return err;
-        return launch_partial_reduce(0, p.partial, p.dtheta, gen_theta_len(p.n, p.width, p.nhid), blocks * 4, s);
+        return launch_partial_reduce(0, p.partial, p.dtheta, gen_theta_len(p.n, p.width, p.nhid), blocks * 2, s);
     }
     return dtype == 0 ? launch_vj<float>(p, s) : launch_vj<double>(p, s);
 }
