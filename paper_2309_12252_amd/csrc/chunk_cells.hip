@@ -19,6 +19,8 @@
 
 namespace deer {
 
+long long chunk_cells_rows(const ChunkParams& p) { return ((long long)p.B * p.groups + 3) / 4; }
+
 namespace {
 
 enum { LSTM = 0, LEM = 1 };
@@ -451,9 +453,9 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
 // ------------------------------------------------------------------------------------------------------------------
 // The walk: one wavefront per group, its sixteen chunks are the columns of every product.
 // ------------------------------------------------------------------------------------------------------------------
-template <int CELL, int UP, int DS, bool VEC, bool REV>
+template <int CELL, int UP, int DS, bool VEC>
 __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
-    constexpr int N = 2 * UP, KS = UP / 4;
+    constexpr int N = 2 * UP;
     __shared__ unsigned s_max[4];
     if (gate_closed<float>(p.gate)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
@@ -469,30 +471,25 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
         const bool part0 = UP == 16 || g < 2, part1 = UP == 16 || g >= 2;   // parts this lane writes
         const float* __restrict__ yb = p.y + first * ld;
         const float* __restrict__ xb = p.x + first * d;
-        const float* __restrict__ gb = REV ? p.g + first * ld : nullptr;
         float* __restrict__ ob = p.out + first * ld;
         const int a = r * Lc, end = T - 16 * grp * Lc;
         auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
 
-        // requested R - 1 (dual: R) steps ahead; slots named by t mod R
+        // requested R - 1 steps ahead; slots named by t mod R
         constexpr int R = 4;
-        Acc y0r[R], y1r[R], g0r[REV ? R : 1], g1r[REV ? R : 1];
+        Acc y0r[R], y1r[R];
         float xr[R][DS];
         auto ask_y = [&](int j, int t) {
-            const unsigned o = row(REV ? a + Lc - 1 - t : a + t) * (unsigned)ld;
+            const unsigned o = row(a + t) * (unsigned)ld;
             y0r[j] = load_units<VEC>(yb + o, j0, n);
             y1r[j] = load_units<VEC>(yb + o + n, j0, n);
-            if constexpr (REV) {
-                g0r[j] = load_units<VEC>(gb + o, j0, n);
-                g1r[j] = load_units<VEC>(gb + o + n, j0, n);
-            }
         };
         auto ask_x = [&](int j, int t) {
-            const unsigned o = row(REV ? a + Lc - t : a + t) * (unsigned)d;
+            const unsigned o = row(a + t) * (unsigned)d;
 #pragma unroll
             for (int s = 0; s < DS; ++s) xr[j][s] = xb[o + min(DS * g + s, d - 1)];
         };
-        if constexpr (!REV) {
+        {
             const bool start = a == 0 && grp == 0;
             const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * ld : nullptr;
             const float* hp = start ? y0b : yb + (long long)(min(a, end) - 1) * ld;
@@ -501,35 +498,16 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
         }
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            if (REV || j < R - 1) ask_y(j, j);
+            if (j < R - 1) ask_y(j, j);
             ask_x(j, j);
         }
         Cell<CELL, UP, DS> cell;
         cell.load(p.theta, n, d, g, r);
-        float ut[REV ? 4 : 1][KS];   // dual: U_gate^T as operand A
-        if constexpr (REV) {
-            const float* __restrict__ U = p.theta + 4 * n * d;
-            const int col = min(r % UP, n - 1);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const int k = Cell<CELL, UP, DS>::kappa(g, s);
-                    const float v = U[(q * n + min(k, n - 1)) * n + col];
-                    ut[q][s] = k < n && r % UP < n ? v : 0.f;
-                }
-        }
-        auto times_t = [&](int q, const Acc& x, Acc acc) {
-#pragma unroll
-            for (int s = 0; s < KS; ++s) acc = mfma(ut[REV ? q : 0][s], Cell<CELL, UP, DS>::operand(x, g, s), acc);
-            return acc;
-        };
-
-        // forward: correction of the state in front of the position; dual: lambda at the time after it
+        // correction of the state in front of the position
         Acc e0, e1;
         {
             Acc e[N / 16];
-            fold_carries<N, REV>(p, b, grp, nq, g, r, e);
+            fold_carries<N, false>(p, b, grp, nq, g, r, e);
             if constexpr (UP == 16) {
                 e0 = e[0];
                 e1 = e[N / 16 - 1];
@@ -545,71 +523,32 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
         for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const int t = t0 + j, rel = REV ? a + Lc - 1 - t : a + t;
+                const int t = t0 + j, rel = a + t;
                 const bool live = rel < end;
-                const int jh = REV ? j : (j + R - 1) % R;
+                const int jh = (j + R - 1) % R;
                 Factors k[4];
                 cell.eval(k, y0r[jh], y1r[jh], xr[j], dt, g);
                 Acc n0, n1;
-                if constexpr (!REV) {
-                    if constexpr (CELL == LSTM) {
-                        const Acc ti = cell.times(0, e0, zero4(), g), tf = cell.times(1, e0, zero4(), g);
-                        const Acc tg = cell.times(2, e0, zero4(), g), to = cell.times(3, e0, zero4(), g);
+                if constexpr (CELL == LSTM) {
+                    const Acc ti = cell.times(0, e0, zero4(), g), tf = cell.times(1, e0, zero4(), g);
+                    const Acc tg = cell.times(2, e0, zero4(), g), to = cell.times(3, e0, zero4(), g);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const float dc = k[v].f * e1[v] + (k[v].a * ti[v] + (k[v].b * tf[v] + k[v].c * tg[v]));
-                            n1[v] = k[v].n1 + dc;
-                            n0[v] = k[v].n0 + (k[v].d * to[v] + k[v].e * dc);
-                        }
-                    } else {
-                        const Acc t1 = cell.times(0, e0, zero4(), g), t2 = cell.times(1, e0, zero4(), g), tz = cell.times(2, e0, zero4(), g);
-                        Acc dz;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            dz[v] = k[v].f * e1[v] + (k[v].a * t1[v] + k[v].b * tz[v]);
-                            n1[v] = k[v].n1 + dz[v];
-                        }
-                        const Acc ty = cell.times(3, dz, zero4(), g);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) n0[v] = k[v].n0 + (k[v].e * e0[v] + (k[v].c * t2[v] + k[v].d * ty[v]));
+                    for (int v = 0; v < 4; ++v) {
+                        const float dc = k[v].f * e1[v] + (k[v].a * ti[v] + (k[v].b * tf[v] + k[v].c * tg[v]));
+                        n1[v] = k[v].n1 + dc;
+                        n0[v] = k[v].n0 + (k[v].d * to[v] + k[v].e * dc);
                     }
                 } else {
-                    const Acc g0 = g0r[REV ? j : 0], g1 = g1r[REV ? j : 0];
-                    if constexpr (CELL == LSTM) {
-                        Acc di, df, dg, dd;
+                    const Acc t1 = cell.times(0, e0, zero4(), g), t2 = cell.times(1, e0, zero4(), g), tz = cell.times(2, e0, zero4(), g);
+                    Acc dz;
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const float dc = e1[v] + k[v].e * e0[v];
-                            di[v] = k[v].a * dc;
-                            df[v] = k[v].b * dc;
-                            dg[v] = k[v].c * dc;
-                            dd[v] = k[v].d * e0[v];
-                            n1[v] = g1[v] + k[v].f * dc;
-                        }
-                        n0 = times_t(0, di, g0);
-                        const Acc s1 = times_t(1, df, zero4()), s2 = times_t(2, dg, zero4()), s3 = times_t(3, dd, zero4());
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) n0[v] += s1[v] + (s2[v] + s3[v]);
-                    } else {
-                        Acc dy, d2, d1, dz;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            dy[v] = k[v].d * e0[v];
-                            d2[v] = k[v].c * e0[v];
-                        }
-                        const Acc zn = times_t(3, dy, e1);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            d1[v] = k[v].a * zn[v];
-                            dz[v] = k[v].b * zn[v];
-                            n1[v] = g1[v] + k[v].f * zn[v];
-                            n0[v] = g0[v] + k[v].e * e0[v];
-                        }
-                        n0 = times_t(0, d1, n0);
-                        const Acc s1 = times_t(1, d2, zero4()), s2 = times_t(2, dz, zero4());
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) n0[v] += s1[v] + s2[v];
+                    for (int v = 0; v < 4; ++v) {
+                        dz[v] = k[v].f * e1[v] + (k[v].a * t1[v] + k[v].b * tz[v]);
+                        n1[v] = k[v].n1 + dz[v];
                     }
+                    const Acc ty = cell.times(3, dz, zero4(), g);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) n0[v] = k[v].n0 + (k[v].e * e0[v] + (k[v].c * t2[v] + k[v].d * ty[v]));
                 }
                 if (live) {
                     float* o = ob + (long long)rel * ld;
@@ -619,22 +558,16 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
                 const unsigned mask = live ? 0x7fffffffu : 0u;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    if constexpr (!REV) {
-                        e0[v] = n0[v] - y0r[j][v];
-                        e1[v] = n1[v] - y1r[j][v];
-                        emax = max(emax, max(__float_as_uint(e0[v]) & mask, __float_as_uint(e1[v]) & mask));
-                    } else {
-                        e0[v] = live ? n0[v] : 0.f;   // nothing follows the last time
-                        e1[v] = live ? n1[v] : 0.f;
-                    }
+                    e0[v] = n0[v] - y0r[j][v];
+                    e1[v] = n1[v] - y1r[j][v];
+                    emax = max(emax, max(__float_as_uint(e0[v]) & mask, __float_as_uint(e1[v]) & mask));
                 }
-                if constexpr (!REV) ask_y((j + R - 1) % R, t - 1 + R);
-                else ask_y(j, t + R);
+                ask_y((j + R - 1) % R, t - 1 + R);
                 ask_x(j, t + R);
             }
         }
     }
-    if (!REV && p.err) {
+    if (p.err) {
         // one read-modify-write per workgroup: all wavefronts end at about the same time and queue on one address
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) emax = max(emax, (unsigned)__shfl_xor((int)emax, o));
@@ -647,17 +580,268 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
     }
 }
 
-template <int CELL, int UP, int DS, bool VEC, bool REV>
-hipError_t launch_all(const ChunkParams& p, hipStream_t s) {
-    hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((cell_walk_kernel<CELL, UP, DS, VEC, REV>), dim3((unsigned)(((long long)p.B * p.groups + 3) / 4)), dim3(256), 0, s, p);
-    return hipGetLastError();
+// ------------------------------------------------------------------------------------------------------------------
+// The dual walk with the vector-Jacobian product inside: lambda_i = g_i + J_{i+1}^T lambda_{i+1} needs the cotangents of the pre-activations
+// at position i + 1, which are all that dL/dx, dL/dtheta and (at the first position) dL/dy0 are made of, so neither lambda nor the
+// gates go through memory.  A step evaluates the cell behind the position it solves for; one more step takes the first position of
+// the sequence.  The sums over positions have the columns on the contraction index: cotangents, state and input cross a slice of LDS.
+// UP = 16: dU per block, and dW^T with the bias sums as a ninth row (the input rows are followed by a row of ones).  UP = 8: two
+// blocks share a tile whose columns are (state | input).
+// Measured, gradient with a kernel of its own for the vector-Jacobian product / now, us: LSTM u = 8, d = 4, 16 x 50,000 positions 455 / 245; LEM u = 16, d = 6, 32 x 17,984 positions 1,020 / 490.
+// ------------------------------------------------------------------------------------------------------------------
+template <int CELL, int UP, int DS, bool VEC>
+__global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
+    constexpr int N = 2 * UP, KS = UP / 4, TILES = UP == 16 ? 4 : 2;
+    constexpr int ST = 256 * TILES, XT = ST + (CELL == LEM ? 512 : 256);   // state tile (LEM: then the new z), UP = 16: input tile
+    constexpr int USED = UP == 16 ? XT + 256 : XT, ROW = 4 * UP * 8 + 4 * UP * UP + 4 * UP;
+    constexpr int SLICE = USED > ROW ? USED : ROW;   // (at the end the wavefront's row of dL/dtheta takes the place of its slice)
+    __shared__ __align__(16) float sT[4][SLICE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int T = p.T, d = p.d, Lc = p.Lc, n = p.cell_units, ld = 2 * n;
+    const float dt = p.dt;
+    const unsigned id = blockIdx.x * 4u + (unsigned)wave;
+    const int b = (int)(id % (unsigned)p.B), grp = (int)(id / (unsigned)p.B);
+    float* __restrict__ S = sT[wave];
+    // UP = 16: aU[q] = dU_q, aW[q] = (dW_q | db_q)^T.  UP = 8: aU[t] = blocks 2t, 2t + 1 by (state | input), aU[2] = block y by (z' | input);
+    // aW[t] = this lane's bias sums of the blocks.
+    Acc aU[4], aW[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) aU[q] = aW[q] = zero4();
+    for (int q = lane; q < SLICE; q += 64) S[q] = 0.f;
+    if (UP == 16 && lane < 16) S[XT + lane * 16 + 8] = 1.f;
+    wave_lds_fence();
+    if (grp < p.groups) {
+        const int chunks = (T + Lc - 1) / Lc, nq = min(16, chunks - 16 * grp);
+        const long long first = (long long)b * T + (long long)16 * grp * Lc;
+        const int j0 = (4 * g) % UP;
+        const float* __restrict__ yb = p.y + first * ld;
+        const float* __restrict__ xb = p.x + first * d;
+        const float* __restrict__ gb = p.g + first * ld;
+        float* __restrict__ dxb = p.dx ? p.dx + first * d : nullptr;
+        const int a = r * Lc, end = T - 16 * grp * Lc;
+        auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
+        constexpr int R = UP == 16 ? 2 : 4;
+        Acc y0r[R], y1r[R], g0r[R], g1r[R];
+        float xr[R][DS];
+        auto ask = [&](int j, int t) {
+            const unsigned o = row(a + Lc - 1 - t) * (unsigned)ld, ox = row(a + Lc - t) * (unsigned)d;
+            y0r[j] = load_units<VEC>(yb + o, j0, n);
+            y1r[j] = load_units<VEC>(yb + o + n, j0, n);
+            g0r[j] = load_units<VEC>(gb + o, j0, n);
+            g1r[j] = load_units<VEC>(gb + o + n, j0, n);
+#pragma unroll
+            for (int s = 0; s < DS; ++s) xr[j][s] = xb[ox + min(DS * g + s, d - 1)];
+        };
+#pragma unroll
+        for (int j = 0; j < R; ++j) ask(j, j);
+        Cell<CELL, UP, DS> cell;
+        cell.load(p.theta, n, d, g, r);
+        float ut[4][KS], wt[4][KS];   // U_gate^T and W_gate^T as operand A
+        {
+            const float* __restrict__ U = p.theta + 4 * n * d;
+            const int col = min(r % UP, n - 1), xc = min(r, d - 1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const int k = Cell<CELL, UP, DS>::kappa(g, s), kc = min(k, n - 1);
+                    const float v = U[(q * n + kc) * n + col], x = p.theta[(q * n + kc) * d + xc];
+                    ut[q][s] = k < n && r % UP < n ? v : 0.f;
+                    wt[q][s] = k < n && r < d ? x : 0.f;
+                }
+        }
+        auto times_t = [&](const float (&m)[KS], const Acc& x, Acc acc) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) acc = mfma(m[s], Cell<CELL, UP, DS>::operand(x, g, s), acc);
+            return acc;
+        };
+        Acc e0, e1;   // lambda at the position the step evaluates
+        {
+            Acc e[N / 16];
+            fold_carries<N, true>(p, b, grp, nq, g, r, e);
+            if constexpr (UP == 16) {
+                e0 = e[0];
+                e1 = e[N / 16 - 1];
+            } else {
+                Acc o;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] = __shfl_xor(e[0][v], 32);
+                e0 = g < 2 ? e[0] : o;
+                e1 = g < 2 ? o : e[0];
+            }
+        }
+        // one step at position `at` (relative) with state (s0 | s1) in front of it: adds J^T lambda to (n0 | n1)
+        auto step = [&](const Acc& s0, const Acc& s1, const float (&x)[DS], int at, Acc& n0, Acc& n1) {
+            Factors k[4];
+            cell.eval(k, s0, s1, x, dt, g);
+            Acc da[4], zn;
+            if constexpr (CELL == LSTM) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float dc = e1[v] + k[v].e * e0[v];
+                    da[0][v] = k[v].a * dc;
+                    da[1][v] = k[v].b * dc;
+                    da[2][v] = k[v].c * dc;
+                    da[3][v] = k[v].d * e0[v];
+                    n1[v] += k[v].f * dc;
+                }
+                n0 = times_t(ut[0], da[0], n0);
+                n0 = times_t(ut[1], da[1], n0);
+                const Acc s2 = times_t(ut[2], da[2], zero4());
+                n0 += times_t(ut[3], da[3], s2);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    da[3][v] = k[v].d * e0[v];
+                    da[1][v] = k[v].c * e0[v];
+                    zn[v] = k[v].n1;
+                }
+                const Acc dz = times_t(ut[3], da[3], e1);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    da[0][v] = k[v].a * dz[v];
+                    da[2][v] = k[v].b * dz[v];
+                    n1[v] += k[v].f * dz[v];
+                    n0[v] += k[v].e * e0[v];
+                }
+                n0 = times_t(ut[0], da[0], n0);
+                const Acc s1t = times_t(ut[1], da[1], zero4());
+                n0 += times_t(ut[2], da[2], s1t);
+            }
+            // ---- products over positions ----
+            if constexpr (UP == 16) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) store4(S + q * 256 + r * 16 + 4 * g, da[q]);
+                store4(S + ST + r * 16 + 4 * g, s0);
+                if constexpr (CELL == LEM) store4(S + ST + 256 + r * 16 + 4 * g, zn);
+#pragma unroll
+                for (int s = 0; s < DS; ++s) S[XT + r * 16 + DS * g + s] = x[s];
+            } else {
+                const Acc t0 = g < 2 ? da[0] : da[1], t1 = g < 2 ? da[2] : da[3];
+                store4(S + r * 16 + 4 * g, t0);
+                store4(S + 256 + r * 16 + 4 * g, t1);
+                if (g < 2) {
+                    store4(S + ST + r * 16 + 4 * g, s0);
+                    if constexpr (CELL == LEM) store4(S + ST + 256 + r * 16 + 4 * g, zn);
+                }
+#pragma unroll
+                for (int s = 0; s < DS; ++s) S[ST + r * 16 + 8 + DS * g + s] = x[s];
+                aW[0] += t0;
+                aW[1] += t1;
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const float* q = S + (4 * m + g) * 16 + r;
+                const float bs = q[ST], bz = CELL == LEM ? q[ST + 256] : 0.f;
+                if constexpr (UP == 16) {
+                    const float bx = q[XT];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float t = q[256 * i];
+                        aU[i] = mfma(t, CELL == LEM && i == 3 ? bz : bs, aU[i]);
+                        aW[i] = mfma(bx, t, aW[i]);
+                    }
+                } else {
+                    const float t1 = q[256];
+                    aU[0] = mfma(q[0], bs, aU[0]);
+                    aU[1] = mfma(t1, bs, aU[1]);
+                    if constexpr (CELL == LEM) aU[2] = mfma(t1, bz, aU[2]);
+                }
+            }
+            wave_lds_fence();
+            if (dxb) {
+                Acc o0 = times_t(wt[0], da[0], zero4()), o1 = times_t(wt[1], da[1], zero4());
+                o0 = times_t(wt[2], da[2], o0);
+                o1 = times_t(wt[3], da[3], o1);
+                if (g < 2 && at < end) {
+                    float* o = dxb + (long long)at * d + 4 * g;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (4 * g + v < d) o[v] = o0[v] + o1[v];
+                }
+            }
+        };
+        // (a column that starts past the end has nothing to store: its positions are not below `end`)
+        for (int t0 = 0; t0 < Lc; t0 += R) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int t = t0 + j, rel = a + Lc - 1 - t;
+                const bool live = rel < end;
+                Acc n0 = g0r[j], n1 = g1r[j];
+                step(y0r[j], y1r[j], xr[j], rel + 1, n0, n1);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    e0[v] = live ? n0[v] : 0.f;   // nothing follows the last position
+                    e1[v] = live ? n1[v] : 0.f;
+                }
+                ask(j, t + R);
+            }
+        }
+        if (grp == 0) {   // the first position of the sequence
+            const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * ld : nullptr;
+            const Acc s0 = y0b ? load_units<VEC>(y0b, j0, n) : zero4(), s1 = y0b ? load_units<VEC>(y0b + n, j0, n) : zero4();
+            Acc n0 = zero4(), n1 = zero4();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                e0[v] = r == 0 ? e0[v] : 0.f;
+                e1[v] = r == 0 ? e1[v] : 0.f;
+            }
+            step(s0, s1, xr[0], r == 0 ? 0 : end, n0, n1);
+            if (p.dy0 && r == 0) {
+                float* o = p.dy0 + (long long)b * ld;
+                if (UP == 16 || g < 2) store_units<false>(o, j0, n, n0);
+                if (UP == 16 || g >= 2) store_units<false>(o + n, j0, n, n1);
+            }
+        }
+    }
+
+    // ---- the workgroup's row of dL/dtheta: W[4n,d] | U[4n,n] | b[4n] ----
+    const int U0 = 4 * n * d, b0 = U0 + 4 * n * n, P = b0 + 4 * n;
+    if constexpr (UP == 16) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = 4 * g + v;
+                if (k < n && r < n) S[U0 + (q * n + k) * n + r] = aU[q][v];
+                if (r < n) {   // row k of (dW | db)^T, column r
+                    if (k < d && k < 8) S[(q * n + r) * d + k] = aW[q][v];
+                    if (k == 8) S[b0 + q * n + r] = aW[q][v];
+                }
+            }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const Acc sb = row_sums4(aW[t], r);
+            const int q = 2 * t + (g >> 1);   // the block of this lane's rows
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = (4 * g + v) & 7;
+                if (k >= n) continue;
+                if (r < 8) {
+                    if (r < n) S[U0 + (q * n + k) * n + r] = CELL == LEM && t == 1 && g >= 2 ? aU[2][v] : aU[t][v];
+                } else if (r - 8 < d) {
+                    S[(q * n + k) * d + r - 8] = aU[t][v];
+                }
+                if (r == 0) S[b0 + q * n + k] = sb[v];
+            }
+        }
+    }
+    __syncthreads();
+    for (int q = tid; q < P; q += 256) p.partial[(long long)blockIdx.x * P + q] = (sT[0][q] + sT[1][q]) + (sT[2][q] + sT[3][q]);
 }
+
 template <int CELL, int UP, int DS, bool VEC>
 hipError_t launch_v(const ChunkParams& p, hipStream_t s) {
-    return p.g ? launch_all<CELL, UP, DS, VEC, true>(p, s) : launch_all<CELL, UP, DS, VEC, false>(p, s);
+    const dim3 units((unsigned)((long long)p.B * p.units)), groups((unsigned)chunk_cells_rows(p));
+    if (p.g) hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, true>), units, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, false>), units, dim3(256), 0, s, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (p.g) hipLaunchKernelGGL((cell_dual_kernel<CELL, UP, DS, VEC>), groups, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((cell_walk_kernel<CELL, UP, DS, VEC>), groups, dim3(256), 0, s, p);
+    return hipGetLastError();
 }
 template <int CELL, int UP, int DS>
 hipError_t launch_d(const ChunkParams& p, hipStream_t s) {
@@ -677,7 +861,11 @@ size_t chunk_cells_map_bytes(int units) { return chunk_map_bytes(units <= 8 ? 16
 
 hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s) {
     if (!chunk_cells_supported(0, p.cell_units, p.d) || !chunk_params_valid(p)) return hipErrorInvalidValue;
-    return lem ? launch_cell<LEM>(p, s) : launch_cell<LSTM>(p, s);
+    if (p.g ? !p.partial || !p.dtheta : !p.out) return hipErrorInvalidValue;
+    const hipError_t e = lem ? launch_cell<LEM>(p, s) : launch_cell<LSTM>(p, s);
+    if (e != hipSuccess || !p.g) return e;
+    const long long n = p.cell_units;
+    return launch_partial_reduce(0, p.partial, p.dtheta, 4 * n * p.d + 4 * n * n + 4 * n, (int)chunk_cells_rows(p), s);
 }
 
 }  // namespace deer

@@ -473,7 +473,9 @@ Plan make_plan(const deer_config* c) {
     p.off_tot = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * map : p.chunk ? B * (size_t)p.chunk_groups * 16 * map : 0);
     p.off_sup = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * map : p.chunk ? B * (size_t)p.chunk_units * map : 0);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
-    p.off_partial = take(p.chunk8_grad ? (size_t)(p.c8.groups / 4) * p.c8.P * p.esz : (size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
+    p.off_partial = take(p.chunk8_grad ? (size_t)(p.c8.groups / 4) * p.c8.P * p.esz
+                         : cell_chunk  ? (B * (size_t)p.chunk_groups + 3) / 4 * theta_count(c) * p.esz
+                                       : (size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
     p.off_timing = take(kTimingBytes);
 #endif
@@ -587,6 +589,22 @@ void prof_collect(deer_ctx* c, int iters_done = 1 << 30) {
     c->ev_used = 0;
 }
 
+ChunkParams chunk_params(deer_ctx* c, const void* theta, const void* x, const void* y0, const void* y) {
+    const deer_config& g = c->cfg;
+    ChunkParams q{};
+    q.theta = reinterpret_cast<const float*>(theta); q.x = reinterpret_cast<const float*>(x);
+    q.y0 = reinterpret_cast<const float*>(y0); q.y = reinterpret_cast<const float*>(y);
+    q.tot = reinterpret_cast<float*>(c->ws + c->plan.off_tot);
+    q.sup = reinterpret_cast<float*>(c->ws + c->plan.off_sup);
+    q.B = g.B; q.T = g.T; q.d = g.d; q.Lc = c->plan.chunk_L; q.groups = c->plan.chunk_groups;
+    q.per_unit = c->plan.chunk_per_unit; q.units = c->plan.chunk_units;
+    if (two_part_cell(g.cell)) {
+        q.cell_units = g.reserved;
+        q.dt = (float)g.t1;
+    }
+    return q;
+}
+
 Chunk8Params chunk8_params(deer_ctx* c, const void* theta, const void* x, const void* y0, const void* y) {
     Chunk8Params q = c->plan.c8;
     q.theta = reinterpret_cast<const float*>(theta); q.x = reinterpret_cast<const float*>(x);
@@ -620,24 +638,12 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
 #endif
     hipError_t e;
     if (fused_theta && c->plan.chunk) {
-        ChunkParams q{};
-        q.theta = reinterpret_cast<const float*>(fused_theta); q.x = reinterpret_cast<const float*>(fused_x);
-        q.y0 = reinterpret_cast<const float*>(y0); q.y = reinterpret_cast<const float*>(yold);
+        ChunkParams q = chunk_params(c, fused_theta, fused_x, y0, yold);
         q.g = reverse ? reinterpret_cast<const float*>(bv) : nullptr;
         q.out = reinterpret_cast<float*>(out);
-        q.tot = reinterpret_cast<float*>(c->ws + c->plan.off_tot);
-        q.sup = reinterpret_cast<float*>(c->ws + c->plan.off_sup);
         q.err = p.err; q.gate = gate;
-        q.B = g.B; q.T = g.T; q.d = g.d; q.Lc = c->plan.chunk_L; q.groups = c->plan.chunk_groups;
-        q.per_unit = c->plan.chunk_per_unit; q.units = c->plan.chunk_units;
         prof_begin(c, KIND_FUSED, iter);
-        if (two_part_cell(g.cell)) {
-            q.cell_units = g.reserved;
-            q.dt = (float)g.t1;
-            e = launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream);
-        } else {
-            e = launch_chunk_gru(g.n, q, c->stream);
-        }
+        e = two_part_cell(g.cell) ? launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream) : launch_chunk_gru(g.n, q, c->stream);
     } else if (fused_theta && c->plan.chunk8) {
         Chunk8Params q = chunk8_params(c, fused_theta, fused_x, y0, yold);
         q.out = reinterpret_cast<float*>(out);
@@ -1174,6 +1180,19 @@ static deer_status grad_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
         prof_begin(c, KIND_FUSED);
         HIPCHK(c, launch_chunk_gru8(q, c->stream));
         if (parts) HIPCHK(c, launch_gru_dy0_mh(q.dy0, reinterpret_cast<float*>(d_dLdy0), g.B, g.T, c->plan.mh_H, c->plan.mh_K, g.n, c->stream));
+        prof_end(c);
+        st = check_status(c);
+        prof_collect(c);
+        return st;
+    }
+    if (c->plan.chunk && two_part_cell(g.cell)) {
+        ChunkParams q = chunk_params(c, d_theta, d_x, d_y0, d_y);
+        q.g = reinterpret_cast<const float*>(d_dLdy);
+        q.dx = reinterpret_cast<float*>(d_dLdx); q.dy0 = reinterpret_cast<float*>(d_dLdy0);
+        q.dtheta = reinterpret_cast<float*>(d_dLdtheta);
+        q.partial = reinterpret_cast<float*>(c->ws + c->plan.off_partial);
+        prof_begin(c, KIND_FUSED);
+        HIPCHK(c, launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream));
         prof_end(c);
         st = check_status(c);
         prof_collect(c);

@@ -95,7 +95,9 @@ struct ChunkParams {
     const float* theta; const float* x; const float* y0;   // y0 may be nullptr (zeros)
     const float* y;            // previous iterate, or the trajectory of the backward pass [B,T,n]
     const float* g;            // dL/dy [B,T,n], or nullptr
-    float* out;                // next iterate, or lambda [B,T,n]
+    float* out;                // next iterate, or (GRU) lambda [B,T,n]
+    // gradient of the LSTM and the LEM: dx [B,T,d] or nullptr, dy0 [B,n] or nullptr, dtheta, one row of its length per workgroup
+    float* dx; float* dy0; float* dtheta; float* partial;
     float* tot; float* sup;    // maps of the chunks [B][groups][16][n*n + n] and of the units [B][units][n*n + n]
     void* err;                 // max|y_new - y| (raw bits), or nullptr
     Gate gate;
@@ -365,6 +367,7 @@ bool chunk_params_valid(const ChunkParams& p);
 // the same for the LSTM and the LEM (fp32, 1..16 units, d <= 8)
 bool chunk_cells_supported(int dtype, int units, int d);
 size_t chunk_cells_map_bytes(int units);
+long long chunk_cells_rows(const ChunkParams& p);   // workgroups of the walk: rows of `partial`
 hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru64(const ChunkParams& p, hipStream_t s);
