@@ -1224,7 +1224,6 @@ static deer_status grad_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
         HIPCHK(c, launch_lem_vjp(g.dtype, vp, c->stream));
     } else if (!c->plan.mh && gru_vjp_mfma_supported(g.dtype, g.n, g.d) && env_int("DEER_VJP_MFMA", 1) != 0) {
         HIPCHK(c, launch_gru_vjp_mfma(vp, c->stream));
-        HIPCHK(c, launch_partial_reduce(g.dtype, vp.partial, d_dLdtheta, (long long)theta_count(&g), vp.blocks * 4, c->stream));
     } else {
         HIPCHK(c, launch_gru_vjp(g.dtype, vp, c->stream));
     }

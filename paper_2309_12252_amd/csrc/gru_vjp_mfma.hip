@@ -1,4 +1,4 @@
-// Vector-Jacobian product of the GRU cell on the matrix cores (fp32, n = 16 or 32, d <= 16): the same
+// Vector-Jacobian product of the GRU cell on the matrix cores (fp32, n = 16, 32 or 64, d <= 16): the same
 // quantities as gru_vjp_kernel (Sec. 3.1.1 eq. 7, outer bracket) -- dL/dx per position, dL/dy0, and partial
 // rows of dL/dtheta for the fixed-order reduction -- with every contraction as 16 x 16 x 4 MFMAs.
 //
@@ -281,6 +281,195 @@ __global__ __launch_bounds__(kThreads, N == 32 ? 2 : 1) void gru_vjp_mfma_kernel
             }
 }
 
+// n = 64: the sums of one wavefront would not fit its registers (48 blocks), so the four wavefronts of a workgroup take the same 16
+// positions and 16 rows of every gate each: gates, cotangents and sums of these rows need nothing from the other wavefronts but
+// the input gradient, whose four parts meet in LDS (one barrier a tile, double-buffered).  One partial row per workgroup.
+// Bound: fp32 matrix instructions, 132 of 32 cycles a wavefront and tile (25 us at 49,865 positions).  The vector-ALU kernel took 742 us
+// there (d = 7), this one 45 us.
+__global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParams p) {
+    constexpr int N = 64, NB = 4;
+    __shared__ __align__(16) float sD[kWaves][5][16][kLD];    // dar, daz, dac, dq, z lam of the wavefront's rows
+    __shared__ float sX[2][kWaves][16][kLD];                  // input gradient: parts of the wavefronts
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c = lane & 15, d = p.d, row0 = 16 * wave;
+    const float* __restrict__ theta = reinterpret_cast<const float*>(p.theta);
+    const float* __restrict__ U = theta + 3 * N * d;
+    const float* __restrict__ bias = U + 3 * N * N;
+    const float* __restrict__ x = reinterpret_cast<const float*>(p.x);
+    const float* __restrict__ y0 = reinterpret_cast<const float*>(p.y0);
+    const float* __restrict__ y = reinterpret_cast<const float*>(p.y);
+    const float* __restrict__ lam = reinterpret_cast<const float*>(p.lam);
+    float* __restrict__ dx = reinterpret_cast<float*>(p.dx);
+    float* __restrict__ dy0 = reinterpret_cast<float*>(p.dy0);
+
+    // operands A of this wavefront's rows; the state and the input supply entry 16 K + 4 g + v and 4 m + g
+    acc4 uA[3][NB], bA[4];
+    float wA[3][4], wT[3][4];   // W rows, and W columns for dL/dx (row 4 g + v of the wavefront's, column c)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+        for (int K = 0; K < NB; ++K)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) uA[a][K][v] = U[(a * N + row0 + c) * N + 16 * K + 4 * g + v];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const float w = theta[(a * N + row0 + c) * d + min(4 * m + g, d - 1)], t = theta[(a * N + row0 + 4 * g + m) * d + min(c, d - 1)];
+            wA[a][m] = 4 * m + g < d ? w : 0.0f;
+            wT[a][m] = c < d ? t : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bA[a][v] = bias[a * N + row0 + 4 * g + v];
+
+    const acc4 zero = {0.f, 0.f, 0.f, 0.f};
+    acc4 accU[3][NB], accW[3], accB[4];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        accW[a] = zero;
+#pragma unroll
+        for (int J = 0; J < NB; ++J) accU[a][J] = zero;
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) accB[a] = zero;
+
+    const long long total = (long long)p.B * p.T, tiles = (total + 15) / 16;
+    auto hrow = [&](long long s) -> const float* {   // state in front of position s (positions past the end read position 0)
+        const long long sc = s < total ? s : 0, bi = sc / p.T;
+        return (sc - bi * p.T == 0) ? (y0 + bi * N) : (y + (sc - 1) * N);
+    };
+    int buf = 0;
+    for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x, buf ^= 1) {
+        const long long s0 = tile * 16, sc = s0 + c;
+        const bool live = sc < total;
+        const long long scl = live ? sc : 0;
+        const float* hc = hrow(sc);
+        acc4 h[NB];
+        float xB[4], hK[4][NB], xK[4];
+#pragma unroll
+        for (int K = 0; K < NB; ++K) {
+            const float4 t = *reinterpret_cast<const float4*>(hc + 16 * K + 4 * g);
+            h[K] = acc4{t.x, t.y, t.z, t.w};
+        }
+        const float4 lv = *reinterpret_cast<const float4*>(lam + scl * N + row0 + 4 * g), hv = *reinterpret_cast<const float4*>(hc + row0 + 4 * g);
+        const acc4 lm = live ? acc4{lv.x, lv.y, lv.z, lv.w} : zero, hw = {hv.x, hv.y, hv.z, hv.w};
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const long long sp = s0 + 4 * m + g;
+            const float* hp = hrow(sp);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) hK[m][J] = hp[16 * J + c];   // entry 16 J + c of position 4 m + g
+            const float a = x[scl * d + min(4 * m + g, d - 1)], b = x[(sp < total ? sp : 0) * d + min(c, d - 1)];
+            xB[m] = 4 * m + g < d ? a : 0.0f;
+            xK[m] = (c < d && sp < total) ? b : 0.0f;
+        }
+        acc4 ar = bA[0], az = bA[1], ac = bA[2], aq = bA[3];
+#pragma unroll
+        for (int K = 0; K < NB; ++K)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                ar = mfma(uA[0][K][v], h[K][v], ar);
+                az = mfma(uA[1][K][v], h[K][v], az);
+                aq = mfma(uA[2][K][v], h[K][v], aq);
+            }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            ar = mfma(wA[0][m], xB[m], ar);
+            az = mfma(wA[1][m], xB[m], az);
+            ac = mfma(wA[2][m], xB[m], ac);
+        }
+        acc4 dar, daz, dac, dq;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float r = feed_sigmoid(ar[v]), z = feed_sigmoid(az[v]);
+            const float cc = feed_tanh(ac[v] + r * aq[v]);
+            dac[v] = lm[v] * (1.0f - z) * (1.0f - cc * cc);
+            daz[v] = lm[v] * (hw[v] - cc) * z * (1.0f - z);
+            dq[v] = dac[v] * r;
+            dar[v] = dac[v] * aq[v] * r * (1.0f - r);
+            const int row = 4 * g + v;
+            sD[wave][0][row][c] = dar[v];
+            sD[wave][1][row][c] = daz[v];
+            sD[wave][2][row][c] = dac[v];
+            sD[wave][3][row][c] = dq[v];
+            sD[wave][4][row][c] = z * lm[v];
+        }
+        accB[0] += dar; accB[1] += daz; accB[2] += dac; accB[3] += dq;
+        if (dx) {   // rows (input index) 4 g + v of position c, this wavefront's share of the sum over rows
+            acc4 ax = zero;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                ax = mfma(wT[0][v], dar[v], ax);
+                ax = mfma(wT[1][v], daz[v], ax);
+                ax = mfma(wT[2][v], dac[v], ax);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sX[buf][wave][c][4 * g + v] = ax[v];
+        }
+        __syncthreads();
+        if (dx) {
+            const int q = tid >> 4, k = tid & 15;
+            if (s0 + q < total && k < d) dx[(s0 + q) * d + k] = (sX[buf][0][q][k] + sX[buf][1][q][k]) + (sX[buf][2][q][k] + sX[buf][3][q][k]);
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const float tr = sD[wave][0][c][4 * m + g], tz = sD[wave][1][c][4 * m + g], tc = sD[wave][2][c][4 * m + g], tq = sD[wave][3][c][4 * m + g];
+#pragma unroll
+            for (int J = 0; J < NB; ++J) {
+                accU[0][J] = mfma(tr, hK[m][J], accU[0][J]);
+                accU[1][J] = mfma(tz, hK[m][J], accU[1][J]);
+                accU[2][J] = mfma(tq, hK[m][J], accU[2][J]);
+            }
+            accW[0] = mfma(tr, xK[m], accW[0]);
+            accW[1] = mfma(tz, xK[m], accW[1]);
+            accW[2] = mfma(tc, xK[m], accW[2]);
+        }
+        // dL/dy0 = J_1^T lam_1 where a sequence starts among the sixteen positions (rare; the same for the whole workgroup)
+        if (dy0) {
+            const long long b0 = (s0 + p.T - 1) / p.T;   // first sequence that starts at s0 or later
+            if (b0 < p.B && b0 * p.T < s0 + 16) {
+                for (long long bi = b0; bi < p.B && bi * p.T < s0 + 16; ++bi) {
+                    const int q = (int)(bi * p.T - s0);
+                    if (tid < N) {
+                        float s = sD[tid / 16][4][tid % 16][q];
+                        for (int i = 0; i < N; ++i) {
+                            s += U[(0 * N + i) * N + tid] * sD[i / 16][0][i % 16][q];
+                            s += U[(1 * N + i) * N + tid] * sD[i / 16][1][i % 16][q];
+                            s += U[(2 * N + i) * N + tid] * sD[i / 16][3][i % 16][q];
+                        }
+                        dy0[bi * N + tid] = s;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+    }
+
+    const long long P = 3LL * N * d + 3LL * N * N + 4LL * N;
+    float* __restrict__ prow = reinterpret_cast<float*>(p.partial) + (long long)blockIdx.x * P;
+    float* pU = prow + 3LL * N * d;
+    float* pb = pU + 3LL * N * N;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = a * N + row0 + 4 * g + v;
+            if (c < d) prow[(long long)row * d + c] = accW[a][v];
+#pragma unroll
+            for (int J = 0; J < NB; ++J) pU[(long long)row * N + 16 * J + c] = accU[a][J][v];
+        }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float s = accB[a][v];
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o);
+            if (c == 0) pb[a * N + row0 + 4 * g + v] = s;
+        }
+}
+
 template <int N>
 hipError_t launch_n(const GruVjpParams& p, hipStream_t s) {
     const size_t shmem = ((size_t)3 * N * kLD + 4 * N + (size_t)kWaves * 5 * N * kLD) * sizeof(float);
@@ -290,12 +479,23 @@ hipError_t launch_n(const GruVjpParams& p, hipStream_t s) {
 
 }  // namespace
 
-bool gru_vjp_mfma_supported(int dtype, int n, int d) { return dtype == 0 && (n == 16 || n == 32) && d >= 1 && d <= kDP; }
+bool gru_vjp_mfma_supported(int dtype, int n, int d) { return dtype == 0 && (n == 16 || n == 32 || n == 64) && d >= 1 && d <= kDP; }
 
-// launches the kernel only; the caller adds the partial rows (blocks * 4 of them) with launch_partial_reduce
+// one partial row per wavefront, at n = 64 per workgroup; added in a fixed order
 hipError_t launch_gru_vjp_mfma(const GruVjpParams& p, hipStream_t s) {
-    if (!gru_vjp_mfma_supported(0, p.n, p.d)) return hipErrorInvalidValue;
-    return p.n == 16 ? launch_n<16>(p, s) : launch_n<32>(p, s);
+    if (!gru_vjp_mfma_supported(0, p.n, p.d) || p.blocks < 1) return hipErrorInvalidValue;
+    int rows = p.blocks * kWaves;
+    hipError_t e;
+    if (p.n == 64) {
+        const long long tiles = ((long long)p.B * p.T + 15) / 16;
+        rows = tiles < p.blocks ? (int)tiles : p.blocks;
+        hipLaunchKernelGGL(gru_vjp_mfma64_kernel, dim3((unsigned)rows), dim3(kThreads), 0, s, p);
+        e = hipGetLastError();
+    } else {
+        e = p.n == 16 ? launch_n<16>(p, s) : launch_n<32>(p, s);
+    }
+    if (e != hipSuccess) return e;
+    return launch_partial_reduce(0, p.partial, p.dtheta, 3LL * p.n * p.d + 3LL * p.n * p.n + 4LL * p.n, rows, s);
 }
 
 }  // namespace deer
