@@ -237,12 +237,14 @@ int chunk_length(const deer_config* c, int* per_unit) {
 
 // Where a step by chunks is faster than the single-pass scan with the cell inside.  The scan's tiles (64 to 96 positions) spread a
 // small problem over more compute units than the chunks' groups (64 positions and more, two launches); its chain of tiles
-// grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 143 / 209 at 1 x 500, 293 / 299 at 1 x 5,000, 347 / 339 at
-// 4 x 5,000, 858 / 643 at 64 x 2,000; n = 16 130 / 142 at 20 x 783, 188 / 158 at 1 x 5,000, 192 / 169 at 4 x 5,000.
+// grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 143 / 209 at 1 x 500, 259 / 304 at 20 x 1,000, 298 / 332 at
+// 10 x 2,500, 264 / 297 at 64 x 500, but 347 / 339 at 4 x 5,000, 797 / 504 at 1 x 20,000, 620 / 559 at 16 x 5,000, 663 / 545 at 60 x 1,500; n = 16
+// 130 / 142 at 20 x 783, 143 / 158 at 16 x 1,300, 157 / 165 at 64 x 500, but 172 / 169 at 10 x 2,500, 188 / 158 at 1 x 5,000, 275 / 241 at 60 x 1,500.
 bool chunk_pays(const deer_config* c) {
     if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
     const long long total = (long long)c->B * c->T;
-    return c->n == 64 || total >= 20000 || (c->n == 16 && c->T >= 1536);
+    if (c->n == 64) return true;
+    return c->n == 16 ? total >= 50000 || c->T >= 1536 : total >= 60000 || (total >= 20000 && c->T >= 5000);
 }
 
 // Steps by chunks at 8 channels: positions per chunk, and whether the Newton step and the gradient go this way.
