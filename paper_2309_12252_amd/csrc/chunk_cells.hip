@@ -19,8 +19,6 @@
 
 namespace deer {
 
-long long chunk_cells_rows(const ChunkParams& p) { return ((long long)p.B * p.groups + 3) / 4; }
-
 namespace {
 
 enum { LSTM = 0, LEM = 1 };
@@ -834,7 +832,7 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
 
 template <int CELL, int UP, int DS, bool VEC>
 hipError_t launch_v(const ChunkParams& p, hipStream_t s) {
-    const dim3 units((unsigned)((long long)p.B * p.units)), groups((unsigned)chunk_cells_rows(p));
+    const dim3 units((unsigned)((long long)p.B * p.units)), groups((unsigned)chunk_rows(p));
     if (p.g) hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, true>), units, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, false>), units, dim3(256), 0, s, p);
     const hipError_t e = hipGetLastError();
@@ -865,7 +863,7 @@ hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s) {
     const hipError_t e = lem ? launch_cell<LEM>(p, s) : launch_cell<LSTM>(p, s);
     if (e != hipSuccess || !p.g) return e;
     const long long n = p.cell_units;
-    return launch_partial_reduce(0, p.partial, p.dtheta, 4 * n * p.d + 4 * n * n + 4 * n, (int)chunk_cells_rows(p), s);
+    return launch_partial_reduce(0, p.partial, p.dtheta, 4 * n * p.d + 4 * n * n + 4 * n, (int)chunk_rows(p), s);
 }
 
 }  // namespace deer

@@ -528,13 +528,197 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
     }
 }
 
+// ------------------------------------------------------------------------------------------------------------------
+// n = 16: the dual walk with the vector-Jacobian product inside (as in chunk_cells.hip).  lambda_i = g_i + J_{i+1}^T lambda_{i+1} needs the
+// cotangents of the pre-activations at position i + 1, which are all that dL/dx, dL/dtheta and (at the first position) dL/dy0 are made of;
+// one more step takes the first position of a sequence.  The sums over positions have the columns on the contraction index:
+// cotangents, state and input cross a slice of LDS.  At n = 32 the sums (72 registers more) would leave one wavefront per SIMD.
+// Measured, d = 6, 32 x 17,984 positions: walk 43 us and a kernel of its own for the product 126 us; now 82 us in all.
+// ------------------------------------------------------------------------------------------------------------------
+template <int DS>
+__global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
+    constexpr int N = 16, SLICE = 1600;   // six tiles of [column][16]; at the end the wavefront's row of dL/dtheta (at most 1,600 scalars)
+    __shared__ __align__(16) float sT[4][SLICE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
+    const int T = p.T, d = p.d, Lc = p.Lc;
+    const float* __restrict__ th = p.theta;
+    const float* __restrict__ U = th + 3 * N * d;
+    const float* __restrict__ bias = U + 3 * N * N;
+    float* __restrict__ S = sT[wave];
+    const unsigned id = blockIdx.x * 4u + (unsigned)wave;
+    const int b = (int)(id % (unsigned)p.B), grp = (int)(id / (unsigned)p.B);
+    Acc aU[3], aW[3], aB[4];   // blocks r, z, c; bias sums of this column's rows: r, z, c, hidden part of c
+#pragma unroll
+    for (int q = 0; q < 3; ++q) aU[q] = aW[q] = zero4();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) aB[q] = zero4();
+    store4(S + 1280 + 4 * lane, zero4());   // (input columns past 4 DS are never written)
+    wave_lds_fence();
+    if (grp < p.groups) {
+        const int chunks = (T + Lc - 1) / Lc, nq = min(16, chunks - 16 * grp);
+        const long long first = (long long)b * T + (long long)16 * grp * Lc;
+        const float* __restrict__ yb = p.y + first * N;
+        const float* __restrict__ xb = p.x + first * d;
+        const float* __restrict__ gb = p.g + first * N;
+        float* __restrict__ dxb = p.dx ? p.dx + first * d : nullptr;
+        const int a = r * Lc, end = T - 16 * grp * Lc;
+        auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
+        constexpr int R = DS == 4 ? 2 : 4;
+        Acc yr[R], gr[R];
+        float xr[R][DS];
+        auto ask = [&](int j, int t) {
+            const unsigned o = row(a + Lc - 1 - t) * N + 4 * g, ox = row(a + Lc - t) * (unsigned)d;
+            yr[j] = load4(yb + o);
+            gr[j] = load4(gb + o);
+#pragma unroll
+            for (int s = 0; s < DS; ++s) xr[j][s] = xb[ox + min(DS * g + s, d - 1)];
+        };
+#pragma unroll
+        for (int j = 0; j < R; ++j) ask(j, j);
+        Acc u[3], ut[3], wt[3], bs[4];   // U_gate, U_gate^T and W_gate^T as operand A
+        float w[3][DS];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            u[q] = load4(U + (q * N + r) * N + 4 * g);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = q * N + 4 * g + v;
+                const float x = th[k * d + min(r, d - 1)];
+                ut[q][v] = U[k * N + r];
+                wt[q][v] = r < d ? x : 0.f;
+            }
+#pragma unroll
+            for (int s = 0; s < DS; ++s) {
+                const float x = th[(q * N + r) * d + min(DS * g + s, d - 1)];
+                w[q][s] = DS * g + s < d ? x : 0.f;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bs[q] = load4(bias + q * N + 4 * g);
+        Acc ev[1];   // lambda at the position the step evaluates
+        fold_carries<N, true>(p, b, grp, nq, g, r, ev);
+        Acc e = ev[0];
+
+        // one step at position `at` (relative) with state h in front of it: adds J^T lambda to y
+        auto step = [&](const Acc& h, const float (&x)[DS], int at, Acc& y) {
+            Acc ar = bs[0], az = bs[1], ac = bs[2], aq = bs[3];
+#pragma unroll
+            for (int s = 0; s < DS; ++s) {
+                ar = mfma(w[0][s], x[s], ar);
+                az = mfma(w[1][s], x[s], az);
+                ac = mfma(w[2][s], x[s], ac);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                ar = mfma(u[0][v], h[v], ar);
+                az = mfma(u[1][v], h[v], az);
+                aq = mfma(u[2][v], h[v], aq);
+            }
+            Acc dr, dz, dc, dq;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const GruGates k = gru_gates(ar[v], az[v], ac[v], aq[v], h[v]);
+                dr[v] = k.st * e[v];
+                dz[v] = k.pz * e[v];
+                dc[v] = k.sc * e[v];
+                dq[v] = k.sr * e[v];
+                y[v] += k.z * e[v];
+            }
+            float* o = S + r * 16 + 4 * g;
+            store4(o, dr); store4(o + 256, dz); store4(o + 512, dq); store4(o + 768, dc); store4(o + 1024, h);
+#pragma unroll
+            for (int s = 0; s < DS; ++s) S[1280 + r * 16 + DS * g + s] = x[s];
+            aB[0] += dr; aB[1] += dz; aB[2] += dc; aB[3] += dq;
+            Acc s1 = zero4(), dx = zero4();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                y = mfma(ut[1][v], dz[v], y);
+                s1 = mfma(ut[0][v], dr[v], s1);
+                dx = mfma(wt[0][v], dr[v], dx);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                s1 = mfma(ut[2][v], dq[v], s1);
+                dx = mfma(wt[1][v], dz[v], dx);
+                dx = mfma(wt[2][v], dc[v], dx);
+            }
+            y += s1;
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const float* q = S + (4 * m + g) * 16 + r;
+                const float tr = q[0], tz = q[256], tq = q[512], tc = q[768], hk = q[1024], xk = q[1280];
+                aU[0] = mfma(tr, hk, aU[0]);
+                aU[1] = mfma(tz, hk, aU[1]);
+                aU[2] = mfma(tq, hk, aU[2]);
+                aW[0] = mfma(tr, xk, aW[0]);
+                aW[1] = mfma(tz, xk, aW[1]);
+                aW[2] = mfma(tc, xk, aW[2]);
+            }
+            wave_lds_fence();
+            if (dxb && at < end) {
+                float* t = dxb + (long long)at * d + 4 * g;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (4 * g + v < d) t[v] = dx[v];
+            }
+        };
+        for (int t0 = 0; t0 < Lc; t0 += R) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int t = t0 + j, rel = a + Lc - 1 - t;
+                const bool live = rel < end;
+                Acc y = gr[j];
+                step(yr[j], xr[j], rel + 1, y);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) e[v] = live ? y[v] : 0.f;   // nothing follows the last position
+                ask(j, t + R);
+            }
+        }
+        if (grp == 0) {   // the first position of the sequence
+            const Acc h = p.y0 ? load4(p.y0 + (long long)b * N + 4 * g) : zero4();
+            Acc y = zero4();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) e[v] = r == 0 ? e[v] : 0.f;
+            step(h, xr[0], r == 0 ? 0 : end, y);
+            if (p.dy0 && r == 0)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) p.dy0[(long long)b * N + 4 * g + v] = y[v];
+        }
+    }
+    // ---- the workgroup's row of dL/dtheta ----
+    const int U0 = 3 * N * d, b0 = U0 + 3 * N * N, P = b0 + 4 * N;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = q * N + 4 * g + v;
+            S[U0 + k * N + r] = aU[q][v];
+            if (r < d) S[k * d + r] = aW[q][v];
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const Acc s = row_sums4(aB[q], r);
+        if (r == 0) store4(S + b0 + q * N + 4 * g, s);
+    }
+    __syncthreads();
+    for (int q = tid; q < P; q += 256) p.partial[(long long)blockIdx.x * P + q] = (sT[0][q] + sT[1][q]) + (sT[2][q] + sT[3][q]);
+}
+
 template <int N, int DS, bool REV>
 hipError_t launch_nd(const ChunkParams& p, hipStream_t s) {
     hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((chunk_walk_kernel<N, DS, REV>), dim3((unsigned)(((long long)p.B * p.groups + 3) / 4)), dim3(256), 0, s, p);
-    return hipGetLastError();
+    const int rows = (int)chunk_rows(p);
+    if constexpr (N == 16 && REV) {
+        hipLaunchKernelGGL((chunk_dual16_kernel<DS>), dim3((unsigned)rows), dim3(256), 0, s, p);
+        e = hipGetLastError();
+        return e != hipSuccess ? e : launch_partial_reduce(0, p.partial, p.dtheta, 3LL * N * p.d + 3LL * N * N + 4 * N, rows, s);
+    } else {
+        hipLaunchKernelGGL((chunk_walk_kernel<N, DS, REV>), dim3((unsigned)rows), dim3(256), 0, s, p);
+        return hipGetLastError();
+    }
 }
 
 template <int N, bool REV>
@@ -550,6 +734,8 @@ bool chunk_gru_supported(int dtype, int n, int d) { return dtype == 0 && (n == 1
 
 size_t chunk_map_bytes(int n) { return ((size_t)n * n + n) * sizeof(float); }
 
+long long chunk_rows(const ChunkParams& p) { return ((long long)p.B * p.groups + 3) / 4; }
+
 bool chunk_params_valid(const ChunkParams& p) {
     return p.Lc >= 4 && p.Lc % 4 == 0 && (p.per_unit == 4 || p.per_unit == 8 || p.per_unit == 16) &&
            p.groups == (int)((p.T + 16LL * p.Lc - 1) / (16LL * p.Lc)) &&
@@ -560,6 +746,7 @@ hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s) {
     if (!chunk_gru_supported(0, n, p.d) || !chunk_params_valid(p)) return hipErrorInvalidValue;
     if (n == 64) return launch_chunk_gru64(p, s);
     const bool rev = p.g != nullptr;
+    if (rev && n == 16 ? !p.partial || !p.dtheta : !p.out) return hipErrorInvalidValue;
     if (n == 16) return rev ? launch_n<16, true>(p, s) : launch_n<16, false>(p, s);
     return rev ? launch_n<32, true>(p, s) : launch_n<32, false>(p, s);
 }

@@ -57,6 +57,7 @@ struct Plan {
     int mh_H, mh_K;      // heads, stride levels
     size_t off_dy0parts, off_mhtable;
     bool chunk;          // GRU, n >= 16, fp32: Newton steps and the dual scan run by chunks (chunk_gru.hip)
+    bool chunk_grad;     // their gradient takes the vector-Jacobian product into the walk
     int chunk_L, chunk_groups, chunk_per_unit, chunk_units;
     bool chunk8, chunk8_grad;   // GRU, 8 channels, fp32, plain or multi-head: the Newton steps, the gradient (chunk_gru8.hip)
     Chunk8Params c8;     // their shapes and chunk lengths
@@ -456,6 +457,7 @@ Plan make_plan(const deer_config* c) {
     // knob settings) whose forward or backward pass runs the cell kernel followed by the plain scan.  With the
     // cell inside both scans the workspace is O(n T) instead of the O(n^2 T) of Sec. 3.5.
     p.need_J = ode || !p.fused || !p.grad_fused;
+    p.chunk_grad = p.chunk && p.grad_fused && (cell_chunk || c->n == 16);
 
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
@@ -476,7 +478,7 @@ Plan make_plan(const deer_config* c) {
     p.off_sup = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * map : p.chunk ? B * (size_t)p.chunk_units * map : 0);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
     p.off_partial = take(p.chunk8_grad ? (size_t)(p.c8.groups / 4) * p.c8.P * p.esz
-                         : cell_chunk  ? (B * (size_t)p.chunk_groups + 3) / 4 * theta_count(c) * p.esz
+                         : p.chunk_grad ? (B * (size_t)p.chunk_groups + 3) / 4 * theta_count(c) * p.esz
                                        : (size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
     p.off_timing = take(kTimingBytes);
@@ -1187,14 +1189,14 @@ static deer_status grad_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
         prof_collect(c);
         return st;
     }
-    if (c->plan.chunk && two_part_cell(g.cell)) {
+    if (c->plan.chunk_grad) {
         ChunkParams q = chunk_params(c, d_theta, d_x, d_y0, d_y);
         q.g = reinterpret_cast<const float*>(d_dLdy);
         q.dx = reinterpret_cast<float*>(d_dLdx); q.dy0 = reinterpret_cast<float*>(d_dLdy0);
         q.dtheta = reinterpret_cast<float*>(d_dLdtheta);
         q.partial = reinterpret_cast<float*>(c->ws + c->plan.off_partial);
         prof_begin(c, KIND_FUSED);
-        HIPCHK(c, launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream));
+        HIPCHK(c, two_part_cell(g.cell) ? launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream) : launch_chunk_gru(g.n, q, c->stream));
         prof_end(c);
         st = check_status(c);
         prof_collect(c);

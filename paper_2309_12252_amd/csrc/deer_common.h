@@ -95,8 +95,8 @@ struct ChunkParams {
     const float* theta; const float* x; const float* y0;   // y0 may be nullptr (zeros)
     const float* y;            // previous iterate, or the trajectory of the backward pass [B,T,n]
     const float* g;            // dL/dy [B,T,n], or nullptr
-    float* out;                // next iterate, or (GRU) lambda [B,T,n]
-    // gradient of the LSTM and the LEM: dx [B,T,d] or nullptr, dy0 [B,n] or nullptr, dtheta, one row of its length per workgroup
+    float* out;                // next iterate, or (GRU with n = 32, 64) lambda [B,T,n]
+    // whole gradient (LSTM, LEM and GRU with n = 16): dx [B,T,d] or nullptr, dy0 [B,n] or nullptr, dtheta, one row of its length per workgroup
     float* dx; float* dy0; float* dtheta; float* partial;
     float* tot; float* sup;    // maps of the chunks [B][groups][16][n*n + n] and of the units [B][units][n*n + n]
     void* err;                 // max|y_new - y| (raw bits), or nullptr
@@ -364,10 +364,10 @@ int scan_mfma_tile(int dtype, int n);
 bool chunk_gru_supported(int dtype, int n, int d);
 size_t chunk_map_bytes(int n);   // bytes of one chunk's map
 bool chunk_params_valid(const ChunkParams& p);
+long long chunk_rows(const ChunkParams& p);   // workgroups of the walk: rows of `partial`
 // the same for the LSTM and the LEM (fp32, 1..16 units, d <= 8)
 bool chunk_cells_supported(int dtype, int units, int d);
 size_t chunk_cells_map_bytes(int units);
-long long chunk_cells_rows(const ChunkParams& p);   // workgroups of the walk: rows of `partial`
 hipError_t launch_chunk_cells(bool lem, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru(int n, const ChunkParams& p, hipStream_t s);
 hipError_t launch_chunk_gru64(const ChunkParams& p, hipStream_t s);
