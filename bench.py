@@ -70,12 +70,12 @@ def dominant_roofline(kind, ms, w, newton_iterations=0.0):
                 "avg_launch_us": round(1e3 * ms, 2), "algorithmic_flops_per_launch": fl,
                 "hbm_bytes_per_launch": 4 * (w.n + w.d) * positions}
     if kind == "fused" and w.n >= 16:
-        # the GRU step with the cell inside the MFMA scan: the matrix products dominate the arithmetic
+        # the GRU step by chunks (reduction and walk, two launches): the matrix products dominate the arithmetic
         fl = fused_flops_per_position(w.n, w.d) * positions
         a = fl / sec / 1e12
         return {"bound": "mfma", "achieved": round(a, 2), "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(a / MFMA_F32_PEAK_TFLOPS, 4), "traffic": None,
-                "kernel": "GRU cell + MFMA affine scan in one launch (n=%d)" % w.n, "avg_launch_us": round(1e3 * ms, 2),
+                "kernel": "GRU step by chunks, reduction + walk (n=%d)" % w.n, "avg_launch_us": round(1e3 * ms, 2),
                 "algorithmic_flops_per_launch": fl, "hbm_bytes_per_launch": 4 * (2 * w.n + w.d) * positions}
     if kind == "fused":
         fl = fused_flops_per_position(w.n, w.d) * positions

@@ -907,12 +907,14 @@ deer_status deer_eval(deer_ctx* c, const void* d_theta, const void* d_x, const v
     char* pth = c->ws + c->pad.off_theta;
     char* py0 = c->ws + c->pad.off_y0;
     char* py = c->ws + c->pad.off_y;
-    if (!lstm) HIPCHK(c, launch_pad_gru_theta(g.dtype, d_theta, pth, n, np, g.d, 0, c->stream));
-    HIPCHK(c, launch_pad_rows(g.dtype, d_y0, py0, g.B, n, np, 0, c->stream));
-    if (d_y_guess) HIPCHK(c, launch_pad_rows(g.dtype, d_y_guess, py, rows, n, np, 0, c->stream));
+    PadJobs in{{}, 0, n, np, g.d, 0, 0};
+    in.job[in.count++] = PadJob{d_y0, py0, g.B};
+    if (!lstm) in.job[in.count++] = PadJob{d_theta, pth, 0};
+    if (d_y_guess) in.job[in.count++] = PadJob{d_y_guess, py, rows};
+    HIPCHK(c, launch_pad(g.dtype, in, c->stream));
     const deer_status st = eval_impl(c, lstm ? d_theta : pth, d_x, py0, d_y_guess ? py : nullptr, tol, max_iter, py, iters, final_err, converged);
     if (st != DEER_OK && st != DEER_ERR_NONFINITE) return st;
-    HIPCHK(c, launch_pad_rows(g.dtype, py, d_y, rows, n, np, 1, c->stream));
+    HIPCHK(c, launch_pad(g.dtype, PadJobs{{{py, d_y, rows}}, 1, n, np, g.d, 1, 0}, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return st;
 }
@@ -1021,12 +1023,12 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
                                    (long long)((T - 1) * n), (long long)(T * n), 0, slot, true, 1, gate, k));
             }
         }
-        // error words of the batch and the status word come back with one synchronisation
+        // error words of the batch and the status word (behind the last slot) come back with one copy
         char* h = reinterpret_cast<char*>(c->h_err);
-        HIPCHK(c, hipMemcpyAsync(h, ctl_err(c, slot0), (size_t)nb * 8, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipMemcpyAsync(h + (size_t)kSlots * 8, ctl_status(c), 4, hipMemcpyDeviceToHost, c->stream));
+        const size_t behind = (size_t)(kSlots - slot0) * 8;
+        HIPCHK(c, hipMemcpyAsync(h, ctl_err(c, slot0), behind + 4, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
-        std::memcpy(&status, h + (size_t)kSlots * 8, 4);
+        std::memcpy(&status, h + behind, 4);
         for (int j = 0; j < nb; ++j) {
             const char* ep = h + (size_t)j * 8;
             if (g.dtype == DEER_F32) {
@@ -1146,14 +1148,15 @@ deer_status deer_grad(deer_ctx* c, const void* d_theta, const void* d_x, const v
     char* pg = c->ws + c->pad.off_g;
     char* pdth = c->ws + c->pad.off_dtheta;
     char* pdy0 = c->ws + c->pad.off_dy0;
-    if (!lstm) HIPCHK(c, launch_pad_gru_theta(g.dtype, d_theta, pth, n, np, g.d, 0, c->stream));
-    HIPCHK(c, launch_pad_rows(g.dtype, d_y0, py0, g.B, n, np, 0, c->stream));
-    HIPCHK(c, launch_pad_rows(g.dtype, d_y, py, rows, n, np, 0, c->stream));
-    HIPCHK(c, launch_pad_rows(g.dtype, d_dLdy, pg, rows, n, np, 0, c->stream));
+    PadJobs in{{{d_y0, py0, g.B}, {d_y, py, rows}, {d_dLdy, pg, rows}}, 3, n, np, g.d, 0, 0};
+    if (!lstm) in.job[in.count++] = PadJob{d_theta, pth, 0};
+    HIPCHK(c, launch_pad(g.dtype, in, c->stream));
     const deer_status st = grad_impl(c, lstm ? d_theta : pth, d_x, py0, py, pg, d_dLdx, lstm ? d_dLdtheta : pdth, d_dLdy0 ? pdy0 : nullptr);
     if (st != DEER_OK) return st;
-    if (!lstm) HIPCHK(c, launch_pad_gru_theta(g.dtype, pdth, d_dLdtheta, n, np, g.d, 1, c->stream));
-    if (d_dLdy0) HIPCHK(c, launch_pad_rows(g.dtype, pdy0, d_dLdy0, g.B, n, np, 1, c->stream));
+    PadJobs back{{}, 0, n, np, g.d, 1, 0};
+    if (!lstm) back.job[back.count++] = PadJob{pdth, d_dLdtheta, 0};
+    if (d_dLdy0) back.job[back.count++] = PadJob{pdy0, d_dLdy0, g.B};
+    if (back.count > 0) HIPCHK(c, launch_pad(g.dtype, back, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return DEER_OK;
 }

@@ -540,73 +540,55 @@ int gru_vjp_blocks(int n, long long steps) {
 // bias are zero.  Extra channels then obey h' = h / 2 and stay at the zero they start from, and the real channels never
 // see them (their columns of U are zero): the recurrence, its Jacobians, the Newton iterates and the cotangents of
 // the real channels are exactly those of the n-channel cell.
+// All the arrays of one direction of a call in one launch (blockIdx.y names the array): a call on a small problem waits for every launch.
 template <typename S>
-__global__ __launch_bounds__(256) void pad_rows_kernel(const S* __restrict__ src, S* __restrict__ dst, long long rows, int n, int np,
-                                                      int unpack) {
-    // pack: dst[rows][np] <- src[rows][n] with zeros behind; unpack: dst[rows][n] <- src[rows][np]
-    const long long total = rows * (unpack ? n : np);
-    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < total; q += (long long)gridDim.x * blockDim.x) {
-        if (unpack) {
-            const long long r = q / n;
-            const int c = (int)(q % n);
-            dst[q] = src[r * np + c];
-        } else {
-            const long long r = q / np;
-            const int c = (int)(q % np);
-            dst[q] = c < n ? src[r * n + c] : S(0);
+__global__ __launch_bounds__(256) void pad_kernel(PadJobs p) {
+    const long long stride = (long long)gridDim.x * blockDim.x, q0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const PadJob& job = p.job[blockIdx.y];
+    const S* __restrict__ src = reinterpret_cast<const S*>(job.src);
+    S* __restrict__ dst = reinterpret_cast<S*>(job.dst);
+    const int n = p.n, np = p.np, d = p.d;
+    if (job.rows > 0) {
+        // rows of n scalars <-> rows of np = 2^log2np (zeros behind)
+        for (long long q = q0; q < (job.rows << p.log2np); q += stride) {
+            const long long r = q >> p.log2np;
+            const int c = (int)(q & (np - 1));
+            if (!p.unpack) dst[q] = c < n ? src[r * n + c] : S(0);
+            else if (c < n) dst[r * n + c] = src[q];
         }
+        return;
     }
-}
-
-// theta of the GRU cell: W[3n,d] | U[3n,n] | b[3n] | b_hc[n]  <->  the same blocks for np channels
-template <typename S>
-__global__ __launch_bounds__(256) void pad_gru_theta_kernel(const S* __restrict__ src, S* __restrict__ dst, int n, int np, int d,
-                                                           int unpack) {
-    const long long Pp = 3LL * np * d + 3LL * np * np + 4LL * np;
-    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < Pp; q += (long long)gridDim.x * blockDim.x) {
+    // theta of the GRU cell: W[3n,d] | U[3n,n] | b[3n] | b_hc[n]  <->  the same blocks for np channels
+    const int Pp = 3 * np * d + 3 * np * np + 4 * np;
+    for (int q = (int)q0; q < Pp; q += (int)stride) {
         // position of entry q of the padded layout in the small one, or -1
-        long long at = -1, r = q;
-        if (r < 3LL * np * d) {
-            const int gate = (int)(r / ((long long)np * d)), row = (int)((r / d) % np), col = (int)(r % d);
-            if (row < n) at = ((long long)gate * n + row) * d + col;
-        } else if ((r -= 3LL * np * d) < 3LL * np * np) {
-            const int gate = (int)(r / ((long long)np * np)), row = (int)((r / np) % np), col = (int)(r % np);
-            if (row < n && col < n) at = 3LL * n * d + ((long long)gate * n + row) * n + col;
+        int at = -1, r = q;
+        if (r < 3 * np * d) {
+            const int gate = r / (np * d), row = (r / d) & (np - 1), col = r % d;
+            if (row < n) at = (gate * n + row) * d + col;
+        } else if ((r -= 3 * np * d) < 3 * np * np) {
+            const int gate = r >> (2 * p.log2np), row = (r >> p.log2np) & (np - 1), col = r & (np - 1);
+            if (row < n && col < n) at = 3 * n * d + (gate * n + row) * n + col;
         } else {
-            r -= 3LL * np * np;   // four bias vectors of np entries
-            const int which = (int)(r / np), row = (int)(r % np);
-            if (row < n) at = 3LL * n * d + 3LL * n * n + (long long)which * n + row;
+            r -= 3 * np * np;   // four bias vectors of np entries
+            const int which = r >> p.log2np, row = r & (np - 1);
+            if (row < n) at = 3 * n * d + 3 * n * n + which * n + row;
         }
-        if (unpack) {
-            if (at >= 0) dst[at] = src[q];
-        } else {
-            dst[q] = at >= 0 ? src[at] : S(0);
-        }
+        if (!p.unpack) dst[q] = at >= 0 ? src[at] : S(0);
+        else if (at >= 0) dst[at] = src[q];
     }
 }
 
-hipError_t launch_pad_rows(int dtype, const void* src, void* dst, long long rows, int n, int np, int unpack, hipStream_t s) {
-    if (rows < 1) return hipSuccess;
-    long long blocks = (rows * np + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    if (dtype == 0)
-        hipLaunchKernelGGL((pad_rows_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<const float*>(src),
-                           reinterpret_cast<float*>(dst), rows, n, np, unpack);
-    else
-        hipLaunchKernelGGL((pad_rows_kernel<double>), dim3((unsigned)blocks), dim3(256), 0, s, reinterpret_cast<const double*>(src),
-                           reinterpret_cast<double*>(dst), rows, n, np, unpack);
-    return hipGetLastError();
-}
-
-hipError_t launch_pad_gru_theta(int dtype, const void* src, void* dst, int n, int np, int d, int unpack, hipStream_t s) {
-    const long long Pp = 3LL * np * d + 3LL * np * np + 4LL * np;
-    const unsigned blocks = (unsigned)((Pp + 255) / 256);
-    if (dtype == 0)
-        hipLaunchKernelGGL((pad_gru_theta_kernel<float>), dim3(blocks), dim3(256), 0, s, reinterpret_cast<const float*>(src),
-                           reinterpret_cast<float*>(dst), n, np, d, unpack);
-    else
-        hipLaunchKernelGGL((pad_gru_theta_kernel<double>), dim3(blocks), dim3(256), 0, s, reinterpret_cast<const double*>(src),
-                           reinterpret_cast<double*>(dst), n, np, d, unpack);
+hipError_t launch_pad(int dtype, PadJobs p, hipStream_t s) {
+    if (p.count < 1 || p.count > 4 || p.n < 1 || p.np < p.n || (p.np & (p.np - 1)) != 0) return hipErrorInvalidValue;
+    p.log2np = 0;
+    while ((1 << p.log2np) < p.np) ++p.log2np;
+    long long most = 3LL * p.np * p.d + 3LL * p.np * p.np + 4LL * p.np;
+    for (int j = 0; j < p.count; ++j)
+        if (p.job[j].rows * p.np > most) most = p.job[j].rows * p.np;
+    const dim3 grid((unsigned)((most + 255) / 256 < 4096 ? (most + 255) / 256 : 4096), (unsigned)p.count);
+    if (dtype == 0) hipLaunchKernelGGL((pad_kernel<float>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((pad_kernel<double>), grid, dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
