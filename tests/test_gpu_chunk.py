@@ -2,6 +2,7 @@
 of sixteen positions: trajectory, iteration count and gradients against the fp64 oracle, plain max-abs at 1e-4."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2309_12252_amd import deer, inputs
@@ -117,5 +118,40 @@ def test_heads_by_chunks(n, d, L, B, T, H, K, monkeypatch):
         _against_oracle(ctx, w, lambda m: oracle.mh_deer_eval(n, d, H, K, w.theta, w.x, w.y0, tol=w.tol, max_iter=m, nthreads=8),
                         lambda: oracle.mh_seq_eval(n, d, H, K, w.theta, w.x, w.y0, nthreads=8),
                         lambda ys, g: oracle.mh_gru_grad(n, d, H, K, w.theta, w.x, w.y0, ys, g))
+    finally:
+        ctx.close()
+
+
+# the gradient alone (no dL/dx, no dL/dy0) is the same sum in the same order, and eight channels need no more than the alignment of a scalar
+@pytest.mark.parametrize("kind,n", [("gru", 8), ("gru", 16), ("gru", 64), ("heads", 8), ("lstm", 8), ("lem", 12)])
+def test_parameter_gradient_alone_and_scalar_alignment(kind, n, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", "12")
+    B, T, d = 3, 413, 5
+    if kind == "heads":
+        w = inputs.mh_gru_workload("chunk_alone_mh", 71, B=B, T=T, n=n, d=d, H=3, K=3)
+    elif kind == "gru":
+        w = inputs.gru_workload("chunk_alone_n%d" % n, 72 + n, B=B, T=T, n=n, d=d)
+    else:
+        w = (inputs.lstm_workload if kind == "lstm" else inputs.lem_workload)("chunk_alone_" + kind, 73, B=B, T=T, units=n, d=d)
+
+    def at_odd_scalar(t):   # the same values one scalar behind an aligned address
+        flat = torch.zeros(t.numel() + 1, dtype=t.dtype, device=t.device)
+        flat[1:] = t.reshape(-1)
+        return flat[1:].reshape(t.shape)
+
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        th, x, y0 = dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0)
+        y = ctx.eval(th, x, y0, tol=w.tol, max_iter=w.max_iter)[0]
+        g = dev((np.random.default_rng(2).standard_normal(tuple(y.shape)) / T).astype(np.float32), 0)
+        dth, dx, dy0 = ctx.grad(th, x, y0, y, g)
+        alone = ctx.grad(th, x, y0, y, g, want_dx=False, want_dy0=False)
+        assert alone[1] is None and alone[2] is None and torch.equal(alone[0], dth)
+        if n == 8 and kind in ("gru", "heads"):
+            odd = [at_odd_scalar(t) for t in (th, x, y0)]
+            assert odd[0].data_ptr() % 8 == 4
+            assert torch.equal(ctx.eval(*odd, tol=w.tol, max_iter=w.max_iter)[0], y)
+            for a, b in zip(ctx.grad(*odd, at_odd_scalar(y), at_odd_scalar(g)), (dth, dx, dy0)):
+                assert torch.equal(a, b)
     finally:
         ctx.close()
