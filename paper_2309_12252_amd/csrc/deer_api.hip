@@ -240,12 +240,12 @@ int chunk_length(const deer_config* c, int* per_unit) {
 // small problem over more compute units than the chunks' groups (64 positions and more, two launches); its chain of tiles
 // grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 143 / 209 at 1 x 500, 259 / 304 at 20 x 1,000, 298 / 332 at
 // 10 x 2,500, 264 / 297 at 64 x 500, but 347 / 339 at 4 x 5,000, 797 / 504 at 1 x 20,000, 620 / 559 at 16 x 5,000, 663 / 545 at 60 x 1,500; n = 16
-// 130 / 142 at 20 x 783, 143 / 158 at 16 x 1,300, 157 / 165 at 64 x 500, but 172 / 169 at 10 x 2,500, 188 / 158 at 1 x 5,000, 275 / 241 at 60 x 1,500.
+// 130 / 142 at 20 x 783, 143 / 158 at 16 x 1,300, 157 / 165 at 64 x 500, 155 / 161 at 3 x 2,500, but 142 / 133 at 1 x 1,600, 188 / 158 at 1 x 5,000, 275 / 241 at 60 x 1,500.
 bool chunk_pays(const deer_config* c) {
     if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
     const long long total = (long long)c->B * c->T;
     if (c->n == 64) return true;
-    return c->n == 16 ? total >= 50000 || c->T >= 1536 : total >= 60000 || (total >= 20000 && c->T >= 5000);
+    return c->n == 16 ? total >= 50000 || c->T >= 3000 || (c->B == 1 && c->T >= 1536) : total >= 60000 || (total >= 20000 && c->T >= 5000);
 }
 
 // Steps by chunks at 8 channels: positions per chunk, and whether the Newton step and the gradient go this way.
@@ -264,10 +264,10 @@ double chunk8_estimate(const Chunk8Params& q) {
 }
 
 // The single-pass scan (all iterations in one launch up to about 260,000 positions) takes 20 us + 0.118 us per 1,000 positions a step.
-// Microseconds a solve, scan / chunks: plain 326 / 287 at 64 x 6,000, 502 / 466 at 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at
+// Microseconds a solve, scan / chunks: plain 303 / 319 at 25 x 14,000, 305 / 290 at 60 x 6,000, 502 / 466 at 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at
 // 4 x 100,000, where the fold is long; 123 / 207 at 16 x 10,000.  Heads (total positions of all heads): 118 / 135 at 9,600, 147 / 147 at
 // 42,000, 300 / 175 at 64,000, 3,898 / 1,112 at 2.1 million.  The gradient, whose walk takes the vector-Jacobian product in: plain
-// 64 / 60 at 4 x 3,000, 85 / 74 at 16 x 10,000, 87 / 92 at 2 x 30,000, 408 / 227 at 16 x 100,000; heads 83 / 63 at 42,000, 1,181 / 273 at 2.1 million.
+// 64 / 60 at 4 x 3,000, 85 / 74 at 16 x 10,000, 68 / 78 at 3 x 16,000, 87 / 92 at 2 x 30,000, 408 / 227 at 16 x 100,000; heads 83 / 63 at 42,000, 1,181 / 273 at 2.1 million.
 void chunk8_plan(const deer_config* c, Plan& p) {
     const int H = c->heads > 1 ? c->heads : 1, forced = env_int("DEER_CHUNK_L", 0);
     if (!chunk_gru8_supported(c->dtype, c->n, c->d, c->T, H)) return;
@@ -289,8 +289,8 @@ void chunk8_plan(const deer_config* c, Plan& p) {
         p.chunk8 = total >= 60000;
         p.chunk8_grad = total >= 20000;
     } else {
-        p.chunk8 = total >= 300000 && best < 20.0 + 1.18e-4 * total;
-        p.chunk8_grad = p.chunk8 || (total >= 30000 && c->T <= 16384);
+        p.chunk8 = total >= 380000 && best < 20.0 + 1.18e-4 * total;
+        p.chunk8_grad = p.chunk8 || (total >= 30000 && c->T <= 12000);
     }
     if (!p.chunk8) return;
     p.fused = true;
