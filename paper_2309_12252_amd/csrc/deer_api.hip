@@ -267,7 +267,7 @@ double chunk8_estimate(const Chunk8Params& q) {
 // Microseconds a solve, scan / chunks: plain 303 / 319 at 25 x 14,000, 305 / 290 at 60 x 6,000, 502 / 466 at 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at
 // 4 x 100,000, where the fold is long; 123 / 207 at 16 x 10,000.  Heads (total positions of all heads): 118 / 135 at 9,600, 147 / 147 at
 // 42,000, 300 / 175 at 64,000, 3,898 / 1,112 at 2.1 million.  The gradient, whose walk takes the vector-Jacobian product in: plain
-// 64 / 60 at 4 x 3,000, 85 / 74 at 16 x 10,000, 68 / 78 at 3 x 16,000, 87 / 92 at 2 x 30,000, 408 / 227 at 16 x 100,000; heads 83 / 63 at 42,000, 1,181 / 273 at 2.1 million.
+// 64 / 60 at 4 x 3,000, 85 / 74 at 16 x 10,000, 158 / 101 at 12 x 30,000, but 69 / 73 at 5 x 11,000, 68 / 78 at 3 x 16,000, 87 / 92 at 2 x 30,000, 408 / 227 at 16 x 100,000; heads 83 / 63 at 42,000, 1,181 / 273 at 2.1 million.
 void chunk8_plan(const deer_config* c, Plan& p) {
     const int H = c->heads > 1 ? c->heads : 1, forced = env_int("DEER_CHUNK_L", 0);
     if (!chunk_gru8_supported(c->dtype, c->n, c->d, c->T, H)) return;
@@ -289,8 +289,9 @@ void chunk8_plan(const deer_config* c, Plan& p) {
         p.chunk8 = total >= 60000;
         p.chunk8_grad = total >= 20000;
     } else {
-        p.chunk8 = total >= 380000 && best < 20.0 + 1.18e-4 * total;
-        p.chunk8_grad = p.chunk8 || (total >= 30000 && c->T <= 12000);
+        const bool cheaper = best < 20.0 + 1.18e-4 * total;
+        p.chunk8 = total >= 380000 && cheaper;
+        p.chunk8_grad = (total >= 300000 && cheaper) || (total >= 30000 && c->T <= 12000 && c->T <= 1500LL * c->B);
     }
     if (!p.chunk8) return;
     p.fused = true;
