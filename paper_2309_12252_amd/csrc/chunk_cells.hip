@@ -584,7 +584,10 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
 // gates go through memory.  A step evaluates the cell behind the position it solves for; one more step takes the first position of
 // the sequence.  The sums over positions have the columns on the contraction index: cotangents, state and input cross a slice of LDS.
 // UP = 16: dU per block, and dW^T with the bias sums as a ninth row (the input rows are followed by a row of ones).  UP = 8: two
-// blocks share a tile whose columns are (state | input).
+// blocks share a tile whose columns are (state | input).  A position's sixteen columns are added up by themselves and then to the sums: one
+// accumulator over all 16 Lc positions had a relative error in dL/dtheta of 3.5e-7 (LSTM and LEM), against 2.7e-7 and 2.9e-7 of
+// a kernel that sums 16 positions at a time; now 2.3e-7.  J^T lambda is added up without the cotangent, as in chunk_gru.hip.  dL/dx leaves before
+// the sums, so that the pre-activations' cotangents end there (17 to 32 registers spilled otherwise).
 // Measured, gradient with a kernel of its own for the vector-Jacobian product / now, us: LSTM u = 8, d = 4, 16 x 50,000 positions 455 / 245; LEM u = 16, d = 6, 32 x 17,984 positions 1,020 / 490.
 // ------------------------------------------------------------------------------------------------------------------
 template <int CELL, int UP, int DS, bool VEC>
@@ -618,7 +621,7 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
         float* __restrict__ dxb = p.dx ? p.dx + first * d : nullptr;
         const int a = r * Lc, end = T - 16 * grp * Lc;
         auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
-        constexpr int R = UP == 16 ? 2 : 4;
+        constexpr int R = 2;
         Acc y0r[R], y1r[R], g0r[R], g1r[R];
         float xr[R][DS];
         auto ask = [&](int j, int t) {
@@ -668,7 +671,7 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
                 e1 = g < 2 ? o : e[0];
             }
         }
-        // one step at position `at` (relative) with state (s0 | s1) in front of it: adds J^T lambda to (n0 | n1)
+        // one step at position `at` (relative) with state (s0 | s1) in front of it: (n0 | n1) = J^T lambda
         auto step = [&](const Acc& s0, const Acc& s1, const float (&x)[DS], int at, Acc& n0, Acc& n1) {
             Factors k[4];
             cell.eval(k, s0, s1, x, dt, g);
@@ -681,9 +684,9 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
                     da[1][v] = k[v].b * dc;
                     da[2][v] = k[v].c * dc;
                     da[3][v] = k[v].d * e0[v];
-                    n1[v] += k[v].f * dc;
+                    n1[v] = k[v].f * dc;
                 }
-                n0 = times_t(ut[0], da[0], n0);
+                n0 = times_t(ut[0], da[0], zero4());
                 n0 = times_t(ut[1], da[1], n0);
                 const Acc s2 = times_t(ut[2], da[2], zero4());
                 n0 += times_t(ut[3], da[3], s2);
@@ -694,17 +697,28 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
                     da[1][v] = k[v].c * e0[v];
                     zn[v] = k[v].n1;
                 }
-                const Acc dz = times_t(ut[3], da[3], e1);
+                const Acc dz = e1 + times_t(ut[3], da[3], zero4());
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     da[0][v] = k[v].a * dz[v];
                     da[2][v] = k[v].b * dz[v];
-                    n1[v] += k[v].f * dz[v];
-                    n0[v] += k[v].e * e0[v];
+                    n1[v] = k[v].f * dz[v];
+                    n0[v] = k[v].e * e0[v];
                 }
                 n0 = times_t(ut[0], da[0], n0);
                 const Acc s1t = times_t(ut[1], da[1], zero4());
                 n0 += times_t(ut[2], da[2], s1t);
+            }
+            if (dxb) {
+                Acc o0 = times_t(wt[0], da[0], zero4()), o1 = times_t(wt[1], da[1], zero4());
+                o0 = times_t(wt[2], da[2], o0);
+                o1 = times_t(wt[3], da[3], o1);
+                if (g < 2 && at < end) {
+                    float* o = dxb + (long long)at * d + 4 * g;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (4 * g + v < d) o[v] = o0[v] + o1[v];
+                }
             }
             // ---- products over positions ----
             if constexpr (UP == 16) {
@@ -728,37 +742,29 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
                 aW[1] += t1;
             }
             wave_lds_fence();
+            const float* q = S + g * 16 + r;   // row m of four: + 64 m
+            float bs[4], bo[4];                // state, and UP = 16: input, UP = 8: the new z
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const float* q = S + (4 * m + g) * 16 + r;
-                const float bs = q[ST], bz = CELL == LEM ? q[ST + 256] : 0.f;
-                if constexpr (UP == 16) {
-                    const float bx = q[XT];
+                bs[m] = q[64 * m + ST];
+                bo[m] = UP == 16 ? q[64 * m + XT] : CELL == LEM ? q[64 * m + ST + 256] : 0.f;
+            }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float t = q[256 * i];
-                        aU[i] = mfma(t, CELL == LEM && i == 3 ? bz : bs, aU[i]);
-                        aW[i] = mfma(bx, t, aW[i]);
-                    }
-                } else {
-                    const float t1 = q[256];
-                    aU[0] = mfma(q[0], bs, aU[0]);
-                    aU[1] = mfma(t1, bs, aU[1]);
-                    if constexpr (CELL == LEM) aU[2] = mfma(t1, bz, aU[2]);
+            for (int i = 0; i < TILES; ++i) {
+                Acc pU = zero4(), pW = zero4();
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const float t = q[64 * m + 256 * i];
+                    pU = mfma(t, UP == 16 && CELL == LEM && i == 3 ? q[64 * m + ST + 256] : bs[m], pU);
+                    if (UP == 16) pW = mfma(bo[m], t, pW);
+                    else if (CELL == LEM && i == 1) pW = mfma(t, bo[m], pW);
                 }
+                __builtin_amdgcn_sched_barrier(0);   // (one block's products at a time: registers)
+                aU[i] += pU;
+                if (UP == 16) aW[i] += pW;
+                else if (CELL == LEM && i == 1) aU[2] += pW;
             }
             wave_lds_fence();
-            if (dxb) {
-                Acc o0 = times_t(wt[0], da[0], zero4()), o1 = times_t(wt[1], da[1], zero4());
-                o0 = times_t(wt[2], da[2], o0);
-                o1 = times_t(wt[3], da[3], o1);
-                if (g < 2 && at < end) {
-                    float* o = dxb + (long long)at * d + 4 * g;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (4 * g + v < d) o[v] = o0[v] + o1[v];
-                }
-            }
         };
         // (a column that starts past the end has nothing to store: its positions are not below `end`)
         for (int t0 = 0; t0 < Lc; t0 += R) {
@@ -766,12 +772,12 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
             for (int j = 0; j < R; ++j) {
                 const int t = t0 + j, rel = a + Lc - 1 - t;
                 const bool live = rel < end;
-                Acc n0 = g0r[j], n1 = g1r[j];
+                Acc n0, n1;
                 step(y0r[j], y1r[j], xr[j], rel + 1, n0, n1);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    e0[v] = live ? n0[v] : 0.f;   // nothing follows the last position
-                    e1[v] = live ? n1[v] : 0.f;
+                    e0[v] = live ? g0r[j][v] + n0[v] : 0.f;   // nothing follows the last position
+                    e1[v] = live ? g1r[j][v] + n1[v] : 0.f;
                 }
                 ask(j, t + R);
             }
@@ -779,7 +785,7 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
         if (grp == 0) {   // the first position of the sequence
             const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * ld : nullptr;
             const Acc s0 = y0b ? load_units<VEC>(y0b, j0, n) : zero4(), s1 = y0b ? load_units<VEC>(y0b + n, j0, n) : zero4();
-            Acc n0 = zero4(), n1 = zero4();
+            Acc n0, n1;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 e0[v] = r == 0 ? e0[v] : 0.f;

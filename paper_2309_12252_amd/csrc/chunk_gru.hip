@@ -471,25 +471,26 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
                             lz[I][v] = k.pz * l;
                             lc[I][v] = k.sr * l;
                             lr[I][v] = k.st * l;
-                            y[I][v] = gr[REV ? j : 0][I][v] + k.z * l;
+                            y[I][v] = k.z * l;
                         }
                     }
                 }
                 if constexpr (REV) {
-                    // lambda_pos = g_pos + J_{pos+1}^T lambda_{pos+1}
+                    // lambda_pos = g_pos + J_{pos+1}^T lambda_{pos+1}.  The products are added up by themselves: with g or z lambda in the accumulator
+                    // every instruction rounds at the size of lambda (dL/dx at n = 27 was 2.65e-7 off, now 2.12e-7, the single-pass scan 2.14e-7)
 #pragma unroll
                     for (int I = 0; I < NB; ++I) {
-                        Acc s1 = zero4(), s2 = zero4();
+                        Acc s0 = zero4(), s1 = zero4();
 #pragma unroll
                         for (int K = 0; K < NB; ++K)
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
-                                y[I] = mfma(ut[1][I][K][v], lz[K][v], y[I]);
+                                s0 = mfma(ut[1][I][K][v], lz[K][v], s0);
                                 s1 = mfma(ut[2][I][K][v], lc[K][v], s1);
-                                s2 = mfma(ut[0][I][K][v], lr[K][v], s2);
+                                s0 = mfma(ut[0][I][K][v], lr[K][v], s0);
                             }
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) y[I][v] += s1[v] + s2[v];
+                        for (int v = 0; v < 4; ++v) y[I][v] = gr[REV ? j : 0][I][v] + (y[I][v] + (s0[v] + s1[v]));
                     }
                 }
                 const unsigned o = (unsigned)(rel * N + 4 * g);
@@ -532,7 +533,8 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
 // n = 16: the dual walk with the vector-Jacobian product inside (as in chunk_cells.hip).  lambda_i = g_i + J_{i+1}^T lambda_{i+1} needs the
 // cotangents of the pre-activations at position i + 1, which are all that dL/dx, dL/dtheta and (at the first position) dL/dy0 are made of;
 // one more step takes the first position of a sequence.  The sums over positions have the columns on the contraction index:
-// cotangents, state and input cross a slice of LDS.  At n = 32 the sums (72 registers more) would leave one wavefront per SIMD.
+// cotangents, state and input cross a slice of LDS.  J^T lambda is added up without g (see the walk above), and a
+// position's sixteen columns by themselves before they join the sums (see chunk_cells.hip; chunks of 32 positions: 3.9e-7 -> 2.4e-7).  At n = 32 the sums (72 registers more) would leave one wavefront per SIMD.
 // Measured, d = 6, 32 x 17,984 positions: walk 43 us and a kernel of its own for the product 126 us; now 82 us in all.
 // ------------------------------------------------------------------------------------------------------------------
 template <int DS>
@@ -563,7 +565,7 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
         float* __restrict__ dxb = p.dx ? p.dx + first * d : nullptr;
         const int a = r * Lc, end = T - 16 * grp * Lc;
         auto row = [&](int rel) { return (unsigned)min(max(rel, 0), end - 1); };
-        constexpr int R = DS == 4 ? 2 : 4;
+        constexpr int R = 2;
         Acc yr[R], gr[R];
         float xr[R][DS];
         auto ask = [&](int j, int t) {
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
         fold_carries<N, true>(p, b, grp, nq, g, r, ev);
         Acc e = ev[0];
 
-        // one step at position `at` (relative) with state h in front of it: adds J^T lambda to y
+        // one step at position `at` (relative) with state h in front of it: y = J^T lambda
         auto step = [&](const Acc& h, const float (&x)[DS], int at, Acc& y) {
             Acc ar = bs[0], az = bs[1], ac = bs[2], aq = bs[3];
 #pragma unroll
@@ -622,7 +624,7 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
                 dz[v] = k.pz * e[v];
                 dc[v] = k.sc * e[v];
                 dq[v] = k.sr * e[v];
-                y[v] += k.z * e[v];
+                y[v] = k.z * e[v];
             }
             float* o = S + r * 16 + 4 * g;
             store4(o, dr); store4(o + 256, dz); store4(o + 512, dq); store4(o + 768, dc); store4(o + 1024, h);
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
             Acc s1 = zero4(), dx = zero4();
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                y = mfma(ut[1][v], dz[v], y);
+                s1 = mfma(ut[1][v], dz[v], s1);
                 s1 = mfma(ut[0][v], dr[v], s1);
                 dx = mfma(wt[0][v], dr[v], dx);
             }
@@ -643,41 +645,49 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
                 dx = mfma(wt[2][v], dc[v], dx);
             }
             y += s1;
-            wave_lds_fence();
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const float* q = S + (4 * m + g) * 16 + r;
-                const float tr = q[0], tz = q[256], tq = q[512], tc = q[768], hk = q[1024], xk = q[1280];
-                aU[0] = mfma(tr, hk, aU[0]);
-                aU[1] = mfma(tz, hk, aU[1]);
-                aU[2] = mfma(tq, hk, aU[2]);
-                aW[0] = mfma(tr, xk, aW[0]);
-                aW[1] = mfma(tz, xk, aW[1]);
-                aW[2] = mfma(tc, xk, aW[2]);
-            }
-            wave_lds_fence();
             if (dxb && at < end) {
                 float* t = dxb + (long long)at * d + 4 * g;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     if (4 * g + v < d) t[v] = dx[v];
             }
+            wave_lds_fence();
+            const float* q = S + g * 16 + r;   // row m of four: + 64 m
+            float hk[4], xk[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                hk[m] = q[64 * m + 1024];
+                xk[m] = q[64 * m + 1280];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {   // r, z, c (hidden part 512, input part 768)
+                Acc pU = zero4(), pW = zero4();
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const float t = q[64 * m + 256 * i];
+                    pU = mfma(t, hk[m], pU);
+                    pW = mfma(i == 2 ? q[64 * m + 768] : t, xk[m], pW);
+                }
+                aU[i] += pU;
+                aW[i] += pW;
+            }
+            wave_lds_fence();
         };
         for (int t0 = 0; t0 < Lc; t0 += R) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const int t = t0 + j, rel = a + Lc - 1 - t;
                 const bool live = rel < end;
-                Acc y = gr[j];
+                Acc y;
                 step(yr[j], xr[j], rel + 1, y);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) e[v] = live ? y[v] : 0.f;   // nothing follows the last position
+                for (int v = 0; v < 4; ++v) e[v] = live ? gr[j][v] + y[v] : 0.f;   // nothing follows the last position
                 ask(j, t + R);
             }
         }
         if (grp == 0) {   // the first position of the sequence
             const Acc h = p.y0 ? load4(p.y0 + (long long)b * N + 4 * g) : zero4();
-            Acc y = zero4();
+            Acc y;
 #pragma unroll
             for (int v = 0; v < 4; ++v) e[v] = r == 0 ? e[v] : 0.f;
             step(h, xr[0], r == 0 ? 0 : end, y);

@@ -438,27 +438,27 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                     lz[v] = k[v].pz * e[v];
                     lc[v] = k[v].sr * e[v];
                     lr[v] = k[v].st * e[v];
-                    y[v] = go[REV ? j : 0][v] + k[v].z * e[v];
+                    y[v] = k[v].z * e[v];
                 }
                 sX[nxt][0][wave][lane] = yr[(j + 1) % R];
                 sX[cur][1][wave][lane] = lz;
                 sX[cur][2][wave][lane] = lc;
                 sX[cur][3][wave][lane] = lr;
                 __syncthreads();
-                Acc s1 = zero4(), s2 = zero4();
+                Acc s0 = zero4(), s1 = zero4(), s2 = zero4();
 #pragma unroll
                 for (int K = 0; K < NB; ++K) {
                     const Acc kz = sX[cur][1][K][lane], kc = sX[cur][2][K][lane], kr = sX[cur][3][K][lane];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        y = mfma(ut[REV ? 1 : 0][K][v], kz[v], y);
+                        s0 = mfma(ut[REV ? 1 : 0][K][v], kz[v], s0);
                         s1 = mfma(ut[REV ? 2 : 0][K][v], kc[v], s1);
                         s2 = mfma(ut[0][K][v], kr[v], s2);
                     }
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    y[v] += s1[v] + s2[v];
+                    y[v] = go[REV ? j : 0][v] + (y[v] + (s0[v] + (s1[v] + s2[v])));
                     e[v] = live ? y[v] : 0.f;   // nothing follows the last time
                 }
             }

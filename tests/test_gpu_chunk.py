@@ -155,3 +155,38 @@ def test_parameter_gradient_alone_and_scalar_alignment(kind, n, monkeypatch):
                 assert torch.equal(a, b)
     finally:
         ctx.close()
+
+
+# Error against 64 bits: no larger than that of the scans, which sum about sixteen positions at a time.  Relative 2-norm, mean over three inputs; a tenth
+# on top for the scatter of such a mean (dL/dtheta has 416 entries and more, dL/dy0 of the few sequences here is left to the parity tests).
+@pytest.mark.parametrize("kind,n,d,B,T,H,K", [("heads", 8, 8, 8, 1024, 32, 8), ("gru", 8, 5, 16, 12003, 0, 0), ("gru", 16, 6, 8, 9001, 0, 0), ("gru", 27, 9, 6, 9001, 0, 0),
+                                              ("lstm", 8, 4, 8, 12000, 0, 0), ("lstm", 12, 3, 5, 7001, 0, 0), ("lem", 8, 3, 5, 7001, 0, 0), ("lem", 16, 6, 8, 9001, 0, 0)])
+def test_gradient_error_no_larger_than_the_scans(kind, n, d, B, T, H, K, monkeypatch):
+    cell = {"lstm": deer.DEER_CELL_LSTM, "lem": deer.DEER_CELL_LEM}.get(kind, deer.DEER_CELL_GRU)
+    ch = 2 * n if kind in ("lstm", "lem") else n
+    lead, state = ((B, T, H), (B, H, n)) if H else ((B, T), (B, ch))
+    config = lambda dtype: deer.make_config(cell, dtype, B, T, n, d=d, t1=1.0 if kind == "lem" else 0.0, heads=H, stride_levels=K)
+    by_scan = {"DEER_FUSED_L": "4"} if n == 8 and cell == deer.DEER_CELL_GRU else {"DEER_FUSED": "0"}
+    err = {}
+    for seed in range(3):
+        gen = torch.Generator(device=DEV)
+        gen.manual_seed(900 + seed)
+        normal = lambda *shape: torch.randn(*shape, generator=gen, device=DEV)
+        theta = normal(deer.theta_count(config(deer.DEER_F32))) / np.sqrt(n)
+        x, y0, g = normal(*lead, d), torch.zeros(*state, device=DEV), normal(*lead, ch) / (B * T)
+        ctx = deer.DeerContext(config(deer.DEER_F64), device=DEV)
+        y = ctx.eval(theta.double(), x.double(), y0.double(), tol=1e-9, max_iter=50)[0]
+        want = ctx.grad(theta.double(), x.double(), y0.double(), y, g.double())
+        ctx.close()
+        for route, knobs in (("chunks", {"DEER_CHUNK_L": "32"}), ("scans", by_scan)):
+            with monkeypatch.context() as m:
+                for k, v in knobs.items():
+                    m.setenv(k, v)
+                ctx = deer.DeerContext(config(deer.DEER_F32), device=DEV)
+                got = ctx.grad(theta, x, y0, y.float(), g)
+                ctx.close()
+            for name, a, b in zip(("dtheta", "dx"), got, want):
+                err[route, name] = err.get((route, name), 0.0) + float((a.double() - b).norm() / b.norm()) / 3
+    for name in ("dtheta", "dx"):
+        print(kind, n, name, "%.3g %.3g" % (err["chunks", name], err["scans", name]), flush=True)
+        assert err["chunks", name] <= 1.1 * err["scans", name], (name, err)
