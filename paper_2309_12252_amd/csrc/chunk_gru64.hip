@@ -445,20 +445,22 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                 sX[cur][2][wave][lane] = lc;
                 sX[cur][3][wave][lane] = lr;
                 __syncthreads();
-                Acc s0 = zero4(), s1 = zero4(), s2 = zero4();
+                Acc s[2][3];   // (by halves of the contraction: every instruction rounds at the size of its partial sum)
+#pragma unroll
+                for (int i = 0; i < 6; ++i) s[i / 3][i % 3] = zero4();
 #pragma unroll
                 for (int K = 0; K < NB; ++K) {
                     const Acc kz = sX[cur][1][K][lane], kc = sX[cur][2][K][lane], kr = sX[cur][3][K][lane];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        s0 = mfma(ut[REV ? 1 : 0][K][v], kz[v], s0);
-                        s1 = mfma(ut[REV ? 2 : 0][K][v], kc[v], s1);
-                        s2 = mfma(ut[0][K][v], kr[v], s2);
+                        s[K >> 1][0] = mfma(ut[REV ? 1 : 0][K][v], kz[v], s[K >> 1][0]);
+                        s[K >> 1][1] = mfma(ut[REV ? 2 : 0][K][v], kc[v], s[K >> 1][1]);
+                        s[K >> 1][2] = mfma(ut[0][K][v], kr[v], s[K >> 1][2]);
                     }
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    y[v] = go[REV ? j : 0][v] + (y[v] + (s0[v] + (s1[v] + s2[v])));
+                    y[v] = go[REV ? j : 0][v] + (y[v] + ((s[0][0][v] + s[1][0][v]) + ((s[0][1][v] + s[1][1][v]) + (s[0][2][v] + s[1][2][v]))));
                     e[v] = live ? y[v] : 0.f;   // nothing follows the last time
                 }
             }

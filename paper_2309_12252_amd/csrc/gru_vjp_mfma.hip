@@ -290,6 +290,10 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
     constexpr int N = 64, NB = 4;
     __shared__ __align__(16) float sD[kWaves][5][16][kLD];    // dar, daz, dac, dq, z lam of the wavefront's rows
     __shared__ float sX[2][kWaves][16][kLD];                  // input gradient: parts of the wavefronts
+    __shared__ float sY[kWaves][N];                           // dL/dy0: the same
+    __shared__ __align__(16) float sH[2][16][N + 4];          // state in front of the sixteen positions
+    __shared__ __align__(16) acc4 sWT[3][kThreads];           // W columns for dL/dx (row 4 g + v of the wavefront's, column c)
+    __shared__ __align__(16) float sBias[4][N];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, c = lane & 15, d = p.d, row0 = 16 * wave;
     const float* __restrict__ theta = reinterpret_cast<const float*>(p.theta);
@@ -303,25 +307,26 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
     float* __restrict__ dy0 = reinterpret_cast<float*>(p.dy0);
 
     // operands A of this wavefront's rows; the state and the input supply entry 16 K + 4 g + v and 4 m + g
-    acc4 uA[3][NB], bA[4];
-    float wA[3][4], wT[3][4];   // W rows, and W columns for dL/dx (row 4 g + v of the wavefront's, column c)
+    // (what is used once a tile waits in LDS: registers)
+    acc4 uA[3][NB];
+    float wA[3][4];   // W rows
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
 #pragma unroll
         for (int K = 0; K < NB; ++K)
 #pragma unroll
             for (int v = 0; v < 4; ++v) uA[a][K][v] = U[(a * N + row0 + c) * N + 16 * K + 4 * g + v];
+        acc4 wT;
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const float w = theta[(a * N + row0 + c) * d + min(4 * m + g, d - 1)], t = theta[(a * N + row0 + 4 * g + m) * d + min(c, d - 1)];
             wA[a][m] = 4 * m + g < d ? w : 0.0f;
-            wT[a][m] = c < d ? t : 0.0f;
+            wT[m] = c < d ? t : 0.0f;
         }
+        sWT[a][tid] = wT;   // (read by the same lane)
     }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) bA[a][v] = bias[a * N + row0 + 4 * g + v];
+    sBias[tid / N][tid % N] = bias[tid];
+    __syncthreads();
 
     const acc4 zero = {0.f, 0.f, 0.f, 0.f};
     acc4 accU[3][NB], accW[3], accB[4];
@@ -340,13 +345,14 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
         return (sc - bi * p.T == 0) ? (y0 + bi * N) : (y + (sc - 1) * N);
     };
     int buf = 0;
+    static_assert(kThreads == 4 * N, "one bias entry per thread");
     for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x, buf ^= 1) {
         const long long s0 = tile * 16, sc = s0 + c;
         const bool live = sc < total;
         const long long scl = live ? sc : 0;
         const float* hc = hrow(sc);
         acc4 h[NB];
-        float xB[4], hK[4][NB], xK[4];
+        float xB[4], xK[4];
 #pragma unroll
         for (int K = 0; K < NB; ++K) {
             const float4 t = *reinterpret_cast<const float4*>(hc + 16 * K + 4 * g);
@@ -357,14 +363,12 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const long long sp = s0 + 4 * m + g;
-            const float* hp = hrow(sp);
-#pragma unroll
-            for (int J = 0; J < NB; ++J) hK[m][J] = hp[16 * J + c];   // entry 16 J + c of position 4 m + g
             const float a = x[scl * d + min(4 * m + g, d - 1)], b = x[(sp < total ? sp : 0) * d + min(c, d - 1)];
             xB[m] = 4 * m + g < d ? a : 0.0f;
             xK[m] = (c < d && sp < total) ? b : 0.0f;
         }
-        acc4 ar = bA[0], az = bA[1], ac = bA[2], aq = bA[3];
+        const float* bs = &sBias[0][row0 + 4 * g];
+        acc4 ar = *reinterpret_cast<const acc4*>(bs), az = *reinterpret_cast<const acc4*>(bs + N), ac = *reinterpret_cast<const acc4*>(bs + 2 * N), aq = *reinterpret_cast<const acc4*>(bs + 3 * N);
 #pragma unroll
         for (int K = 0; K < NB; ++K)
 #pragma unroll
@@ -396,14 +400,17 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
             sD[wave][4][row][c] = z * lm[v];
         }
         accB[0] += dar; accB[1] += daz; accB[2] += dac; accB[3] += dq;
+        *reinterpret_cast<acc4*>(&sH[buf][c][row0 + 4 * g]) = hw;
         if (dx) {   // rows (input index) 4 g + v of position c, this wavefront's share of the sum over rows
-            acc4 ax = zero;
+            acc4 ax = zero, bx = zero, cx = zero;
+            const acc4 wr = sWT[0][tid], wz = sWT[1][tid], wc = sWT[2][tid];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                ax = mfma(wT[0][v], dar[v], ax);
-                ax = mfma(wT[1][v], daz[v], ax);
-                ax = mfma(wT[2][v], dac[v], ax);
+                ax = mfma(wr[v], dar[v], ax);
+                bx = mfma(wz[v], daz[v], bx);
+                cx = mfma(wc[v], dac[v], cx);
             }
+            ax += bx + cx;
 #pragma unroll
             for (int v = 0; v < 4; ++v) sX[buf][wave][c][4 * g + v] = ax[v];
         }
@@ -412,18 +419,26 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
             const int q = tid >> 4, k = tid & 15;
             if (s0 + q < total && k < d) dx[(s0 + q) * d + k] = (sX[buf][0][q][k] + sX[buf][1][q][k]) + (sX[buf][2][q][k] + sX[buf][3][q][k]);
         }
+        // the tile's sixteen positions by themselves, then added to the sums (one chain over all tiles of a workgroup rounds at the size of the sums)
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const float tr = sD[wave][0][c][4 * m + g], tz = sD[wave][1][c][4 * m + g], tc = sD[wave][2][c][4 * m + g], tq = sD[wave][3][c][4 * m + g];
+        for (int a = 0; a < 3; ++a) {
+            float tu[4], tw[4];   // cotangents in front of U and W (block c: dq and dac)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                tw[m] = sD[wave][a][c][4 * m + g];
+                tu[m] = a == 2 ? sD[wave][3][c][4 * m + g] : tw[m];
+            }
 #pragma unroll
             for (int J = 0; J < NB; ++J) {
-                accU[0][J] = mfma(tr, hK[m][J], accU[0][J]);
-                accU[1][J] = mfma(tz, hK[m][J], accU[1][J]);
-                accU[2][J] = mfma(tq, hK[m][J], accU[2][J]);
+                acc4 s = zero;
+#pragma unroll
+                for (int m = 0; m < 4; ++m) s = mfma(tu[m], sH[buf][4 * m + g][16 * J + c], s);
+                accU[a][J] += s;
             }
-            accW[0] = mfma(tr, xK[m], accW[0]);
-            accW[1] = mfma(tz, xK[m], accW[1]);
-            accW[2] = mfma(tc, xK[m], accW[2]);
+            acc4 s = zero;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) s = mfma(tw[m], xK[m], s);
+            accW[a] += s;
         }
         // dL/dy0 = J_1^T lam_1 where a sequence starts among the sixteen positions (rare; the same for the whole workgroup)
         if (dy0) {
@@ -431,17 +446,18 @@ __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParam
             if (b0 < p.B && b0 * p.T < s0 + 16) {
                 for (long long bi = b0; bi < p.B && bi * p.T < s0 + 16; ++bi) {
                     const int q = (int)(bi * p.T - s0);
-                    if (tid < N) {
-                        float s = sD[tid / 16][4][tid % 16][q];
-                        for (int i = 0; i < N; ++i) {
-                            s += U[(0 * N + i) * N + tid] * sD[i / 16][0][i % 16][q];
-                            s += U[(1 * N + i) * N + tid] * sD[i / 16][1][i % 16][q];
-                            s += U[(2 * N + i) * N + tid] * sD[i / 16][3][i % 16][q];
-                        }
-                        dy0[bi * N + tid] = s;
+                    // short partial sums, z lambda last (one chain of 192 products on top of it was twice as far off)
+                    float part[3] = {0.0f, 0.0f, 0.0f};
+                    for (int i = 0; i < 16; ++i) {
+                        part[0] += U[(0 * N + row0 + i) * N + lane] * sD[wave][0][i][q];
+                        part[1] += U[(1 * N + row0 + i) * N + lane] * sD[wave][1][i][q];
+                        part[2] += U[(2 * N + row0 + i) * N + lane] * sD[wave][3][i][q];
                     }
+                    sY[wave][lane] = part[0] + (part[1] + part[2]);
+                    __syncthreads();
+                    if (tid < N) dy0[bi * N + tid] = ((sY[0][tid] + sY[1][tid]) + (sY[2][tid] + sY[3][tid])) + sD[tid / 16][4][tid % 16][q];
+                    __syncthreads();
                 }
-                __syncthreads();
             }
         }
     }

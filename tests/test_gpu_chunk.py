@@ -158,15 +158,16 @@ def test_parameter_gradient_alone_and_scalar_alignment(kind, n, monkeypatch):
 
 
 # Error against 64 bits: no larger than that of the scans, which sum about sixteen positions at a time.  Relative 2-norm, mean over three inputs; a tenth
-# on top for the scatter of such a mean (dL/dtheta has 416 entries and more, dL/dy0 of the few sequences here is left to the parity tests).
+# on top for the scatter of such a mean (dL/dtheta has 416 entries and more; dL/dy0 is compared where it has as many).
 @pytest.mark.parametrize("kind,n,d,B,T,H,K", [("heads", 8, 8, 8, 1024, 32, 8), ("gru", 8, 5, 16, 12003, 0, 0), ("gru", 16, 6, 8, 9001, 0, 0), ("gru", 27, 9, 6, 9001, 0, 0),
+                                              ("gru", 50, 7, 9, 4001, 0, 0), ("gru", 64, 16, 8, 4003, 0, 0),
                                               ("lstm", 8, 4, 8, 12000, 0, 0), ("lstm", 12, 3, 5, 7001, 0, 0), ("lem", 8, 3, 5, 7001, 0, 0), ("lem", 16, 6, 8, 9001, 0, 0)])
 def test_gradient_error_no_larger_than_the_scans(kind, n, d, B, T, H, K, monkeypatch):
     cell = {"lstm": deer.DEER_CELL_LSTM, "lem": deer.DEER_CELL_LEM}.get(kind, deer.DEER_CELL_GRU)
     ch = 2 * n if kind in ("lstm", "lem") else n
     lead, state = ((B, T, H), (B, H, n)) if H else ((B, T), (B, ch))
     config = lambda dtype: deer.make_config(cell, dtype, B, T, n, d=d, t1=1.0 if kind == "lem" else 0.0, heads=H, stride_levels=K)
-    by_scan = {"DEER_FUSED_L": "4"} if n == 8 and cell == deer.DEER_CELL_GRU else {"DEER_FUSED": "0"}
+    by_scan = {"DEER_FUSED_L": "4"} if n == 8 and cell == deer.DEER_CELL_GRU else {"DEER_FUSED": "0", "DEER_VJP_MFMA": "1" if n <= 32 else "0"}
     err = {}
     for seed in range(3):
         gen = torch.Generator(device=DEV)
@@ -174,10 +175,16 @@ def test_gradient_error_no_larger_than_the_scans(kind, n, d, B, T, H, K, monkeyp
         normal = lambda *shape: torch.randn(*shape, generator=gen, device=DEV)
         theta = normal(deer.theta_count(config(deer.DEER_F32))) / np.sqrt(n)
         x, y0, g = normal(*lead, d), torch.zeros(*state, device=DEV), normal(*lead, ch) / (B * T)
-        ctx = deer.DeerContext(config(deer.DEER_F64), device=DEV)
-        y = ctx.eval(theta.double(), x.double(), y0.double(), tol=1e-9, max_iter=50)[0]
-        want = ctx.grad(theta.double(), x.double(), y0.double(), y, g.double())
-        ctx.close()
+        if n <= 32:
+            ctx = deer.DeerContext(config(deer.DEER_F64), device=DEV)
+            y = ctx.eval(theta.double(), x.double(), y0.double(), tol=1e-9, max_iter=50)[0]
+            want = ctx.grad(theta.double(), x.double(), y0.double(), y, g.double())
+            ctx.close()
+        else:   # (state sizes above 32 run in fp32 only)
+            h = [t.double().cpu().numpy() for t in (theta, x, y0, g)]
+            y = oracle.seq_eval(oracle.make_cell(oracle.CELL_GRU, n, d), h[0], h[1], h[2], nthreads=8)
+            want = [torch.from_numpy(a).to(DEV) for a in oracle.gru_grad(n, d, h[0], h[1], h[2], y, h[3])]
+            y = torch.from_numpy(y).to(DEV)
         for route, knobs in (("chunks", {"DEER_CHUNK_L": "32"}), ("scans", by_scan)):
             with monkeypatch.context() as m:
                 for k, v in knobs.items():
@@ -185,8 +192,27 @@ def test_gradient_error_no_larger_than_the_scans(kind, n, d, B, T, H, K, monkeyp
                 ctx = deer.DeerContext(config(deer.DEER_F32), device=DEV)
                 got = ctx.grad(theta, x, y0, y.float(), g)
                 ctx.close()
-            for name, a, b in zip(("dtheta", "dx"), got, want):
+            for name, a, b in zip(("dtheta", "dx", "dy0"), got, want):
                 err[route, name] = err.get((route, name), 0.0) + float((a.double() - b).norm() / b.norm()) / 3
-    for name in ("dtheta", "dx"):
+    for name in ("dtheta", "dx") + (("dy0",) if y0.numel() >= 400 else ()):
         print(kind, n, name, "%.3g %.3g" % (err["chunks", name], err["scans", name]), flush=True)
         assert err["chunks", name] <= 1.1 * err["scans", name], (name, err)
+
+
+# n = 64: the four wavefronts of a workgroup go through several blocks of sixteen positions each (512 workgroups: more than 8,192 positions),
+# sequences start in later ones, with and without dL/dx and dL/dy0; chunk lengths by default
+@pytest.mark.parametrize("n,d,B,T", [(64, 8, 5, 9973), (50, 7, 300, 61), (64, 16, 2, 20011)])
+def test_parameter_sums_over_many_positions_at_64(n, d, B, T):
+    w = inputs.gru_workload("many64", 3100 + n + T, B=B, T=T, n=n, d=d)
+    w.y0 = np.random.default_rng(5).standard_normal((B, n)).astype(np.float32)
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        _against_oracle(ctx, w, lambda m: oracle_eval(w, max_iter=m), lambda: oracle.seq_eval(oracle_cell(w), w.theta, w.x, w.y0, nthreads=8),
+                        lambda ys, g: oracle.gru_grad(w.n, w.d, w.theta, w.x, w.y0, ys, g))
+        y = ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=w.max_iter)[0]
+        g = dev((np.random.default_rng(2).standard_normal(tuple(y.shape)) / T).astype(np.float32), 0)
+        run = lambda **kw: ctx.grad(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), y, g, **kw)
+        whole, alone = run(), run(want_dx=False, want_dy0=False)
+        assert torch.equal(whole[0], alone[0]) and torch.equal(run(want_dx=False)[2], whole[2]) and torch.equal(run(want_dy0=False)[1], whole[1])
+    finally:
+        ctx.close()
