@@ -147,25 +147,24 @@ __device__ __forceinline__ void compose_unit(const float* __restrict__ tot, floa
 // add over the lane groups, which leaves row 16I + r in lane r; odd steps start from there, multiply columns and add
 // over the lanes of a row, which leaves the operand order again: no step moves x between lanes.  The maps are requested PD
 // steps ahead (a step is shorter than a trip to the last-level cache).
+// The map of a unit spans up to 16 chunks and can overflow where the map of no chunk does (an iterate far from the solution whose
+// Jacobians expand); applied to a small or zero x it gives an infinity or a NaN that the chunks one by one would not give.  Such a value
+// stays in x to the end, so the carries tell: they are then folded again from the chunks' maps alone.
 template <int N, bool REV>
 __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int grp, int nq, int g, int r, Acc (&e)[N / 16]) {
     constexpr int NB = N / 16, MS = map_size<N>(), PD = N == 16 ? 4 : 2;   // even
     Acc A[PD][NB][NB], V[PD][NB];
     Acc xk[NB];      // x[16K + 4g + v]
     float xr[NB];    // x[16K + r]
-#pragma unroll
-    for (int K = 0; K < NB; ++K) {
-        xk[K] = e[K] = zero4();
-        xr[K] = 0.f;
-    }
     const int pu = 16 / p.per_unit;   // units of a group
-    const int before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
-    const float* __restrict__ sup = p.sup + (long long)b * p.units * MS;
-    const float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+    const float* __restrict__ own = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+    // the maps in front of the group: those of the units, in the second pass those of the chunks
+    const float* __restrict__ front = p.sup + (long long)b * p.units * MS;
+    int maps = p.units, before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
     auto request = [&](int j, int i) {
         i = min(i, steps - 1);
         const int k = i - before;
-        const float* m = i < before ? sup + (long long)(REV ? p.units - 1 - i : i) * MS : tot + (long long)(REV ? nq - 1 - k : k) * MS;
+        const float* m = i < before ? front + (long long)(REV ? maps - 1 - i : i) * MS : own + (long long)(REV ? nq - 1 - k : k) * MS;
 #pragma unroll
         for (int I = 0; I < NB; ++I) {
             if (j & 1) {
@@ -222,22 +221,40 @@ __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int gr
             for (int I = 0; I < NB; ++I) xr[I] = y[I];
         }
     };
-    if (steps > 0) {
+    for (int pass = 0;; ++pass) {
 #pragma unroll
-        for (int j = 0; j < PD; ++j) request(j, j);
-        int i = 0;
-        for (; i + PD <= steps; i += PD) {
-#pragma unroll
-            for (int j = 0; j < PD; ++j) {
-                step(j, i + j);
-                request(j, i + j + PD);
-            }
+        for (int K = 0; K < NB; ++K) {
+            xk[K] = e[K] = zero4();
+            xr[K] = 0.f;
         }
+        if (steps > 0) {
 #pragma unroll
-        for (int j = 0; j < PD - 1; ++j)
-            if (i + j < steps) step(j, i + j);
+            for (int j = 0; j < PD; ++j) request(j, j);
+            int i = 0;
+            for (; i + PD <= steps; i += PD) {
+#pragma unroll
+                for (int j = 0; j < PD; ++j) {
+                    step(j, i + j);
+                    request(j, i + j + PD);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < PD - 1; ++j)
+                if (i + j < steps) step(j, i + j);
+        }
+        select(steps, steps & 1);
+        if (pass > 0 || before == 0) return;
+        float sum = 0.f;   // (not a finite number if one of its terms is none)
+#pragma unroll
+        for (int K = 0; K < NB; ++K)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sum += 0.f * e[K][v];
+        if (!__ballot(sum != 0.f)) return;
+        maps = (p.T + p.Lc - 1) / p.Lc;
+        front = p.tot + (long long)b * p.groups * 16 * MS;
+        before = REV ? max(maps - 16 * (grp + 1), 0) : 16 * grp;
+        steps = before + nq - 1;
     }
-    select(steps, steps & 1);
 }
 
 }  // namespace

@@ -343,50 +343,68 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     {
         constexpr int PD = REV ? 2 : 4;
         const int pu = 16 / p.per_unit;   // units of a group
-        const int before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
-        const float* __restrict__ sup = p.sup + (long long)b * p.units * MS;
-        const float* __restrict__ tot = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+        const float* __restrict__ own = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+        // the maps in front of the group: those of the units, and again those of the chunks if that overflowed (see fold_carries)
+        const float* __restrict__ front = p.sup + (long long)b * p.units * MS;
+        int maps = p.units, before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
         Acc A[PD][NB];
         float V[PD];
         auto request = [&](int j, int i) {
             i = min(i, steps - 1);
             const int k = i - before;
-            const float* m = i < before ? sup + (long long)(REV ? p.units - 1 - i : i) * MS : tot + (long long)(REV ? nq - 1 - k : k) * MS;
+            const float* m = i < before ? front + (long long)(REV ? maps - 1 - i : i) * MS : own + (long long)(REV ? nq - 1 - k : k) * MS;
 #pragma unroll
             for (int K = 0; K < NB; ++K) A[j][K] = load4(m + (16 * wave + r) * N + 16 * K + 4 * g);
             V[j] = m[N * N + 16 * wave + r];
         };
-        if (steps > 0) {
+        for (int pass = 0;; ++pass) {
+            if (steps > 0) {
 #pragma unroll
-            for (int j = 0; j < PD; ++j) request(j, j);
-        }
-        if (tid < N) sx[0][tid] = 0.f;
-        __syncthreads();
-        for (int i0 = 0; i0 <= steps; i0 += PD) {
-#pragma unroll
-            for (int j = 0; j < PD; ++j) {
-                const int i = i0 + j;
-                if (i <= steps) {
-                    const int k = i - before, qs = REV ? nq - 1 - k : k;
-                    const Acc mine = load4(&sx[i & 1][16 * wave + 4 * g]);
-                    e = (k >= 0 && r == qs) ? mine : e;
-                    if (i < steps) {
-                        float s = 0.f;
-                        if (i > 0) {   // in front of the sequence x is zero and M is not looked at (it may have overflowed)
-#pragma unroll
-                            for (int K = 0; K < NB; ++K) {
-                                const Acc xk = load4(&sx[i & 1][16 * K + 4 * g]);
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) s += A[j][K][v] * xk[v];
-                            }
-                            s = sum_groups(s);
-                        }
-                        if (g == 0) sx[(i + 1) & 1][16 * wave + r] = s + V[j];
-                        __syncthreads();
-                    }
-                }
-                if (steps > 0) request(j, i + PD);
+                for (int j = 0; j < PD; ++j) request(j, j);
             }
+            if (tid < N) sx[0][tid] = 0.f;
+            __syncthreads();
+            for (int i0 = 0; i0 <= steps; i0 += PD) {
+#pragma unroll
+                for (int j = 0; j < PD; ++j) {
+                    const int i = i0 + j;
+                    if (i <= steps) {
+                        const int k = i - before, qs = REV ? nq - 1 - k : k;
+                        const Acc mine = load4(&sx[i & 1][16 * wave + 4 * g]);
+                        e = (k >= 0 && r == qs) ? mine : e;
+                        if (i < steps) {
+                            float s = 0.f;
+                            if (i > 0) {   // in front of the sequence x is zero and M is not looked at (it may have overflowed)
+#pragma unroll
+                                for (int K = 0; K < NB; ++K) {
+                                    const Acc xk = load4(&sx[i & 1][16 * K + 4 * g]);
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v) s += A[j][K][v] * xk[v];
+                                }
+                                s = sum_groups(s);
+                            }
+                            if (g == 0) sx[(i + 1) & 1][16 * wave + r] = s + V[j];
+                            __syncthreads();
+                        }
+                    }
+                    if (steps > 0) request(j, i + PD);
+                }
+            }
+            if (pass > 0 || before == 0) break;   // (the same for the four wavefronts)
+            float sum = 0.f;   // (not a finite number if one of its terms is none)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sum += 0.f * e[v];
+            const unsigned long long bad = __ballot(sum != 0.f);
+            if (lane == 0) s_max[wave] = bad ? 1u : 0u;
+            __syncthreads();
+            const bool again = (s_max[0] | s_max[1] | s_max[2] | s_max[3]) != 0u;
+            __syncthreads();
+            if (!again) break;
+            maps = chunks;
+            front = p.tot + (long long)b * p.groups * 16 * MS;
+            before = REV ? max(chunks - 16 * (grp + 1), 0) : 16 * grp;
+            steps = before + nq - 1;
+            e = zero4();
         }
     }
 

@@ -276,15 +276,17 @@ __global__ __launch_bounds__(256, 2) void chunk8_totals_kernel(Chunk8Params p) {
 template <bool REV>
 __device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, int id, int Cc, unsigned live, int g, int r, float (&e)[2]) {
     constexpr int PD = 4;
-    const int before = REV ? c.gpr - 1 - c.gi : c.gi, steps = before + 15, own = min(Cc, 16);
+    const int own = min(Cc, 16);
+    int maps = c.gpr, before = REV ? c.gpr - 1 - c.gi : c.gi, steps = before + 15;
     const int im = 2 * (r >> 2) + (r & 1), which = (r >> 1) & 1;
-    const float* __restrict__ sup = p.sup + (long long)(id - c.gi) * MS8;
+    // the maps in front of the group: those of the groups, and again those of the chunks if that overflowed (see fold_carries)
+    const float* __restrict__ front = p.sup + (long long)(id - c.gi) * MS8;
     const float* __restrict__ tot = p.tot + (long long)id * 16 * MS8;
     F2 A[PD], V[PD];
     auto request = [&](int j, int i) {
         i = min(i, steps - 1);
         const int q = i - before;
-        const float* m = i < before ? sup + (REV ? c.gpr - 1 - i : i) * MS8 : tot + (REV ? 15 - q : q) * MS8;
+        const float* m = i < before ? front + (long long)(REV ? maps - 1 - i : i) * MS8 : tot + (REV ? 15 - q : q) * MS8;
         A[j] = *reinterpret_cast<const F2*>(m + im * 8 + 2 * g);
         V[j] = *reinterpret_cast<const F2*>(m + 64 + 2 * g);
     };
@@ -313,20 +315,29 @@ __device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, in
         x[1] = D[1];
         fresh = false;
     };
+    for (int pass = 0;; ++pass) {
 #pragma unroll
-    for (int j = 0; j < PD; ++j) request(j, j);
-    int i = 0;
-    for (; i + PD <= steps; i += PD) {
+        for (int j = 0; j < PD; ++j) request(j, j);
+        int i = 0;
+        for (; i + PD <= steps; i += PD) {
 #pragma unroll
-        for (int j = 0; j < PD; ++j) {
-            step(j, i + j);
-            request(j, i + j + PD);
+            for (int j = 0; j < PD; ++j) {
+                step(j, i + j);
+                request(j, i + j + PD);
+            }
         }
-    }
 #pragma unroll
-    for (int j = 0; j < PD - 1; ++j)
-        if (i + j < steps) step(j, i + j);
-    keep(steps);
+        for (int j = 0; j < PD - 1; ++j)
+            if (i + j < steps) step(j, i + j);
+        keep(steps);
+        if (pass > 0 || before == 0 || !__ballot(0.f * e[0] + 0.f * e[1] != 0.f)) return;
+        maps = 16 * c.gpr;
+        front = p.tot + (long long)(id - c.gi) * 16 * MS8;
+        before *= 16;
+        steps = before + 15;
+        x[0] = x[1] = e[0] = e[1] = 0.f;
+        fresh = true;
+    }
 }
 
 template <int DS>

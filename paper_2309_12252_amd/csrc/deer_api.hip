@@ -210,6 +210,8 @@ std::vector<unsigned> mh_table(const deer_config* c, int tile) {
 // reduction: the workgroups of a compute unit one after the other, `total` for a position of each of sixteen chunks, `unit` and
 // `compose` per further chunk of a unit.  The walk: `walk` a position for the groups that run side by side, and `fold` for every map in
 // front of the last group.  The estimate's choice is within a tenth of the best of 33 combinations tried at each of 18 shapes.
+// At most 64 positions: the product of a chunk's Jacobians then overflows no earlier than that of a tile of the single-pass scan (64 to 96
+// positions).  Longer chunks (64 x 100,000 positions would take 200) gain 1 to 3 % of a step by the estimate.
 int chunk_length(const deer_config* c, int* per_unit) {
     struct Cost { double total, unit, compose, walk, fold; int side_by_side; };
     const bool cell = two_part_cell(c->cell);
@@ -219,16 +221,17 @@ int chunk_length(const deer_config* c, int* per_unit) {
     int best_L = 4;
     *per_unit = 16;
     double best = 1e300;
-    for (int L = 4; L <= 2048; L += L < 64 ? 4 : (L < 256 ? 8 : 32)) {
+    for (int L = 4; L <= 64; L += 4) {
         if (forced >= 4 && L != 4) break;
         if (forced >= 4) L = forced / 4 * 4;
         for (int pu = 4; pu <= 16; pu *= 2) {
             if (forced_unit >= 4 && pu != forced_unit) continue;
             const long long per_seq = ((long long)c->T + 16LL * L - 1) / (16LL * L), groups = per_seq * c->B;
             const long long units = ((long long)c->T + (long long)pu * L - 1) / ((long long)pu * L);
-            // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes 1.3 times as long as half of two)
+            // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes 1.3 times as long as half of two, which is not seen any
+            // more from seven on: n = 32, 16 x 100,000, 10,030 us a solve with units of 16 x 56 positions and 10,330 with twice as many of 8 x 56)
             const long long share = (units * c->B + 255) / 256;
-            const double est = ((double)share + (!cell && c->n >= 32 && (share & 1) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
+            const double est = ((double)share + (!cell && c->n >= 32 && share < 6 && (share & 1) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
                                (double)((groups + k.side_by_side - 1) / k.side_by_side) * k.walk * L + k.fold * (double)units;
             if (est < best) { best = est; best_L = L; *per_unit = pu; }
         }

@@ -216,3 +216,73 @@ def test_parameter_sums_over_many_positions_at_64(n, d, B, T):
         assert torch.equal(whole[0], alone[0]) and torch.equal(run(want_dx=False)[2], whole[2]) and torch.equal(run(want_dy0=False)[1], whole[1])
     finally:
         ctx.close()
+
+
+# Jacobians that expand where the correction is zero: no input over the first 2,000 steps and no bias, so the state stays at the origin, where a step
+# multiplies by 1.5 to 1.9; then a signal that saturates the cell.  Chunks of 32 positions do not overflow, units and groups of sixteen of them do
+# (1.5^512), and so would the product over all 2,000 steps.  The solve starts from the solution and the cotangent ends after ten steps, so nothing that
+# is computed is large: the trajectory and the gradient are those of the oracle.
+@pytest.mark.parametrize("kind,n", [("gru", 8), ("gru", 16), ("gru", 27), ("gru", 64), ("heads", 8), ("lstm", 8), ("lstm", 12), ("lem", 7), ("lem", 16)])
+@pytest.mark.parametrize("unit", ["4", "16"])
+def test_expanding_jacobians_and_no_correction(kind, n, unit, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", "32" if unit == "16" else "64")
+    monkeypatch.setenv("DEER_CHUNK_UNIT", unit)
+    rng = np.random.default_rng(17 + n)
+    B, T, d, quiet, H, K = 2, 3001, 3, 2000, 3, 2
+    gates = 3 if kind in ("gru", "heads") else 4
+    cells = H if kind == "heads" else 1
+    theta = []
+    for _ in range(cells):
+        W, U = rng.standard_normal((gates, n, d)), 0.1 * rng.standard_normal((gates, n, n)) / np.sqrt(n)
+        for gate in (2, 3) if kind == "lem" else (2,):
+            U[gate] += (2.0 if kind == "lem" else 4.0) * np.eye(n)
+        theta += [W.ravel(), U.ravel(), np.zeros(4 * n)]
+    ch = 2 * n if kind in ("lstm", "lem") else n
+    lead = (B, T, H) if kind == "heads" else (B, T)
+    x = rng.standard_normal(lead + (d,))
+    x[:, :quiet] = 0.0
+    y0 = np.zeros((B, H, n) if kind == "heads" else (B, ch))
+    g = np.zeros(lead + (ch,))
+    g[:, :10] = 1e-3 * rng.standard_normal(g[:, :10].shape)
+    f32 = lambda a: np.ascontiguousarray(a, dtype=np.float32).astype(np.float64)
+    theta, x, g = f32(np.concatenate(theta)), f32(x), f32(g)
+    if kind == "heads":
+        solve = lambda th: oracle.mh_seq_eval(n, d, H, K, th, x, y0, nthreads=8)
+        ys = solve(theta)
+        want = oracle.mh_gru_grad(n, d, H, K, theta, x, y0, ys, g)
+    else:
+        c = oracle.make_cell({"gru": oracle.CELL_GRU, "lstm": oracle.CELL_LSTM, "lem": oracle.CELL_LEM}[kind], ch, d, **({"dt": 1.0} if kind == "lem" else {}))
+        solve = lambda th: oracle.seq_eval(c, th, x, y0, nthreads=8)
+        ys = solve(theta)
+        want = oracle.gru_grad(n, d, theta, x, y0, ys, g) if kind == "gru" else oracle.rnn_grad(c, theta, x, y0, ys, g)
+    assert np.abs(ys[:, :quiet]).max() == 0.0 and np.abs(ys[:, quiet + 200:]).max() > 0.5
+    # where the signal sets in, a state near the origin carries every rounding along: what weights off by one in 2^24 change in the solution, times
+    # eight for the products, the gates and the state that are rounded too (1e-4 where that is less)
+    bound = max(1e-4, 8.0 * np.abs(solve(theta * (1.0 + 2.0 ** -24 * rng.choice([-1.0, 1.0], theta.shape))) - ys).max())
+    cell = {"lstm": deer.DEER_CELL_LSTM, "lem": deer.DEER_CELL_LEM}.get(kind, deer.DEER_CELL_GRU)
+    ctx = deer.DeerContext(deer.make_config(cell, deer.DEER_F32, B, T, n, d=d, t1=1.0 if kind == "lem" else 0.0, heads=H if kind == "heads" else 0,
+                                            stride_levels=K if kind == "heads" else 0), device=DEV)
+    try:
+        th, xd, y0d = dev(theta, 0), dev(x, 0), dev(y0, 0)
+        y, it, _, conv, st = ctx.eval(th, xd, y0d, y_guess=dev(ys, 0), tol=1e-4, max_iter=20)
+        assert st == deer.DEER_OK and conv
+        print(kind, n, "%.2e of %.2e" % (np.abs(host(y) - ys).max(), bound), flush=True)
+        assert np.abs(host(y) - ys).max() <= bound
+        for name, a, b in zip(("dtheta", "dx", "dy0"), ctx.grad(th, xd, y0d, dev(ys, 0), dev(g, 0)), want):
+            assert np.abs(host(a).reshape(-1) - b.reshape(-1)).max() <= 1e-4 * max(1.0, np.abs(b).max()), (name, np.abs(host(a).reshape(-1) - b.reshape(-1)).max())
+    finally:
+        ctx.close()
+
+
+# the same at the chunk length the dispatch takes by itself: with 64 sequences of 100,000 positions nothing but a limit keeps the chunks short (a step
+# multiplies by two: 2^127 is the largest power)
+@pytest.mark.parametrize("kind,n", [("gru", 16), ("gru", 8)])
+def test_expanding_jacobians_at_the_default_chunk_length(kind, n):
+    B, T = 64, 100000
+    theta = np.concatenate([np.zeros(3 * n + 2 * n * n), 6.0 * np.eye(n).ravel(), np.zeros(4 * n)])
+    ctx = deer.DeerContext(deer.make_config(deer.DEER_CELL_GRU, deer.DEER_F32, B, T, n, d=1), device=DEV)
+    try:
+        y, it, _, conv, st = ctx.eval(dev(theta, 0), torch.zeros(B, T, 1, device=DEV), torch.zeros(B, n, device=DEV), tol=1e-6, max_iter=5)
+        assert st == deer.DEER_OK and conv and it == 1 and not y.any()
+    finally:
+        ctx.close()
