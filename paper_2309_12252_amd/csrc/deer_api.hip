@@ -301,7 +301,8 @@ void chunk8_plan(const deer_config* c, Plan& p) {
     p.fused_L = p.fused_W = p.fused_tiles = 0;
 }
 
-Plan make_plan(const deer_config* c) {
+// chunks = false: the plan of a context that never steps by chunks (deer_linrec_solve_static, whose limit it sets)
+Plan make_plan(const deer_config* c, bool chunks = true) {
     Plan p{};
     p.esz = c->dtype == DEER_F32 ? 4 : 8;
     const size_t n = (size_t)c->n, B = (size_t)c->B, T = (size_t)c->T;
@@ -439,9 +440,9 @@ Plan make_plan(const deer_config* c) {
         p.fused_tiles = (p.scan_T + ft - 1) / ft;
         if (p.fused_tiles < 1) p.fused_tiles = 1;
     }
-    if (gru) chunk8_plan(c, p);
+    if (gru && chunks) chunk8_plan(c, p);
     const bool cell_chunk = two_part_cell(c->cell) && c->mlp_width == 1;
-    if (cell_chunk || (gru && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c))) {
+    if (cell_chunk || (gru && chunks && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c))) {
         p.chunk = true;
         p.fused = true;
         p.fused_tiles = 0;
@@ -1294,7 +1295,7 @@ deer_status deer_linrec_solve_static(int32_t dtype, int32_t B, int32_t T, int32_
     if (native_n(n) != n) return fail(nullptr, DEER_ERR_UNSUPPORTED, "the scan alone needs a state size of 1, 2, 4, 8, 16, 32 or (fp32) 64");
     if (!d_A || !d_b || !d_y) return fail(nullptr, DEER_ERR_INVALID_ARG, "a required pointer is NULL");
     // the part of the plan the scan uses, re-based to the start of the static array
-    Plan plan = make_plan(&cfg);
+    Plan plan = make_plan(&cfg, false);
     const size_t base = plan.off_aggW;
     const size_t need = plan.off_ctl - base + ctl_bytes();
     if (need > kStaticBytes)

@@ -84,3 +84,15 @@ def test_create_rejects_bad_arguments_without_touching_the_gpu():
     assert st == deer.DEER_ERR_WORKSPACE and not handle.value
     assert b"workspace" in lib.deer_last_error(None)
     assert lib.deer_eval(None, None, None, None, None, 1e-4, 1, None, None, None, None) == deer.DEER_ERR_INVALID_ARG
+
+
+# The limit of the static scratch is that of the single-pass scan's words, whatever route the steps of a context of that shape take: (n, B, the longest
+# T that fits).  A shape beyond it is refused before anything is enqueued.
+@pytest.mark.parametrize("n,B,T", [(4, 16, 41293824), (8, 16, 6546432), (8, 4096, 24576), (16, 16, 115904), (32, 16, 30720), (64, 16, 992)])
+def test_limit_of_the_static_scratch(n, B, T):
+    lib = deer.load_library()
+    word = ctypes.c_void_p(256)   # (looked at for NULL only)
+    solve = lambda steps: lib.deer_linrec_solve_static(deer.DEER_F32, B, steps, n, word, word, None, word, 0, None, None)
+    assert solve(T + 1) == deer.DEER_ERR_WORKSPACE
+    if not os.path.exists("/dev/kfd"):   # without a GPU the next check fails: the device is asked for
+        assert solve(T) == deer.DEER_ERR_HIP
