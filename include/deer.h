@@ -128,7 +128,9 @@ size_t deer_theta_count(const deer_config* cfg);
  * tiles publish for each other, counters, partial sums of dL/dtheta -- and, only where a kernel pair exchanges
  * them through memory (MLP_ODE; GRU in fp64 with n >= 16, with d beyond what the in-scan cell takes, or with the
  * DEER_FUSED / DEER_GRAD_FUSED knobs at 0), the Jacobian stream [B,T,n,n] and the right-hand side, the O(n^2 T)
- * memory of Sec. 3.5.  Where the cell is evaluated inside the scans the workspace is O(n T).
+ * memory of Sec. 3.5.  Where the cell is evaluated inside the scans the workspace is O(n T).  Where steps run by chunks
+ * (see deer_eval) every chunk has a map of N^2 + N scalars (N = state size, for LSTM and LEM 2u rounded up to 16 or 32): one for every 4 to 64
+ * positions, so short sequences in large numbers take up to (N + 1) / 4 trajectories of it, long ones a fraction of one.
  * The environment variables listed under "Environment" below are read here and in deer_create(); both calls must
  * see the same values. */
 deer_status deer_workspace_bytes(const deer_config* cfg, size_t* bytes);

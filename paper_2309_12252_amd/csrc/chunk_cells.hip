@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
     const float* __restrict__ xb = p.x + (long long)b * T * d;
     const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * ld : nullptr;
     const float* __restrict__ gb = REV ? p.g + (long long)b * T * ld : nullptr;
-    float* __restrict__ tot = p.tot + ((long long)b * p.groups * 16 + first) * MS;
+    float* __restrict__ tot = p.tot + ((long long)b * chunks + first) * MS;
     float* __restrict__ sFw = sF[wave];
     const int q_lo = cpw * wave, q_hi = min(q_lo + cpw, chunks - first);   // chunks of this wavefront (inside the unit)
     const int lo = (first + q_lo) * Lc, hi = min(T, (first + q_hi) * Lc), blocks = (hi - lo + 15) / 16;

@@ -157,7 +157,8 @@ __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int gr
     Acc xk[NB];      // x[16K + 4g + v]
     float xr[NB];    // x[16K + r]
     const int pu = 16 / p.per_unit;   // units of a group
-    const float* __restrict__ own = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+    const int chunks = (p.T + p.Lc - 1) / p.Lc;
+    const float* __restrict__ own = p.tot + ((long long)b * chunks + 16 * grp) * MS;
     // the maps in front of the group: those of the units, in the second pass those of the chunks
     const float* __restrict__ front = p.sup + (long long)b * p.units * MS;
     int maps = p.units, before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
@@ -250,8 +251,8 @@ __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int gr
 #pragma unroll
             for (int v = 0; v < 4; ++v) sum += 0.f * e[K][v];
         if (!__ballot(sum != 0.f)) return;
-        maps = (p.T + p.Lc - 1) / p.Lc;
-        front = p.tot + (long long)b * p.groups * 16 * MS;
+        maps = chunks;
+        front = p.tot + (long long)b * chunks * MS;
         before = REV ? max(maps - 16 * (grp + 1), 0) : 16 * grp;
         steps = before + nq - 1;
     }

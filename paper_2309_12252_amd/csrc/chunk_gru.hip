@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
     const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N : nullptr;
     const float* __restrict__ gb = REV ? p.g + (long long)b * T * N : nullptr;
     const int first = unit * p.per_unit, cpw = p.per_unit / 4;   // first chunk, chunks of a wavefront
-    float* __restrict__ tot = p.tot + ((long long)b * p.groups * 16 + first) * MS;
+    float* __restrict__ tot = p.tot + ((long long)b * chunks + first) * MS;
     float* __restrict__ sFw = sF[wave];
 
     const int q_lo = cpw * wave, q_hi = min(q_lo + cpw, chunks - first);   // chunks of this wavefront (inside the unit)

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     const float* __restrict__ xb = p.x + (long long)b * T * d;
     const float* __restrict__ y0b = p.y0 ? p.y0 + (long long)b * N : nullptr;
     const float* __restrict__ gb = REV ? p.g + (long long)b * T * N : nullptr;
-    float* __restrict__ tot = p.tot + ((long long)b * p.groups * 16 + first) * MS;
+    float* __restrict__ tot = p.tot + ((long long)b * chunks + first) * MS;
     float* __restrict__ sFw = sF[wave];
 
     const int lo = first * Lc, hi = min(T, (first + nq) * Lc), blocks = (hi - lo + 15) / 16;
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     {
         constexpr int PD = REV ? 2 : 4;
         const int pu = 16 / p.per_unit;   // units of a group
-        const float* __restrict__ own = p.tot + ((long long)b * p.groups + grp) * 16 * MS;
+        const float* __restrict__ own = p.tot + ((long long)b * chunks + 16 * grp) * MS;
         // the maps in front of the group: those of the units, and again those of the chunks if that overflowed (see fold_carries)
         const float* __restrict__ front = p.sup + (long long)b * p.units * MS;
         int maps = p.units, before = REV ? max(p.units - (grp + 1) * pu, 0) : grp * pu, steps = before + nq - 1;
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
             __syncthreads();
             if (!again) break;
             maps = chunks;
-            front = p.tot + (long long)b * p.groups * 16 * MS;
+            front = p.tot + (long long)b * chunks * MS;
             before = REV ? max(chunks - 16 * (grp + 1), 0) : 16 * grp;
             steps = before + nq - 1;
             e = zero4();

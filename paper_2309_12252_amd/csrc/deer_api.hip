@@ -42,6 +42,7 @@ constexpr size_t kTimingBytes = (size_t)1 << 26;
 #endif
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
+size_t ctl_bytes() { return align_up((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16); }   // tickets, error slots, status word
 
 struct Plan {
     size_t esz;          // bytes per scalar
@@ -62,6 +63,8 @@ struct Plan {
     bool chunk8, chunk8_grad;   // GRU, 8 channels, fp32, plain or multi-head: the Newton steps, the gradient (chunk_gru8.hip)
     Chunk8Params c8;     // their shapes and chunk lengths
     size_t off_tot, off_sup;
+    size_t words;        // bytes of published words from off_aggW on
+    bool shared;         // the maps of the chunks lie in their place: only deer_linrec_solve() and what a knob keeps off the chunks publish words
     bool grad_fused;     // deer_grad computes the transposed Jacobians inside the reverse scan
     bool need_J;         // some kernel of this plan reads or writes the Jacobian stream [B,T,n,n] and the right-hand side
     int vjp_blocks;
@@ -341,6 +344,7 @@ Plan make_plan(const deer_config* c, bool chunks = true) {
         p.off_aggW = take(nt * (n * n + n) * (p.esz / 4) * 8);
         p.off_inclW = take(nt * n * (p.esz / 4) * 8);
         p.off_barrier = take(0);
+        p.words = off - p.off_aggW;
         p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);
         p.off_tot = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * chunk_map_bytes(8) : 0);
         p.off_sup = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * chunk_map_bytes(8) : 0);
@@ -473,18 +477,29 @@ Plan make_plan(const deer_config* c, bool chunks = true) {
     p.off_zbar = take(ode ? B * (T - 1) * n * p.esz : 0);
     const size_t nt = B * (size_t)(p.tiles > p.fused_tiles ? p.tiles : p.fused_tiles);
     // published tile totals and carries: one 64-bit tagged word per 32 bits of payload
+    const size_t words0 = off;
     p.off_aggW = take(nt * (n * n + n) * (p.esz / 4) * 8);
     p.off_inclW = take(nt * n * (p.esz / 4) * 8);
     // slots of the one-launch solve's grid barrier (two banks, one tagged scalar per workgroup)
     p.off_barrier = take(p.fused ? 2 * (B * (size_t)p.fused_tiles + 4) * (p.esz / 4) * 8 : 0);   // (+4: test hook)
-    p.off_ctl = take((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16);   // tickets, err bits, status
+    p.words = off - words0;
     const size_t map = cell_chunk ? chunk_cells_map_bytes(c->reserved) : chunk_map_bytes(c->n);
-    p.off_tot = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * map : p.chunk ? B * (size_t)p.chunk_groups * 16 * map : 0);
-    p.off_sup = take(p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * map : p.chunk ? B * (size_t)p.chunk_units * map : 0);
+    const size_t tot = p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * map : p.chunk ? B * ((T + p.chunk_L - 1) / p.chunk_L) * map : 0;
+    const size_t sup = p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * map : p.chunk && p.chunk_groups > 1 ? B * (size_t)p.chunk_units * map : 0;
+    p.shared = p.chunk || p.chunk8;
+    if (p.shared) off = words0;
+    else p.off_ctl = take(ctl_bytes());   // tickets, err bits, status
+    p.off_tot = take(tot);
+    p.off_sup = take(sup);
     // partial rows of dL/dtheta: four per block (one per wavefront), two per block in the vector-ALU MLP kernel (one per thread group)
     p.off_partial = take(p.chunk8_grad ? (size_t)(p.c8.groups / 4) * p.c8.P * p.esz
                          : p.chunk_grad ? (B * (size_t)p.chunk_groups + 3) / 4 * theta_count(c) * p.esz
-                                       : (size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
+                                       : 0);
+    if (p.shared) {
+        if (off < words0 + p.words) off = words0 + p.words;
+        p.off_ctl = take(ctl_bytes());
+    }
+    if (!p.chunk8_grad && !p.chunk_grad) p.off_partial = take((size_t)p.vjp_blocks * 4 * theta_count(c) * p.esz);
 #ifdef DEER_SCAN_TIMING
     p.off_timing = take(kTimingBytes);
 #endif
@@ -529,6 +544,7 @@ struct deer_ctx {
     hipStream_t stream;
     char* ws;
     unsigned epoch;
+    bool words_dirty;       // the chunks' maps have been written over the published words
     void* h_err;            // pinned: kSlots * 8 bytes of error words, then the status word and a result word
     void* d_h_err;          // the same memory as the device sees it
     int batch;              // Newton iterations enqueued per host round trip when nothing better is known
@@ -566,7 +582,6 @@ void* ctl_err(deer_ctx* c, int slot) { return c->ws + c->plan.off_ctl + (size_t)
 unsigned* ctl_status(deer_ctx* c) {
     return reinterpret_cast<unsigned*>(c->ws + c->plan.off_ctl + (size_t)kSlots * 4 + (size_t)kSlots * 8);
 }
-size_t ctl_bytes() { return align_up((size_t)kSlots * 4 + (size_t)kSlots * 8 + 16); }
 
 void prof_begin(deer_ctx* c, int kind, int iter = -1) {
     if (!c->profiling || c->ev_used >= kMaxEvents) return;
@@ -646,6 +661,15 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
     p.timing = reinterpret_cast<unsigned long long*>(c->ws + c->plan.off_timing) + (size_t)(p.epoch & 7u) * ((size_t)1 << 20);
 #endif
     hipError_t e;
+    const bool by_chunks = fused_theta && (c->plan.chunk || c->plan.chunk8);
+    if (by_chunks) {
+        c->words_dirty = c->plan.shared;
+    } else if (c->words_dirty) {
+        // what the chunks left there must not pass for a published word
+        e = launch_fill_zero(c->ws + c->plan.off_aggW, c->plan.words, c->stream);
+        if (e != hipSuccess) return e;
+        c->words_dirty = false;
+    }
     if (fused_theta && c->plan.chunk) {
         ChunkParams q = chunk_params(c, fused_theta, fused_x, y0, yold);
         q.g = reverse ? reinterpret_cast<const float*>(bv) : nullptr;
@@ -693,7 +717,7 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
 // in stream order: the clearing kernel is enqueued on the same stream.
 deer_status reserve_epochs(deer_ctx* c, unsigned count) {
     if (c->epoch + count + 1u >= (1u << 30)) {
-        HIPCHK(c, launch_fill_zero(c->ws + c->plan.off_aggW, c->plan.off_ctl - c->plan.off_aggW, c->stream));
+        HIPCHK(c, launch_fill_zero(c->ws + c->plan.off_aggW, c->plan.words, c->stream));
         c->epoch = 0;
     }
     return DEER_OK;
@@ -844,6 +868,7 @@ deer_status deer_create(const deer_config* cfg, void* d_workspace, size_t worksp
     c->stream = reinterpret_cast<hipStream_t>(hip_stream);
     c->ws = reinterpret_cast<char*>(d_workspace);
     c->epoch = 0;
+    c->words_dirty = false;
     c->h_err = nullptr;
     c->profiling = false;
     c->prof = deer_profile{};
@@ -865,7 +890,7 @@ deer_status deer_create(const deer_config* cfg, void* d_workspace, size_t worksp
     if (e == hipSuccess) e = launch_fill_zero(c->ws + plan.off_ctl, ctl_bytes(), c->stream);
     // tagged words must not carry a valid tag by accident: epochs start at 1, so zeros never match
     if (e == hipSuccess)
-        e = launch_fill_zero(c->ws + plan.off_aggW, plan.off_ctl - plan.off_aggW, c->stream);
+        e = launch_fill_zero(c->ws + plan.off_aggW, plan.words, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         std::string msg = std::string("deer_create: ") + hipGetErrorString(e);
@@ -1189,6 +1214,7 @@ static deer_status grad_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
         q.dy0 = parts ? reinterpret_cast<float*>(c->ws + c->plan.off_dy0parts) : reinterpret_cast<float*>(d_dLdy0);
         q.dtheta = reinterpret_cast<float*>(d_dLdtheta);
         q.partial = reinterpret_cast<float*>(c->ws + c->plan.off_partial);
+        c->words_dirty = c->plan.shared;
         prof_begin(c, KIND_FUSED);
         HIPCHK(c, launch_chunk_gru8(q, c->stream));
         if (parts) HIPCHK(c, launch_gru_dy0_mh(q.dy0, reinterpret_cast<float*>(d_dLdy0), g.B, g.T, c->plan.mh_H, c->plan.mh_K, g.n, c->stream));
@@ -1203,6 +1229,7 @@ static deer_status grad_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
         q.dx = reinterpret_cast<float*>(d_dLdx); q.dy0 = reinterpret_cast<float*>(d_dLdy0);
         q.dtheta = reinterpret_cast<float*>(d_dLdtheta);
         q.partial = reinterpret_cast<float*>(c->ws + c->plan.off_partial);
+        c->words_dirty = c->plan.shared;
         prof_begin(c, KIND_FUSED);
         HIPCHK(c, two_part_cell(g.cell) ? launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream) : launch_chunk_gru(g.n, q, c->stream));
         prof_end(c);
@@ -1333,6 +1360,7 @@ deer_status deer_linrec_solve_static(int32_t dtype, int32_t B, int32_t T, int32_
     c.plan = plan;
     c.stream = reinterpret_cast<hipStream_t>(hip_stream);
     c.ws = reinterpret_cast<char*>(scratch);
+    c.words_dirty = false;
     c.epoch = 1;   // the same tag in every call: everything published by the previous call is cleared below
     c.h_err = nullptr;
     c.d_h_err = nullptr;

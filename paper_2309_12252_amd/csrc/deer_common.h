@@ -98,7 +98,7 @@ struct ChunkParams {
     float* out;                // next iterate, or (GRU with n = 32, 64) lambda [B,T,n]
     // whole gradient (LSTM, LEM and GRU with n = 16): dx [B,T,d] or nullptr, dy0 [B,n] or nullptr, dtheta, one row of its length per workgroup
     float* dx; float* dy0; float* dtheta; float* partial;
-    float* tot; float* sup;    // maps of the chunks [B][groups][16][n*n + n] and of the units [B][units][n*n + n]
+    float* tot; float* sup;    // maps of the chunks [B][ceil(T / Lc)][n*n + n] and, with more than one group, of the units [B][units][n*n + n]
     void* err;                 // max|y_new - y| (raw bits), or nullptr
     Gate gate;
     int B, T, d, Lc;

@@ -96,3 +96,16 @@ def test_limit_of_the_static_scratch(n, B, T):
     assert solve(T + 1) == deer.DEER_ERR_WORKSPACE
     if not os.path.exists("/dev/kfd"):   # without a GPU the next check fails: the device is asked for
         assert solve(T) == deer.DEER_ERR_HIP
+
+
+# Many short sequences: a chunk has at least four positions, so the maps of the chunks take (n^2 + n) scalars for every four positions of a sequence
+# and no more (a quarter on top: the maps of the units), beside the second trajectory, the published words and the rows of dL/dtheta.
+@pytest.mark.parametrize("cell,n,d,B,T", [(deer.DEER_CELL_GRU, 16, 6, 100000, 8), (deer.DEER_CELL_GRU, 32, 8, 20000, 8), (deer.DEER_CELL_GRU, 32, 8, 4096, 28),
+                                          (deer.DEER_CELL_LSTM, 16, 8, 20000, 8), (deer.DEER_CELL_LEM, 8, 4, 20000, 12)])
+def test_workspace_of_many_short_sequences(cell, n, d, B, T):
+    cfg = deer.make_config(cell, deer.DEER_F32, B, T, n, d=d, t1=1.0 if cell == deer.DEER_CELL_LEM else 0.0)
+    state = n if cell == deer.DEER_CELL_GRU else 2 * n
+    maps = B * -(-T // 4) * (state * state + state) * 4 * 1.25
+    words = B * -(-T // 64) * (state * state + 2 * state) * 8
+    rows = max(2048, B / 4) * deer.theta_count(cfg) * 4
+    assert deer.workspace_bytes(cfg) <= 1.02 * (B * T * state * 4 + max(maps + rows, words + rows))

@@ -286,3 +286,29 @@ def test_expanding_jacobians_at_the_default_chunk_length(kind, n):
         assert st == deer.DEER_OK and conv and it == 1 and not y.any()
     finally:
         ctx.close()
+
+
+# the maps of the chunks lie where the recurrence alone publishes its words: calls of one context in any order, and a gradient that a knob keeps on the scans
+@pytest.mark.parametrize("n,d", [(8, 4), (16, 6), (32, 8), (64, 5)])
+def test_recurrence_alone_between_steps_by_chunks(n, d, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", "8")
+    if n > 8:
+        monkeypatch.setenv("DEER_GRAD_FUSED", "0")
+    B, T = 3, 2500
+    w = inputs.gru_workload("between_n%d" % n, 3300 + n, B=B, T=T, n=n, d=d)
+    rng = np.random.default_rng(n)
+    A, b, v = dev(rng.standard_normal((B, T, n, n)) * 0.45 / np.sqrt(n), 0), dev(rng.standard_normal((B, T, n)), 0), dev(rng.standard_normal((B, n)), 0)
+    g = dev(rng.standard_normal((B, T, n)) / T, 0)
+    th, x, y0 = dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0)
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        first, back = ctx.linrec_solve(A, b, v), ctx.linrec_solve(A, b, reverse=True)
+        y = ctx.eval(th, x, y0, tol=w.tol, max_iter=w.max_iter)[0]
+        grads = ctx.grad(th, x, y0, y, g)
+        for _ in range(2):
+            assert torch.equal(ctx.linrec_solve(A, b, v), first)
+            assert torch.equal(ctx.eval(th, x, y0, tol=w.tol, max_iter=w.max_iter)[0], y)
+            assert torch.equal(ctx.linrec_solve(A, b, reverse=True), back)
+            assert all(torch.equal(p, q) for p, q in zip(ctx.grad(th, x, y0, y, g), grads))
+    finally:
+        ctx.close()
