@@ -57,7 +57,7 @@ struct Plan {
     bool mh;             // multi-head GRU with strides: the scan's sequences are the heads' strided recurrences
     int mh_H, mh_K;      // heads, stride levels
     size_t off_dy0parts, off_mhtable;
-    bool chunk;          // GRU, n >= 16, fp32: Newton steps and the dual scan run by chunks (chunk_gru.hip)
+    bool chunk;          // GRU, n >= 16, LSTM and LEM in fp32: Newton steps (where `fused`) and the dual scan run by chunks (chunk_gru.hip, chunk_cells.hip)
     bool chunk_grad;     // their gradient takes the vector-Jacobian product into the walk
     int chunk_L, chunk_groups, chunk_per_unit, chunk_units;
     bool chunk8, chunk8_grad;   // GRU, 8 channels, fp32, plain or multi-head: the Newton steps, the gradient (chunk_gru8.hip)
@@ -125,11 +125,17 @@ bool is_multihead(const deer_config* c);
 // at 5 to 8 units a small problem is all latency.  Measured, microseconds a solve, Jacobian kernel and scan / chunks: LSTM of 4 units
 // 301 / 337 at 64 x 2,000 and 1,058 / 1,162 at 16 x 50,000; 8 units 119 / 132 at 1 x 500, 159 / 155 at 1 x 2,000, 303 / 210 at 4 x 5,000; 16 units
 // 184 / 165 at 1 x 500; LEM of 8 units 126 / 138 at 8 x 500, of 16 units 226 / 204 at 1 x 500.
-bool cell_by_chunks(const deer_config* user) {
-    if (!two_part_cell(user->cell) || !chunk_cells_supported(user->dtype, user->n, user->d)) return false;
-    if (env_int("DEER_FUSED", 1) == 0 || env_int("DEER_GRAD_FUSED", 1) == 0) return false;
-    if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
-    return user->n > 8 || (user->n > 4 && (user->T >= 1536 || (long long)user->B * user->T >= 8192));
+// The LEM of 8 units, which needs no embedding, steps by chunks later than its gradient goes that way (solve 142 / 152 at 40 x 210,
+// 138 / 155 at 1 x 1,536, 154 / 161 at 1 x 2,000, 152 / 158 at 16 x 600, but 191 / 184 at 1 x 3,500, 190 / 168 at 4 x 2,300, 164 / 160 at 10 x 1,000; gradient
+// 79 / 59 at 40 x 210).
+enum { kCellScan = 0, kCellChunks = 1, kCellChunkGradient = 2 };
+int cell_by_chunks(const deer_config* user) {
+    if (!two_part_cell(user->cell) || !chunk_cells_supported(user->dtype, user->n, user->d)) return kCellScan;
+    if (env_int("DEER_FUSED", 1) == 0 || env_int("DEER_GRAD_FUSED", 1) == 0) return kCellScan;
+    if (env_int("DEER_CHUNK_L", 0) >= 4 || user->n > 8) return kCellChunks;
+    const long long total = (long long)user->B * user->T;
+    if (user->n <= 4 || (user->T < 1536 && total < 8192)) return kCellScan;
+    return user->cell == DEER_CELL_LEM && user->n == 8 && (total < 8192 ? user->T < 2500 : total < 10000 && user->T < 1000) ? kCellChunkGradient : kCellChunks;
 }
 
 // The configuration the kernels run: a plain GRU whose state size has no kernels of its own is embedded in the next
@@ -140,7 +146,7 @@ deer_config internal_config(const deer_config* user) {
     if (c.cell == DEER_CELL_GRU && !is_multihead(user) && native_n(c.n) > 0) c.n = native_n(c.n);
     if (two_part_cell(c.cell)) {   // state (h | c) or (y | z) of 2 units entries in the next state size with a scan kernel
         c.reserved = user->n;
-        c.mlp_width = cell_by_chunks(user) ? 1 : 0;   // (a field these cells do not use: tells the plan)
+        c.mlp_width = cell_by_chunks(user);   // (a field these cells do not use: tells the plan)
         c.n = c.mlp_width ? 2 * user->n : native_n(2 * user->n);
     }
     return c;
@@ -247,6 +253,9 @@ int chunk_length(const deer_config* c, int* per_unit) {
 // grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 143 / 209 at 1 x 500, 259 / 304 at 20 x 1,000, 298 / 332 at
 // 10 x 2,500, 264 / 297 at 64 x 500, but 347 / 339 at 4 x 5,000, 797 / 504 at 1 x 20,000, 620 / 559 at 16 x 5,000, 663 / 545 at 60 x 1,500; n = 16
 // 130 / 142 at 20 x 783, 143 / 158 at 16 x 1,300, 157 / 165 at 64 x 500, 155 / 161 at 3 x 2,500, but 142 / 133 at 1 x 1,600, 188 / 158 at 1 x 5,000, 275 / 241 at 60 x 1,500.
+// Short sequences in large numbers gain most (a tile holds one sequence): n = 16 14,300 / 3,220 at 100,000 x 8, 253 / 173 at 1,000 x 50; n = 32 1,510 / 710 at
+// 4,096 x 28, 449 / 372 at 1,000 x 64.  At n = 64, where the scan reads stored Jacobians in tiles of eight positions, chunks are faster from the start:
+// 264 / 239 at 1 x 50, 247 / 214 at 16 x 32, 853 / 357 at 1 x 500, 595 / 248 at 64 x 64 (gradient 132 / 93, 151 / 88, 270 / 127, 392 / 104).
 bool chunk_pays(const deer_config* c) {
     if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
     const long long total = (long long)c->B * c->T;
@@ -269,11 +278,16 @@ double chunk8_estimate(const Chunk8Params& q) {
     return base + std::max(1.45 * L, 1.15 * work) + 8.0 * std::max(0.0, waves - 1.0);
 }
 
-// The single-pass scan (all iterations in one launch up to about 260,000 positions) takes 20 us + 0.118 us per 1,000 positions a step.
-// Microseconds a solve, scan / chunks: plain 303 / 319 at 25 x 14,000, 305 / 290 at 60 x 6,000, 502 / 466 at 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at
-// 4 x 100,000, where the fold is long; 123 / 207 at 16 x 10,000.  Heads (total positions of all heads): 118 / 135 at 9,600, 147 / 147 at
-// 42,000, 300 / 175 at 64,000, 3,898 / 1,112 at 2.1 million.  The gradient, whose walk takes the vector-Jacobian product in: plain
-// 64 / 60 at 4 x 3,000, 85 / 74 at 16 x 10,000, 158 / 101 at 12 x 30,000, but 69 / 73 at 5 x 11,000, 68 / 78 at 3 x 16,000, 87 / 92 at 2 x 30,000, 408 / 227 at 16 x 100,000; heads 83 / 63 at 42,000, 1,181 / 273 at 2.1 million.
+// The single-pass scan takes 20 us + 0.118 us per 1,000 positions a step, and 0.13 to 0.145 us per 1,000 in at most two rounds of tiles (512); heads 28 to 34 us
+// where every compute unit has one tile at most.
+// Microseconds a solve, scan / chunks: plain 281 / 304 at 12 x 32,000, 270 / 295 at 30 x 13,000, 276 / 266 at 64 x 6,000, 352 / 318 at 20 x 20,000, 502 / 466 at
+// 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at 4 x 100,000, where the fold is long; 123 / 207 at 16 x 10,000.  Heads (steps x heads): one
+// tile a compute unit 139 / 143 at 4 x 2,000 x 8, 148 / 180 at 1 x 8,000 x 8, 171 / 215 at 1 x 16,000 x 4, beyond that 199 / 172 at 10 x 800 x 8, 219 / 179 at
+// 8 x 2,000 x 8, 239 / 237 at 2 x 20,000 x 2 (estimate 48 us), 331 / 260 at 1 x 30,000 x 4, 334 / 306 at 1 x 50,000 x 2 (392 tiles), 3,898 / 1,112 at 2.1 million positions,
+// but 266 / 289 at 1 x 40,000 x 2 (315 tiles, 61 us) and 316 / 344 at 1 x 70,000 (274 tiles, 74 us).
+// The gradient, whose walk takes the vector-Jacobian product in: plain 64 / 60 at
+// 4 x 3,000, 81 / 73 at 16 x 10,000, 158 / 101 at 12 x 30,000, but 64 / 67 at 5 x 7,400, 72 / 74 at 8 x 12,000, 68 / 78 at 3 x 16,000, 408 / 227 at
+// 16 x 100,000; heads 73 / 59 at 4 x 2,000 x 8, 75 / 69 at 1 x 8,000 x 8 (estimate 37 us), 68 / 71 at 1 x 10,000 x 4 (39 us), 114 / 92 at 1 x 30,000 x 4.
 void chunk8_plan(const deer_config* c, Plan& p) {
     const int H = c->heads > 1 ? c->heads : 1, forced = env_int("DEER_CHUNK_L", 0);
     if (!chunk_gru8_supported(c->dtype, c->n, c->d, c->T, H)) return;
@@ -292,12 +306,13 @@ void chunk8_plan(const deer_config* c, Plan& p) {
     if (forced >= 4) {
         p.chunk8 = p.chunk8_grad = true;
     } else if (is_multihead(c)) {
-        p.chunk8 = total >= 60000;
-        p.chunk8_grad = total >= 20000;
+        const long long tiles = (long long)c->B * (long long)mh_table(c, scan_valu_tile(c->n, p.fused_L, 8)).size();
+        p.chunk8 = total >= 60000 && tiles > 256 && (best < 55.0 || tiles > 380);
+        p.chunk8_grad = total >= 20000 && (tiles > 256 || best < 38.0);
     } else {
-        const bool cheaper = best < 20.0 + 1.18e-4 * total;
-        p.chunk8 = total >= 380000 && cheaper;
-        p.chunk8_grad = (total >= 300000 && cheaper) || (total >= 30000 && c->T <= 12000 && c->T <= 1500LL * c->B);
+        const double scan = 20.0 + 1.18e-4 * total;
+        p.chunk8 = total >= 380000 && best < ((long long)c->B * p.fused_tiles <= 512 ? 1.3e-4 * total : scan);
+        p.chunk8_grad = (total >= 300000 && best < scan) || (total >= 30000 && c->T <= 12000 && c->T <= 1200LL * c->B);
     }
     if (!p.chunk8) return;
     p.fused = true;
@@ -445,12 +460,12 @@ Plan make_plan(const deer_config* c, bool chunks = true) {
         if (p.fused_tiles < 1) p.fused_tiles = 1;
     }
     if (gru && chunks) chunk8_plan(c, p);
-    const bool cell_chunk = two_part_cell(c->cell) && c->mlp_width == 1;
+    const bool cell_chunk = two_part_cell(c->cell) && c->mlp_width != kCellScan, gradient_only = cell_chunk && c->mlp_width == kCellChunkGradient;
     if (cell_chunk || (gru && chunks && env_int("DEER_FUSED", 1) != 0 && chunk_gru_supported(c->dtype, c->n, c->d) && chunk_pays(c))) {
         p.chunk = true;
-        p.fused = true;
+        p.fused = !gradient_only;
         p.fused_tiles = 0;
-        if (cell_chunk) p.tiles = 0;
+        if (cell_chunk && !gradient_only) p.tiles = 0;
         p.chunk_L = chunk_length(c, &p.chunk_per_unit);
         p.chunk_units = (int)((T + (size_t)p.chunk_per_unit * p.chunk_L - 1) / ((size_t)p.chunk_per_unit * p.chunk_L));
         p.chunk_groups = (int)((T + 16 * (size_t)p.chunk_L - 1) / (16 * (size_t)p.chunk_L));
@@ -466,7 +481,7 @@ Plan make_plan(const deer_config* c, bool chunks = true) {
     // knob settings) whose forward or backward pass runs the cell kernel followed by the plain scan.  With the
     // cell inside both scans the workspace is O(n T) instead of the O(n^2 T) of Sec. 3.5.
     p.need_J = ode || !p.fused || !p.grad_fused;
-    p.chunk_grad = p.chunk && p.grad_fused && (cell_chunk || c->n == 16);
+    p.chunk_grad = gradient_only || (p.chunk && p.grad_fused && (cell_chunk || c->n == 16));
 
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
@@ -486,7 +501,7 @@ Plan make_plan(const deer_config* c, bool chunks = true) {
     const size_t map = cell_chunk ? chunk_cells_map_bytes(c->reserved) : chunk_map_bytes(c->n);
     const size_t tot = p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * 16 * map : p.chunk ? B * ((T + p.chunk_L - 1) / p.chunk_L) * map : 0;
     const size_t sup = p.chunk8 || p.chunk8_grad ? (size_t)p.c8.map_groups * map : p.chunk && p.chunk_groups > 1 ? B * (size_t)p.chunk_units * map : 0;
-    p.shared = p.chunk || p.chunk8;
+    p.shared = (p.chunk && p.fused) || p.chunk8;
     if (p.shared) off = words0;
     else p.off_ctl = take(ctl_bytes());   // tickets, err bits, status
     p.off_tot = take(tot);

@@ -312,3 +312,32 @@ def test_recurrence_alone_between_steps_by_chunks(n, d, monkeypatch):
             assert all(torch.equal(p, q) for p, q in zip(ctx.grad(th, x, y0, y, g), grads))
     finally:
         ctx.close()
+
+
+# the routes that the dispatch takes by itself: plain n = 8 by chunks (from 380,000 positions), on the scan (up to 512 tiles there), in one launch, each with
+# the gradient by chunks; heads on the scan with their gradient by chunks (one tile a compute unit) and by chunks; the LEM of 8 units with the gradient alone by chunks
+@pytest.mark.parametrize("kind,n,d,B,T,H,K", [("gru", 8, 4, 40, 9501, 0, 0), ("gru", 7, 3, 21, 18103, 0, 0), ("gru", 8, 4, 16, 2049, 0, 0), ("heads", 8, 4, 2, 4001, 8, 1),
+                                              ("heads", 8, 8, 9, 903, 11, 3), ("lem", 8, 4, 40, 211, 0, 0), ("lem", 8, 4, 1, 2501, 0, 0)])
+def test_routes_of_the_dispatch(kind, n, d, B, T, H, K):
+    if kind == "heads":
+        w = inputs.mh_gru_workload("route_mh", 3400 + T, B=B, T=T, n=n, d=d, H=H, K=K)
+        solve = lambda m: oracle.mh_deer_eval(n, d, H, K, w.theta, w.x, w.y0, tol=w.tol, max_iter=m, nthreads=8)
+        seq, grad = lambda: oracle.mh_seq_eval(n, d, H, K, w.theta, w.x, w.y0, nthreads=8), lambda ys, g: oracle.mh_gru_grad(n, d, H, K, w.theta, w.x, w.y0, ys, g)
+    else:
+        w = (inputs.gru_workload("route", 3400 + T, B=B, T=T, n=n, d=d) if kind == "gru" else inputs.lem_workload("route", 3400 + T, B=B, T=T, units=n, d=d))
+        c = oracle_cell(w) if kind == "gru" else oracle.make_cell(oracle.CELL_LEM, 2 * n, d, dt=w.t1)
+        solve = lambda m: oracle.deer_eval(c, w.theta, w.x, w.y0, tol=w.tol, max_iter=m, nthreads=8)
+        seq = lambda: oracle.seq_eval(c, w.theta, w.x, w.y0, nthreads=8)
+        grad = lambda ys, g: (oracle.gru_grad(w.n, w.d, w.theta, w.x, w.y0, ys, g) if kind == "gru" else oracle.rnn_grad(c, w.theta, w.x, w.y0, ys, g))
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        ctx.set_profiling(True)
+        _against_oracle(ctx, w, solve, seq, grad)
+        p = ctx.profile()
+        # which kernels ran: a launch per iteration by chunks or on the multi-head scan, a whole solve in one launch, or Jacobian kernel and scan;
+        # where the gradient goes by chunks there is no launch of a vector-Jacobian product
+        one_launch = kind == "gru" and T == 2049
+        assert p["vjp_launches"] == 0 and (p["newton_launches"] > 0) == one_launch
+        assert (p["scan_launches"] > 0) == (kind == "lem" and T == 211) and (p["fused_launches"] > 1) == (not one_launch and not (kind == "lem" and T == 211))
+    finally:
+        ctx.close()
