@@ -49,22 +49,24 @@ def test_two_part_cells_by_chunks(cell, u, d, monkeypatch):
         monkeypatch.setenv("DEER_CHUNK_L", str(L))
         monkeypatch.setenv("DEER_CHUNK_UNIT", str((4, 8, 16)[k % 3]))
         make = inputs.lstm_workload if cell == oracle.CELL_LSTM else inputs.lem_workload
-        w = make("chunk_u%d_L%d_T%d" % (u, L, T), 1700 + 20 * u + k, B=B, T=T, units=u, d=d)
+        # (one input of the LEM is drawn with another seed: with the plain one the oracle's iterates reach 1e16 before they converge after 22 iterations,
+        # and how many it takes depends on every rounding)
+        far = cell == oracle.CELL_LEM and (u, d, T) == (9, 1, 1543)
+        w = make("chunk_u%d_L%d_T%d" % (u, L, T), 1700 + 20 * u + k + (1000 if far else 0), B=B, T=T, units=u, d=d)
         w.y0 = (np.random.default_rng(k).standard_normal((B, 2 * u)) * 0.5).astype(np.float32)
         print(cell, w.name, B, d, flush=True)
         c = oracle.make_cell(cell, 2 * u, d, **({} if cell == oracle.CELL_LSTM else {"dt": w.t1}))
         ctx = deer.context_for(w, device=DEV)
         try:
             th, x, y0 = dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0)
-            for max_iter in (w.max_iter, 2):
-                yo, ito, _, _ = oracle.deer_eval(c, w.theta, w.x, w.y0, tol=w.tol, max_iter=max_iter, nthreads=8)
-                y, it, _, _, st = ctx.eval(th, x, y0, tol=w.tol, max_iter=max_iter)
-                # (one of the inputs, LEM u = 9, d = 1, T = 1,543, is a Newton iteration far from its solution: the oracle's iterates
-                # reach 1e16 before they converge after 22 iterations, and how many it takes depends on every rounding -- 26 with
-                # stored Jacobians in fp32.  The count is compared where the iteration is not of that kind, an iterate
-                # relative to its own largest entry.)
-                assert st == deer.DEER_OK and (abs(it - ito) <= 1 or ito > 10), (w.name, it, ito)
-                assert np.abs(host(y) - yo).max() <= 1e-4 * max(1.0, np.abs(yo).max()), (w.name, max_iter, np.abs(host(y) - yo).max())
+            yo, ito, erro, _ = oracle.deer_eval(c, w.theta, w.x, w.y0, tol=w.tol, max_iter=w.max_iter, nthreads=8)
+            y, it, _, conv, st = ctx.eval(th, x, y0, tol=w.tol, max_iter=w.max_iter)
+            assert st == deer.DEER_OK and conv and erro <= w.tol and abs(it - ito) <= 1, (w.name, it, ito)
+            assert np.abs(host(y) - yo).max() <= 1e-4, (w.name, np.abs(host(y) - yo).max())
+            # an iterate far from the solution: every position against its own size
+            yo = oracle.deer_eval(c, w.theta, w.x, w.y0, tol=w.tol, max_iter=2, nthreads=8)[0]
+            off = np.abs(host(ctx.eval(th, x, y0, tol=w.tol, max_iter=2)[0]) - yo).max(axis=-1)
+            assert (off <= 1e-4 * np.maximum(1.0, np.abs(yo).max(axis=-1))).all(), (w.name, off.max())
             ys = oracle.seq_eval(c, w.theta, w.x, w.y0, nthreads=8)
             g = (np.random.default_rng(k + 1).standard_normal(ys.shape) / np.sqrt(T)).astype(np.float32).astype(np.float64)
             want = oracle.rnn_grad(c, w.theta, w.x, w.y0, ys, g)
