@@ -39,7 +39,8 @@
  *       i = sigmoid(W_i x + U_i h + b_i)   f = sigmoid(W_f x + U_f h + b_f)
  *       g = tanh(W_g x + U_g h + b_g)      o = sigmoid(W_o x + U_o h + b_o)
  *       c' = f * c + i * g                 h' = o * tanh(c')
- *     theta (flat): W[4u,d], U[4u,u], b[4u].  An iteration is a Jacobian kernel followed by the scan over the 2u x 2u
+ *     theta (flat): W[4u,d], U[4u,u], b[4u].  In fp32 with more than 4 units an iteration is a step by chunks (see
+ *     deer_eval; with 5 to 8 units from some 8,000 positions or 1,500 steps on); otherwise a Jacobian kernel followed by the scan over the 2u x 2u
  *     Jacobians (embedded in the next state size with a scan kernel).
  *   LEM cell (the cell of the paper's last experiment, which trains it with DEER; the paper prints no equations, the
  *   ones of the publication it cites are used; cell = DEER_CELL_LEM, n = number of units u, 1..16, d = 1..8, t1 = the
@@ -47,7 +48,8 @@
  *       s1 = dt * sigmoid(W_1 x + U_1 y + b_1)   s2 = dt * sigmoid(W_2 x + U_2 y + b_2)
  *       z' = (1 - s1) * z + s1 * tanh(W_z x + U_z y + b_z)
  *       y' = (1 - s2) * y + s2 * tanh(W_y x + U_y z' + b_y)
- *     theta (flat): W[4u,d], U[4u,u], b[4u], row blocks in the order 1 | 2 | z | y.  Kernels as for the LSTM.
+ *     theta (flat): W[4u,d], U[4u,u], b[4u], row blocks in the order 1 | 2 | z | y.  Kernels as for the LSTM (with 8 units
+ *     a small problem has its gradient alone by chunks).
  *   Multi-head GRU with strides (Sec. 4.4, App. B.4; heads > 1 or stride_levels > 1): the state is H heads of n
  *   channels, every head a GRU cell of its own on its own d input channels, and head h looks back
  *   s_h = 2^(h mod K) steps instead of one (the K stride levels are dealt out to the heads in turn):
@@ -126,8 +128,8 @@ size_t deer_theta_count(const deer_config* cfg);
 
 /* Bytes of device workspace deer_create() needs for cfg: a second trajectory buffer, the words the scan's
  * tiles publish for each other, counters, partial sums of dL/dtheta -- and, only where a kernel pair exchanges
- * them through memory (MLP_ODE; GRU in fp64 with n >= 16, with d beyond what the in-scan cell takes, or with the
- * DEER_FUSED / DEER_GRAD_FUSED knobs at 0), the Jacobian stream [B,T,n,n] and the right-hand side, the O(n^2 T)
+ * them through memory (MLP_ODE; GRU in fp64 with n >= 16, with d beyond what the in-scan cell or the chunks take, or with the
+ * DEER_FUSED / DEER_GRAD_FUSED knobs at 0; LSTM and LEM where they do not step by chunks), the Jacobian stream [B,T,n,n] and the right-hand side, the O(n^2 T)
  * memory of Sec. 3.5.  Where the cell is evaluated inside the scans the workspace is O(n T).  Where steps run by chunks
  * (see deer_eval) every chunk has a map of N^2 + N scalars (N = state size, for LSTM and LEM 2u rounded up to 16 or 32): one for every 4 to 64
  * positions, so short sequences in large numbers take up to (N + 1) / 4 trajectories of it, long ones a fraction of one.
@@ -161,7 +163,12 @@ deer_status deer_create(const deer_config* cfg, void* d_workspace, size_t worksp
  * chosen from the shapes: for the GRU with n <= 8 the cell is evaluated inside the scan kernel (the
  * Jacobians never reach memory), and when all tiles of the problem fit on the device at once the
  * whole solve is one kernel launch; for n = 16, 32 in fp32 the cell is evaluated inside the matrix-core
- * scan; otherwise an iteration is a Jacobian kernel followed by a scan kernel (see "Environment").
+ * scan.  In fp32 large problems of the GRU with n = 5..8 (plain and multi-head with n = 8) and n = 9..32, the GRU with n = 33..64 at every
+ * size (each with d up to 8 or 16), LSTM and LEM step by chunks instead: chunks of 4 to 64 positions are reduced to one affine map each, the
+ * maps are folded into carries and the chunks walked side by side, two launches an iteration.  Otherwise an iteration is a
+ * Jacobian kernel followed by a scan kernel (see "Environment").
+ * A solve whose Jacobians expand can overflow single precision before its iterates do: the product of the Jacobians over one tile of a scan or
+ * one chunk (up to 64 positions; 1,024 in the n <= 8 scan) has to be representable.
  * The Jacobians of the last iteration are not kept for deer_grad(): Sec. 3.1.1 offers that as a way to trade memory
  * for speed, this library always recomputes them at the trajectory it is given (exact for any trajectory, and the
  * O(n^2 T) buffer is not needed), so there is no save-the-Jacobian option in deer_config. */
@@ -185,9 +192,9 @@ deer_status deer_eval(deer_ctx* ctx, const void* d_theta, const void* d_x, const
  *   d_dLdy0    out [B,n], or NULL to skip
  * The parameter gradient is summed in a fixed order: two calls with the same inputs return the same bits.
  * For the GRU the transposed Jacobians are computed inside the reverse scan wherever deer_eval() evaluates the
- * cell inside the forward scan (n <= 8 with d <= 8; fp32 n = 16, 32 with d <= 16), and in fp32 with n = 16, 32
+ * cell inside the forward scan (n <= 8 with d <= 8; fp32 n = 16, 32 with d <= 16), and in fp32 with n = 16, 32, 64
  * the vector-Jacobian product runs on the matrix cores (so does the MLP field's for fp32, n = 8 and width 16,
- * 32 or 64); see "Environment" for the knobs that select the separate kernels instead. */
+ * 32 or 64).  By chunks the vector-Jacobian product is part of the reverse walk (n = 8, 16, multi-head, LSTM, LEM); see "Environment" for the knobs that select the separate kernels instead. */
 deer_status deer_grad(deer_ctx* ctx, const void* d_theta, const void* d_x, const void* d_y0,
                       const void* d_y, const void* d_dLdy, void* d_dLdx, void* d_dLdtheta,
                       void* d_dLdy0);
@@ -195,7 +202,7 @@ deer_status deer_grad(deer_ctx* ctx, const void* d_theta, const void* d_x, const
 /* The inverse linear operator alone (Sec. 3.3 eq. 9-10, Sec. 3.4 eq. 11):
  * y_i = A_i y_{i-1} + b_i for i = 1..T from y_0, for B independent sequences, by the blocked
  * associative scan.  Shapes come from the context (B, T, n, dtype).
- * (plain GRU-shaped contexts with n = 1, 2, 4, 8, 16 or 32 only).
+ * (plain GRU-shaped contexts with n = 1, 2, 4, 8, 16, 32 or, in fp32, 64 only).
  *   d_A [B,T,n,n]   d_b [B,T,n]   d_y0 [B,n] (NULL = zeros)   d_y out [B,T,n]
  *   reverse != 0 applies the dual (transposed, time-reversed) operator of Sec. 3.1.1 eq. 7 instead:
  *   y_T = b_T, y_i = b_i + A_{i+1}^T y_{i+1}; d_y0 is ignored.  A is read as stored and transposed
@@ -210,7 +217,7 @@ deer_status deer_linrec_solve(deer_ctx* ctx, const void* d_A, const void* d_b, c
  * and no context is needed.  The call allocates nothing (no hipMalloc/hipFree, no pinned host memory, no events),
  * enqueues three kernels on hip_stream (a fill that clears the part of the array it uses, the scan, a one-word
  * copy) and returns without synchronising: outputs are complete when the stream reaches that point.
- *   dtype, B, T, n   as in deer_config (n = 1, 2, 4, 8, 16 or 32)
+ *   dtype, B, T, n   as in deer_config (n = 1, 2, 4, 8, 16, 32 or, in fp32, 64)
  *   d_A [B,T,n,n]  d_b [B,T,n]  d_y0 [B,n] or NULL (zeros)  d_y out [B,T,n]  reverse: as in deer_linrec_solve()
  *   hip_stream     hipStream_t (NULL = the default stream)
  *   d_status       out, DEVICE int32, or NULL: 0, or non-zero if a tile waited too long for its predecessors
@@ -241,17 +248,20 @@ void deer_destroy(deer_ctx* ctx);
  *   DEER_FUSED=0        GRU, LSTM, LEM: run the cell kernel and the plain scan as two launches per iteration (needs the
  *                       Jacobian stream in the workspace) instead of the scan with the cell inside
  *   DEER_GRAD_FUSED=0   GRU deer_grad(): Jacobian kernel + plain reverse scan instead of the reverse scan with the
- *                       cell inside (needs the Jacobian stream in the workspace)
+ *                       cell inside (needs the Jacobian stream in the workspace); LSTM, LEM and the GRU with n = 5..8 then
+ *                       do not step by chunks in deer_eval() either
  *   DEER_ONE_LAUNCH=0   GRU, n <= 8: one launch per iteration even when the whole solve fits one launch
  *   DEER_FUSED_L, DEER_FUSED_W, DEER_SCAN_L
  *                       tile shapes of the n <= 8 kernels: positions per lane group (1, 2, 4, 8, 10, 12, 16; 24 for
- *                       the plain n = 4 scan) and wavefronts per tile (4 or 8); ignored when no such variant exists
+ *                       the plain n = 4 scan) and wavefronts per tile (4 or 8); ignored when no such variant exists.  DEER_FUSED_L also keeps the GRU with n = 5..8
+ *                       and the multi-head GRU off the chunks
  *   DEER_CHUNK_L, DEER_CHUNK_UNIT
  *                       GRU with n = 5..8, 16, 32, 64, multi-head GRU with n = 8, LSTM and LEM in fp32: positions per chunk of the step by chunks (a multiple of
  *                       four, at least four), which is then taken at every size (by default where it is faster), and
  *                       chunks per workgroup of its first launch (4, 8 or 16)
  *   DEER_BATCH          Newton iterations enqueued per host round trip on a fresh context (1..8, default 4)
- *   DEER_VJP_MFMA=0     vector-ALU kernels for the vector-Jacobian products instead of the matrix-core ones
+ *   DEER_VJP_MFMA=0     vector-ALU kernels for the vector-Jacobian products instead of the matrix-core ones; no effect where
+ *                       the product is part of the reverse walk by chunks (DEER_FUSED=0 or DEER_FUSED_L leave that route)
  *   DEER_MLP_MFMA=0     MLP fields outside the two-layer tanh shapes (fp32, n = 8, width 32 or 64): vector-ALU field
  *                       kernel instead of the matrix-core one
  * Test hooks (exercise paths that ordinary runs reach rarely; never set them in production):

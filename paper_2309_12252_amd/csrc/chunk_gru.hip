@@ -17,7 +17,7 @@
 // the reduction costs 32 x 32 + 72 x 4 cycles at n = 32 (4 x 32 + 20 x 4 at n = 16) beside its share of the gates; the tree over
 // wavefronts, the look-back and the second walk of the single-pass scan (a third of its tile's life at n = 32, with one to
 // four of eight wavefronts busy) are gone.  A Newton step, single-pass scan before / both launches now: n = 32, d = 8, 16 x 100,000
-// positions 2,650 / 1,400 us (1,090 + 300); n = 16, d = 6, 32 x 17,984 positions 240 / 130 us (88 + 42); the dual scan there 206 / 135.
+// positions 2,650 / 1,420 us (1,120 + 300); n = 16, d = 6, 32 x 17,984 positions 240 / 130 us (88 + 42); the dual scan there 206 / 135.
 //
 // Everything is in correction form: with e = y_new - y the recurrence of a Newton step is e_i = J_i e_{i-1} + (f_i - y_i),
 // e_0 = 0, so neither J h nor a right-hand side is needed and rounding is relative to the correction.
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
 // one more step takes the first position of a sequence.  The sums over positions have the columns on the contraction index:
 // cotangents, state and input cross a slice of LDS.  J^T lambda is added up without g (see the walk above), and a
 // position's sixteen columns by themselves before they join the sums (see chunk_cells.hip; chunks of 32 positions: 3.9e-7 -> 2.4e-7).  At n = 32 the sums (72 registers more) would leave one wavefront per SIMD.
-// Measured, d = 6, 32 x 17,984 positions: walk 43 us and a kernel of its own for the product 126 us; now 82 us in all.
+// Measured, d = 6, 32 x 17,984 positions: walk 43 us and a kernel of its own for the product 126 us; now 79 us in all.
 // ------------------------------------------------------------------------------------------------------------------
 template <int DS>
 __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {

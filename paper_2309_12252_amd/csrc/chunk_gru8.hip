@@ -1,4 +1,4 @@
-// Newton step and dual scan of the GRU with 4 or 8 channels in fp32 by chunks, plain (n = 8) and multi-head with strides: the reduction of
+// Newton step and gradient of the GRU with 8 channels in fp32 by chunks, plain (n = 8) and multi-head with strides: the reduction of
 // every chunk to one affine map, the fold of the maps and the walk of sixteen chunks side by side, as for the larger
 // states (chunk_gru.hip), with a matrix-core layout of its own (Sec. 3.1 eq. 3 and 5, Sec. 3.1.1 eq. 7, Sec. 4.4, App. B.4).
 //

@@ -378,7 +378,7 @@ void chunk_gru8_layout(Chunk8Params& p, int L);   // from B, T, H, levels: chunk
 hipError_t launch_chunk_gru8(const Chunk8Params& p, hipStream_t s);
 hipError_t launch_gru_funceval(int dtype, const GruParams& p, hipStream_t s);
 hipError_t launch_gru_vjp(int dtype, const GruVjpParams& p, hipStream_t s);
-// the same on the matrix cores (fp32, n = 16 or 32, d <= 16): kernel only, partial rows = blocks * 4
+// the same on the matrix cores (fp32, n = 16, 32 or 64, d <= 16): kernel and reduction of its partial rows (blocks * 4 of them at most) into dtheta
 bool gru_vjp_mfma_supported(int dtype, int n, int d);
 hipError_t launch_gru_vjp_mfma(const GruVjpParams& p, hipStream_t s);
 int gru_vjp_blocks(int n, long long steps);

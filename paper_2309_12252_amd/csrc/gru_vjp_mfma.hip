@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kThreads, N == 32 ? 2 : 1) void gru_vjp_mfma_kernel
 // positions and 16 rows of every gate each: gates, cotangents and sums of these rows need nothing from the other wavefronts but
 // the input gradient, whose four parts meet in LDS (one barrier a tile, double-buffered).  One partial row per workgroup.
 // Bound: fp32 matrix instructions, 132 of 32 cycles a wavefront and tile (25 us at 49,865 positions).  The vector-ALU kernel took 742 us
-// there (d = 7), this one 58 us.
+// there (d = 7), this one 66 us (58 with one chain of sums over all tiles and the biases and W columns in registers).
 __global__ __launch_bounds__(kThreads, 2) void gru_vjp_mfma64_kernel(GruVjpParams p) {
     constexpr int N = 64, NB = 4;
     __shared__ __align__(16) float sD[kWaves][5][16][kLD];    // dar, daz, dac, dq, z lam of the wavefront's rows

@@ -82,7 +82,7 @@ __host__ __device__ inline long long gen_theta_len(int n, int w, int L) { return
 //               z = f - J y is added up from the columns.
 // The derivative factors of all layers stay in registers (L * WB * 4); the weights are A operands read from
 // LDS (rows padded to W + 4 words: 16-byte reads, lanes of a row group on different banks).
-// Bound: fp32 matrix instructions, 8 (L - 1) W^2 / 512 of 32 cycles for 16 points: 0.31 ms at five layers of 64 and 160,000 points.
+// Bound: fp32 matrix instructions, 8 (L - 1) W^2 / 64 of 32 cycles for 16 points (0.27 ms) and those of the values and the outer layers: 0.31 ms at five layers of 64 and 160,000 points.
 // With two points x 8 entries as the columns the factors crossed the lanes (640 shuffles a block) and J y took a second chain: 0.547 ms
 // there, now 0.461 ms.
 typedef float gacc __attribute__((ext_vector_type(4)));
@@ -310,7 +310,7 @@ bool fe_mfma_supported(int dtype, int n, int width, int nhid) {
 // and block of rows), so the WB wavefronts of a team share sixteen points: wavefront w owns rows 16 w .. 16 w + 15 of every
 // hidden layer -- its rows of the activations, of the cotangents and of the sums (16 registers a layer) -- and the rows the others own come
 // through LDS, one barrier a layer each way.  Forward weights stay in registers, the transposed ones are read from LDS down
-// a column (row stride = 4 mod 64 words: no bank conflicts).  Two teams a workgroup; a partial row per team, the fixed-order reduction
+// a column (row stride W + 4 words: at width 64 the four rows of a lane group are on different banks).  Two teams a workgroup; a partial row per team, the fixed-order reduction
 // adds the rows.
 // Bound: fp32 matrix instructions, 3 (L - 1) W^2 / 64 of 32 cycles for 16 points (0.11 ms at five layers of 64 and 160,000 points).  A
 // workgroup per layer that ran the forward and the reverse pass for its own layer alone took 0.841 ms there; now 0.231 ms.
