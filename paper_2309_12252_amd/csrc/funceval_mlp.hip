@@ -137,7 +137,8 @@ __global__ __launch_bounds__(kThreads) void mlp_funceval_kernel(MlpParams p) {
 //   J   = W3 D2 W2 D1 W1, one column of the sixteen points' Jacobians at a time: the columns of the products stay
 //         the points, so D1 and D2 are already where they are needed;  z = f - J y from the columns
 // (two points x 8 columns in a product took a shuffle for every factor and a chain of its own for J y: width 32, 800,000 points
-// 234 us, now 211).
+// 234 us, now 211).  Width 16, where the Jacobians' way to memory weighs most, has four columns in work at a time and stores whole lines (pairs of
+// columns in pieces of 8 bytes: a solve of 550,000 points took 1,590 us, now 1,400; with two points x 8 columns 1,435).
 // Rows 8..15 of the W3 products are padding (n = 8).
 typedef float mlp_acc __attribute__((ext_vector_type(4)));
 
@@ -146,7 +147,7 @@ template <int WB, bool JONLY>   // hidden width / 16; JONLY: Jacobians only (z i
 // with part of the operands in accumulation registers, measured 8 % slower, five with spills 10 % slower)
 __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_kernel(MlpParams p) {
     if (gate_closed<float>(p.gate)) return;
-    constexpr int W = 16 * WB, N = 8;
+    constexpr int W = 16 * WB, N = 8, KC = WB == 1 ? 4 : 2;   // KC: columns of the Jacobians in work at a time
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4, c = lane & 15;
     const float* __restrict__ th = reinterpret_cast<const float*>(p.theta);
@@ -168,6 +169,7 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
     mlp_acc b3c;
     // W1 transposed: column k's factor of D1 W1 as 16-byte reads
     __shared__ __align__(16) float sW1[N][W];
+    __shared__ __align__(16) float sG[WB == 1 ? kThreads / 64 : 1][WB == 1 ? 16 * 68 : 4];
     for (int q = threadIdx.x; q < W * N; q += kThreads) sW1[q % N][q / N] = W1[q];
     __syncthreads();
 #pragma unroll
@@ -236,13 +238,15 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
 #pragma unroll
                 for (int v = 0; v < 4; ++v) f = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], a2[K][v], f, 0, 0, 0);
         }
-        // columns k, k + 1 of the Jacobians
-#pragma unroll 1
-        for (int k = 0; k < N; k += 2) {
-            const float2 yk = *reinterpret_cast<const float2*>(y + sc * N + k);
-            mlp_acc u1[2][WB], u2[2][WB], jb[2];
+        // columns k .. k + KC - 1; width 16 stores whole rows at the end, wider ones a pair of columns at a time (registers)
+        mlp_acc rows[WB == 1 ? N : 1];
+#pragma unroll WB == 1 ? 2 : 1
+        for (int k = 0; k < N; k += KC) {
+            float yk[KC];
+            vload<float, KC>(yk, y + sc * N + k);
+            mlp_acc u1[KC][WB], u2[KC][WB], jb[KC];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < KC; ++j) {
                 jb[j] = mlp_acc{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int K = 0; K < WB; ++K) {
@@ -257,9 +261,9 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
 #pragma unroll
                     for (int I = 0; I < WB; ++I)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j) u2[j][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], u1[j][K][v], u2[j][I], 0, 0, 0);
+                        for (int j = 0; j < KC; ++j) u2[j][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[I][K][v], u1[j][K][v], u2[j][I], 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < KC; ++j)
 #pragma unroll
                 for (int I = 0; I < WB; ++I) u2[j][I] *= d2[I];
 #pragma unroll
@@ -267,13 +271,40 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) jb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], u2[j][K][v], jb[j], 0, 0, 0);
-            if constexpr (!JONLY) f -= jb[0] * yk.x + jb[1] * yk.y;
-            if (g < 2 && s0 + c < total) {
+                    for (int j = 0; j < KC; ++j) jb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], u2[j][K][v], jb[j], 0, 0, 0);
+            if constexpr (!JONLY)
+#pragma unroll
+                for (int j = 0; j < KC; j += 2) f -= jb[j] * yk[j] + jb[j + 1] * yk[j + 1];
+            if constexpr (WB == 1) {
+#pragma unroll
+                for (int j = 0; j < KC; ++j) rows[WB == 1 ? k + j : 0] = jb[j];
+            } else if (g < 2 && s0 + c < total) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     *reinterpret_cast<float2*>(G + ((s0 + c) * N + 4 * g + v) * N + k) = float2{-jb[0][v], -jb[1][v]};
             }
+        }
+        if constexpr (WB == 1) {
+            // the sixteen matrices cross a slice of LDS and leave as whole lines
+            float* S = sG[threadIdx.x / 64];
+            if (g < 2) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float o[N];
+#pragma unroll
+                    for (int j = 0; j < N; ++j) o[j] = -rows[WB == 1 ? j : 0][v];
+                    vstore<float, N>(S + c * 68 + (4 * g + v) * N, o);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {   // lane q: a quarter of point 4 i + q / 16
+                const int pt = 4 * i + g;
+                if (s0 + pt < total) *reinterpret_cast<mlp_acc*>(G + (s0 + pt) * 64 + 4 * c) = *reinterpret_cast<const mlp_acc*>(S + pt * 68 + 4 * c);
+            }
+            __builtin_amdgcn_wave_barrier();
         }
         if (g < 2 && s0 + c < total) *reinterpret_cast<mlp_acc*>(z + (s0 + c) * N + 4 * g) = f;
     }

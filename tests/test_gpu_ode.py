@@ -151,3 +151,12 @@ def test_config5_grad_full_size():
     # over 800,000 grid points of a cotangent that went through a 100,000-step dual recurrence with matrices I + O(dt);
     # the bar for this case is 5e-4 absolute (1.5e-5 of the largest entry), dL/dy0 keeps 1e-4.
     check_grad(inputs.config(5), deer.DEER_F32, bar_theta=5e-4)
+
+
+@pytest.mark.parametrize("B,T", [(1, 3), (1, 16), (3, 11), (3, 30001)])
+def test_width_16_stores_whole_lines(B, T):
+    # sixteen points cross a slice of LDS: fewer points than that, exactly as many, a remainder, and more than one pass of a wavefront (65,536 points)
+    w = inputs.mlp_ode_workload("w16_T%d" % T, 610 + T, B=B, T=T, n=8, width=16, nhid=2, t0=0.0, t1=2.0, tol=1e-4)
+    check(w, deer.DEER_F32)
+    w.tol = 1e-7
+    check_grad(w, deer.DEER_F32, seed=B)
