@@ -28,6 +28,7 @@ enum { LSTM = 0, LEM = 1 };
 struct Factors {
     float n0, n1;   // new state, first and second part
     float a, b, c, d, e, f;
+    float g0, g1;   // what the linear terms leave of it: LSTM c' - f c; LEM y' - (1 - s2) y, z' - (1 - s1) z
 };
 
 template <int CELL, int UP, int DS>
@@ -95,6 +96,8 @@ struct Cell {
             for (int v = 0; v < 4; ++v) {
                 const float i = feed_sigmoid(a[0][v]), f = feed_sigmoid(a[1][v]), gg = feed_tanh(a[2][v]), oo = feed_sigmoid(a[3][v]);
                 const float cn = f * s1[v] + i * gg, tc = feed_tanh(cn);
+                o[v].g0 = 0.f;
+                o[v].g1 = i * gg;
                 o[v].n0 = oo * tc;
                 o[v].n1 = cn;
                 o[v].a = gg * i * (1.f - i);
@@ -114,6 +117,7 @@ struct Cell {
                 s2[v] = dt * feed_sigmoid(a[1][v]);
                 zn[v] = (1.f - t1) * s1[v] + t1 * gz;
                 o[v].n1 = zn[v];
+                o[v].g1 = t1 * gz;
                 o[v].a = t1 * (1.f - t1 * inv) * (gz - s1[v]);
                 o[v].b = t1 * (1.f - gz * gz);
                 o[v].f = 1.f - t1;
@@ -122,7 +126,8 @@ struct Cell {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const float gy = feed_tanh(a[3][v]);
-                o[v].n0 = (1.f - s2[v]) * s0[v] + s2[v] * gy;
+                o[v].g0 = s2[v] * gy;
+                o[v].n0 = (1.f - s2[v]) * s0[v] + o[v].g0;
                 o[v].c = s2[v] * (1.f - s2[v] * inv) * (gy - s0[v]);
                 o[v].d = s2[v] * (1.f - gy * gy);
                 o[v].e = 1.f - s2[v];
@@ -167,11 +172,11 @@ template <int CELL> struct Slice<CELL, 16> { static constexpr int kinds = 8; }; 
 template <> struct Slice<LSTM, 8> { static constexpr int kinds = 6; };            // factors of U_i, U_f, U_g, U_o, diagonal, vector; row of the state
 template <> struct Slice<LEM, 8> { static constexpr int kinds = 4; };             // two factors and the diagonal of the row's step, vector
 
-template <int CELL, int UP, int DS, bool VEC, bool REV>
+template <int CELL, int UP, int DS, bool VEC, bool REV, bool FAR>
 __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
     constexpr int N = 2 * UP, NB = N / 16, MS = map_size<N>(), KINDS = Slice<CELL, UP>::kinds;
     __shared__ __align__(16) float sF[4][KINDS * 256];
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
     const int T = p.T, d = p.d, Lc = p.Lc, n = p.cell_units, ld = 2 * n;
@@ -264,9 +269,38 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
                 Factors k[4];
                 cell.eval(k, s0, s1, x, dt, g);
                 Acc r0 = v0, r1 = v1;
-                if constexpr (!REV)
+                if constexpr (!REV) {
+                    if constexpr (FAR) {   // the cell minus J times its state
+                        // (one product after the other: registers)
+                        Acc q, j1;   // j1: second part of J times the state
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) { r0[v] = k[v].n0 - v0[v]; r1[v] = k[v].n1 - v1[v]; }
+                        for (int i = 0; i < 3; ++i) {
+                            if (CELL == LEM && i == 1) continue;
+                            const Acc t = cell.times(i, s0, zero4(), g);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) q[v] = i == 0 ? k[v].a * t[v] : q[v] + (CELL == LSTM && i == 2 ? k[v].c : k[v].b) * t[v];
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            j1[v] = k[v].f * s1[v] + q[v];
+                            r1[v] = k[v].g1 - q[v];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        const Acc t3 = cell.times(3, CELL == LSTM ? s0 : j1, zero4(), g);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) r0[v] = CELL == LSTM ? k[v].n0 - (k[v].d * t3[v] + k[v].e * j1[v]) : k[v].g0 - k[v].d * t3[v];
+                        if constexpr (CELL == LEM) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            const Acc t1 = cell.times(1, s0, zero4(), g);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) r0[v] -= k[v].c * t1[v];
+                        }
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) { r0[v] = k[v].n0 - v0[v]; r1[v] = k[v].n1 - v1[v]; }
+                    }
+                }
                 Acc o[KINDS];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -455,7 +489,7 @@ template <int CELL, int UP, int DS, bool VEC>
 __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
     constexpr int N = 2 * UP;
     __shared__ unsigned s_max[4];
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, p.far != 0)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int T = p.T, d = p.d, Lc = p.Lc, n = p.cell_units, ld = 2 * n;
     const float dt = p.dt;
@@ -501,11 +535,15 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
         }
         Cell<CELL, UP, DS> cell;
         cell.load(p.theta, n, d, g, r);
-        // correction of the state in front of the position
-        Acc e0, e1;
+        // correction of the state in front of the position, and the new state there
+        Acc e0, e1, x0, x1;
+        const bool far = p.far;
         {
             Acc e[N / 16];
-            fold_carries<N, false>(p, b, grp, nq, g, r, e);
+            fold_carries<N, false>(p, b, grp, nq, g, r, e, far, [&](int row) {
+                const int unit = row % UP;
+                return p.y0 && unit < n ? p.y0[(long long)b * ld + (row / UP) * n + unit] : 0.f;
+            });
             if constexpr (UP == 16) {
                 e0 = e[0];
                 e1 = e[N / 16 - 1];
@@ -516,6 +554,13 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
                 e0 = g < 2 ? e[0] : o;
                 e1 = g < 2 ? o : e[0];
             }
+        }
+
+        x0 = far ? e0 : y0r[R - 1] + e0;
+        x1 = far ? e1 : y1r[R - 1] + e1;
+        if (far) {
+            e0 = x0 - y0r[R - 1];
+            e1 = x1 - y1r[R - 1];
         }
 
         for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
@@ -532,21 +577,22 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
                     const Acc tg = cell.times(2, e0, zero4(), g), to = cell.times(3, e0, zero4(), g);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const float dc = k[v].f * e1[v] + (k[v].a * ti[v] + (k[v].b * tf[v] + k[v].c * tg[v]));
-                        n1[v] = k[v].n1 + dc;
-                        n0[v] = k[v].n0 + (k[v].d * to[v] + k[v].e * dc);
+                        const float q = k[v].a * ti[v] + (k[v].b * tf[v] + k[v].c * tg[v]);
+                        n1[v] = k[v].g1 + (k[v].f * x1[v] + q);
+                        n0[v] = k[v].n0 + (k[v].d * to[v] + k[v].e * (k[v].f * e1[v] + q));
                     }
                 } else {
                     const Acc t1 = cell.times(0, e0, zero4(), g), t2 = cell.times(1, e0, zero4(), g), tz = cell.times(2, e0, zero4(), g);
                     Acc dz;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        dz[v] = k[v].f * e1[v] + (k[v].a * t1[v] + k[v].b * tz[v]);
-                        n1[v] = k[v].n1 + dz[v];
+                        const float q = k[v].a * t1[v] + k[v].b * tz[v];
+                        dz[v] = k[v].f * e1[v] + q;
+                        n1[v] = k[v].g1 + (k[v].f * x1[v] + q);
                     }
                     const Acc ty = cell.times(3, dz, zero4(), g);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) n0[v] = k[v].n0 + (k[v].e * e0[v] + (k[v].c * t2[v] + k[v].d * ty[v]));
+                    for (int v = 0; v < 4; ++v) n0[v] = k[v].g0 + (k[v].e * x0[v] + (k[v].c * t2[v] + k[v].d * ty[v]));
                 }
                 if (live) {
                     float* o = ob + (long long)rel * ld;
@@ -556,6 +602,8 @@ __global__ __launch_bounds__(256, 2) void cell_walk_kernel(ChunkParams p) {
                 const unsigned mask = live ? 0x7fffffffu : 0u;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
+                    x0[v] = n0[v];
+                    x1[v] = n1[v];
                     e0[v] = n0[v] - y0r[j][v];
                     e1[v] = n1[v] - y1r[j][v];
                     emax = max(emax, max(__float_as_uint(e0[v]) & mask, __float_as_uint(e1[v]) & mask));
@@ -659,7 +707,7 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
         Acc e0, e1;   // lambda at the position the step evaluates
         {
             Acc e[N / 16];
-            fold_carries<N, true>(p, b, grp, nq, g, r, e);
+            fold_carries<N, true>(p, b, grp, nq, g, r, e, false, [](int) { return 0.f; });
             if constexpr (UP == 16) {
                 e0 = e[0];
                 e1 = e[N / 16 - 1];
@@ -839,8 +887,9 @@ __global__ __launch_bounds__(256, 2) void cell_dual_kernel(ChunkParams p) {
 template <int CELL, int UP, int DS, bool VEC>
 hipError_t launch_v(const ChunkParams& p, hipStream_t s) {
     const dim3 units((unsigned)((long long)p.B * p.units)), groups((unsigned)chunk_rows(p));
-    if (p.g) hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, true>), units, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, false>), units, dim3(256), 0, s, p);
+    if (p.g) hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, true, false>), units, dim3(256), 0, s, p);
+    else if (p.far) hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, false, true>), units, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((cell_totals_kernel<CELL, UP, DS, VEC, false, false>), units, dim3(256), 0, s, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.g) hipLaunchKernelGGL((cell_dual_kernel<CELL, UP, DS, VEC>), groups, dim3(256), 0, s, p);

@@ -52,7 +52,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 struct GruGates {
-    float f, pz, sr, st, z, sc;
+    float f, pz, sr, st, z, sc, c;
 };
 
 // gates of one row from the pre-activations ar, az, the candidate's input part ac and its hidden part q
@@ -63,6 +63,7 @@ __device__ __forceinline__ GruGates gru_gates(float ar, float az, float ac, floa
     const float c = feed_tanh(ac + rg * q);
     const float zc = 1.0f - o.z;
     const float dh = h - c;
+    o.c = c;
     o.f = c + o.z * dh;
     o.pz = dh * o.z * zc;
     o.sc = zc * (1.0f - c * c);
@@ -79,6 +80,22 @@ __device__ __forceinline__ void load_x(float* o, const float* __restrict__ xrow,
         const int k = DS * g + s;
         o[s] = xrow[k < d ? k : d - 1];
     }
+}
+
+// A Newton iterate can be huge where the next one is small again (the LEM passes through 1e27 and more on ordinary inputs): a correction
+// to it is then known to 1e-7 of its size only and the next iterate with it.  After a step of more than kFarStep (and from a caller's guess) the
+// maps and carries therefore stand for the iterate itself, as in the single-pass scan: the right-hand side is f - J h with the products that cancel
+// left out, and the recurrence starts from y0.  The caller says so (`far`); launches enqueued before such a step was known return at
+// once, and the caller enqueues them again.  (A branch inside the reduction instead of a kernel of its own cost 3 to 8 % of a solve.)
+__device__ __forceinline__ bool step_closed(const Gate& g, bool far) {
+    if (!g.prev_err) return false;
+    const float e = *reinterpret_cast<const float*>(g.prev_err);
+    return (double)e <= g.tol || (!far && !(e <= kFarStep));
+}
+
+// f - J h of one row; hr, hz, hc: U_gate h
+__device__ __forceinline__ float gru_rhs(const GruGates& k, float hr, float hz, float hc) {
+    return (k.c - k.z * k.c) - (k.pz * hz + (k.sr * hc + k.st * hr));
 }
 
 template <int N> constexpr int map_size() { return N * N + N; }
@@ -150,8 +167,9 @@ __device__ __forceinline__ void compose_unit(const float* __restrict__ tot, floa
 // The map of a unit spans up to 16 chunks and can overflow where the map of no chunk does (an iterate far from the solution whose
 // Jacobians expand); applied to a small or zero x it gives an infinity or a NaN that the chunks one by one would not give.  Such a value
 // stays in x to the end, so the carries tell: they are then folded again from the chunks' maps alone.
-template <int N, bool REV>
-__device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int grp, int nq, int g, int r, Acc (&e)[N / 16]) {
+// Of a far iterate x is the state itself and starts at start(row) = y0.
+template <int N, bool REV, typename Start>
+__device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int grp, int nq, int g, int r, Acc (&e)[N / 16], bool far, Start start) {
     constexpr int NB = N / 16, MS = map_size<N>(), PD = N == 16 ? 4 : 2;   // even
     Acc A[PD][NB][NB], V[PD][NB];
     Acc xk[NB];      // x[16K + 4g + v]
@@ -194,7 +212,7 @@ __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int gr
             e[K] = r == q ? c : e[K];
         }
     };
-    // in front of the sequence x is zero and M is not looked at (it may have overflowed)
+    bool zero = true;   // in front of the sequence x is zero (unless y0 is not) and M is not looked at (it may have overflowed)
     auto step = [&](int j, int i) {
         select(i, j & 1);
         if (j & 1) {
@@ -216,7 +234,7 @@ __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int gr
                 for (int K = 0; K < NB; ++K)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) q[v & 1] += A[j][I][K][v] * xk[K][v];
-                y[I] = V[j][I][0] + (i > 0 ? sum_groups(q[0] + q[1]) : 0.f);
+                y[I] = V[j][I][0] + (i > 0 || !zero ? sum_groups(q[0] + q[1]) : 0.f);
             }
 #pragma unroll
             for (int I = 0; I < NB; ++I) xr[I] = y[I];
@@ -227,6 +245,17 @@ __device__ __forceinline__ void fold_carries(const ChunkParams& p, int b, int gr
         for (int K = 0; K < NB; ++K) {
             xk[K] = e[K] = zero4();
             xr[K] = 0.f;
+        }
+        if (!REV && far) {
+            bool any = false;
+#pragma unroll
+            for (int K = 0; K < NB; ++K)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    xk[K][v] = start(16 * K + 4 * g + v);
+                    any |= xk[K][v] != 0.f;
+                }
+            zero = __ballot(any) == 0;
         }
         if (steps > 0) {
 #pragma unroll

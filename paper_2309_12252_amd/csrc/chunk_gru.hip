@@ -95,14 +95,14 @@ __device__ __forceinline__ void w_row(float* o, const Weights<N, DS>& w, int gat
 // the row factors to the lanes that assemble J instead of its transpose); the row factors reach the assembly through an
 // LDS slice of the wavefront.
 // ------------------------------------------------------------------------------------------------------------------
-template <int N, int DS, bool REV>
+template <int N, int DS, bool REV, bool FAR>
 __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(ChunkParams p) {
     constexpr int NB = N / 16, MS = map_size<N>();
     __shared__ __align__(16) Weights<N, DS> sW;
     // forward: [kind: p_z, s_r, s_t, z, residual][position][row]; dual: [position][row][p_z, s_r, s_t, z], then [position][row] of g
     __shared__ __align__(16) float sF[4][5 * 16 * N];
 
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
 
@@ -202,13 +202,32 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
                         ac = mfma(wc[s], xB[s], ac);
                     }
                     Acc fpz, fsr, fst, fz, fr;
+                    GruGates o[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const GruGates o = gru_gates(ar[v], az[v], ac[v], aq[v], hB[I][v]);
-                        fpz[v] = o.pz; fsr[v] = o.sr; fst[v] = o.st; fz[v] = o.z; fr[v] = o.f - oB[I][v];
+                        o[v] = gru_gates(ar[v], az[v], ac[v], aq[v], hB[I][v]);
+                        fpz[v] = o[v].pz; fsr[v] = o[v].sr; fst[v] = o[v].st; fz[v] = o[v].z;
                     }
-                    float* o = sFw + r * N + 16 * I + 4 * g;
-                    store4(o, fpz); store4(o + 16 * N, fsr); store4(o + 32 * N, fst); store4(o + 48 * N, fz); store4(o + 64 * N, fr);
+                    if constexpr (FAR) {
+                        Acc hr = zero4(), hz = zero4(), hc = zero4();
+#pragma unroll
+                        for (int K = 0; K < NB; ++K) {
+                            const Acc ur = u_row(sW, 0, 16 * I + r, K, g), uz = u_row(sW, 1, 16 * I + r, K, g), uc = u_row(sW, 2, 16 * I + r, K, g);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                hr = mfma(ur[v], hB[K][v], hr);
+                                hz = mfma(uz[v], hB[K][v], hz);
+                                hc = mfma(uc[v], hB[K][v], hc);
+                            }
+                        }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) fr[v] = gru_rhs(o[v], hr[v], hz[v], hc[v]);
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) fr[v] = o[v].f - oB[I][v];
+                    }
+                    float* q = sFw + r * N + 16 * I + 4 * g;
+                    store4(q, fpz); store4(q + 16 * N, fsr); store4(q + 32 * N, fst); store4(q + 48 * N, fz); store4(q + 64 * N, fr);
                 }
             } else {
                 // the state entries of the rows this lane evaluates (positions 4g + v, row 16 I + r) come through the slice too
@@ -353,7 +372,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
     constexpr int NB = N / 16;
     __shared__ unsigned s_max[4];
     __shared__ __align__(16) float sB[4 * N];
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, p.far != 0)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int T = p.T, d = p.d, Lc = p.Lc;
     const float* __restrict__ th = p.theta;
@@ -426,7 +445,15 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
             }
 
         Acc e[NB];   // forward: correction of the state in front of the position; dual: lambda at the time after it
-        fold_carries<N, REV>(p, b, grp, nq, g, r, e);
+        Acc x[REV ? 1 : NB];   // forward: the new state in front of the position
+        const bool far = !REV && p.far;
+        fold_carries<N, REV>(p, b, grp, nq, g, r, e, far, [&](int row) { return p.y0 ? p.y0[(long long)b * N + row] : 0.f; });
+        if constexpr (!REV)
+#pragma unroll
+            for (int K = 0; K < NB; ++K) {
+                x[K] = far ? e[K] : yr[R - 1][K] + e[K];
+                if (far) e[K] = x[K] - yr[R - 1][K];
+            }
 
         for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
 #pragma unroll
@@ -465,7 +492,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
                     for (int v = 0; v < 4; ++v) {
                         const GruGates k = gru_gates(ar[v], az[v], ac[v], aq[v], h[I][v]);
                         if constexpr (!REV) {
-                            y[I][v] = k.f + (k.z * e[I][v] + (k.pz * ez[v] + (k.sr * ec[v] + k.st * er[v])));
+                            y[I][v] = k.c + (k.z * (x[REV ? 0 : I][v] - k.c) + (k.pz * ez[v] + (k.sr * ec[v] + k.st * er[v])));
                         } else {
                             const float l = e[I][v];
                             lz[I][v] = k.pz * l;
@@ -504,6 +531,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         if constexpr (!REV) {
+                            x[REV ? 0 : I][v] = y[I][v];
                             e[I][v] = y[I][v] - yr[j][I][v];
                             emax = max(emax, __float_as_uint(e[I][v]) & mask);
                         } else {
@@ -598,7 +626,7 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) bs[q] = load4(bias + q * N + 4 * g);
         Acc ev[1];   // lambda at the position the step evaluates
-        fold_carries<N, true>(p, b, grp, nq, g, r, ev);
+        fold_carries<N, true>(p, b, grp, nq, g, r, ev, false, [](int) { return 0.f; });
         Acc e = ev[0];
 
         // one step at position `at` (relative) with state h in front of it: y = J^T lambda
@@ -717,7 +745,9 @@ __global__ __launch_bounds__(256, 2) void chunk_dual16_kernel(ChunkParams p) {
 
 template <int N, int DS, bool REV>
 hipError_t launch_nd(const ChunkParams& p, hipStream_t s) {
-    hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
+    const dim3 units((unsigned)((long long)p.B * p.units));
+    if (!REV && p.far) hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV, !REV>), units, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((chunk_totals_kernel<N, DS, REV, false>), units, dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int rows = (int)chunk_rows(p);

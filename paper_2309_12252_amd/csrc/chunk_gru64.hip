@@ -64,13 +64,13 @@ __device__ __forceinline__ void gates16(GruGates (&o)[4], const GateRows<DS>& k,
     for (int v = 0; v < 4; ++v) o[v] = gru_gates(ar[v], az[v], ac[v], aq[v], hw[v]);
 }
 
-template <int DS, bool REV>
+template <int DS, bool REV, bool FAR>
 __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     // row factors of this wavefront's 16 rows; forward [kind][position][row], dual [position][row][kind]
     __shared__ __align__(16) float sF[4][4 * 16 * 16];
     __shared__ __align__(16) float sR[16 * N];            // forward: residual, dual: cotangent, [position][row]
     __shared__ __align__(16) Acc sJ[2][NB * NB][64];      // factor in operand order, [block][lane]
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
     const int T = p.T, d = p.d, Lc = p.Lc, chunks = (T + Lc - 1) / Lc;
@@ -161,8 +161,24 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
             Acc rv = ow;
             if constexpr (!REV) {
                 Acc fpz, fsr, fst, fz;
+                if constexpr (FAR) {
+                    Acc hr = zero4(), hz = zero4(), hc = zero4();
 #pragma unroll
-                for (int v = 0; v < 4; ++v) { fpz[v] = k[v].pz; fsr[v] = k[v].sr; fst[v] = k[v].st; fz[v] = k[v].z; rv[v] = k[v].f - ow[v]; }
+                    for (int K = 0; K < NB; ++K)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            hr = mfma(gr.u[0][K][v], h[K][v], hr);
+                            hz = mfma(gr.u[1][K][v], h[K][v], hz);
+                            hc = mfma(gr.u[2][K][v], h[K][v], hc);
+                        }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) rv[v] = gru_rhs(k[v], hr[v], hz[v], hc[v]);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) rv[v] = k[v].f - ow[v];
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) { fpz[v] = k[v].pz; fsr[v] = k[v].sr; fst[v] = k[v].st; fz[v] = k[v].z; }
                 float* o = sFw + r * 16 + 4 * g;
                 store4(o, fpz); store4(o + 256, fsr); store4(o + 512, fst); store4(o + 768, fz);
             } else {
@@ -286,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     __shared__ __align__(16) Acc sX[2][KINDS][NB][64];   // [step parity][state, then correction or weighted cotangents][wavefront][lane]
     __shared__ __align__(16) float sx[2][N];
     __shared__ unsigned s_max[4];
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, p.far != 0)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), grp = (int)(blockIdx.x / (unsigned)p.B);
     const int T = p.T, d = p.d, Lc = p.Lc, chunks = (T + Lc - 1) / Lc, nq = min(16, chunks - 16 * grp);
@@ -340,8 +356,11 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     // ---- carries: x <- M x + v over the units in front, then over the group's own chunks; a row of M per lane, a quarter
     // of the rows per wavefront, x in LDS ----
     Acc e = zero4();
+    const bool far = !REV && p.far;
     {
         constexpr int PD = REV ? 2 : 4;
+        const float y0v = far && p.y0 ? p.y0[(long long)b * N + lane] : 0.f;
+        const bool zero = __ballot(y0v != 0.f) == 0;   // (the same for the four wavefronts)
         const int pu = 16 / p.per_unit;   // units of a group
         const float* __restrict__ own = p.tot + ((long long)b * chunks + 16 * grp) * MS;
         // the maps in front of the group: those of the units, and again those of the chunks if that overflowed (see fold_carries)
@@ -362,7 +381,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
 #pragma unroll
                 for (int j = 0; j < PD; ++j) request(j, j);
             }
-            if (tid < N) sx[0][tid] = 0.f;
+            if (tid < N) sx[0][tid] = y0v;
             __syncthreads();
             for (int i0 = 0; i0 <= steps; i0 += PD) {
 #pragma unroll
@@ -374,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                         e = (k >= 0 && r == qs) ? mine : e;
                         if (i < steps) {
                             float s = 0.f;
-                            if (i > 0) {   // in front of the sequence x is zero and M is not looked at (it may have overflowed)
+                            if (i > 0 || !zero) {   // in front of the sequence x is zero (unless y0 is not) and M is not looked at (it may have overflowed)
 #pragma unroll
                                 for (int K = 0; K < NB; ++K) {
                                     const Acc xk = load4(&sx[i & 1][16 * K + 4 * g]);
@@ -408,6 +427,11 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
         }
     }
 
+    Acc xv = zero4();   // forward: the new state in front of the position
+    if constexpr (!REV) {
+        xv = far ? e : yr[R - 1] + e;
+        if (far) e = xv - yr[R - 1];
+    }
     unsigned emax = 0u;   // largest |y_new - y| as raw bits (a NaN compares above everything)
     sX[0][0][wave][lane] = yr[REV ? 0 : R - 1];
     if constexpr (!REV) sX[0][1][wave][lane] = e;
@@ -438,10 +462,11 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                     }
                 }
 #pragma unroll
-                for (int v = 0; v < 4; ++v) y[v] = k[v].f + (k[v].z * e[v] + (k[v].pz * ez[v] + (k[v].sr * ec[v] + k[v].st * er[v])));
+                for (int v = 0; v < 4; ++v) y[v] = k[v].c + (k[v].z * (xv[v] - k[v].c) + (k[v].pz * ez[v] + (k[v].sr * ec[v] + k[v].st * er[v])));
                 const unsigned mask = live ? 0x7fffffffu : 0u;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
+                    xv[v] = y[v];
                     e[v] = y[v] - yr[j][v];
                     emax = max(emax, __float_as_uint(e[v]) & mask);
                 }
@@ -502,7 +527,9 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
 
 template <int DS, bool REV>
 hipError_t launch_ds(const ChunkParams& p, hipStream_t s) {
-    hipLaunchKernelGGL((chunk_totals64_kernel<DS, REV>), dim3((unsigned)((long long)p.B * p.units)), dim3(256), 0, s, p);
+    const dim3 units((unsigned)((long long)p.B * p.units));
+    if (!REV && p.far) hipLaunchKernelGGL((chunk_totals64_kernel<DS, REV, !REV>), units, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((chunk_totals64_kernel<DS, REV, false>), units, dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((chunk_walk64_kernel<DS, REV>), dim3((unsigned)((long long)p.B * p.groups)), dim3(256), 0, s, p);

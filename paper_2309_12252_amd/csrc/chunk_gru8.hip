@@ -116,11 +116,11 @@ __device__ __forceinline__ void load_rows(float (&o)[2], const float* __restrict
 // ------------------------------------------------------------------------------------------------------------------
 // Maps of the chunks (see chunk_totals_kernel of chunk_gru.hip for the two directions).
 // ------------------------------------------------------------------------------------------------------------------
-template <int DS, bool REV>
+template <int DS, bool REV, bool FAR>
 __global__ __launch_bounds__(256, 2) void chunk8_totals_kernel(Chunk8Params p) {
     // per wavefront: row factors [chunk][row][p_z, s_r, s_t, z] and vectors [chunk][row]; at the end the sixteen maps
     __shared__ __align__(16) float sF[4][16 * MS8];
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int id = (int)(blockIdx.x * 4u) + wave;
     if (id >= p.map_groups) return;
@@ -199,6 +199,16 @@ __global__ __launch_bounds__(256, 2) void chunk8_totals_kernel(Chunk8Params p) {
                 res[v] = live ? (REV ? gr[REV ? j : 0][v] : k[v].f - o[v]) : 0.f;
                 if constexpr (!REV) o[v] = yr[j][v];
             }
+            if constexpr (FAR) {
+                Acc hA = zero4(), hB = zero4();   // U h
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {
+                    hA = mfma(w.uA[v], yr[j][v], hA);
+                    hB = mfma(w.uB[v], yr[j][v], hB);
+                }
+#pragma unroll
+                for (int v = 0; v < 2; ++v) res[v] = live ? gru_rhs(k[v], hA[v], hA[2 + v], hB[v]) : 0.f;
+            }
             *reinterpret_cast<F2*>(V + r * 8 + 2 * g) = res;
             ask(j, t + R);
             wave_lds_fence();
@@ -274,7 +284,7 @@ __global__ __launch_bounds__(256, 2) void chunk8_totals_kernel(Chunk8Params p) {
 // x; each column keeps the x in front of its chunk.
 // ------------------------------------------------------------------------------------------------------------------
 template <bool REV>
-__device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, int id, int Cc, unsigned live, int g, int r, float (&e)[2]) {
+__device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, int id, int Cc, unsigned live, int g, int r, float (&e)[2], bool far) {
     constexpr int PD = 4;
     const int own = min(Cc, 16);
     int maps = c.gpr, before = REV ? c.gpr - 1 - c.gi : c.gi, steps = before + 15;
@@ -292,13 +302,22 @@ __device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, in
     };
     float x[2] = {0.f, 0.f};
     bool fresh = true;   // nothing in front: x is zero and M is not looked at (it may have overflowed)
+    // of a far iterate x starts at the y0 of the recurrence that column q belongs to
+    float start[2] = {0.f, 0.f};
+    if (!REV && far && p.y0) load_rows(start, p.y0 + ((long long)c.b * p.H + c.head) * N, g);
+    auto begin = [&](int q) {
+        x[0] = x[1] = 0.f;
+        fresh = true;
+        if (!REV && far) {
+            x[0] = __shfl(start[0], 16 * g + q);
+            x[1] = __shfl(start[1], 16 * g + q);
+            fresh = __ballot(x[0] != 0.f || x[1] != 0.f) == 0;
+        }
+    };
     auto keep = [&](int i) {
         const int k = i - before, q = REV ? 15 - k : k;
         if (k < 0) return;
-        if (k % own == 0 && (Cc < 16 || before == 0)) {
-            x[0] = x[1] = 0.f;
-            fresh = true;
-        }
+        if (k % own == 0 && (Cc < 16 || before == 0)) begin(q);
         e[0] = r == q ? x[0] : e[0];
         e[1] = r == q ? x[1] : e[1];
     };
@@ -316,6 +335,7 @@ __device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, in
         fresh = false;
     };
     for (int pass = 0;; ++pass) {
+        begin(0);
 #pragma unroll
         for (int j = 0; j < PD; ++j) request(j, j);
         int i = 0;
@@ -335,15 +355,14 @@ __device__ __forceinline__ void fold8(const Chunk8Params& p, const Column& c, in
         front = p.tot + (long long)(id - c.gi) * 16 * MS8;
         before *= 16;
         steps = before + 15;
-        x[0] = x[1] = e[0] = e[1] = 0.f;
-        fresh = true;
+        e[0] = e[1] = 0.f;
     }
 }
 
-template <int DS>
+template <int DS, bool FAR>
 __global__ __launch_bounds__(256, 3) void chunk8_walk_kernel(Chunk8Params p) {
     __shared__ unsigned s_max[4];
-    if (gate_closed<float>(p.gate)) return;
+    if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int id = (int)(blockIdx.x * 4u) + wave;   // (the number of groups is a multiple of four)
     unsigned emax = 0u;   // largest |y_new - y| as raw bits (a NaN compares above everything)
@@ -377,7 +396,14 @@ __global__ __launch_bounds__(256, 3) void chunk8_walk_kernel(Chunk8Params p) {
         Cell8<DS> w;
         load_cell(w, p.theta + (long long)c.head * p.P, d, g, r);
         float e[2] = {0.f, 0.f};   // correction of the state in front of the position
-        if (p.lv[c.level].C > 1) fold8<false>(p, c, id, p.lv[c.level].Cc, (unsigned)__ballot(c.lim > 0) & 0xffffu, g, r, e);
+        if (p.lv[c.level].C > 1) fold8<false>(p, c, id, p.lv[c.level].Cc, (unsigned)__ballot(c.lim > 0) & 0xffffu, g, r, e, FAR);
+        float xn[2] = {0.f, 0.f};   // of a far iterate: the new state in front of the position
+        if constexpr (FAR)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                xn[v] = p.lv[c.level].C > 1 ? e[v] : yr[R - 1][v];   // (a recurrence of one chunk: y0)
+                e[v] = xn[v] - yr[R - 1][v];
+            }
 
         for (int t0 = 0; t0 < Lc; t0 += R) {
 #pragma unroll
@@ -391,12 +417,15 @@ __global__ __launch_bounds__(256, 3) void chunk8_walk_kernel(Chunk8Params p) {
                 eB = mfma(w.uB[1], e[1], eB);
                 float y[2];
 #pragma unroll
-                for (int v = 0; v < 2; ++v)
-                    y[v] = k[v].f + (k[v].z * e[v] + (k[v].pz * eA[2 + v] + (k[v].sr * eB[v] + k[v].st * eA[v])));
+                for (int v = 0; v < 2; ++v) {
+                    if constexpr (FAR) y[v] = k[v].c + (k[v].z * (xn[v] - k[v].c) + (k[v].pz * eA[2 + v] + (k[v].sr * eB[v] + k[v].st * eA[v])));
+                    else y[v] = k[v].f + (k[v].z * e[v] + (k[v].pz * eA[2 + v] + (k[v].sr * eB[v] + k[v].st * eA[v])));
+                }
                 if (live) *reinterpret_cast<F2*>(ob + (unsigned)pos * sy + 2 * g) = F2{y[0], y[1]};
                 const unsigned mask = live ? 0x7fffffffu : 0u;
 #pragma unroll
                 for (int v = 0; v < 2; ++v) {
+                    if constexpr (FAR) xn[v] = y[v];
                     e[v] = y[v] - yr[j][v];
                     emax = max(emax, __float_as_uint(e[v]) & mask);
                 }
@@ -481,7 +510,7 @@ __global__ __launch_bounds__(256, 2) void chunk8_dual_kernel(Chunk8Params p) {
             }
         }
         float e[2] = {0.f, 0.f};   // lambda at the position the step evaluates
-        if (p.lv[c.level].C > 1) fold8<true>(p, c, id, p.lv[c.level].Cc, (unsigned)__ballot(c.lim > 0) & 0xffffu, g, r, e);
+        if (p.lv[c.level].C > 1) fold8<true>(p, c, id, p.lv[c.level].Cc, (unsigned)__ballot(c.lim > 0) & 0xffffu, g, r, e, false);
         if (DS == 1 && g == 0) store4(S + 512 + r * 16 + 12, zero4());   // (columns of x that no lane writes)
 
         // one step at position `at` = pos + 1 with state h in front of it; returns J^T lambda
@@ -626,12 +655,14 @@ template <int DS>
 hipError_t launch8(const Chunk8Params& p, hipStream_t s) {
     const dim3 maps((unsigned)((p.map_groups + 3) / 4)), all((unsigned)(p.groups / 4));
     if (p.g) {
-        if (p.map_groups > 0) hipLaunchKernelGGL((chunk8_totals_kernel<DS, true>), maps, dim3(256), 0, s, p);
+        if (p.map_groups > 0) hipLaunchKernelGGL((chunk8_totals_kernel<DS, true, false>), maps, dim3(256), 0, s, p);
         hipLaunchKernelGGL((chunk8_dual_kernel<DS>), all, dim3(256), 0, s, p);
         hipLaunchKernelGGL(chunk8_reduce_kernel, dim3((unsigned)((p.P + 15) / 16), (unsigned)p.H), dim3(256), 0, s, p);
     } else {
-        if (p.map_groups > 0) hipLaunchKernelGGL((chunk8_totals_kernel<DS, false>), maps, dim3(256), 0, s, p);
-        hipLaunchKernelGGL((chunk8_walk_kernel<DS>), all, dim3(256), 0, s, p);
+        if (p.map_groups > 0 && p.far) hipLaunchKernelGGL((chunk8_totals_kernel<DS, false, true>), maps, dim3(256), 0, s, p);
+        else if (p.map_groups > 0) hipLaunchKernelGGL((chunk8_totals_kernel<DS, false, false>), maps, dim3(256), 0, s, p);
+        if (p.far) hipLaunchKernelGGL((chunk8_walk_kernel<DS, true>), all, dim3(256), 0, s, p);
+        else hipLaunchKernelGGL((chunk8_walk_kernel<DS, false>), all, dim3(256), 0, s, p);
     }
     return hipGetLastError();
 }

@@ -559,6 +559,7 @@ struct deer_ctx {
     hipStream_t stream;
     char* ws;
     unsigned epoch;
+    bool far;               // deer_eval: the iterate in front of the next batch may be far from the solution
     bool words_dirty;       // the chunks' maps have been written over the published words
     void* h_err;            // pinned: kSlots * 8 bytes of error words, then the status word and a result word
     void* d_h_err;          // the same memory as the device sees it
@@ -690,12 +691,14 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
         q.g = reverse ? reinterpret_cast<const float*>(bv) : nullptr;
         q.out = reinterpret_cast<float*>(out);
         q.err = p.err; q.gate = gate;
+        q.far = !reverse && c->far;
         prof_begin(c, KIND_FUSED, iter);
         e = two_part_cell(g.cell) ? launch_chunk_cells(g.cell == DEER_CELL_LEM, q, c->stream) : launch_chunk_gru(g.n, q, c->stream);
     } else if (fused_theta && c->plan.chunk8) {
         Chunk8Params q = chunk8_params(c, fused_theta, fused_x, y0, yold);
         q.out = reinterpret_cast<float*>(out);
         q.err = p.err; q.gate = gate;
+        q.far = c->far;
         prof_begin(c, KIND_FUSED, iter);
         e = launch_chunk_gru8(q, c->stream);
     } else if (fused_theta && c->plan.mh) {
@@ -884,6 +887,7 @@ deer_status deer_create(const deer_config* cfg, void* d_workspace, size_t worksp
     c->ws = reinterpret_cast<char*>(d_workspace);
     c->epoch = 0;
     c->words_dirty = false;
+    c->far = false;
     c->h_err = nullptr;
     c->profiling = false;
     c->prof = deer_profile{};
@@ -1032,6 +1036,7 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
         int nb = max_iter - it;
         if (nb > want) nb = want;
         if (nb > kSlots - slot0) nb = kSlots - slot0;
+        c->far = it == 0 ? d_y_guess != nullptr : !(err <= (double)kFarStep);
         for (int j = 0; j < nb; ++j) {
             const int k = it + j, slot = slot0 + j;
             char* src = buf[k & 1];
@@ -1086,6 +1091,8 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
             ++it;
             if (!std::isfinite(err)) { nonfinite = true; break; }
             if (!(err > tol)) break;
+            // steps by chunks behind one that leads far away have returned at once: they are enqueued again
+            if (c->plan.fused && (c->plan.chunk || c->plan.chunk8) && !c->far && !(err <= (double)kFarStep)) break;
         }
         prof_collect(c, it);
         if (status != 0) break;
@@ -1376,6 +1383,7 @@ deer_status deer_linrec_solve_static(int32_t dtype, int32_t B, int32_t T, int32_
     c.stream = reinterpret_cast<hipStream_t>(hip_stream);
     c.ws = reinterpret_cast<char*>(scratch);
     c.words_dirty = false;
+    c.far = false;
     c.epoch = 1;   // the same tag in every call: everything published by the previous call is cleared below
     c.h_err = nullptr;
     c.d_h_err = nullptr;

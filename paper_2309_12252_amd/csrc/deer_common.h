@@ -90,6 +90,9 @@ __device__ __forceinline__ float feed_tanh(float a) {
 __device__ __forceinline__ double feed_sigmoid(double a) { return 1.0 / (1.0 + exp(-a)); }
 __device__ __forceinline__ double feed_tanh(double a) { return tanh(a); }
 
+// a step by chunks after a step larger than this works on the iterate itself instead of the correction
+constexpr float kFarStep = 1000.0f;
+
 // Newton step (g == nullptr) or dual scan (g: cotangent) of the GRU by chunks of Lc positions, sixteen chunks to a group
 struct ChunkParams {
     const float* theta; const float* x; const float* y0;   // y0 may be nullptr (zeros)
@@ -101,6 +104,7 @@ struct ChunkParams {
     float* tot; float* sup;    // maps of the chunks [B][ceil(T / Lc)][n*n + n] and, with more than one group, of the units [B][units][n*n + n]
     void* err;                 // max|y_new - y| (raw bits), or nullptr
     Gate gate;
+    int far;                   // Newton step: the iterate may be far from the solution (see step_closed)
     int B, T, d, Lc;
     int cell_units; float dt;  // LSTM and LEM: units of the cell (rows of 2 cell_units scalars), the LEM's step
     int groups;                // of sixteen chunks, per sequence: ceil(T / (16 Lc))
@@ -123,6 +127,7 @@ struct Chunk8Params {
     float* tot; float* sup;    // maps of the chunks [map_groups][16][72] and of the groups [map_groups][72]
     void* err;
     Gate gate;
+    int far;                   // as above
     long long P;               // parameters per head
     int B, T, d, H, levels;    // levels <= 8
     int groups, map_groups;    // groups in all, and of the levels whose recurrences have more than one chunk (these come first)

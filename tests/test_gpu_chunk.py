@@ -343,3 +343,36 @@ def test_routes_of_the_dispatch(kind, n, d, B, T, H, K):
         assert (p["scan_launches"] > 0) == (kind == "lem" and T == 211) and (p["fused_launches"] > 1) == (not one_launch and not (kind == "lem" and T == 211))
     finally:
         ctx.close()
+
+
+# Solves whose iterates pass through values of 1e16 to 1e37 before they converge (by the oracle): the next iterate comes from one that is larger by
+# 1e15 and more, which leaves nothing of a correction.  The count of such iterations depends on every rounding, the solution does not.
+@pytest.mark.parametrize("kind,n,scale,seed", [("lem", 9, 1.0, 1887), ("lstm", 8, 1.5, 5012), ("lstm", 16, 2.5, 5005), ("gru", 8, 1.5, 5012), ("gru", 8, 2.5, 5009), ("gru", 16, 2.5, 5012),
+                                               ("heads", 8, 1.5, 5012), ("heads", 8, 2.5, 5009)])
+@pytest.mark.parametrize("L", ["4", "32"])
+def test_iterates_far_from_the_solution(kind, n, scale, seed, L, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", L)
+    if kind == "heads":
+        w = inputs.mh_gru_workload("far", seed, B=6, T=1252, n=n, d=2, H=3, K=2)
+    elif kind == "lem":
+        w = inputs.lem_workload("far", seed, B=3, T=1543, units=n, d=1)
+        w.y0 = (np.random.default_rng(7).standard_normal((3, 2 * n)) * 0.5).astype(np.float32)
+    else:
+        w = (inputs.gru_workload("far", seed, B=6, T=1252, n=n, d=2) if kind == "gru" else inputs.lstm_workload("far", seed, B=6, T=1252, units=n, d=2))
+    w.theta = (w.theta * np.float32(scale)).astype(np.float32)
+    if kind == "heads":
+        _, ito, erro, hist = oracle.mh_deer_eval(n, 2, 3, 2, w.theta, w.x, w.y0, tol=1e-4, max_iter=100, nthreads=8)
+        ys = oracle.mh_seq_eval(n, 2, 3, 2, w.theta, w.x, w.y0, nthreads=8)
+    else:
+        c = oracle.make_cell({"gru": oracle.CELL_GRU, "lstm": oracle.CELL_LSTM, "lem": oracle.CELL_LEM}[kind], n if kind == "gru" else 2 * n, w.d, **({"dt": w.t1} if kind == "lem" else {}))
+        _, ito, erro, hist = oracle.deer_eval(c, w.theta, w.x, w.y0, tol=1e-4, max_iter=100, nthreads=8)
+        ys = oracle.seq_eval(c, w.theta, w.x, w.y0, nthreads=8)
+    assert erro <= 1e-4 and np.nanmax(hist) > 1e10
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        y, it, _, conv, st = ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=1e-4, max_iter=200)
+        print(kind, n, "%d iterations (oracle %d, largest step %.1e)" % (it, ito, np.nanmax(hist)), np.abs(host(y) - ys).max(), flush=True)
+        assert st == deer.DEER_OK and conv
+        assert np.abs(host(y) - ys).max() <= 1e-4   # (weights off by one in 2^24 change these solutions by 2e-6 at most)
+    finally:
+        ctx.close()
