@@ -278,9 +278,9 @@ double chunk8_estimate(const Chunk8Params& q) {
     return base + std::max(1.45 * L, 1.15 * work) + 8.0 * std::max(0.0, waves - 1.0);
 }
 
-// The single-pass scan takes 20 us + 0.118 us per 1,000 positions a step, and 0.13 to 0.145 us per 1,000 in at most two rounds of tiles (512); heads 28 to 34 us
+// The single-pass scan takes 20 us + 0.118 us per 1,000 positions a step, and 5 + 1.6 L us a round in at most two rounds of tiles (512) of L positions a lane group; heads 28 to 34 us
 // where every compute unit has one tile at most.
-// Microseconds a solve, scan / chunks: plain 281 / 304 at 12 x 32,000, 270 / 295 at 30 x 13,000, 276 / 266 at 64 x 6,000, 352 / 318 at 20 x 20,000, 502 / 466 at
+// Microseconds a solve, scan / chunks: plain 281 / 304 at 12 x 32,000, 270 / 295 at 30 x 13,000, 276 / 266 at 64 x 6,000, 379 / 339 at 59 x 6,835 (L = 16), 352 / 318 at 20 x 20,000, 502 / 466 at
 // 16 x 40,000, 1,045 / 848 at 16 x 100,000, but 494 / 536 at 4 x 100,000, where the fold is long; 123 / 207 at 16 x 10,000.  Heads (steps x heads): one
 // tile a compute unit 139 / 143 at 4 x 2,000 x 8, 148 / 180 at 1 x 8,000 x 8, 171 / 215 at 1 x 16,000 x 4, beyond that 199 / 172 at 10 x 800 x 8, 219 / 179 at
 // 8 x 2,000 x 8, 239 / 237 at 2 x 20,000 x 2 (estimate 48 us), 331 / 260 at 1 x 30,000 x 4, 334 / 306 at 1 x 50,000 x 2 (392 tiles), 3,898 / 1,112 at 2.1 million positions,
@@ -311,7 +311,8 @@ void chunk8_plan(const deer_config* c, Plan& p) {
         p.chunk8_grad = total >= 20000 && (tiles > 256 || best < 38.0);
     } else {
         const double scan = 20.0 + 1.18e-4 * total;
-        p.chunk8 = total >= 380000 && best < ((long long)c->B * p.fused_tiles <= 512 ? 1.3e-4 * total : scan);
+        const long long tiles = (long long)c->B * p.fused_tiles;
+        p.chunk8 = total >= 380000 && best < (tiles <= 512 ? (double)((tiles + 255) / 256) * (5.0 + 1.6 * p.fused_L) + 4.0 : scan);
         p.chunk8_grad = (total >= 300000 && best < scan) || (total >= 30000 && c->T <= 12000 && c->T <= 1200LL * c->B);
     }
     if (!p.chunk8) return;
