@@ -238,9 +238,9 @@ int chunk_length(const deer_config* c, int* per_unit) {
             const long long per_seq = ((long long)c->T + 16LL * L - 1) / (16LL * L), groups = per_seq * c->B;
             const long long units = ((long long)c->T + (long long)pu * L - 1) / ((long long)pu * L);
             // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes 1.3 times as long as half of two, which is not seen any
-            // more from seven on: n = 32, 16 x 100,000, 10,030 us a solve with units of 16 x 56 positions and 10,330 with twice as many of 8 x 56)
+            // more from seven long ones on: n = 32, 16 x 100,000, 10,030 us a solve with units of 16 x 56 positions and 10,330 with twice as many of 8 x 56)
             const long long share = (units * c->B + 255) / 256;
-            const double est = ((double)share + (!cell && c->n >= 32 && share < 6 && (share & 1) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
+            const double est = ((double)share + (!cell && c->n >= 32 && (share & 1) && (share < 6 || pu < 16) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
                                (double)((groups + k.side_by_side - 1) / k.side_by_side) * k.walk * L + k.fold * (double)units;
             if (est < best) { best = est; best_L = L; *per_unit = pu; }
         }
