@@ -22,7 +22,9 @@
 // (row length = 4 mod 32 words, so that the 16-byte reads of consecutive points fall on different banks).
 // The weights are read from memory as they are (rows by 16-byte loads, the same address in all lanes of a
 // point group); the reverse sweep reads them down a column.
-#include "deer_common.h"
+#include "split_f16.h"
+
+#include <algorithm>
 
 namespace deer {
 
@@ -80,11 +82,15 @@ __host__ __device__ inline long long gen_theta_len(int n, int w, int L) { return
 //               W_out U_L.  The columns stay the points, so the derivative factors D_l of a lane's rows and point are
 //               already in its registers; two columns k share every weight read and are independent chains.
 //               z = f - J y is added up from the columns.
-// The derivative factors of all layers stay in registers (L * WB * 4); the weights are A operands read from
-// LDS (rows padded to W + 4 words: 16-byte reads, lanes of a row group on different banks).
-// Bound: fp32 matrix instructions, 8 (L - 1) W^2 / 64 of 32 cycles for 16 points (0.27 ms) and those of the values and the outer layers: 0.31 ms at five layers of 64 and 160,000 points.
-// With two points x 8 entries as the columns the factors crossed the lanes (640 shuffles a block) and J y took a second chain: 0.547 ms
-// there, now 0.461 ms.
+// The derivative factors of all layers stay in registers (L * WB * 4).  Layer 1 and f run on the fp32 matrix instructions, the hidden layers
+// on the fp16 ones with every factor split in two (split_f16.h), the weights once per workgroup.
+// Scales (powers of two): the weights of a layer by their largest entry; the activations of a point by their largest one (tanh: fixed); the
+// columns of the Jacobians by the weights' largest row sums, so that none can overflow, and once more by their own largest entry after the
+// third layer of four or five.
+// Bound: issue, matrix and vector instructions in turn: a layer of the Jacobians at width 64 takes 8 x 24 matrix instructions of 18 cycles and 8
+// x 48 vector instructions of 2.4 for 16 points.  At five layers of 64 and 160,000 points 464 us with fp32 instructions of 32 cycles, 203 us
+// now.  Errors there against 64 bits (mean of 30 solves, 5,000 points to a sequence): trajectory 2.74e-8 to 2.84e-8, dL/dtheta 9.1e-7 to
+// 8.9e-7, dL/dy0 1.21e-6 to 1.22e-6.
 typedef float gacc __attribute__((ext_vector_type(4)));
 
 // softplus and its derivative (the logistic function) from one exp2, one log2 and one reciprocal of the hardware:
@@ -101,30 +107,112 @@ __device__ __forceinline__ void fast_act(int kind, float pre, float& a, float& d
     }
 }
 
+// LDS: W_1 and the biases as they are, the others as parts of operand A (hidden layers: [layer][rows / 16][columns / 32][hi, lo,
+// rest], W_out: [columns / 32] with its hi part as rows 0..7 and its lo part as rows 8..15), 64 lanes x 8 entries each.  The rest of a weight
+// (0 or its last bit) is for the values only: what the split leaves out would be the same error of the field at every point.
 template <int WB, int L>
-__global__ __launch_bounds__(kThreads) void mlp_gen_funceval_mfma_kernel(MlpParams p) {
+struct FieldLds {
+    static constexpr int W = 16 * WB, KS = WB / 2, W1S = W + 4;
+    Half8 hidden[L > 1 ? L - 1 : 1][WB][KS][3][64];
+    Half8 out[KS][64];
+    float w1[8][W1S];     // W_1 transposed
+    float bias[L][W], bias_out[16];
+    unsigned top[L + 1];  // largest entry of W_1, W_2 .. W_L, W_out (raw bits)
+    unsigned row[L];      // largest sum of a row's magnitudes of W_2 .. W_L (raw bits; entry 0 unused)
+};
+
+constexpr int kFieldThreads = 512;
+
+template <int WB, int L>
+__global__ __launch_bounds__(kFieldThreads, 2) void mlp_gen_funceval_mfma_kernel(MlpParams p) {
     if (gate_closed<float>(p.gate)) return;
-    constexpr int W = 16 * WB, N = 8, WS = W + 4, W1S = W + 4;
+    constexpr int W = 16 * WB, N = 8, KS = WB / 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    float* sW1 = reinterpret_cast<float*>(smem_raw);   // [8][W1S]: W_1 transposed
-    float* sWh = sW1 + N * W1S;                        // [L - 1][W][WS]
-    float* sWo = sWh + (L - 1) * W * WS;               // [16][WS]: W_out, rows 8..15 zero
-    float* sb = sWo + 16 * WS;                         // [L][W] hidden biases, then [16] output bias (entries 8..15 zero)
-    const int tid = threadIdx.x, lane = tid & 63;
+    FieldLds<WB, L>& lds = *reinterpret_cast<FieldLds<WB, L>*>(smem_raw);
+    const int tid = threadIdx.x, lane = tid & 63, NT = blockDim.x;   // 256 or 512
     const int g = lane >> 4, c = lane & 15;
     const float* __restrict__ th = reinterpret_cast<const float*>(p.theta);
     const int kind = p.act;
-    for (int q = tid; q < W * N; q += kThreads) sW1[(q % N) * W1S + q / N] = th[q];
-    for (int q = tid; q < W; q += kThreads) sb[q] = th[W * N + q];
+
+    // ---- weights: scales first, then the parts ----
+    if (tid <= L) lds.top[tid] = 0u;
+    if (tid < L) lds.row[tid] = 0u;
+    __syncthreads();
+    auto raise = [&](unsigned* to, float m) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+        if (lane == 0) atomicMax(to, __float_as_uint(m));
+    };
+    {
+        float m = 0.f;
+        for (int q = tid; q < W * N; q += NT) {
+            const float t = th[q];
+            lds.w1[q % N][q / N] = t;
+            m = fmaxf(m, fabsf(t));
+        }
+        raise(&lds.top[0], m);
+        for (int q = tid; q < W; q += NT) lds.bias[0][q] = th[W * N + q];
+        const float* src = th + layer_offset(N, W, L);
+        m = 0.f;
+        for (int q = tid; q < N * W; q += NT) m = fmaxf(m, fabsf(src[q]));
+        raise(&lds.top[L], m);
+        if (tid < 16) lds.bias_out[tid] = (tid < N) ? src[N * W + tid] : 0.0f;
+    }
+#pragma unroll
     for (int l = 1; l < L; ++l) {
         const float* src = th + layer_offset(N, W, l);
-        for (int q = tid; q < W * W; q += kThreads) sWh[((l - 1) * W + q / W) * WS + (q % W)] = src[q];
-        for (int q = tid; q < W; q += kThreads) sb[l * W + q] = src[W * W + q];
+        float m = 0.f, rows = 0.f;
+        for (int q = tid; q < W * W; q += NT) {   // W consecutive threads read a row
+            const float t = fabsf(src[q]);
+            m = fmaxf(m, t);
+            float s = t;
+#pragma unroll
+            for (int o = W / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+            rows = fmaxf(rows, s);
+        }
+        raise(&lds.top[l], m);
+        raise(&lds.row[l], rows);
+        for (int q = tid; q < W; q += NT) lds.bias[l][q] = src[W * W + q];
+    }
+    __syncthreads();
+    // operand A is W 2^ea with entries below 2^8
+    int ea[L + 1];
+#pragma unroll
+    for (int l = 1; l <= L; ++l) ea[l] = min(8 - exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.top[l]))), 100);
+#pragma unroll
+    for (int l = 1; l < L; ++l) {
+        const float* src = th + layer_offset(N, W, l);
+        for (int q = tid; q < W * W / 2; q += NT) {
+            const int row = q / (W / 2), col = 2 * (q % (W / 2)), k = col % 32;
+            const float a = ldexpf(src[2 * q], ea[l]), b = ldexpf(src[2 * q + 1], ea[l]);
+            const unsigned hi = split_hi(a, b), lo = split_lo(a, b, hi), at = split_place(k) / 2;
+            Half8(&to)[3][64] = lds.hidden[l - 1][row / 16][col / 32];
+            reinterpret_cast<unsigned*>(&to[0][split_lane(row, k)])[at] = hi;
+            reinterpret_cast<unsigned*>(&to[1][split_lane(row, k)])[at] = lo;
+            reinterpret_cast<unsigned*>(&to[2][split_lane(row, k)])[at] = split_rest(a, b, hi, lo);
+        }
     }
     {
         const float* src = th + layer_offset(N, W, L);
-        for (int q = tid; q < 16 * W; q += kThreads) sWo[(q / W) * WS + (q % W)] = (q / W < N) ? src[q] : 0.0f;
-        if (tid < 16) sb[L * W + tid] = (tid < N) ? src[N * W + tid] : 0.0f;
+        for (int q = tid; q < N * W / 2; q += NT) {
+            const int row = q / (W / 2), col = 2 * (q % (W / 2)), k = col % 32;
+            const float a = ldexpf(src[2 * q], ea[L]), b = ldexpf(src[2 * q + 1], ea[L]);
+            const unsigned hi = split_hi(a, b), at = split_place(k) / 2;
+            reinterpret_cast<unsigned*>(&lds.out[col / 32][split_lane(row, k)])[at] = hi;
+            reinterpret_cast<unsigned*>(&lds.out[col / 32][split_lane(row + 8, k)])[at] = split_lo(a, b, hi);
+        }
+    }
+    // Scales of the Jacobians' columns: U_1 starts below 2^13, a hidden layer multiplies by at most its largest row sum 2^er (the
+    // derivatives are at most 1) and the factor 2^-(ea + er) that goes with D_l keeps it there.
+    const int e1 = min(13 - exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.top[0]))), 100);
+    float s_d[L];
+    int e_out = e1 + ea[L];   // J carries 2^e_out
+    s_d[0] = ldexpf(1.0f, e1);
+#pragma unroll
+    for (int l = 1; l < L; ++l) {
+        const int er = exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.row[l])));
+        s_d[l] = ldexpf(1.0f, -ea[l] - er);
+        e_out -= er;
     }
     __syncthreads();
 
@@ -147,130 +235,177 @@ __global__ __launch_bounds__(kThreads) void mlp_gen_funceval_mfma_kernel(MlpPara
         // layer 1
 #pragma unroll
         for (int I = 0; I < WB; ++I) {
-            gacc acc;
+            gacc acc = *reinterpret_cast<const gacc*>(&lds.bias[0][16 * I + 4 * g]);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = sb[16 * I + 4 * g + v];
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sW1[(4 * kk + g) * W1S + 16 * I + c], yb[kk], acc, 0, 0, 0);
+            for (int kk = 0; kk < 2; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(lds.w1[4 * kk + g][16 * I + c], yb[kk], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 float av, dv;
                 fast_act(kind, acc[v], av, dv);
                 a[I][v] = av;
-                d[0][I][v] = dv;
+                d[0][I][v] = dv * s_d[0];
             }
         }
         // hidden layers 2..L
 #pragma unroll
         for (int l = 1; l < L; ++l) {
+            // the activations of a point, scaled: tanh by 2^12, softplus to a largest one of 2^12 to 2^13
+            int ev = 12;
+            if (kind != 0) {
+                float m = 0.f;
+#pragma unroll
+                for (int I = 0; I < WB; ++I) m = fmaxf(fmaxf(fmaxf(a[I][0], a[I][1]), fmaxf(a[I][2], a[I][3])), m);
+                ev = min(13 - exponent(max_groups(m)), 100);
+            }
+            const float s = __builtin_amdgcn_ldexpf(1.0f, ev), up = __builtin_amdgcn_ldexpf(1.0f, ev + ea[l]);
+            const float down = __builtin_amdgcn_ldexpf(1.0f, -ev - ea[l]);
+            Split8 as[KS];
+#pragma unroll
+            for (int k = 0; k < KS; ++k) as[k] = split8(a[2 * k] * s, a[2 * k + 1] * s);
             gacc an[WB];
 #pragma unroll
             for (int I = 0; I < WB; ++I) {
+                // (the bias first: added last it was a third of the error that the layer adds)
+                gacc big = *reinterpret_cast<const gacc*>(&lds.bias[l][16 * I + 4 * g]) * up, small = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int v = 0; v < 4; ++v) an[I][v] = sb[l * W + 16 * I + 4 * g + v];
-#pragma unroll
-                for (int K = 0; K < WB; ++K) {
-                    float wa[4];
-                    vload<float, 4>(wa, &sWh[((l - 1) * W + 16 * I + c) * WS + 16 * K + 4 * g]);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) an[I] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], an[I], 0, 0, 0);
+                for (int k = 0; k < KS; ++k) {
+                    const Half8(&w)[3][64] = lds.hidden[l - 1][I][k];
+                    const Half8 hi = w[0][lane];
+                    big = mfma16(hi, as[k].hi, big);
+                    small = mfma16(w[2][lane], as[k].hi, small);
+                    small = mfma16(hi, as[k].lo, small);
+                    small = mfma16(w[1][lane], as[k].hi, small);
                 }
+                an[I] = big + small;
             }
 #pragma unroll
-            for (int I = 0; I < WB; ++I)
+            for (int I = 0; I < WB; ++I) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     float av, dv;
-                    fast_act(kind, an[I][v], av, dv);
+                    fast_act(kind, an[I][v] * down, av, dv);
                     a[I][v] = av;
-                    d[l][I][v] = dv;
+                    d[l][I][v] = dv * s_d[l];
                 }
+            }
         }
-        // output layer: f at point s0 + c, rows 4g + v < 8; J y is taken off column by column
+        // output layer: f at point s0 + c, rows 4 (g mod 2) + v.  Lane groups 0 and 1 start from f, 2 and 3 from zero; J y is taken off column
+        // by column, even columns in the former, odd ones in the latter.
         gacc f = {0.f, 0.f, 0.f, 0.f};
         if (!p.jac_only) {
+            // (fp32: nothing after it takes its rounding in; rows 8..15 repeat rows 0..7)
+            const float* __restrict__ wo = th + layer_offset(N, W, L) + (c & 7) * W + 4 * g;
+            f = *reinterpret_cast<const gacc*>(&lds.bias_out[4 * (g & 1)]);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) f[v] = sb[L * W + 4 * g + v];
+            for (int K = 0; K < WB; ++K)
 #pragma unroll
-            for (int K = 0; K < WB; ++K) {
-                float wa[4];
-                vload<float, 4>(wa, &sWo[c * WS + 16 * K + 4 * g]);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) f = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], a[K][v], f, 0, 0, 0);
-            }
+                for (int v = 0; v < 4; ++v) f = __builtin_amdgcn_mfma_f32_16x16x4f32(wo[16 * K + v], a[K][v], f, 0, 0, 0);
+            if (g >= 2) f = gacc{0.f, 0.f, 0.f, 0.f};
         }
         // columns k, k + 1 of the Jacobians
 #pragma unroll 1
         for (int k = 0; k < N; k += 2) {
             // (an offset the compiler cannot see through: the weight reads of a round stay in the round instead of being
             // hoisted into hundreds of registers in front of the loop)
-            int zoff = 0;
-            asm volatile("" : "+v"(zoff));
-            const float2 yk = *reinterpret_cast<const float2*>(y + sc * N + k);
+            int at = lane;
+            asm volatile("" : "+v"(at));
+            const float yk = y[sc * N + k + (g >> 1)];
             gacc u[2][WB];
+            int eu[2] = {0, 0};
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int K = 0; K < WB; ++K) {
-                    float w1[4];
-                    vload<float, 4>(w1, &sW1[(k + j) * W1S + 16 * K + 4 * g + zoff]);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) u[j][K][v] = d[0][K][v] * w1[v];
+                    const gacc w1 = *reinterpret_cast<const gacc*>(&lds.w1[k + j][16 * K + 4 * g]);
+                    u[j][K] = d[0][K] * w1;
                 }
 #pragma unroll
             for (int l = 1; l < L; ++l) {
-                gacc un[2][WB];
-#pragma unroll
-                for (int I = 0; I < WB; ++I) {
-                    un[0][I] = un[1][I] = gacc{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int K = 0; K < WB; ++K) {
-                        float wa[4];
-                        vload<float, 4>(wa, &sWh[((l - 1) * W + 16 * I + c) * WS + 16 * K + 4 * g + zoff]);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-#pragma unroll
-                            for (int j = 0; j < 2; ++j) un[j][I] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], u[j][K][v], un[j][I], 0, 0, 0);
-                    }
-                }
+                Split8 us[2][KS];
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int I = 0; I < WB; ++I)
+                    for (int q = 0; q < KS; ++q) us[j][q] = split8(u[j][2 * q], u[j][2 * q + 1]);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) u[j][I][v] = d[l][I][v] * un[j][I][v];
+                for (int I = 0; I < WB; ++I) {
+                    gacc un[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                    Half8 w[KS];
+#pragma unroll
+                    for (int q = 0; q < KS; ++q) {
+                        const Half8 wl = lds.hidden[l - 1][I][q][1][at];
+                        w[q] = lds.hidden[l - 1][I][q][0][at];
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) un[j] = mfma16(wl, us[j][q].hi, un[j]);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) un[j] = mfma16(w[q], us[j][q].lo, un[j]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < KS; ++q)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) un[j] = mfma16(w[q], us[j][q].hi, un[j]);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) u[j][I] = d[l][I] * un[j];
+                }
+                // (the scale above is that of the worst case; typical columns lose four powers of two a layer against it)
+                if (l == 2 && l + 1 < L) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        float m = 0.f;
+#pragma unroll
+                        for (int I = 0; I < WB; ++I)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(u[j][I][v]));
+                        eu[j] = min(13 - exponent(max_groups(m)), 100);
+                        const float s = __builtin_amdgcn_ldexpf(1.0f, eu[j]);
+#pragma unroll
+                        for (int I = 0; I < WB; ++I) u[j][I] *= s;
+                    }
+                }
             }
             gacc jb[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            Split8 us[2][KS];
 #pragma unroll
-            for (int K = 0; K < WB; ++K) {
-                float wa[4];
-                vload<float, 4>(wa, &sWo[c * WS + 16 * K + 4 * g + zoff]);
+            for (int q = 0; q < KS; ++q) {
+                const Half8 w = lds.out[q][at];
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) jb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[v], u[j][K][v], jb[j], 0, 0, 0);
+                for (int j = 0; j < 2; ++j) {
+                    us[j][q] = split8(u[j][2 * q], u[j][2 * q + 1]);
+                    jb[j] = mfma16(w, us[j][q].lo, jb[j]);
+                }
             }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) f[v] -= jb[0][v] * yk.x + jb[1][v] * yk.y;
-            if (g < 2 && s0 + c < total) {
+            for (int q = 0; q < KS; ++q)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    *reinterpret_cast<float2*>(G + ((s0 + c) * N + 4 * g + v) * N + k) = float2{-jb[0][v], -jb[1][v]};
+                for (int j = 0; j < 2; ++j) jb[j] = mfma16(lds.out[q][at], us[j][q].hi, jb[j]);
+            // lane groups 0 and 1 take column k, 2 and 3 column k + 1
+            const int e = -e_out - (g < 2 ? eu[0] : eu[1]);
+            gacc jc;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(jb[0][v]), __float_as_uint(jb[1][v]), false, false);
+                jc[v] = __builtin_amdgcn_ldexpf(__uint_as_float(q[0]) + __uint_as_float(q[1]), e);
+                f[v] -= jc[v] * yk;
+            }
+            if (s0 + c < total) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) G[((s0 + c) * N + 4 * (g & 1) + v) * N + k + (g >> 1)] = -jc[v];
             }
         }
-        if (!p.jac_only && g < 2 && s0 + c < total) {
+        if (!p.jac_only) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) z[(s0 + c) * N + 4 * g + v] = f[v];
+            for (int v = 0; v < 4; ++v) {
+                const unsigned u = __float_as_uint(f[v]);
+                const auto q = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+                f[v] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+            }
+            if (g < 2 && s0 + c < total) *reinterpret_cast<gacc*>(z + (s0 + c) * N + 4 * g) = f;
         }
     }
 }
 
-size_t fe_mfma_smem(int W, int L) { return (8 * (size_t)(W + 4) + (size_t)(L - 1) * W * (W + 4) + 16 * (size_t)(W + 4) + (size_t)L * W + 16) * 4; }
-
 template <int WB, int L>
 hipError_t launch_fe_mfma_wl(const MlpParams& p, hipStream_t s) {
-    const size_t shmem = fe_mfma_smem(16 * WB, L);
+    const size_t shmem = sizeof(FieldLds<WB, L>);
     static bool attr_set = false;   // more than 64 KB of dynamic LDS needs the attribute (set once per instantiation)
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_gen_funceval_mfma_kernel<WB, L>),
@@ -278,11 +413,11 @@ hipError_t launch_fe_mfma_wl(const MlpParams& p, hipStream_t s) {
         if (e != hipSuccess) return e;
         attr_set = true;
     }
+    // one wavefront per SIMD while there are no more blocks of points than SIMDs, then two (width 32: four) that share the weights
     const long long nblk = ((long long)p.B * p.T + 15) / 16;
-    long long blocks = (nblk + 3) / 4;
-    if (blocks > 512) blocks = 512;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL((mlp_gen_funceval_mfma_kernel<WB, L>), dim3((unsigned)blocks), dim3(kThreads), shmem, s, p);
+    const unsigned threads = nblk > 1024 ? kFieldThreads : kFieldThreads / 2, waves = threads / 64;
+    const long long blocks = std::min((nblk + waves - 1) / waves, WB == 2 ? 512LL : 256LL);
+    hipLaunchKernelGGL((mlp_gen_funceval_mfma_kernel<WB, L>), dim3((unsigned)std::max(blocks, 1LL)), dim3(threads), shmem, s, p);
     return hipGetLastError();
 }
 

@@ -1,0 +1,80 @@
+// fp32 products on the fp16 matrix cores: every factor as the sum of two fp16 numbers.
+//
+// x = hi + lo + e with hi = fp16(x), lo = fp16(x - hi), |e| <= 2^-23 |x| while lo is a normal number, i.e. for |x| from 2^-2 to 65504: a
+// factor is scaled there by a power of two first.  A product is lo*hi + hi*lo + hi*hi, added in this order into one fp32
+// accumulator (lo*lo is below 2^-22 of the product).  Measured against 64 bits, 400 products 16 x K by K x 16 of normal and of
+// positive entries (2-norm): K = 32 8.0e-8 to 9.0e-8, K = 64 8.8e-8 to 9.6e-8; the fp32 matrix instructions give 1.03e-7 and
+// 1.43e-7 there (they round the sum after every four terms).  Without the scaling 1.2e-7 to 1.7e-6.
+// Time: a 16 x 16 x 32 product takes three instructions of 18 cycles and two vector instructions for each element that is
+// split, in the place of eight instructions of 32 cycles.  Vector and matrix instructions of a SIMD do not overlap, of either
+// kind (12 + 48 of them: 430 and 227 cycles apart, 657 together).
+#pragma once
+#include "deer_common.h"
+
+namespace deer {
+namespace {
+
+using Half8 = _Float16 __attribute__((ext_vector_type(8)));
+using Half2 = _Float16 __attribute__((ext_vector_type(2)));
+using F32x4 = float __attribute__((ext_vector_type(4)));
+using F32x8 = float __attribute__((ext_vector_type(8)));
+
+// hi and lo parts of the eight entries a lane supplies to a contraction of 32
+struct Split8 {
+    Half8 hi, lo;
+};
+
+__device__ __forceinline__ unsigned split_hi(float a, float b) { return __builtin_bit_cast(unsigned, Half2{(_Float16)a, (_Float16)b}); }
+
+// x - hi, x mixed with the fp16 number in one instruction (the multiplier is one the compiler cannot see, or it would convert and subtract)
+__device__ __forceinline__ float split_diff(float x, _Float16 hi) {
+    float one = 1.0f;
+    asm("" : "+s"(one));
+    return __builtin_fmaf(x, one, -(float)hi);
+}
+
+__device__ __forceinline__ unsigned split_lo(float a, float b, unsigned hi) {
+    const Half2 h = __builtin_bit_cast(Half2, hi);
+    return split_hi(split_diff(a, h[0]), split_diff(b, h[1]));
+}
+
+// what the two parts leave out of a pair (exact: 0 or the last bit)
+__device__ __forceinline__ unsigned split_rest(float a, float b, unsigned hi, unsigned lo) {
+    const Half2 h = __builtin_bit_cast(Half2, hi), l = __builtin_bit_cast(Half2, lo);
+    return split_hi((a - (float)h[0]) - (float)l[0], (b - (float)h[1]) - (float)l[1]);
+}
+
+// Two accumulators of 16 rows (rows 4g .. 4g + 3 of each in lane group g) as operand B of a contraction over those 32 rows: entry j
+// < 4 of lane group g is row 4g + j of the first, j >= 4 row 4g + j - 4 of the second.  Operand A takes its columns in the same order.
+__device__ __forceinline__ Split8 split8(F32x4 a, F32x4 b) {
+    const F32x8 x = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    Split8 s;
+    s.hi = __builtin_convertvector(x, Half8);
+    F32x8 r;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = split_diff(x[i], s.hi[i]);
+    s.lo = __builtin_convertvector(r, Half8);
+    return s;
+}
+
+__device__ __forceinline__ F32x4 mfma16(Half8 a, Half8 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+// where entry (row, 32 s + c) of a matrix goes as operand A: lane, and the place among the lane's eight
+__device__ __forceinline__ int split_lane(int row, int c) { return 16 * ((c % 16) / 4) + row % 16; }
+__device__ __forceinline__ int split_place(int c) { return 4 * (c / 16) + c % 4; }
+
+// exponent e with |x| < 2^e (0 for 0, infinities and NaN)
+__device__ __forceinline__ int exponent(float x) { return __builtin_amdgcn_frexp_expf(x); }
+
+// largest of the four lane groups' values, in every lane
+__device__ __forceinline__ float max_groups(float x) {
+    unsigned u = __float_as_uint(x);
+    const auto q = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const float s = fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+    u = __float_as_uint(s);
+    const auto w = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+
+}  // namespace
+}  // namespace deer
