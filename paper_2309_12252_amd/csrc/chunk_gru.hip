@@ -13,11 +13,17 @@
 // Nothing in a launch waits for another workgroup, the number of wavefronts does not depend on the length (the chunk does),
 // and the state that travels between the two launches is one map per chunk.
 //
-// Bound: issue.  The fp32 matrix instructions (32 cycles each) and the vector ALU of a SIMD do not overlap, so a position of
-// the reduction costs 32 x 32 + 72 x 4 cycles at n = 32 (4 x 32 + 20 x 4 at n = 16) beside its share of the gates; the tree over
-// wavefronts, the look-back and the second walk of the single-pass scan (a third of its tile's life at n = 32, with one to
-// four of eight wavefronts busy) are gone.  A Newton step, single-pass scan before / both launches now: n = 32, d = 8, 16 x 100,000
-// positions 2,650 / 1,420 us (1,120 + 300); n = 16, d = 6, 32 x 17,984 positions 240 / 130 us (88 + 42); the dual scan there 206 / 135.
+// Bound: issue.  The matrix instructions and the vector ALU of a SIMD do not overlap.  The reduction of a Newton step has both factors of a
+// product split in two fp16 numbers (split_f16.h): a position costs 12 matrix instructions of 18 cycles and 120 vector instructions of 2.4 at n = 32 (3 and 40 at n =
+// 16) beside its share of the gates (60 fp32 matrix instructions for sixteen positions), in the place of 32 fp32 matrix instructions of 32 cycles and 72 (4 and 20).
+// Two wavefronts a SIMD (registers, LDS) issue in 71 % of the time.  Newton step, reduction alone, fp32 products before / now: n = 32, d = 8, 16 x 100,000
+// positions 1,128 / 734 us; n = 16, d = 6, 32 x 17,984 positions 88 / 68 us (the walk 303 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
+// the factor of the next position behind the products of this one: 785 and 74 (20 more vector instructions a position).
+//
+// The split reduction: the entries of J and of the product (which starts from 16 I) are split as they are: what is lost of small ones is 2^-25 of the
+// largest that a correction can be multiplied by.  Corrections of the last step are below tol, so the trajectory does not see it (2-norm error against 64
+// bits 1.344e-7 with either, n = 32).  The dual scan, where the maps multiply the result itself, keeps fp32 products, and so do steps from far iterates.  A product that leaves the range
+// of fp16 (a chunk that expands 4,000 times) leaves infinities or NaN in the map; the wavefront then reduces its chunks again with fp32 products.
 //
 // Everything is in correction form: with e = y_new - y the recurrence of a Newton step is e_i = J_i e_{i-1} + (f_i - y_i),
 // e_0 = 0, so neither J h nor a right-hand side is needed and rounding is relative to the correction.
@@ -27,6 +33,9 @@
 // accumulator is a valid B operand, four consecutive scalars of a row-major matrix are an A operand, and an accumulator of
 // X is the A operand of its transpose.
 #include "chunk_common.h"
+#include "split_f16.h"
+
+#include <type_traits>
 
 namespace deer {
 
@@ -95,12 +104,23 @@ __device__ __forceinline__ void w_row(float* o, const Weights<N, DS>& w, int gat
 // the row factors to the lanes that assemble J instead of its transpose); the row factors reach the assembly through an
 // LDS slice of the wavefront.
 // ------------------------------------------------------------------------------------------------------------------
+// one row block of a factor as operand A, split in two
+template <int N>
+__device__ __forceinline__ auto split_row(const float (&a)[N / 16][4]) {
+    if constexpr (N == 16) return split4(Acc{a[0][0], a[0][1], a[0][2], a[0][3]});
+    else return split8(Acc{a[0][0], a[0][1], a[0][2], a[0][3]}, Acc{a[1][0], a[1][1], a[1][2], a[1][3]});
+}
+
 template <int N, int DS, bool REV, bool FAR>
 __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(ChunkParams p) {
     constexpr int NB = N / 16, MS = map_size<N>();
+    constexpr bool SPLIT = !FAR && !REV;
+    constexpr float kUnit = 16.f;
+    using Parts = typename std::conditional<N == 16, Split4, Split8>::type;
     __shared__ __align__(16) Weights<N, DS> sW;
     // forward: [kind: p_z, s_r, s_t, z, residual][position][row]; dual: [position][row][p_z, s_r, s_t, z], then [position][row] of g
-    __shared__ __align__(16) float sF[4][5 * 16 * N];
+    constexpr int PS = REV ? N : N + 4, KS = 16 * PS;   // (forward: sixteen positions' rows of 16 bytes fall on different banks)
+    __shared__ __align__(16) float sF[4][5 * KS];
 
     if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
@@ -157,7 +177,9 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 #pragma unroll
     for (int v = 0; v < 4; ++v) dsel[v] = (4 * g + v == r) ? 1.f : 0.f;
 
-    if (q_lo < q_hi) {
+    bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
+    while (q_lo < q_hi) {
+        const float unit_q = wide ? 1.f : kUnit;
         Acc Q[NB][NB];
         float vec[NB];
         auto reset = [&]() {
@@ -167,7 +189,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 #pragma unroll
                 for (int C = 0; C < NB; ++C)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] : 0.f;
+                    for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] * unit_q : 0.f;
             }
         };
         reset();
@@ -226,8 +248,8 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 #pragma unroll
                         for (int v = 0; v < 4; ++v) fr[v] = o[v].f - oB[I][v];
                     }
-                    float* q = sFw + r * N + 16 * I + 4 * g;
-                    store4(q, fpz); store4(q + 16 * N, fsr); store4(q + 32 * N, fst); store4(q + 48 * N, fz); store4(q + 64 * N, fr);
+                    float* q = sFw + r * PS + 16 * I + 4 * g;
+                    store4(q, fpz); store4(q + KS, fsr); store4(q + 2 * KS, fst); store4(q + 3 * KS, fz); store4(q + 4 * KS, fr);
                 }
             } else {
                 // the state entries of the rows this lane evaluates (positions 4g + v, row 16 I + r) come through the slice too
@@ -275,18 +297,16 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
             if (blk + 1 < blocks) request(blk + 1);
 
             // ---- the running product takes the positions of the block in one after the other ----
-            const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16;
-#pragma unroll 2
-            for (int k = 0; k < c_hi - c_lo; ++k) {
-                const int c = REV ? c_lo + k : c_hi - 1 - k;
-                float a[NB][NB][4];
-                Acc rv[NB];
+            const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16, cnt = c_hi - c_lo;
+            auto at = [&](int k) { return REV ? c_lo + k : c_hi - 1 - k; };
+            // factor and right-hand side of the position in column c
+            auto assemble = [&](int c, float (&a)[NB][NB][4], Acc (&rv)[NB]) {
                 if constexpr (!REV) {
 #pragma unroll
                     for (int Y = 0; Y < NB; ++Y) {
-                        const float* o = sFw + c * N + 16 * Y + 4 * g;
-                        const Acc pz = load4(o), sr = load4(o + 16 * N), st = load4(o + 32 * N), z = load4(o + 48 * N);
-                        rv[Y] = load4(o + 64 * N);
+                        const float* o = sFw + c * PS + 16 * Y + 4 * g;
+                        const Acc pz = load4(o), sr = load4(o + KS), st = load4(o + 2 * KS), z = load4(o + 3 * KS);
+                        rv[Y] = load4(o + 4 * KS);
 #pragma unroll
                         for (int X = 0; X < NB; ++X)
 #pragma unroll
@@ -311,6 +331,8 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
                             }
                     }
                 }
+            };
+            auto add_vector = [&](const Acc (&rv)[NB]) {
 #pragma unroll
                 for (int C = 0; C < NB; ++C) {
                     float s = vec[C];
@@ -320,40 +342,76 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
                         for (int v = 0; v < 4; ++v) s += Q[K][C][v] * rv[K][v];
                     vec[C] = s;
                 }
-                Acc Qn[NB][NB];
+            };
+            // at the end of a chunk its map leaves: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
+            auto finish = [&](int c) {
+                if (base + c != edge) return;
+                float* o = tot + (long long)q * MS;
+                const float down = wide ? 1.f : 1.f / kUnit;
+                float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
-                for (int X = 0; X < NB; ++X)
+                for (int C = 0; C < NB; ++C) {
 #pragma unroll
-                    for (int C = 0; C < NB; ++C) Qn[X][C] = zero4();
+                    for (int X = 0; X < NB; ++X) {
+                        if (SPLIT)
 #pragma unroll
-                for (int K = 0; K < NB; ++K)
+                            for (int v = 0; v < 4; ++v) sum += 0.f * Q[X][C][v];
+                        store4(o + (16 * C + r) * N + 16 * X + 4 * g, Q[X][C] * down);
+                    }
+                    const float s = sum_groups(vec[C]) * down;
+                    if (g == 0) o[N * N + 16 * C + r] = s;
+                }
+                again |= sum != 0.f;
+                reset();
+                q += REV ? 1 : -1;
+                edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
+            };
+#pragma unroll 2
+            for (int k = 0; k < cnt; ++k) {
+                float a[NB][NB][4];
+                Acc rv[NB], Qn[NB][NB];
+                assemble(at(k), a, rv);
+                add_vector(rv);
+                if (SPLIT && !wide) {
+                    Parts A[NB], B[NB];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
+                    for (int X = 0; X < NB; ++X) {
+                        A[X] = split_row<N>(a[X]);
+                        if constexpr (N == 16) B[X] = split4(Q[0][X]);
+                        else B[X] = split8(Q[0][X], Q[NB - 1][X]);
+                    }
+#pragma unroll
+                    for (int part = 0; part < 3; ++part)
 #pragma unroll
                         for (int X = 0; X < NB; ++X)
 #pragma unroll
-                            for (int C = 0; C < NB; ++C) Qn[X][C] = mfma(a[X][K][v], Q[K][C][v], Qn[X][C]);
+                            for (int C = 0; C < NB; ++C)
+                                Qn[X][C] = mfma16(part == 0 ? A[X].lo : A[X].hi, part == 1 ? B[C].lo : B[C].hi, part == 0 ? zero4() : Qn[X][C]);
+                } else {
+#pragma unroll
+                    for (int X = 0; X < NB; ++X)
+#pragma unroll
+                        for (int C = 0; C < NB; ++C) Qn[X][C] = zero4();
+#pragma unroll
+                    for (int K = 0; K < NB; ++K)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+#pragma unroll
+                            for (int X = 0; X < NB; ++X)
+#pragma unroll
+                                for (int C = 0; C < NB; ++C) Qn[X][C] = mfma(a[X][K][v], Q[K][C][v], Qn[X][C]);
+                }
 #pragma unroll
                 for (int X = 0; X < NB; ++X)
 #pragma unroll
                     for (int C = 0; C < NB; ++C) Q[X][C] = Qn[X][C];
-                if (base + c == edge) {
-                    // the chunk's map: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
-                    float* o = tot + (long long)q * MS;
-#pragma unroll
-                    for (int C = 0; C < NB; ++C) {
-#pragma unroll
-                        for (int X = 0; X < NB; ++X) store4(o + (16 * C + r) * N + 16 * X + 4 * g, Q[X][C]);
-                        const float s = sum_groups(vec[C]);
-                        if (g == 0) o[N * N + 16 * C + r] = s;
-                    }
-                    reset();
-                    q += REV ? 1 : -1;
-                    edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
-                }
+                finish(at(k));
             }
             wave_lds_fence();
         }
+        if (wide || !__ballot(again)) break;
+        wide = true;
+        request(0);
     }
     __syncthreads();
 

@@ -4,10 +4,12 @@
 //     every factor (the rows of J whose gates it has evaluated) into LDS in operand order, double-buffered, one barrier a
 //     position; all four read the whole factor (64 KB of LDS reads against 4 x 2,048 matrix-core cycles).
 //   walk: wavefront w evaluates rows 16 w .. 16 w + 15 of all products; the column vectors cross LDS, one barrier a step.
-// Bound: issue of the matrix instructions, 64 x 32 cycles of about 2,450 a wavefront spends on a position.  Measured, a Newton
-// step at 16 x 10,000 positions, d = 8: 940 us; before (Jacobian kernel 1,220 us, then the scan of the stored matrices in tiles of eight
-// positions 3,570 us) 4,790 us.
+// Bound: the reduction of a Newton step has its factors split in two fp16 numbers like that at n = 32 (chunk_gru.hip; wavefronts split the
+// quarter that they assemble): 24 matrix instructions of 18 cycles a wavefront and position and about 110 vector instructions of 2.4, then the barrier and the LDS
+// (one workgroup a compute unit at 5 x 9,973 positions: 2,100 cycles a position).  The dual scan and far iterates: 64 fp32 matrix
+// instructions of 32 cycles.  Reduction of a step at 5 x 9,973 positions, d = 7: 307 us with fp32 products, now 184.
 #include "chunk_common.h"
+#include "split_f16.h"
 
 namespace deer {
 
@@ -69,7 +71,11 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     // row factors of this wavefront's 16 rows; forward [kind][position][row], dual [position][row][kind]
     __shared__ __align__(16) float sF[4][4 * 16 * 16];
     __shared__ __align__(16) float sR[16 * N];            // forward: residual, dual: cotangent, [position][row]
-    __shared__ __align__(16) Acc sJ[2][NB * NB][64];      // factor in operand order, [block][lane]
+    // factor in operand order, [block][lane]; split in two [column blocks / 2][row block][hi, lo][lane], in the same place
+    __shared__ __align__(16) Acc sJ[2][NB * NB][64];
+    __shared__ unsigned s_again[4];
+    constexpr bool SPLIT = !FAR && !REV;
+    constexpr float kUnit = 16.f;
     if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
@@ -115,14 +121,16 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
 
     Acc Q[NB];   // columns 16 w + r of the running product, rows 16 X + 4g + v
     float vec = 0.f;
+    bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
+    float unit_q = wide ? 1.f : kUnit;
     auto reset = [&]() {
         vec = 0.f;
 #pragma unroll
         for (int X = 0; X < NB; ++X)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Q[X][v] = X == wave ? dsel[v] : 0.f;
+            for (int v = 0; v < 4; ++v) Q[X][v] = X == wave ? dsel[v] * unit_q : 0.f;
     };
-    reset();
+    auto parts = [&](int buf, int K2, int X, int part) { return reinterpret_cast<Half8*>(&sJ[buf][(K2 * NB + X) * 2 + part][0]); };
 
     auto assemble = [&](int buf, int c) {
         if constexpr (!REV) {
@@ -135,7 +143,13 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     a[v] = pz[v] * ua[1][X][v] + (sr[v] * ua[2][X][v] + (st[v] * ua[0][X][v] + diag * dsel[v] * z[v]));
-                sJ[buf][X * NB + wave][lane] = a;
+                if (SPLIT && !wide) {
+                    const Split4 h4 = split4(a);
+                    reinterpret_cast<Half4*>(parts(buf, wave >> 1, X, 0) + lane)[wave & 1] = h4.hi;
+                    reinterpret_cast<Half4*>(parts(buf, wave >> 1, X, 1) + lane)[wave & 1] = h4.lo;
+                } else {
+                    sJ[buf][X * NB + wave][lane] = a;
+                }
             }
         } else {
             const Acc ff = load4(sFw + (c * 16 + r) * 4);
@@ -151,85 +165,121 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
         }
     };
 
-    int q = REV ? 0 : nq - 1;   // chunk being reduced
-    int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
-    for (int blk = 0; blk < blocks; ++blk) {
-        const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
-        {
-            GruGates k[4];
-            gates16<DS>(k, gr, h, x, wave == 0 ? h[0] : wave == 1 ? h[1] : wave == 2 ? h[2] : h[3]);
-            Acc rv = ow;
-            if constexpr (!REV) {
-                Acc fpz, fsr, fst, fz;
-                if constexpr (FAR) {
-                    Acc hr = zero4(), hz = zero4(), hc = zero4();
+    for (;;) {
+        reset();
+        int q = REV ? 0 : nq - 1;   // chunk being reduced
+        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+        for (int blk = 0; blk < blocks; ++blk) {
+            const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            {
+                GruGates k[4];
+                gates16<DS>(k, gr, h, x, wave == 0 ? h[0] : wave == 1 ? h[1] : wave == 2 ? h[2] : h[3]);
+                Acc rv = ow;
+                if constexpr (!REV) {
+                    Acc fpz, fsr, fst, fz;
+                    if constexpr (FAR) {
+                        Acc hr = zero4(), hz = zero4(), hc = zero4();
 #pragma unroll
-                    for (int K = 0; K < NB; ++K)
+                        for (int K = 0; K < NB; ++K)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            hr = mfma(gr.u[0][K][v], h[K][v], hr);
-                            hz = mfma(gr.u[1][K][v], h[K][v], hz);
-                            hc = mfma(gr.u[2][K][v], h[K][v], hc);
-                        }
+                            for (int v = 0; v < 4; ++v) {
+                                hr = mfma(gr.u[0][K][v], h[K][v], hr);
+                                hz = mfma(gr.u[1][K][v], h[K][v], hz);
+                                hc = mfma(gr.u[2][K][v], h[K][v], hc);
+                            }
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) rv[v] = gru_rhs(k[v], hr[v], hz[v], hc[v]);
+                        for (int v = 0; v < 4; ++v) rv[v] = gru_rhs(k[v], hr[v], hz[v], hc[v]);
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) rv[v] = k[v].f - ow[v];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) { fpz[v] = k[v].pz; fsr[v] = k[v].sr; fst[v] = k[v].st; fz[v] = k[v].z; }
+                    float* o = sFw + r * 16 + 4 * g;
+                    store4(o, fpz); store4(o + 256, fsr); store4(o + 512, fst); store4(o + 768, fz);
                 } else {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) rv[v] = k[v].f - ow[v];
+                    for (int v = 0; v < 4; ++v) store4(sFw + (r * 16 + 4 * g + v) * 4, Acc{k[v].pz, k[v].sr, k[v].st, k[v].z});
+                }
+                store4(sR + r * N + 16 * wave + 4 * g, rv);
+            }
+            wave_lds_fence();
+            const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16, cnt = c_hi - c_lo;
+            assemble(0, REV ? c_lo : c_hi - 1);
+            __syncthreads();
+            if (blk + 1 < blocks) request(blk + 1);
+#pragma unroll 1
+            for (int k = 0; k < cnt; ++k) {
+                const int c = REV ? c_lo + k : c_hi - 1 - k;
+                if (k + 1 < cnt) assemble((k + 1) & 1, REV ? c + 1 : c - 1);
+#pragma unroll
+                for (int K = 0; K < NB; ++K) {
+                    const Acc rv = load4(sR + c * N + 16 * K + 4 * g);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) vec += Q[K][v] * rv[v];
+                }
+                Acc Qn[NB];
+#pragma unroll
+                for (int X = 0; X < NB; ++X) Qn[X] = zero4();
+                if (SPLIT && !wide) {
+                    const Split8 B[2] = {split8(Q[0], Q[1]), split8(Q[2], Q[3])};
+#pragma unroll
+                    for (int K2 = 0; K2 < 2; ++K2) {
+                        Half8 hi[NB];
+#pragma unroll
+                        for (int X = 0; X < NB; ++X) {
+                            hi[X] = parts(k & 1, K2, X, 0)[lane];
+                            Qn[X] = mfma16(parts(k & 1, K2, X, 1)[lane], B[K2].hi, Qn[X]);
+                        }
+#pragma unroll
+                        for (int X = 0; X < NB; ++X) Qn[X] = mfma16(hi[X], B[K2].lo, Qn[X]);
+#pragma unroll
+                        for (int X = 0; X < NB; ++X) Qn[X] = mfma16(hi[X], B[K2].hi, Qn[X]);
+                    }
+                } else {
+#pragma unroll
+                    for (int K = 0; K < NB; ++K) {
+                        Acc a[NB];
+#pragma unroll
+                        for (int X = 0; X < NB; ++X) a[X] = sJ[k & 1][X * NB + K][lane];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+#pragma unroll
+                            for (int X = 0; X < NB; ++X) Qn[X] = mfma(a[X][v], Q[K][v], Qn[X]);
+                    }
                 }
 #pragma unroll
-                for (int v = 0; v < 4; ++v) { fpz[v] = k[v].pz; fsr[v] = k[v].sr; fst[v] = k[v].st; fz[v] = k[v].z; }
-                float* o = sFw + r * 16 + 4 * g;
-                store4(o, fpz); store4(o + 256, fsr); store4(o + 512, fst); store4(o + 768, fz);
-            } else {
+                for (int X = 0; X < NB; ++X) Q[X] = Qn[X];
+                if (base + c == edge) {
+                    // the chunk's map: M[16 w + r][16 X + 4g + v] = Q[X][v]
+                    float* o = tot + (long long)q * MS;
+                    const float down = wide ? 1.f : 1.f / kUnit;
+                    float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) store4(sFw + (r * 16 + 4 * g + v) * 4, Acc{k[v].pz, k[v].sr, k[v].st, k[v].z});
+                    for (int X = 0; X < NB; ++X) {
+                        if (SPLIT)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) sum += 0.f * Q[X][v];
+                        store4(o + (16 * wave + r) * N + 16 * X + 4 * g, Q[X] * down);
+                    }
+                    again |= sum != 0.f;
+                    const float s = sum_groups(vec) * down;
+                    if (g == 0) o[N * N + 16 * wave + r] = s;
+                    reset();
+                    q += REV ? 1 : -1;
+                    edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
+                }
+                __syncthreads();   // the next factor is complete, this one and (at the end of a block) the residuals are free
             }
-            store4(sR + r * N + 16 * wave + 4 * g, rv);
         }
-        wave_lds_fence();
-        const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16, cnt = c_hi - c_lo;
-        assemble(0, REV ? c_lo : c_hi - 1);
+        if (wide) break;
+        if (lane == 0) s_again[wave] = 0u;
+        if (again) s_again[wave] = 1u;
         __syncthreads();
-        if (blk + 1 < blocks) request(blk + 1);
-#pragma unroll 1
-        for (int k = 0; k < cnt; ++k) {
-            const int c = REV ? c_lo + k : c_hi - 1 - k;
-            if (k + 1 < cnt) assemble((k + 1) & 1, REV ? c + 1 : c - 1);
-#pragma unroll
-            for (int K = 0; K < NB; ++K) {
-                const Acc rv = load4(sR + c * N + 16 * K + 4 * g);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) vec += Q[K][v] * rv[v];
-            }
-            Acc Qn[NB];
-#pragma unroll
-            for (int X = 0; X < NB; ++X) Qn[X] = zero4();
-#pragma unroll
-            for (int K = 0; K < NB; ++K) {
-                Acc a[NB];
-#pragma unroll
-                for (int X = 0; X < NB; ++X) a[X] = sJ[k & 1][X * NB + K][lane];
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int X = 0; X < NB; ++X) Qn[X] = mfma(a[X][v], Q[K][v], Qn[X]);
-            }
-#pragma unroll
-            for (int X = 0; X < NB; ++X) Q[X] = Qn[X];
-            if (base + c == edge) {
-                // the chunk's map: M[16 w + r][16 X + 4g + v] = Q[X][v]
-                float* o = tot + (long long)q * MS;
-#pragma unroll
-                for (int X = 0; X < NB; ++X) store4(o + (16 * wave + r) * N + 16 * X + 4 * g, Q[X]);
-                const float s = sum_groups(vec);
-                if (g == 0) o[N * N + 16 * wave + r] = s;
-                reset();
-                q += REV ? 1 : -1;
-                edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
-            }
-            __syncthreads();   // the next factor is complete, this one and (at the end of a block) the residuals are free
-        }
+        if ((s_again[0] | s_again[1] | s_again[2] | s_again[3]) == 0u) break;   // (the same for the four wavefronts)
+        wide = true;
+        unit_q = 1.f;
+        request(0);
     }
 
     // ---- the unit's map; none where no group follows ----

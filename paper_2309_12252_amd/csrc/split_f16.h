@@ -15,6 +15,7 @@ namespace deer {
 namespace {
 
 using Half8 = _Float16 __attribute__((ext_vector_type(8)));
+using Half4 = _Float16 __attribute__((ext_vector_type(4)));
 using Half2 = _Float16 __attribute__((ext_vector_type(2)));
 using F32x4 = float __attribute__((ext_vector_type(4)));
 using F32x8 = float __attribute__((ext_vector_type(8)));
@@ -58,6 +59,23 @@ __device__ __forceinline__ Split8 split8(F32x4 a, F32x4 b) {
 }
 
 __device__ __forceinline__ F32x4 mfma16(Half8 a, Half8 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+// the same for a contraction of 16, i.e. one accumulator
+struct Split4 {
+    Half4 hi, lo;
+};
+
+__device__ __forceinline__ Split4 split4(F32x4 x) {
+    Split4 s;
+    s.hi = __builtin_convertvector(x, Half4);
+    F32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = split_diff(x[i], s.hi[i]);
+    s.lo = __builtin_convertvector(r, Half4);
+    return s;
+}
+
+__device__ __forceinline__ F32x4 mfma16(Half4 a, Half4 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0); }
 
 // where entry (row, 32 s + c) of a matrix goes as operand A: lane, and the place among the lane's eight
 __device__ __forceinline__ int split_lane(int row, int c) { return 16 * ((c % 16) / 4) + row % 16; }
