@@ -13,9 +13,13 @@
 // (the products with U then contract over 8 entries in two instructions: lane groups 0, 1 supply two of their four
 // units, groups 2, 3 the other two), groups 0, 1 answer for the rows of the first part, 2, 3 for those of the second.
 //
-// Bound: issue (matrix and vector instructions of a SIMD do not overlap).  Measured, a Newton step (Jacobian kernel and scan
-// before / both launches now): LSTM u = 8, d = 4, 16 x 50,000 positions 710 / 192 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 375 us.
+// Bound: issue (matrix and vector instructions of a SIMD do not overlap).  Above 8 units the reduction of a Newton step has the factors of its
+// products split in two fp16 numbers, as in chunk_gru.hip.  Measured, a Newton step (Jacobian kernel and scan before / both launches now): LSTM u
+// = 8, d = 4, 16 x 50,000 positions 710 / 180 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 290 us (reduction 304 with fp32 products, now 227).
 #include "chunk_common.h"
+#include "split_f16.h"
+
+#include <type_traits>
 
 namespace deer {
 
@@ -172,9 +176,33 @@ template <int CELL> struct Slice<CELL, 16> { static constexpr int kinds = 8; }; 
 template <> struct Slice<LSTM, 8> { static constexpr int kinds = 6; };            // factors of U_i, U_f, U_g, U_o, diagonal, vector; row of the state
 template <> struct Slice<LEM, 8> { static constexpr int kinds = 4; };             // two factors and the diagonal of the row's step, vector
 
+// Product with a 16 x 16 factor: of fp32 scalars, or of both factors split in two fp16 numbers
+template <bool SPLIT>
+struct Product16 {
+    static __device__ __forceinline__ auto left(const Acc& a) {
+        if constexpr (SPLIT) return split4(a);
+        else return a;
+    }
+    static __device__ __forceinline__ auto right(const Acc& b) {
+        if constexpr (SPLIT) return split4(b);
+        else return b;
+    }
+    template <typename A, typename B>
+    static __device__ __forceinline__ Acc add(const A& a, const B& b, Acc c) {
+        if constexpr (SPLIT) {
+            return split_product(a, b, c);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) c = mfma(a[v], b[v], c);
+            return c;
+        }
+    }
+};
+
 template <int CELL, int UP, int DS, bool VEC, bool REV, bool FAR>
 __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
     constexpr int N = 2 * UP, NB = N / 16, MS = map_size<N>(), KINDS = Slice<CELL, UP>::kinds;
+    constexpr bool SPLIT = UP == 16 && !REV && !FAR;   // (a factor of 16 x 16 a position: the split costs what it saves, LSTM u = 8, 16 x 50,000, 120 us with fp32 products, 133)
     __shared__ __align__(16) float sF[4][KINDS * 256];
     if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
@@ -248,231 +276,249 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
         for (int v = 0; v < 4; ++v) dsel[v] = (4 * g + v == r) ? 1.f : 0.f;
 
         Acc Q[NB][NB];
-        float vec[NB];
+        float vec[NB], unit_q = SPLIT ? (float)(1 << ColumnScale::kStart) : 1.f;
+        ColumnScale scale[NB];
         auto reset = [&]() {
 #pragma unroll
             for (int X = 0; X < NB; ++X) {
                 vec[X] = 0.f;
+                scale[X].reset(unit_q != 1.f);
 #pragma unroll
                 for (int C = 0; C < NB; ++C)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] : 0.f;
+                    for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] * unit_q : 0.f;
             }
         };
-        reset();
-        int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
-        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+        bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
+        for (;;) {
+            reset();
+            int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
+            int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
 
-        for (int blk = 0; blk < blocks; ++blk) {
-            const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
-            {
-                Factors k[4];
-                cell.eval(k, s0, s1, x, dt, g);
-                Acc r0 = v0, r1 = v1;
-                if constexpr (!REV) {
-                    if constexpr (FAR) {   // the cell minus J times its state
-                        // (one product after the other: registers)
-                        Acc q, j1;   // j1: second part of J times the state
+            for (int blk = 0; blk < blocks; ++blk) {
+                const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+                if (SPLIT && !wide) {
+                    // (in front of the gates: nothing waits for it there)
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            if (CELL == LEM && i == 1) continue;
-                            const Acc t = cell.times(i, s0, zero4(), g);
+                    for (int C = 0; C < NB; ++C) {
+                        float m = 0.f;
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) q[v] = i == 0 ? k[v].a * t[v] : q[v] + (CELL == LSTM && i == 2 ? k[v].c : k[v].b) * t[v];
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
+                        for (int X = 0; X < NB; ++X)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            j1[v] = k[v].f * s1[v] + q[v];
-                            r1[v] = k[v].g1 - q[v];
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        const Acc t3 = cell.times(3, CELL == LSTM ? s0 : j1, zero4(), g);
+                            for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(Q[X][C][v]));
+                        const float f = scale[C].next(max_groups(m));
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) r0[v] = CELL == LSTM ? k[v].n0 - (k[v].d * t3[v] + k[v].e * j1[v]) : k[v].g0 - k[v].d * t3[v];
-                        if constexpr (CELL == LEM) {
-                            __builtin_amdgcn_sched_barrier(0);
-                            const Acc t1 = cell.times(1, s0, zero4(), g);
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) r0[v] -= k[v].c * t1[v];
-                        }
-                    } else {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) { r0[v] = k[v].n0 - v0[v]; r1[v] = k[v].n1 - v1[v]; }
+                        for (int X = 0; X < NB; ++X) Q[X][C] *= f;
                     }
                 }
-                Acc o[KINDS];
+                {
+                    Factors k[4];
+                    cell.eval(k, s0, s1, x, dt, g);
+                    Acc r0 = v0, r1 = v1;
+                    if constexpr (!REV) {
+                        if constexpr (FAR) {   // the cell minus J times its state
+                            // (one product after the other: registers)
+                            Acc q, j1;   // j1: second part of J times the state
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if constexpr (UP == 16) {
-                        o[0][v] = k[v].a; o[1][v] = k[v].b; o[2][v] = k[v].c; o[3][v] = k[v].d; o[4][v] = k[v].e; o[5][v] = k[v].f;
-                        o[6][v] = r0[v]; o[KINDS - 1][v] = r1[v];
-                    } else if constexpr (CELL == LSTM) {
-                        const float s = g < 2 ? k[v].e : 1.f;   // rows of h: dh' = d U_o h + e dc'
-                        o[0][v] = s * k[v].a; o[1][v] = s * k[v].b; o[2][v] = s * k[v].c;
-                        o[3][v] = g < 2 ? k[v].d : 0.f;
-                        o[4][v] = s * k[v].f;
-                        o[KINDS - 1][v] = g < 2 ? r0[v] : r1[v];
-                    } else {
-                        o[0][v] = g < 2 ? k[v].c : k[v].a;
-                        o[1][v] = g < 2 ? k[v].d : k[v].b;
-                        o[2][v] = g < 2 ? k[v].e : k[v].f;
-                        o[KINDS - 1][v] = g < 2 ? r0[v] : r1[v];
+                            for (int i = 0; i < 3; ++i) {
+                                if (CELL == LEM && i == 1) continue;
+                                const Acc t = cell.times(i, s0, zero4(), g);
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) q[v] = i == 0 ? k[v].a * t[v] : q[v] + (CELL == LSTM && i == 2 ? k[v].c : k[v].b) * t[v];
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                j1[v] = k[v].f * s1[v] + q[v];
+                                r1[v] = k[v].g1 - q[v];
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                            const Acc t3 = cell.times(3, CELL == LSTM ? s0 : j1, zero4(), g);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) r0[v] = CELL == LSTM ? k[v].n0 - (k[v].d * t3[v] + k[v].e * j1[v]) : k[v].g0 - k[v].d * t3[v];
+                            if constexpr (CELL == LEM) {
+                                __builtin_amdgcn_sched_barrier(0);
+                                const Acc t1 = cell.times(1, s0, zero4(), g);
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) r0[v] -= k[v].c * t1[v];
+                            }
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) { r0[v] = k[v].n0 - v0[v]; r1[v] = k[v].n1 - v1[v]; }
+                        }
                     }
-                }
-#pragma unroll
-                for (int i = 0; i < KINDS; ++i) store4(sFw + i * 256 + r * 16 + 4 * g, o[i]);
-            }
-            wave_lds_fence();
-            if (blk + 1 < blocks) request(blk + 1);
-
-            const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16;
-#pragma unroll 2
-            for (int k = 0; k < c_hi - c_lo; ++k) {
-                const int c = REV ? c_lo + k : c_hi - 1 - k;
-                const float* fp = sFw + c * 16;   // factors of the position: of rows 4g + v, or of row r
-                auto rows = [&](int i) { return load4(fp + i * 256 + 4 * g); };
-                auto row_r = [&](int i) { return fp[i * 256 + r]; };
-                // a factor of operand A: forward it goes with the contraction index 4g + v, dual with the row r
-                auto fac = [&](int i) {
-                    if constexpr (!REV) return rows(i);
-                    else { const float t = row_r(i); return Acc{t, t, t, t}; }
-                };
-                if constexpr (UP == 16) {
-                    const Acc r0 = rows(6), r1 = rows(KINDS - 1);
-#pragma unroll
-                    for (int C = 0; C < NB; ++C)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) vec[C] += Q[0][C][v] * r0[v] + Q[NB - 1][C][v] * r1[v];
-                    const Acc fa = fac(0), fb = fac(1), fc = fac(2), fd = fac(3), fe = rows(4), ff = rows(5);
-                    Acc m, n2, n3;   // M; LSTM: D U_o; LEM: E U_y and F U_2
+                    Acc o[KINDS];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        if constexpr (CELL == LSTM) {
-                            m[v] = fa[v] * wa[0][v] + (fb[v] * wa[1][v] + fc[v] * wa[2][v]);
-                            n2[v] = fd[v] * wa[3][v];
-                        } else {
-                            m[v] = fa[v] * wa[0][v] + fb[v] * wa[2][v];
-                            n2[v] = fd[v] * wa[3][v];
-                            n3[v] = fc[v] * wa[1][v];
-                        }
-                    }
-#pragma unroll
-                    for (int C = 0; C < NB; ++C) {
-                        Acc &Q0 = Q[0][C], &Q1 = Q[NB - 1][C];
-                        if constexpr (CELL == LSTM && !REV) {
-                            // Z = Q1 + e Q0;  Q0 <- (D U_o)^T Q0 + M^T Z,  Q1 <- f Z
-                            Acc z, t = zero4();
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) z[v] = Q1[v] + fe[v] * Q0[v];
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) t = mfma(n2[v], Q0[v], t);
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) t = mfma(m[v], z[v], t);
-                            Q0 = t;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) Q1[v] = ff[v] * z[v];
+                        if constexpr (UP == 16) {
+                            o[0][v] = k[v].a; o[1][v] = k[v].b; o[2][v] = k[v].c; o[3][v] = k[v].d; o[4][v] = k[v].e; o[5][v] = k[v].f;
+                            o[6][v] = r0[v]; o[KINDS - 1][v] = r1[v];
                         } else if constexpr (CELL == LSTM) {
-                            // S1 <- f S1 + M S0,  S0 <- D U_o S0 + e S1
-                            Acc t, w;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) t[v] = ff[v] * Q1[v];
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) t = mfma(m[v], Q0[v], t);
-                            w = zero4();
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) w = mfma(n2[v], Q0[v], w);
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) Q0[v] = w[v] + fe[v] * t[v];
-                            Q1 = t;
-                        } else if constexpr (!REV) {
-                            // Z = Q1 + (E U_y)^T Q0;  Q0 <- (1 - s2) Q0 + (F U_2)^T Q0 + M^T Z,  Q1 <- (1 - s1) Z
-                            Acc z = Q1, t;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) t[v] = fe[v] * Q0[v];
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                z = mfma(n2[v], Q0[v], z);
-                                t = mfma(n3[v], Q0[v], t);
-                            }
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) t = mfma(m[v], z[v], t);
-                            Q0 = t;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) Q1[v] = ff[v] * z[v];
+                            const float s = g < 2 ? k[v].e : 1.f;   // rows of h: dh' = d U_o h + e dc'
+                            o[0][v] = s * k[v].a; o[1][v] = s * k[v].b; o[2][v] = s * k[v].c;
+                            o[3][v] = g < 2 ? k[v].d : 0.f;
+                            o[4][v] = s * k[v].f;
+                            o[KINDS - 1][v] = g < 2 ? r0[v] : r1[v];
                         } else {
-                            // S1 <- (1 - s1) S1 + M S0,  S0 <- (1 - s2) S0 + F U_2 S0 + E U_y S1
-                            Acc t, w;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                t[v] = ff[v] * Q1[v];
-                                w[v] = fe[v] * Q0[v];
-                            }
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                t = mfma(m[v], Q0[v], t);
-                                w = mfma(n3[v], Q0[v], w);
-                            }
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) w = mfma(n2[v], t[v], w);
-                            Q0 = w;
-                            Q1 = t;
+                            o[0][v] = g < 2 ? k[v].c : k[v].a;
+                            o[1][v] = g < 2 ? k[v].d : k[v].b;
+                            o[2][v] = g < 2 ? k[v].e : k[v].f;
+                            o[KINDS - 1][v] = g < 2 ? r0[v] : r1[v];
                         }
                     }
-                } else {
-                    const Acc rv = rows(KINDS - 1);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) vec[0] += Q[0][0][v] * rv[v];
-                    if constexpr (CELL == LSTM) {
-                        const Acc fi = fac(0), ff = fac(1), fg = fac(2), fo = fac(3), fd = fac(4);
-                        Acc t = zero4();
+                    for (int i = 0; i < KINDS; ++i) store4(sFw + i * 256 + r * 16 + 4 * g, o[i]);
+                }
+                wave_lds_fence();
+                if (blk + 1 < blocks) request(blk + 1);
+
+                const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16;
+                // the running product takes in the position in column c
+                auto advance = [&](auto split, int c) {
+                    using P = Product16<decltype(split)::value>;
+                    const float* fp = sFw + c * 16;   // factors of the position: of rows 4g + v, or of row r
+                    auto rows = [&](int i) { return load4(fp + i * 256 + 4 * g); };
+                    auto row_r = [&](int i) { return fp[i * 256 + r]; };
+                    // a factor of operand A: forward it goes with the contraction index 4g + v, dual with the row r
+                    auto fac = [&](int i) {
+                        if constexpr (!REV) return rows(i);
+                        else { const float t = row_r(i); return Acc{t, t, t, t}; }
+                    };
+                    if constexpr (UP == 16) {
+                        const Acc r0 = rows(6), r1 = rows(KINDS - 1);
+#pragma unroll
+                        for (int C = 0; C < NB; ++C) {
+                            float s = SPLIT ? 0.f : vec[C];
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) s += Q[0][C][v] * r0[v] + Q[NB - 1][C][v] * r1[v];
+                            vec[C] = SPLIT ? vec[C] + s * scale[C].down : s;
+                        }
+                        const Acc fa = fac(0), fb = fac(1), fc = fac(2), fd = fac(3), fe = rows(4), ff = rows(5);
+                        Acc m, n2, n3;   // M; LSTM: D U_o; LEM: E U_y and F U_2
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const float a = fi[v] * wa[0][v] + (ff[v] * wa[1][v] + (fg[v] * wa[2][v] + (fo[v] * wa[3][v] + fd[v] * dm[v])));
-                            t = mfma(a, Q[0][0][v], t);
+                            if constexpr (CELL == LSTM) {
+                                m[v] = fa[v] * wa[0][v] + (fb[v] * wa[1][v] + fc[v] * wa[2][v]);
+                                n2[v] = fd[v] * wa[3][v];
+                            } else {
+                                m[v] = fa[v] * wa[0][v] + fb[v] * wa[2][v];
+                                n2[v] = fd[v] * wa[3][v];
+                                n3[v] = fc[v] * wa[1][v];
+                            }
                         }
-                        Q[0][0] = t;
+                        const auto lm = P::left(m), ln2 = P::left(n2);
+                        decltype(P::left(n3)) ln3;
+                        if constexpr (CELL == LEM) ln3 = P::left(n3);
+#pragma unroll
+                        for (int C = 0; C < NB; ++C) {
+                            Acc &Q0 = Q[0][C], &Q1 = Q[NB - 1][C];
+                            if constexpr (CELL == LSTM && !REV) {
+                                // Z = Q1 + e Q0;  Q0 <- (D U_o)^T Q0 + M^T Z,  Q1 <- f Z
+                                Acc z;
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) z[v] = Q1[v] + fe[v] * Q0[v];
+                                Q0 = P::add(lm, P::right(z), P::add(ln2, P::right(Q0), zero4()));
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) Q1[v] = ff[v] * z[v];
+                            } else if constexpr (CELL == LSTM) {
+                                // S1 <- f S1 + M S0,  S0 <- D U_o S0 + e S1
+                                Acc t, w;
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) t[v] = ff[v] * Q1[v];
+                                t = P::add(lm, P::right(Q0), t);
+                                w = P::add(ln2, P::right(Q0), zero4());
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) Q0[v] = w[v] + fe[v] * t[v];
+                                Q1 = t;
+                            } else if constexpr (!REV) {
+                                // Z = Q1 + (E U_y)^T Q0;  Q0 <- (1 - s2) Q0 + (F U_2)^T Q0 + M^T Z,  Q1 <- (1 - s1) Z
+                                Acc t;
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) t[v] = fe[v] * Q0[v];
+                                const auto q0 = P::right(Q0);
+                                const Acc z = P::add(ln2, q0, Q1);
+                                Q0 = P::add(lm, P::right(z), P::add(ln3, q0, t));
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) Q1[v] = ff[v] * z[v];
+                            } else {
+                                // S1 <- (1 - s1) S1 + M S0,  S0 <- (1 - s2) S0 + F U_2 S0 + E U_y S1
+                                Acc t, w;
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) {
+                                    t[v] = ff[v] * Q1[v];
+                                    w[v] = fe[v] * Q0[v];
+                                }
+                                t = P::add(lm, P::right(Q0), t);
+                                w = P::add(ln2, P::right(t), P::add(ln3, P::right(Q0), w));
+                                Q0 = w;
+                                Q1 = t;
+                            }
+                        }
                     } else {
-                        const Acc f0 = fac(0), f1 = fac(1), fd = fac(2);
-                        // factor of the second step: F in front of y, E in front of z
-                        Acc a1, a2;
+                        const Acc rv = rows(KINDS - 1);
+                        float s = SPLIT ? 0.f : vec[0];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int col = REV ? 4 * g + v : r;
-                            a2[v] = (col < 8 ? f0[v] : f1[v]) * wa[0][v] + (fd[v] * dm[v] + im[v]);
-                            a1[v] = f0[v] * wa[1][v] + (f1[v] * wa[2][v] + (fd[v] * im[v] + dm[v]));
-                        }
-                        Acc t = zero4(), w = zero4();
-                        if constexpr (!REV) {
+                        for (int v = 0; v < 4; ++v) s += Q[0][0][v] * rv[v];
+                        vec[0] = SPLIT ? vec[0] + s * scale[0].down : s;
+                        if constexpr (CELL == LSTM) {
+                            const Acc fi = fac(0), ff = fac(1), fg = fac(2), fo = fac(3), fd = fac(4);
+                            Acc a;
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) t = mfma(a2[v], Q[0][0][v], t);
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) w = mfma(a1[v], t[v], w);
+                            for (int v = 0; v < 4; ++v)
+                                a[v] = fi[v] * wa[0][v] + (ff[v] * wa[1][v] + (fg[v] * wa[2][v] + (fo[v] * wa[3][v] + fd[v] * dm[v])));
+                            Q[0][0] = P::add(P::left(a), P::right(Q[0][0]), zero4());
                         } else {
+                            const Acc f0 = fac(0), f1 = fac(1), fd = fac(2);
+                            // factor of the second step: F in front of y, E in front of z
+                            Acc a1, a2;
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) t = mfma(a1[v], Q[0][0][v], t);
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) w = mfma(a2[v], t[v], w);
+                            for (int v = 0; v < 4; ++v) {
+                                const int col = REV ? 4 * g + v : r;
+                                a2[v] = (col < 8 ? f0[v] : f1[v]) * wa[0][v] + (fd[v] * dm[v] + im[v]);
+                                a1[v] = f0[v] * wa[1][v] + (f1[v] * wa[2][v] + (fd[v] * im[v] + dm[v]));
+                            }
+                            const Acc t = P::add(P::left(REV ? a1 : a2), P::right(Q[0][0]), zero4());
+                            Q[0][0] = P::add(P::left(REV ? a2 : a1), P::right(t), zero4());
                         }
-                        Q[0][0] = w;
                     }
-                }
-                if (base + c == edge) {
-                    // the chunk's map: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
-                    float* o = tot + (long long)q * MS;
+                    if (base + c == edge) {
+                        // the chunk's map: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
+                        float* o = tot + (long long)q * MS;
+                        float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
-                    for (int C = 0; C < NB; ++C) {
+                        for (int C = 0; C < NB; ++C) {
 #pragma unroll
-                        for (int X = 0; X < NB; ++X) store4(o + (16 * C + r) * N + 16 * X + 4 * g, Q[X][C]);
-                        const float s = sum_groups(vec[C]);
-                        if (g == 0) o[N * N + 16 * C + r] = s;
+                            for (int X = 0; X < NB; ++X) {
+                                if (SPLIT)
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v) sum += 0.f * Q[X][C][v];
+                                Acc m = Q[X][C];
+                                if (SPLIT)
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v) m[v] = __builtin_amdgcn_ldexpf(m[v], -scale[C].e);
+                                store4(o + (16 * C + r) * N + 16 * X + 4 * g, m);
+                            }
+                            const float s = sum_groups(vec[C]);
+                            if (g == 0) o[N * N + 16 * C + r] = s;
+                        }
+                        again |= sum != 0.f;
+                        reset();
+                        q += REV ? 1 : -1;
+                        edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
                     }
-                    reset();
-                    q += REV ? 1 : -1;
-                    edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;
+                };
+#pragma unroll 2
+                for (int k = 0; k < c_hi - c_lo; ++k) {
+                    const int c = REV ? c_lo + k : c_hi - 1 - k;
+                    if (SPLIT && !wide) advance(std::bool_constant<SPLIT>{}, c);
+                    else advance(std::false_type{}, c);
                 }
+                wave_lds_fence();
             }
-            wave_lds_fence();
+            if (wide || !__ballot(again)) break;
+            wide = true;
+            unit_q = 1.f;
+            request(0);
         }
     }
     __syncthreads();

@@ -17,13 +17,14 @@
 // product split in two fp16 numbers (split_f16.h): a position costs 12 matrix instructions of 18 cycles and 120 vector instructions of 2.4 at n = 32 (3 and 40 at n =
 // 16) beside its share of the gates (60 fp32 matrix instructions for sixteen positions), in the place of 32 fp32 matrix instructions of 32 cycles and 72 (4 and 20).
 // Two wavefronts a SIMD (registers, LDS) issue in 71 % of the time.  Newton step, reduction alone, fp32 products before / now: n = 32, d = 8, 16 x 100,000
-// positions 1,128 / 734 us; n = 16, d = 6, 32 x 17,984 positions 88 / 68 us (the walk 303 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
+// positions 1,128 / 737 us; n = 16, d = 6, 32 x 17,984 positions 88 / 72 us (the walk 303 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
 // the factor of the next position behind the products of this one: 785 and 74 (20 more vector instructions a position).
 //
-// The split reduction: the entries of J and of the product (which starts from 16 I) are split as they are: what is lost of small ones is 2^-25 of the
-// largest that a correction can be multiplied by.  Corrections of the last step are below tol, so the trajectory does not see it (2-norm error against 64
-// bits 1.344e-7 with either, n = 32).  The dual scan, where the maps multiply the result itself, keeps fp32 products, and so do steps from far iterates.  A product that leaves the range
-// of fp16 (a chunk that expands 4,000 times) leaves infinities or NaN in the map; the wavefront then reduces its chunks again with fp32 products.
+// The split reduction: every column of the product has a power of two of its own, looked at before each sixteen positions (ColumnScale), so that what
+// decays keeps its digits; the entries of J are split as they are (what is lost of one is 2^-25 of the largest ones, which z or 1 - z bounds from below, and J's own
+// rounding is as large).  2-norm error of the trajectory against 64 bits 1.344e-7 with either product, n = 32.  The dual scan, where the maps
+// multiply the result itself, keeps fp32 products, and so do steps from far iterates.  A product that leaves the range of fp16 leaves infinities or NaN in the map; the
+// wavefront then reduces its chunks again with fp32 products.
 //
 // Everything is in correction form: with e = y_new - y the recurrence of a Newton step is e_i = J_i e_{i-1} + (f_i - y_i),
 // e_0 = 0, so neither J h nor a right-hand side is needed and rounding is relative to the correction.
@@ -34,8 +35,6 @@
 // X is the A operand of its transpose.
 #include "chunk_common.h"
 #include "split_f16.h"
-
-#include <type_traits>
 
 namespace deer {
 
@@ -104,19 +103,10 @@ __device__ __forceinline__ void w_row(float* o, const Weights<N, DS>& w, int gat
 // the row factors to the lanes that assemble J instead of its transpose); the row factors reach the assembly through an
 // LDS slice of the wavefront.
 // ------------------------------------------------------------------------------------------------------------------
-// one row block of a factor as operand A, split in two
-template <int N>
-__device__ __forceinline__ auto split_row(const float (&a)[N / 16][4]) {
-    if constexpr (N == 16) return split4(Acc{a[0][0], a[0][1], a[0][2], a[0][3]});
-    else return split8(Acc{a[0][0], a[0][1], a[0][2], a[0][3]}, Acc{a[1][0], a[1][1], a[1][2], a[1][3]});
-}
-
 template <int N, int DS, bool REV, bool FAR>
 __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(ChunkParams p) {
     constexpr int NB = N / 16, MS = map_size<N>();
     constexpr bool SPLIT = !FAR && !REV;
-    constexpr float kUnit = 16.f;
-    using Parts = typename std::conditional<N == 16, Split4, Split8>::type;
     __shared__ __align__(16) Weights<N, DS> sW;
     // forward: [kind: p_z, s_r, s_t, z, residual][position][row]; dual: [position][row][p_z, s_r, s_t, z], then [position][row] of g
     constexpr int PS = REV ? N : N + 4, KS = 16 * PS;   // (forward: sixteen positions' rows of 16 bytes fall on different banks)
@@ -179,13 +169,15 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 
     bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
     while (q_lo < q_hi) {
-        const float unit_q = wide ? 1.f : kUnit;
+        const float unit_q = wide ? 1.f : (float)(1 << ColumnScale::kStart);
         Acc Q[NB][NB];
         float vec[NB];
+        ColumnScale scale[NB];
         auto reset = [&]() {
 #pragma unroll
             for (int X = 0; X < NB; ++X) {
                 vec[X] = 0.f;
+                scale[X].reset(!wide);
 #pragma unroll
                 for (int C = 0; C < NB; ++C)
 #pragma unroll
@@ -199,6 +191,20 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 
         for (int blk = 0; blk < blocks; ++blk) {
             const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            if (SPLIT && !wide) {
+                // (in front of the gates: nothing waits for it there)
+#pragma unroll
+                for (int C = 0; C < NB; ++C) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int X = 0; X < NB; ++X)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(Q[X][C][v]));
+                    const float f = scale[C].next(max_groups(m));
+#pragma unroll
+                    for (int X = 0; X < NB; ++X) Q[X][C] *= f;
+                }
+            }
             // ---- gates of the sixteen positions ----
             if constexpr (!REV) {
 #pragma unroll
@@ -335,19 +341,18 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
             auto add_vector = [&](const Acc (&rv)[NB]) {
 #pragma unroll
                 for (int C = 0; C < NB; ++C) {
-                    float s = vec[C];
+                    float s = SPLIT ? 0.f : vec[C];
 #pragma unroll
                     for (int K = 0; K < NB; ++K)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) s += Q[K][C][v] * rv[K][v];
-                    vec[C] = s;
+                    vec[C] = SPLIT ? vec[C] + s * scale[C].down : s;
                 }
             };
             // at the end of a chunk its map leaves: M[16 C + r][16 X + 4g + v] = Q[X][C][v]
             auto finish = [&](int c) {
                 if (base + c != edge) return;
                 float* o = tot + (long long)q * MS;
-                const float down = wide ? 1.f : 1.f / kUnit;
                 float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
                 for (int C = 0; C < NB; ++C) {
@@ -356,9 +361,13 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
                         if (SPLIT)
 #pragma unroll
                             for (int v = 0; v < 4; ++v) sum += 0.f * Q[X][C][v];
-                        store4(o + (16 * C + r) * N + 16 * X + 4 * g, Q[X][C] * down);
+                        Acc m = Q[X][C];
+                        if (SPLIT)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) m[v] = __builtin_amdgcn_ldexpf(m[v], -scale[C].e);
+                        store4(o + (16 * C + r) * N + 16 * X + 4 * g, m);
                     }
-                    const float s = sum_groups(vec[C]) * down;
+                    const float s = sum_groups(vec[C]);
                     if (g == 0) o[N * N + 16 * C + r] = s;
                 }
                 again |= sum != 0.f;
@@ -373,20 +382,24 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
                 assemble(at(k), a, rv);
                 add_vector(rv);
                 if (SPLIT && !wide) {
-                    Parts A[NB], B[NB];
+                    auto row = [&](int X, int Y) { return Acc{a[X][Y][0], a[X][Y][1], a[X][Y][2], a[X][Y][3]}; };
+                    if constexpr (N == 16) {
+                        Qn[0][0] = split_product(split4(row(0, 0)), split4(Q[0][0]), zero4());
+                    } else {
+                        Split8 A[NB], B[NB];
 #pragma unroll
-                    for (int X = 0; X < NB; ++X) {
-                        A[X] = split_row<N>(a[X]);
-                        if constexpr (N == 16) B[X] = split4(Q[0][X]);
-                        else B[X] = split8(Q[0][X], Q[NB - 1][X]);
+                        for (int X = 0; X < NB; ++X) {
+                            A[X] = split8(row(X, 0), row(X, NB - 1));
+                            B[X] = split8(Q[0][X], Q[NB - 1][X]);
+                        }
+#pragma unroll
+                        for (int part = 0; part < 3; ++part)
+#pragma unroll
+                            for (int X = 0; X < NB; ++X)
+#pragma unroll
+                                for (int C = 0; C < NB; ++C)
+                                    Qn[X][C] = mfma16(part == 0 ? A[X].lo : A[X].hi, part == 1 ? B[C].lo : B[C].hi, part == 0 ? zero4() : Qn[X][C]);
                     }
-#pragma unroll
-                    for (int part = 0; part < 3; ++part)
-#pragma unroll
-                        for (int X = 0; X < NB; ++X)
-#pragma unroll
-                            for (int C = 0; C < NB; ++C)
-                                Qn[X][C] = mfma16(part == 0 ? A[X].lo : A[X].hi, part == 1 ? B[C].lo : B[C].hi, part == 0 ? zero4() : Qn[X][C]);
                 } else {
 #pragma unroll
                     for (int X = 0; X < NB; ++X)

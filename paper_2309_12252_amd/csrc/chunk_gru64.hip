@@ -7,7 +7,7 @@
 // Bound: the reduction of a Newton step has its factors split in two fp16 numbers like that at n = 32 (chunk_gru.hip; wavefronts split the
 // quarter that they assemble): 24 matrix instructions of 18 cycles a wavefront and position and about 110 vector instructions of 2.4, then the barrier and the LDS
 // (one workgroup a compute unit at 5 x 9,973 positions: 2,100 cycles a position).  The dual scan and far iterates: 64 fp32 matrix
-// instructions of 32 cycles.  Reduction of a step at 5 x 9,973 positions, d = 7: 307 us with fp32 products, now 184.
+// instructions of 32 cycles.  Reduction of a step at 5 x 9,973 positions, d = 7: 307 us with fp32 products, now 177.
 #include "chunk_common.h"
 #include "split_f16.h"
 
@@ -75,7 +75,6 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     __shared__ __align__(16) Acc sJ[2][NB * NB][64];
     __shared__ unsigned s_again[4];
     constexpr bool SPLIT = !FAR && !REV;
-    constexpr float kUnit = 16.f;
     if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
@@ -122,9 +121,11 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     Acc Q[NB];   // columns 16 w + r of the running product, rows 16 X + 4g + v
     float vec = 0.f;
     bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
-    float unit_q = wide ? 1.f : kUnit;
+    ColumnScale scale;
     auto reset = [&]() {
         vec = 0.f;
+        scale.reset(!wide);
+        const float unit_q = wide ? 1.f : (float)(1 << ColumnScale::kStart);
 #pragma unroll
         for (int X = 0; X < NB; ++X)
 #pragma unroll
@@ -144,9 +145,9 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
                 for (int v = 0; v < 4; ++v)
                     a[v] = pz[v] * ua[1][X][v] + (sr[v] * ua[2][X][v] + (st[v] * ua[0][X][v] + diag * dsel[v] * z[v]));
                 if (SPLIT && !wide) {
-                    const Split4 h4 = split4(a);
-                    reinterpret_cast<Half4*>(parts(buf, wave >> 1, X, 0) + lane)[wave & 1] = h4.hi;
-                    reinterpret_cast<Half4*>(parts(buf, wave >> 1, X, 1) + lane)[wave & 1] = h4.lo;
+                    const Split4 s = split4(a);
+                    reinterpret_cast<Half4*>(parts(buf, wave >> 1, X, 0) + lane)[wave & 1] = s.hi;
+                    reinterpret_cast<Half4*>(parts(buf, wave >> 1, X, 1) + lane)[wave & 1] = s.lo;
                 } else {
                     sJ[buf][X * NB + wave][lane] = a;
                 }
@@ -171,6 +172,16 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
         int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
         for (int blk = 0; blk < blocks; ++blk) {
             const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            if (SPLIT && !wide) {
+                float m = 0.f;
+#pragma unroll
+                for (int X = 0; X < NB; ++X)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(Q[X][v]));
+                const float f = scale.next(max_groups(m));
+#pragma unroll
+                for (int X = 0; X < NB; ++X) Q[X] *= f;
+            }
             {
                 GruGates k[4];
                 gates16<DS>(k, gr, h, x, wave == 0 ? h[0] : wave == 1 ? h[1] : wave == 2 ? h[2] : h[3]);
@@ -212,12 +223,14 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
             for (int k = 0; k < cnt; ++k) {
                 const int c = REV ? c_lo + k : c_hi - 1 - k;
                 if (k + 1 < cnt) assemble((k + 1) & 1, REV ? c + 1 : c - 1);
+                float sum_r = SPLIT ? 0.f : vec;
 #pragma unroll
                 for (int K = 0; K < NB; ++K) {
                     const Acc rv = load4(sR + c * N + 16 * K + 4 * g);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) vec += Q[K][v] * rv[v];
+                    for (int v = 0; v < 4; ++v) sum_r += Q[K][v] * rv[v];
                 }
+                vec = SPLIT ? vec + sum_r * scale.down : sum_r;
                 Acc Qn[NB];
 #pragma unroll
                 for (int X = 0; X < NB; ++X) Qn[X] = zero4();
@@ -253,17 +266,20 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
                 if (base + c == edge) {
                     // the chunk's map: M[16 w + r][16 X + 4g + v] = Q[X][v]
                     float* o = tot + (long long)q * MS;
-                    const float down = wide ? 1.f : 1.f / kUnit;
                     float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
                     for (int X = 0; X < NB; ++X) {
                         if (SPLIT)
 #pragma unroll
                             for (int v = 0; v < 4; ++v) sum += 0.f * Q[X][v];
-                        store4(o + (16 * wave + r) * N + 16 * X + 4 * g, Q[X] * down);
+                        Acc m = Q[X];
+                        if (SPLIT)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) m[v] = __builtin_amdgcn_ldexpf(m[v], -scale.e);
+                        store4(o + (16 * wave + r) * N + 16 * X + 4 * g, m);
                     }
                     again |= sum != 0.f;
-                    const float s = sum_groups(vec) * down;
+                    const float s = sum_groups(vec);
                     if (g == 0) o[N * N + 16 * wave + r] = s;
                     reset();
                     q += REV ? 1 : -1;
@@ -278,7 +294,6 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
         __syncthreads();
         if ((s_again[0] | s_again[1] | s_again[2] | s_again[3]) == 0u) break;   // (the same for the four wavefronts)
         wide = true;
-        unit_q = 1.f;
         request(0);
     }
 

@@ -60,11 +60,12 @@ __device__ __forceinline__ Split8 split8(F32x4 a, F32x4 b) {
 
 __device__ __forceinline__ F32x4 mfma16(Half8 a, Half8 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
-// the same for a contraction of 16, i.e. one accumulator
+// The same for a contraction of 16, i.e. one accumulator, with instructions for 16.  (Two of those for 32 that take (lo | hi) and (hi | lo) of A and (hi | lo) of B cost
+// four moves a factor more.  Never one for 16 after one for 32 on the same accumulator: the compiler puts no wait between two lengths, and
+// what it adds to is not there yet.)
 struct Split4 {
     Half4 hi, lo;
 };
-
 __device__ __forceinline__ Split4 split4(F32x4 x) {
     Split4 s;
     s.hi = __builtin_convertvector(x, Half4);
@@ -74,8 +75,9 @@ __device__ __forceinline__ Split4 split4(F32x4 x) {
     s.lo = __builtin_convertvector(r, Half4);
     return s;
 }
-
 __device__ __forceinline__ F32x4 mfma16(Half4 a, Half4 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0); }
+// c + A B
+__device__ __forceinline__ F32x4 split_product(const Split4& a, const Split4& b, F32x4 c) { return mfma16(a.hi, b.hi, mfma16(a.hi, b.lo, mfma16(a.lo, b.hi, c))); }
 
 // where entry (row, 32 s + c) of a matrix goes as operand A: lane, and the place among the lane's eight
 __device__ __forceinline__ int split_lane(int row, int c) { return 16 * ((c % 16) / 4) + row % 16; }
@@ -83,6 +85,27 @@ __device__ __forceinline__ int split_place(int c) { return 4 * (c / 16) + c % 4;
 
 // exponent e with |x| < 2^e (0 for 0, infinities and NaN)
 __device__ __forceinline__ int exponent(float x) { return __builtin_amdgcn_frexp_expf(x); }
+
+// A running product of split factors, Q <- A Q, whose columns are scaled by powers of two of their own: a column is 2^e times what it stands for.
+// Columns decay and grow along a chunk; below 2^-2 the lo parts of a split lose digits, above 65504 the hi parts overflow.
+struct ColumnScale {
+    static constexpr int kStart = 4;   // the product starts from 2^kStart I
+    int e;
+    float down;
+    __device__ __forceinline__ void reset(bool split) {
+        e = split ? kStart : 0;
+        down = split ? 1.f / (1 << kStart) : 1.f;
+    }
+    // does this lane's column, whose largest entry is m, want another scale (nothing to do for 0, infinities and NaN)
+    __device__ __forceinline__ bool off(float m) const { return (m < 8.f || m > 2048.f) && m > 0.f && m < __builtin_huge_valf(); }
+    // ... and the factor that goes to the column
+    __device__ __forceinline__ float next(float m) {
+        const int k = off(m) ? 7 - __builtin_amdgcn_frexp_expf(m) : 0;
+        e += k;
+        down = __builtin_amdgcn_ldexpf(1.f, -e);
+        return __builtin_amdgcn_ldexpf(1.f, k);
+    }
+};
 
 // largest of the four lane groups' values, in every lane
 __device__ __forceinline__ float max_groups(float x) {
