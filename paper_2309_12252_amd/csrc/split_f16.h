@@ -39,10 +39,18 @@ __device__ __forceinline__ unsigned split_lo(float a, float b, unsigned hi) {
     return split_hi(split_diff(a, h[0]), split_diff(b, h[1]));
 }
 
-// what the two parts leave out of a pair (exact: 0 or the last bit)
+// what the two parts leave out (exact: 0 or the last bit)
 __device__ __forceinline__ unsigned split_rest(float a, float b, unsigned hi, unsigned lo) {
     const Half2 h = __builtin_bit_cast(Half2, hi), l = __builtin_bit_cast(Half2, lo);
     return split_hi((a - (float)h[0]) - (float)l[0], (b - (float)h[1]) - (float)l[1]);
+}
+
+// the same of eight entries
+__device__ __forceinline__ Half8 split8_rest(F32x4 a, F32x4 b, Half8 hi, Half8 lo) {
+    F32x8 x = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = (x[i] - (float)hi[i]) - (float)lo[i];
+    return __builtin_convertvector(x, Half8);
 }
 
 // Two accumulators of 16 rows (rows 4g .. 4g + 3 of each in lane group g) as operand B of a contraction over those 32 rows: entry j
