@@ -414,6 +414,7 @@ hipError_t launch_mlp_vjp_mfma(const MlpVjpParams& p, hipStream_t s);
 // vector-Jacobian product with its reduction (partial rows = p.blocks, from mlp_general_vjp_blocks())
 bool mlp_general_supported(int n, int width, int nhid, int act);
 int mlp_general_vjp_blocks(int dtype, int n, int width, int nhid, long long points);
+hipError_t launch_mlp_split_funceval(const MlpParams& p, hipStream_t s);   // fp32, n = 8, width 32 or 64
 hipError_t launch_mlp_general_funceval(int dtype, const MlpParams& p, hipStream_t s);
 hipError_t launch_mlp_general_vjp(int dtype, const MlpVjpParams& p, hipStream_t s);
 // fixed-order sum of partial rows [rows][P] into out[P]

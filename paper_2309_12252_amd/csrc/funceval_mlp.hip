@@ -17,6 +17,8 @@
 // addresses (scalar loads).  fp32 with n = 8 runs on the matrix cores (mlp_funceval_mfma_kernel).
 #include "deer_common.h"
 
+#include <algorithm>
+
 namespace deer {
 
 namespace {
@@ -126,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void mlp_funceval_kernel(MlpParams p) {
     }
 }
 
-// ---- MLP field on the matrix cores (fp32, n = 8, hidden width a multiple of 16) ----
+// ---- MLP field on the matrix cores (fp32, n = 8, hidden width 16; widths 32 and 64: mlp_general.hip) ----
 //
 // A wavefront handles 16 grid points at a time.  All products run on v_mfma_f32_16x16x4f32; matrices
 // flow from one stage to the next in accumulator layout, which is directly a valid B operand (lane
@@ -136,18 +138,17 @@ __global__ __launch_bounds__(kThreads) void mlp_funceval_kernel(MlpParams p) {
 //   f  = W3 A2 + b3
 //   J   = W3 D2 W2 D1 W1, one column of the sixteen points' Jacobians at a time: the columns of the products stay
 //         the points, so D1 and D2 are already where they are needed;  z = f - J y from the columns
-// (two points x 8 columns in a product took a shuffle for every factor and a chain of its own for J y: width 32, 800,000 points
-// 234 us, now 211).  Width 16, where the Jacobians' way to memory weighs most, has four columns in work at a time and stores whole lines (pairs of
+// The Jacobians' way to memory weighs most: four columns are in work at a time and whole lines are stored (pairs of
 // columns in pieces of 8 bytes: a solve of 550,000 points took 1,590 us, now 1,400; with two points x 8 columns 1,435).
 // Rows 8..15 of the W3 products are padding (n = 8).
 typedef float mlp_acc __attribute__((ext_vector_type(4)));
 
-template <int WB, bool JONLY>   // hidden width / 16; JONLY: Jacobians only (z is written as zeros)
-// (width 16 and 32: four wavefronts per SIMD through the launch bounds -- the compiler's own choice of three,
+// JONLY: Jacobians only (z is written as zeros); four wavefronts per SIMD through the launch bounds (the compiler's own choice of three,
 // with part of the operands in accumulation registers, measured 8 % slower, five with spills 10 % slower)
-__global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_kernel(MlpParams p) {
+template <bool JONLY>
+__global__ __launch_bounds__(kThreads, 4) void mlp_funceval_mfma_kernel(MlpParams p) {
     if (gate_closed<float>(p.gate)) return;
-    constexpr int W = 16 * WB, N = 8, KC = WB == 1 ? 4 : 2;   // KC: columns of the Jacobians in work at a time
+    constexpr int WB = 1, W = 16 * WB, N = 8, KC = 4;   // KC: columns of the Jacobians in work at a time
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4, c = lane & 15;
     const float* __restrict__ th = reinterpret_cast<const float*>(p.theta);
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
     mlp_acc b3c;
     // W1 transposed: column k's factor of D1 W1 as 16-byte reads
     __shared__ __align__(16) float sW1[N][W];
-    __shared__ __align__(16) float sG[WB == 1 ? kThreads / 64 : 1][WB == 1 ? 16 * 68 : 4];
+    __shared__ __align__(16) float sG[kThreads / 64][16 * 68];
     for (int q = threadIdx.x; q < W * N; q += kThreads) sW1[q % N][q / N] = W1[q];
     __syncthreads();
 #pragma unroll
@@ -238,9 +239,9 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
 #pragma unroll
                 for (int v = 0; v < 4; ++v) f = __builtin_amdgcn_mfma_f32_16x16x4f32(w3a[K][v], a2[K][v], f, 0, 0, 0);
         }
-        // columns k .. k + KC - 1; width 16 stores whole rows at the end, wider ones a pair of columns at a time (registers)
-        mlp_acc rows[WB == 1 ? N : 1];
-#pragma unroll WB == 1 ? 2 : 1
+        // columns k .. k + KC - 1
+        mlp_acc rows[N];
+#pragma unroll 2
         for (int k = 0; k < N; k += KC) {
             float yk[KC];
             vload<float, KC>(yk, y + sc * N + k);
@@ -275,16 +276,10 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
             if constexpr (!JONLY)
 #pragma unroll
                 for (int j = 0; j < KC; j += 2) f -= jb[j] * yk[j] + jb[j + 1] * yk[j + 1];
-            if constexpr (WB == 1) {
 #pragma unroll
-                for (int j = 0; j < KC; ++j) rows[WB == 1 ? k + j : 0] = jb[j];
-            } else if (g < 2 && s0 + c < total) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    *reinterpret_cast<float2*>(G + ((s0 + c) * N + 4 * g + v) * N + k) = float2{-jb[0][v], -jb[1][v]};
-            }
+            for (int j = 0; j < KC; ++j) rows[k + j] = jb[j];
         }
-        if constexpr (WB == 1) {
+        {
             // the sixteen matrices cross a slice of LDS and leave as whole lines
             float* S = sG[threadIdx.x / 64];
             if (g < 2) {
@@ -292,7 +287,7 @@ __global__ __launch_bounds__(kThreads, WB <= 2 ? 4 : 1) void mlp_funceval_mfma_k
                 for (int v = 0; v < 4; ++v) {
                     float o[N];
 #pragma unroll
-                    for (int j = 0; j < N; ++j) o[j] = -rows[WB == 1 ? j : 0][v];
+                    for (int j = 0; j < N; ++j) o[j] = -rows[j][v];
                     vstore<float, N>(S + c * 68 + (4 * g + v) * N, o);
                 }
             }
@@ -672,21 +667,12 @@ hipError_t launch_dual_s(const OdeDualParams& p, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_mlp_funceval(int dtype, const MlpParams& p, hipStream_t s) {
-    if (dtype == 0 && p.n == 8 && (p.width == 16 || p.width == 32 || p.width == 64)) {
+    if (dtype == 0 && p.n == 8 && (p.width == 32 || p.width == 64)) return launch_mlp_split_funceval(p, s);
+    if (dtype == 0 && p.n == 8 && p.width == 16) {
         const long long nblk = ((long long)p.B * p.T + 15) / 16;   // one wavefront per 16 grid points
-        long long blocks = (nblk + 3) / 4;
-        if (blocks > 256 * 4) blocks = 256 * 4;
-        if (blocks < 1) blocks = 1;
-        dim3 grid((unsigned)blocks), blk(kThreads);
-        if (p.jac_only) {
-            if (p.width == 16) hipLaunchKernelGGL((mlp_funceval_mfma_kernel<1, true>), grid, blk, 0, s, p);
-            else if (p.width == 32) hipLaunchKernelGGL((mlp_funceval_mfma_kernel<2, true>), grid, blk, 0, s, p);
-            else hipLaunchKernelGGL((mlp_funceval_mfma_kernel<4, true>), grid, blk, 0, s, p);
-        } else {
-            if (p.width == 16) hipLaunchKernelGGL((mlp_funceval_mfma_kernel<1, false>), grid, blk, 0, s, p);
-            else if (p.width == 32) hipLaunchKernelGGL((mlp_funceval_mfma_kernel<2, false>), grid, blk, 0, s, p);
-            else hipLaunchKernelGGL((mlp_funceval_mfma_kernel<4, false>), grid, blk, 0, s, p);
-        }
+        const dim3 grid((unsigned)std::max(std::min((nblk + 3) / 4, 256LL * 4), 1LL)), blk(kThreads);
+        if (p.jac_only) hipLaunchKernelGGL((mlp_funceval_mfma_kernel<true>), grid, blk, 0, s, p);
+        else hipLaunchKernelGGL((mlp_funceval_mfma_kernel<false>), grid, blk, 0, s, p);
         return hipGetLastError();
     }
     return dtype == 0 ? launch_mlp_s<float>(p, s) : launch_mlp_s<double>(p, s);

@@ -89,9 +89,18 @@ __host__ __device__ inline long long gen_theta_len(int n, int w, int L) { return
 // third layer of four or five.
 // Bound: issue, matrix and vector instructions in turn: a layer of the Jacobians at width 64 takes 8 x 24 matrix instructions of 18 cycles and 8
 // x 48 vector instructions of 2.4 for 16 points.  At five layers of 64 and 160,000 points 464 us with fp32 instructions of 32 cycles, 203 us
-// now.  Errors there against 64 bits (mean of 30 solves, 5,000 points to a sequence): trajectory 2.74e-8 to 2.84e-8, dL/dtheta 9.1e-7 to
+// now; two layers of 32 and 800,000 points 214 us, now 120.  Errors against 64 bits, five layers of 64 (mean of 30 solves, 5,000 points to a sequence): trajectory 2.74e-8 to 2.84e-8, dL/dtheta 9.1e-7 to
 // 8.9e-7, dL/dy0 1.21e-6 to 1.22e-6.
 typedef float gacc __attribute__((ext_vector_type(4)));
+
+// the LDS slice of a wavefront is written and read by its own lanes only: LDS operations of a wavefront complete in order,
+// the fence keeps the compiler from moving them
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 
 // softplus and its derivative (the logistic function) from one exp2, one log2 and one reciprocal of the hardware:
 // absolute errors below 3e-7
@@ -110,6 +119,9 @@ __device__ __forceinline__ void fast_act(int kind, float pre, float& a, float& d
 // LDS: W_1 and the biases as they are, the others as parts of operand A (hidden layers: [layer][rows / 16][columns / 32][hi, lo,
 // rest], W_out: [columns / 32] with its hi part as rows 0..7 and its lo part as rows 8..15), 64 lanes x 8 entries each.  The rest of a weight
 // (0 or its last bit) is for the values only: what the split leaves out would be the same error of the field at every point.
+constexpr int field_threads(int WB) { return WB == 2 ? 256 : 512; }   // largest workgroup
+constexpr int kJacStride = 68;
+
 template <int WB, int L>
 struct FieldLds {
     static constexpr int W = 16 * WB, KS = WB / 2, W1S = W + 4;
@@ -117,14 +129,13 @@ struct FieldLds {
     Half8 out[KS][64];
     float w1[8][W1S];     // W_1 transposed
     float bias[L][W], bias_out[16];
+    float jac[field_threads(WB) / 64][16 * kJacStride];   // per wavefront: Jacobians of sixteen points, rows of 8
     unsigned top[L + 1];  // largest entry of W_1, W_2 .. W_L, W_out (raw bits)
     unsigned row[L];      // largest sum of a row's magnitudes of W_2 .. W_L (raw bits; entry 0 unused)
 };
 
-constexpr int kFieldThreads = 512;
-
 template <int WB, int L>
-__global__ __launch_bounds__(kFieldThreads, 2) void mlp_gen_funceval_mfma_kernel(MlpParams p) {
+__global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_funceval_mfma_kernel(MlpParams p) {
     if (gate_closed<float>(p.gate)) return;
     constexpr int W = 16 * WB, N = 8, KS = WB / 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -386,11 +397,17 @@ __global__ __launch_bounds__(kFieldThreads, 2) void mlp_gen_funceval_mfma_kernel
                 jc[v] = __builtin_amdgcn_ldexpf(__uint_as_float(q[0]) + __uint_as_float(q[1]), e);
                 f[v] -= jc[v] * yk;
             }
-            if (s0 + c < total) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) G[((s0 + c) * N + 4 * (g & 1) + v) * N + k + (g >> 1)] = -jc[v];
-            }
+            for (int v = 0; v < 4; ++v) lds.jac[tid >> 6][c * kJacStride + (4 * (g & 1) + v) * N + k + (g >> 1)] = -jc[v];
         }
+        // the sixteen matrices leave as whole lines (in pieces of 4 bytes, as they come, two layers of 32 took 176 us for 800,000 points)
+        wave_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pt = 4 * i + g;
+            if (s0 + pt < total) *reinterpret_cast<gacc*>(G + (s0 + pt) * 64 + 4 * c) = *reinterpret_cast<const gacc*>(&lds.jac[tid >> 6][pt * kJacStride + 4 * c]);
+        }
+        wave_fence();
         if (!p.jac_only) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -413,10 +430,10 @@ hipError_t launch_fe_mfma_wl(const MlpParams& p, hipStream_t s) {
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    // one wavefront per SIMD while there are no more blocks of points than SIMDs, then two (width 32: four) that share the weights
+    // one wavefront per SIMD while there are no more blocks of points than SIMDs, then two that share the weights (width 32: up to four)
     const long long nblk = ((long long)p.B * p.T + 15) / 16;
-    const unsigned threads = nblk > 1024 ? kFieldThreads : kFieldThreads / 2, waves = threads / 64;
-    const long long blocks = std::min((nblk + waves - 1) / waves, WB == 2 ? 512LL : 256LL);
+    const unsigned threads = nblk > 1024 ? field_threads(WB) : 256, waves = threads / 64;
+    const long long blocks = std::min((nblk + waves - 1) / waves, WB == 2 ? 1024LL : 256LL);
     hipLaunchKernelGGL((mlp_gen_funceval_mfma_kernel<WB, L>), dim3((unsigned)std::max(blocks, 1LL)), dim3(threads), shmem, s, p);
     return hipGetLastError();
 }
@@ -1081,8 +1098,13 @@ hipError_t launch_mlp_general_funceval(int dtype, const MlpParams& p, hipStream_
     // fp32, n = 8, width 32 or 64: on the matrix cores (DEER_MLP_MFMA=0 keeps the vector-ALU kernel)
     const char* e = getenv("DEER_MLP_MFMA");   // (read per call: the tests run both kernels in one process)
     const bool mfma = !(e && *e && atoi(e) == 0);
-    if (mfma && fe_mfma_supported(dtype, p.n, p.width, p.nhid)) return p.width == 32 ? launch_fe_mfma_w<2>(p, s) : launch_fe_mfma_w<4>(p, s);
+    if (mfma && fe_mfma_supported(dtype, p.n, p.width, p.nhid)) return launch_mlp_split_funceval(p, s);
     return dtype == 0 ? launch_fe<float>(p, s) : launch_fe<double>(p, s);
+}
+
+hipError_t launch_mlp_split_funceval(const MlpParams& p, hipStream_t s) {
+    if (!fe_mfma_supported(0, p.n, p.width, p.nhid)) return hipErrorInvalidValue;
+    return p.width == 32 ? launch_fe_mfma_w<2>(p, s) : launch_fe_mfma_w<4>(p, s);
 }
 
 hipError_t launch_mlp_general_vjp(int dtype, const MlpVjpParams& p, hipStream_t s) {
