@@ -371,9 +371,15 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
 
 // Step t of a chunk needs all rows of the state and of the correction (dual: of the state and of the three weighted
 // cotangents) from the four wavefronts.
-template <int DS, bool REV>
+// SPLIT (not from far iterates): the products with the state and the correction have their factors split in two fp16 numbers, as in the walk at n = 32
+// (chunk_gru.hip).  The wavefronts split their rows and hand the parts round; a column's scale needs the largest entry of all four, which takes
+// a second barrier a step.  5 x 9,973 positions, d = 7: 142 us with fp32 products (102 instructions of 32 cycles a step and wavefront), now 118
+// (6 of those and 42 of 18); 2-norm error of the trajectory against 64 bits 1.55e-7, now 1.48e-7 (n = 64).
+template <int DS, bool REV, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     constexpr int KINDS = REV ? 4 : 2;
+    static_assert(!(SPLIT && REV), "");
+    __shared__ float sM[2][4][16];   // largest entry of a column among a wavefront's rows: state, correction
     __shared__ __align__(16) Acc sX[2][KINDS][NB][64];   // [step parity][state, then correction or weighted cotangents][wavefront][lane]
     __shared__ __align__(16) float sx[2][N];
     __shared__ unsigned s_max[4];
@@ -417,6 +423,31 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     }
     GateRows<DS> gr;
     load_gate_rows<DS>(gr, p.theta, d, wave, g, r);
+    Half8 uh[SPLIT ? 3 : 1][2], ul[SPLIT ? 3 : 1][2], um[SPLIT ? 3 : 1][2];   // parts of U_gate 2^eu with entries below 2^8
+    int eu = 0;
+    if constexpr (SPLIT) {
+        float m = 0.f;
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int K = 0; K < NB; ++K)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(gr.u[gate][K][v]));
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        eu = min(8 - exponent(max_groups(m)), 100);
+        const float up = __builtin_amdgcn_ldexpf(1.f, eu);
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const Acc x = gr.u[gate][2 * q] * up, y = gr.u[gate][2 * q + 1] * up;
+                const Split8 s = split8(x, y);
+                uh[gate][q] = s.hi;
+                ul[gate][q] = s.lo;
+                um[gate][q] = split8_rest(x, y, s.hi, s.lo);
+            }
+    }
     Acc ut[REV ? 3 : 1][NB];   // dual: rows 16 w + r of U_gate^T
     if constexpr (REV) {
         const float* __restrict__ U = p.theta + 3 * N * d;
@@ -508,24 +539,109 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
         if (far) e = xv - yr[R - 1];
     }
     unsigned emax = 0u;   // largest |y_new - y| as raw bits (a NaN compares above everything)
-    sX[0][0][wave][lane] = yr[REV ? 0 : R - 1];
-    if constexpr (!REV) sX[0][1][wave][lane] = e;
-    __syncthreads();
+    float down_h = 1.f, down_e = 1.f;
+    // this wavefront's rows of the state and of the correction to all four (split: [hi, lo][column blocks / 2][lane], two wavefronts to a block of 16 bytes)
+    auto publish = [&](int buf, const Acc& h, const Acc& c) {
+        if constexpr (SPLIT) {
+            float mh = 0.f, mc = 0.f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                mh = fmaxf(mh, fabsf(h[v]));
+                mc = fmaxf(mc, fabsf(c[v]));
+            }
+            mh = max_groups(mh);
+            mc = max_groups(mc);
+            if (g == 0) {
+                sM[0][wave][r] = mh;
+                sM[1][wave][r] = mc;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                mh = fmaxf(mh, sM[0][w][r]);
+                mc = fmaxf(mc, sM[1][w][r]);
+            }
+            const int kh = min(13 - exponent(mh), 100), kc = min(13 - exponent(mc), 100);
+            const Split4 hs = split4(h * __builtin_amdgcn_ldexpf(1.f, kh)), cs = split4(c * __builtin_amdgcn_ldexpf(1.f, kc));
+            auto put = [&](int kind, int part, Half4 x) { reinterpret_cast<Half4*>(&sX[buf][kind][2 * part + (wave >> 1)][lane])[wave & 1] = x; };
+            put(0, 0, hs.hi);
+            put(0, 1, hs.lo);
+            put(KINDS - 1, 0, cs.hi);
+            put(KINDS - 1, 1, cs.lo);
+            down_h = __builtin_amdgcn_ldexpf(1.f, -kh - eu);
+            down_e = __builtin_amdgcn_ldexpf(1.f, -kc - eu);
+        } else {
+            sX[buf][0][wave][lane] = h;
+            if constexpr (!REV) sX[buf][1][wave][lane] = c;
+        }
+        __syncthreads();
+    };
+    publish(0, yr[REV ? 0 : R - 1], e);
     for (int t0 = 0; t0 < Lc; t0 += R) {   // Lc is a multiple of four
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int t = t0 + j, rel = REV ? a + Lc - 1 - t : a + t;
             const bool live = rel < end;
             const int cur = j & 1, nxt = cur ^ 1;
-            Acc h[NB];
-#pragma unroll
-            for (int K = 0; K < NB; ++K) h[K] = sX[cur][0][K][lane];
             GruGates k[4];
             const Acc hw = yr[REV ? j : (j + R - 1) % R];
-            gates16<DS>(k, gr, h, xr[j], hw);
+            Half8 eh[2], el[2];
+            if constexpr (SPLIT) {
+                Half8 hh[2], hl[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    hh[q] = __builtin_bit_cast(Half8, sX[cur][0][q][lane]);
+                    hl[q] = __builtin_bit_cast(Half8, sX[cur][0][2 + q][lane]);
+                    eh[q] = __builtin_bit_cast(Half8, sX[cur][KINDS - 1][q][lane]);
+                    el[q] = __builtin_bit_cast(Half8, sX[cur][KINDS - 1][2 + q][lane]);
+                }
+                Acc a[4] = {gr.b[0], gr.b[1], gr.b[3], gr.b[2]};   // r, z, the candidate's hidden part, its input part
+#pragma unroll
+                for (int gate = 0; gate < 3; ++gate) {
+                    Acc t = zero4();
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        t = mfma16(um[gate][q], hh[q], t);
+                        t = mfma16(ul[gate][q], hh[q], t);
+                        t = mfma16(uh[gate][q], hl[q], t);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) t = mfma16(uh[gate][q], hh[q], t);
+                    a[gate] += t * down_h;
+                }
+#pragma unroll
+                for (int s = 0; s < DS; ++s) {
+                    a[0] = mfma(gr.w[0][s], xr[j][s], a[0]);
+                    a[1] = mfma(gr.w[1][s], xr[j][s], a[1]);
+                    a[3] = mfma(gr.w[2][s], xr[j][s], a[3]);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) k[v] = gru_gates(a[0][v], a[1][v], a[3][v], a[2][v], hw[v]);
+            } else {
+                Acc h[NB];
+#pragma unroll
+                for (int K = 0; K < NB; ++K) h[K] = sX[cur][0][K][lane];
+                gates16<DS>(k, gr, h, xr[j], hw);
+            }
             Acc y;
             if constexpr (!REV) {
                 Acc er = zero4(), ez = zero4(), ec = zero4();
+                if constexpr (SPLIT) {
+                    auto correction = [&](int gate) {
+                        Acc t = zero4();
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            t = mfma16(ul[gate][q], eh[q], t);
+                            t = mfma16(uh[gate][q], el[q], t);
+                        }
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) t = mfma16(uh[gate][q], eh[q], t);
+                        return t * down_e;
+                    };
+                    er = correction(0);
+                    ez = correction(1);
+                    ec = correction(2);
+                } else
 #pragma unroll
                 for (int K = 0; K < NB; ++K) {
                     const Acc ek = sX[cur][1][K][lane];
@@ -545,9 +661,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                     e[v] = y[v] - yr[j][v];
                     emax = max(emax, __float_as_uint(e[v]) & mask);
                 }
-                sX[nxt][0][wave][lane] = yr[j];
-                sX[nxt][1][wave][lane] = e;
-                __syncthreads();
+                publish(nxt, yr[j], e);
             } else {
                 // lambda_pos = g_pos + J_{pos+1}^T lambda_{pos+1}
                 Acc lz, lc, lr;
@@ -607,7 +721,9 @@ hipError_t launch_ds(const ChunkParams& p, hipStream_t s) {
     else hipLaunchKernelGGL((chunk_totals64_kernel<DS, REV, false>), units, dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((chunk_walk64_kernel<DS, REV>), dim3((unsigned)((long long)p.B * p.groups)), dim3(256), 0, s, p);
+    const dim3 groups((unsigned)((long long)p.B * p.groups));
+    if (!REV && !p.far) hipLaunchKernelGGL((chunk_walk64_kernel<DS, REV, !REV>), groups, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((chunk_walk64_kernel<DS, REV, false>), groups, dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
