@@ -31,7 +31,7 @@ struct Column {
     int head, level, gi, gpr;   // (uniform) head, its stride level, group within its recurrence, groups per recurrence
     int a, lim;                 // first position, one past the last that exists (0: no such chunk)
     int shift;                  // log2 of the stride
-    long long row;              // (b T + first time index) H + head
+    long long row;              // row of the first time index
     int b, r0;
 };
 
@@ -53,7 +53,7 @@ __device__ __forceinline__ Column column_of(const Chunk8Params& p, int id, int r
     c.lim = (b < p.B && c.a < len) ? len : 0;
     c.b = min(b, p.B - 1);
     c.r0 = r0;
-    c.row = ((long long)c.b * p.T + r0) * p.H + c.head;
+    c.row = (long long)c.b * p.T * p.H + (long long)r0 * p.time_rows + (long long)c.head * p.head_rows;
     return c;
 }
 
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256, 2) void chunk8_totals_kernel(Chunk8Params p) {
     const float* __restrict__ xb = p.x + c.row * d;
     const float* __restrict__ gb = REV ? p.g + c.row * N : nullptr;
     const float* __restrict__ y0b = p.y0 ? p.y0 + ((long long)c.b * p.H + c.head) * N : nullptr;
-    const unsigned sy = (unsigned)(p.H * N) << c.shift, sx = (unsigned)(p.H * d) << c.shift;
+    const unsigned sy = (unsigned)(p.time_rows * N) << c.shift, sx = (unsigned)(p.time_rows * d) << c.shift;
     const float* __restrict__ th = p.theta + (long long)c.head * p.P;
     float* __restrict__ F = sF[wave];
     float* __restrict__ V = F + 16 * 32;
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256, 3) void chunk8_walk_kernel(Chunk8Params p) {
         const float* __restrict__ yb = p.y + c.row * N;
         const float* __restrict__ xb = p.x + c.row * d;
         float* __restrict__ ob = p.out + c.row * N;
-        const unsigned sy = (unsigned)(p.H * N) << c.shift, sx = (unsigned)(p.H * d) << c.shift;
+        const unsigned sy = (unsigned)(p.time_rows * N) << c.shift, sx = (unsigned)(p.time_rows * d) << c.shift;
         const int last = max(c.lim, 1) - 1;
 
         // slot t mod R holds y at the position (the state in front of the next one) and the input of the cell the step evaluates
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256, 2) void chunk8_dual_kernel(Chunk8Params p) {
         const float* __restrict__ xb = p.x + c.row * d;
         const float* __restrict__ gb = p.g + c.row * N;
         float* __restrict__ dxb = p.dx ? p.dx + c.row * d : nullptr;
-        const unsigned sy = (unsigned)(p.H * N) << c.shift, sx = (unsigned)(p.H * d) << c.shift;
+        const unsigned sy = (unsigned)(p.time_rows * N) << c.shift, sx = (unsigned)(p.time_rows * d) << c.shift;
         const float* __restrict__ th = p.theta + (long long)c.head * p.P;
         const int last = max(c.lim, 1) - 1;
 
@@ -623,6 +623,20 @@ __global__ __launch_bounds__(256, 2) void chunk8_dual_kernel(Chunk8Params p) {
         p.partial[(long long)blockIdx.x * P + q] = (sT[0][q] + (&sT[0][0])[512 + q]) + ((&sT[0][0])[1024 + q] + (&sT[0][0])[1536 + q]);
 }
 
+// Transposed copies of x and of the iterates: rows of R scalars, heads and times change places.  A thread takes consecutive scalars of what is contiguous
+// on the caller's side ([B,T,H,R]); on the other one a row's pieces of lines meet in the L2.
+template <int V, bool BACK>
+__global__ __launch_bounds__(256) void heads_transpose_kernel(const float* __restrict__ src, float* __restrict__ dst, int T, int H, int R) {
+    using F = float __attribute__((ext_vector_type(V)));
+    const int words = H * R / V, t0 = blockIdx.x * 32, rows = min(32, T - t0), b = blockIdx.y;
+    for (int q = threadIdx.x; q < rows * words; q += 256) {
+        const int t = t0 + q / words, w = q % words, h = w / (R / V), r = w % (R / V);
+        const long long user = ((long long)b * T + t) * words + w, mine = (((long long)b * H + h) * T + t) * (R / V) + r;
+        if constexpr (BACK) reinterpret_cast<F*>(dst)[user] = reinterpret_cast<const F*>(src)[mine];
+        else reinterpret_cast<F*>(dst)[mine] = reinterpret_cast<const F*>(src)[user];
+    }
+}
+
 // dL/dtheta of a head: the rows of its workgroups in a fixed order (16 strided sums per parameter, then these in order)
 __global__ __launch_bounds__(256) void chunk8_reduce_kernel(Chunk8Params p) {
     __shared__ float part[16][17];
@@ -696,6 +710,19 @@ hipError_t launch_chunk_gru8(const Chunk8Params& p, hipStream_t s) {
     if (!chunk_gru8_supported(0, N, p.d, p.T, p.H) || p.groups < 4 || p.groups % 4 != 0 || p.levels < 1 || p.levels > 8) return hipErrorInvalidValue;
     if (p.g ? !p.partial || !p.dtheta : !p.out) return hipErrorInvalidValue;
     return p.d <= 4 ? launch8<1>(p, s) : launch8<2>(p, s);
+}
+
+hipError_t launch_heads_transpose(const void* src, void* dst, int B, int T, int H, int R, bool back, hipStream_t s) {
+    const float* in = reinterpret_cast<const float*>(src);
+    float* out = reinterpret_cast<float*>(dst);
+    const dim3 grid((unsigned)((T + 31) / 32), (unsigned)B);
+    // (the caller's arrays need no more than their scalars' alignment)
+    const bool wide = R % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
+    if (wide && back) hipLaunchKernelGGL((heads_transpose_kernel<4, true>), grid, dim3(256), 0, s, in, out, T, H, R);
+    else if (wide) hipLaunchKernelGGL((heads_transpose_kernel<4, false>), grid, dim3(256), 0, s, in, out, T, H, R);
+    else if (back) hipLaunchKernelGGL((heads_transpose_kernel<1, true>), grid, dim3(256), 0, s, in, out, T, H, R);
+    else hipLaunchKernelGGL((heads_transpose_kernel<1, false>), grid, dim3(256), 0, s, in, out, T, H, R);
+    return hipGetLastError();
 }
 
 }  // namespace deer

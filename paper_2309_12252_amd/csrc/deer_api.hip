@@ -60,6 +60,8 @@ struct Plan {
     bool chunk;          // GRU, n >= 16, LSTM and LEM in fp32: Newton steps (where `fused`) and the dual scan run by chunks (chunk_gru.hip, chunk_cells.hip)
     bool chunk_grad;     // their gradient takes the vector-Jacobian product into the walk
     int chunk_L, chunk_groups, chunk_per_unit, chunk_units;
+    bool head_major;            // multi-head by chunks: the Newton steps run on copies [B,heads,T,.] of x and the iterates
+    size_t off_yh, off_xh;
     bool chunk8, chunk8_grad;   // GRU, 8 channels, fp32, plain or multi-head: the Newton steps, the gradient (chunk_gru8.hip)
     Chunk8Params c8;     // their shapes and chunk lengths
     size_t off_tot, off_sup;
@@ -189,6 +191,16 @@ bool supported(const deer_config* c, std::string& why) {
         if (!(c->t1 > c->t0)) { why = "MLP_ODE needs t1 > t0"; return false; }
     }
     return true;
+}
+
+// Multi-head steps by chunks on copies [B,heads,T,.] of x and the iterates (two transpositions a solve and a synchronisation).  In the caller's layout
+// a line holds the rows of four heads, which meet it at other times where their strides differ: of 200 MB the walk fetches 500.  Copies pay where the
+// arrays are far larger than the L2s and there are three levels.  Microseconds a solve, caller's layout / copies (steps x heads, levels,
+// d): 1,112 / 898 at 64 x 1,024 x 32, 8, 8; 3,032 / 2,187 at 64 x 2,000 x 32, 4, 8; 530 / 495 at 24 x 1,024 x 32, 8, 8; 1,048 / 1,014 at 64 x 1,024 x 32, 3, 4; 702 /
+// 677 at 64 x 1,500 x 16, 4, 3 (rows of 3 scalars are transposed one by one); but 398 / 391 at 16 x 1,024 x 32, 8, 8, 416 / 417 at 20 x 1,024 x 32, 8, 4, 518 / 527 at 40 x
+// 1,800 x 12, 8, 7, 459 / 478 at 32 x 2,000 x 12, 5, 3, 548 / 552 at 64 x 2,000 x 8, 2, 8, 563 / 587 at 32 x 1,024 x 32, 2, 2.
+bool head_major_pays(const deer_config* c) {
+    return c->heads > 1 && c->stride_levels >= 3 && (long long)c->B * c->T * c->heads * (c->n + c->d) >= (c->d % 4 == 0 ? 12000000 : 16500000);
 }
 
 // Multi-head GRU: the tiles of one batch entry, head by head, recurrence by recurrence (first time index r < stride),
@@ -354,6 +366,9 @@ Plan make_plan(const deer_config* c, bool chunks = true) {
         auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
         p.off_J = take(0); p.off_rhs = take(0);
         p.off_ybuf = take(B * T * (size_t)H * n * p.esz);
+        p.head_major = p.chunk8 && head_major_pays(c);
+        p.off_yh = take(p.head_major ? B * T * (size_t)H * n * p.esz : 0);
+        p.off_xh = take(p.head_major ? B * T * (size_t)H * c->d * p.esz : 0);
         p.off_Gbar = take(0); p.off_zbar = take(0);
         const size_t nt = B * (size_t)p.fused_tiles;
         p.off_mhtable = take((size_t)p.fused_tiles * 4);
@@ -652,6 +667,7 @@ Chunk8Params chunk8_params(deer_ctx* c, const void* theta, const void* x, const 
     q.y0 = reinterpret_cast<const float*>(y0); q.y = reinterpret_cast<const float*>(y);
     q.tot = reinterpret_cast<float*>(c->ws + c->plan.off_tot);
     q.sup = reinterpret_cast<float*>(c->ws + c->plan.off_sup);
+    q.head_rows = 1; q.time_rows = q.H;
     return q;
 }
 
@@ -700,6 +716,7 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
         q.out = reinterpret_cast<float*>(out);
         q.err = p.err; q.gate = gate;
         q.far = c->far;
+        if (c->plan.head_major) { q.head_rows = q.T; q.time_rows = 1; }
         prof_begin(c, KIND_FUSED, iter);
         e = launch_chunk_gru8(q, c->stream);
     } else if (fused_theta && c->plan.mh) {
@@ -1000,12 +1017,19 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
     char* buf[2];
     buf[expect & 1] = reinterpret_cast<char*>(d_y);
     buf[(expect + 1) & 1] = c->ws + c->plan.off_ybuf;
+    if (c->plan.head_major) {
+        buf[expect & 1] = c->ws + c->plan.off_yh;
+        HIPCHK(c, launch_heads_transpose(d_x, c->ws + c->plan.off_xh, g.B, g.T, c->plan.mh_H, g.d, false, c->stream));
+        d_x = c->ws + c->plan.off_xh;
+    }
 
     deer_status st = DEER_OK;
     if (d_y_guess) {
         st = zero_ctl(c);
         if (st != DEER_OK) return st;
-        if (d_y_guess != buf[0])
+        if (c->plan.head_major)
+            HIPCHK(c, launch_heads_transpose(d_y_guess, buf[0], g.B, g.T, c->plan.mh_H, g.n, false, c->stream));
+        else if (d_y_guess != buf[0])
             HIPCHK(c, hipMemcpyAsync(buf[0], d_y_guess, ybytes, hipMemcpyDeviceToDevice, c->stream));
     } else {
         st = reserve_epochs(c, (unsigned)kSlots + 8u);
@@ -1100,7 +1124,10 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
     }
     if (it > 0) c->last_iters = it;
     char* fin = buf[it & 1];
-    if (fin != reinterpret_cast<char*>(d_y)) {
+    if (c->plan.head_major) {
+        HIPCHK(c, launch_heads_transpose(fin, d_y, g.B, g.T, c->plan.mh_H, g.n, true, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+    } else if (fin != reinterpret_cast<char*>(d_y)) {
         HIPCHK(c, hipMemcpyAsync(d_y, fin, ybytes, hipMemcpyDeviceToDevice, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
     }

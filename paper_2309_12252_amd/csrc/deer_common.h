@@ -130,6 +130,7 @@ struct Chunk8Params {
     int far;                   // as above
     long long P;               // parameters per head
     int B, T, d, H, levels;    // levels <= 8
+    int head_rows, time_rows;  // rows from head to head and from time to time: 1 and heads, or (Newton steps on transposed copies) T and 1
     int groups, map_groups;    // groups in all, and of the levels whose recurrences have more than one chunk (these come first)
     Chunk8Level lv[8];
 };
@@ -414,6 +415,8 @@ hipError_t launch_mlp_vjp_mfma(const MlpVjpParams& p, hipStream_t s);
 // vector-Jacobian product with its reduction (partial rows = p.blocks, from mlp_general_vjp_blocks())
 bool mlp_general_supported(int n, int width, int nhid, int act);
 int mlp_general_vjp_blocks(int dtype, int n, int width, int nhid, long long points);
+// [B,T,H,R] to [B,H,T,R] (back: the other way round), fp32
+hipError_t launch_heads_transpose(const void* src, void* dst, int B, int T, int H, int R, bool back, hipStream_t s);
 hipError_t launch_mlp_split_funceval(const MlpParams& p, hipStream_t s);   // fp32, n = 8, width 32 or 64
 hipError_t launch_mlp_general_funceval(int dtype, const MlpParams& p, hipStream_t s);
 hipError_t launch_mlp_general_vjp(int dtype, const MlpVjpParams& p, hipStream_t s);
