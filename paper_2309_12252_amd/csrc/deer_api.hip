@@ -230,14 +230,15 @@ std::vector<unsigned> mh_table(const deer_config* c, int tile) {
 // Positions per chunk (a multiple of four) and chunks per unit.  Estimate in microseconds of one step (measured on MI355X).  The
 // reduction: the workgroups of a compute unit one after the other, `total` for a position of each of sixteen chunks, `unit` and
 // `compose` per further chunk of a unit.  The walk: `walk` a position for the groups that run side by side, and `fold` for every map in
-// front of the last group.  The estimate's choice is within a tenth of the best of 33 combinations tried at each of 18 shapes.
+// front of the last group.  Of the lengths 4 to 64 and the three units, measured at 33 shapes (n = 16, 32, 64, LEM of 16 units), the estimate's choice is the fastest at all but
+// four of n = 16 (at most 5 % off); with the figures of fp32 products n = 32, n = 64 and the LEM were up to 13, 12 and 6 % off.
 // At most 64 positions: the product of a chunk's Jacobians then overflows no earlier than that of a tile of the single-pass scan (64 to 96
 // positions).  Longer chunks (64 x 100,000 positions would take 200) gain 1 to 3 % of a step by the estimate.
 int chunk_length(const deer_config* c, int* per_unit) {
-    struct Cost { double total, unit, compose, walk, fold; int side_by_side; };
+    struct Cost { double total, unit, compose, walk, fold; int side_by_side; double odd; };
     const bool cell = two_part_cell(c->cell);
-    const Cost k = cell ? (c->reserved <= 8 ? Cost{0.75, 1.5, 0.1, 1.2, 0.04, 1024} : Cost{1.6, 2.0, 0.35, 1.8, 0.1, 1024})
-                 : c->n == 16 ? Cost{0.66, 1.5, 0.1, 0.95, 0.04, 1024} : c->n == 32 ? Cost{2.5, 2.0, 0.35, 2.5, 0.1, 1024} : Cost{16.3, 4.0, 1.5, 1.9, 0.15, 256};
+    const Cost k = cell ? (c->reserved <= 8 ? Cost{0.75, 1.5, 0.1, 1.2, 0.04, 1024, 0.0} : Cost{1.3, 2.1, 0.36, 0.81, 0.107, 1024, 0.0})
+                 : c->n == 16 ? Cost{0.66, 1.5, 0.1, 0.95, 0.04, 1024, 0.0} : c->n == 32 ? Cost{1.7, 2.2, 0.53, 1.8, 0.2, 1024, 0.15} : Cost{11.0, 4.0, 1.56, 1.93, 0.45, 256, 0.3};
     const int forced = env_int("DEER_CHUNK_L", 0), forced_unit = env_int("DEER_CHUNK_UNIT", 0);
     int best_L = 4;
     *per_unit = 16;
@@ -249,10 +250,10 @@ int chunk_length(const deer_config* c, int* per_unit) {
             if (forced_unit >= 4 && pu != forced_unit) continue;
             const long long per_seq = ((long long)c->T + 16LL * L - 1) / (16LL * L), groups = per_seq * c->B;
             const long long units = ((long long)c->T + (long long)pu * L - 1) / ((long long)pu * L);
-            // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes 1.3 times as long as half of two, which is not seen any
-            // more from seven long ones on: n = 32, 16 x 100,000, 10,030 us a solve with units of 16 x 56 positions and 10,330 with twice as many of 8 x 56)
+            // (two workgroups of a compute unit overlap at n = 32 and 64; one alone takes longer than half of two, which is not seen any
+            // more from seven long ones on: n = 32, 16 x 100,000, units of 16 x 56 positions 4,570 us a solve, twice as many of 8 x 56 4,760)
             const long long share = (units * c->B + 255) / 256;
-            const double est = ((double)share + (!cell && c->n >= 32 && (share & 1) && (share < 6 || pu < 16) ? 0.3 : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
+            const double est = ((double)share + ((share & 1) && (share < 6 || pu < 16) ? k.odd : 0.0)) * (k.total * L * pu / 16 + k.unit + k.compose * (pu - 1)) +
                                (double)((groups + k.side_by_side - 1) / k.side_by_side) * k.walk * L + k.fold * (double)units;
             if (est < best) { best = est; best_L = L; *per_unit = pu; }
         }
@@ -262,8 +263,9 @@ int chunk_length(const deer_config* c, int* per_unit) {
 
 // Where a step by chunks is faster than the single-pass scan with the cell inside.  The scan's tiles (64 to 96 positions) spread a
 // small problem over more compute units than the chunks' groups (64 positions and more, two launches); its chain of tiles
-// grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 143 / 209 at 1 x 500, 259 / 304 at 20 x 1,000, 298 / 332 at
-// 10 x 2,500, 264 / 297 at 64 x 500, but 347 / 339 at 4 x 5,000, 797 / 504 at 1 x 20,000, 620 / 559 at 16 x 5,000, 663 / 545 at 60 x 1,500; n = 16
+// grows with the length.  Measured, microseconds a solve, scan / chunks: n = 32 145 / 160 at 1 x 500, 279 / 284 at 1 x 3,000, 208 / 256 at 10 x 1,000,
+// 288 / 304 at 4 x 3,000, but 403 / 356 at 1 x 6,000, 389 / 362 at 4 x 4,900, 321 / 303 at 20 x 1,000, 305 / 271 at 40 x 500, 367 / 339 at 10 x 2,500, 480 / 377 at 20 x
+// 2,000, 612 / 417 at 16 x 3,500; with d = 16 367 / 371 at 10 x 2,500 (gradient 189 / 153 at 1 x 12,000, 127 / 129 at 20 x 1,000, 195 / 166 at 16 x 3,500); n = 16
 // 130 / 142 at 20 x 783, 143 / 158 at 16 x 1,300, 157 / 165 at 64 x 500, 155 / 161 at 3 x 2,500, but 142 / 133 at 1 x 1,600, 188 / 158 at 1 x 5,000, 275 / 241 at 60 x 1,500.
 // Short sequences in large numbers gain most (a tile holds one sequence): n = 16 14,300 / 3,220 at 100,000 x 8, 253 / 173 at 1,000 x 50; n = 32 1,510 / 710 at
 // 4,096 x 28, 449 / 372 at 1,000 x 64.  At n = 64, where the scan reads stored Jacobians in tiles of eight positions, chunks are faster from the start:
@@ -272,7 +274,7 @@ bool chunk_pays(const deer_config* c) {
     if (env_int("DEER_CHUNK_L", 0) >= 4) return true;
     const long long total = (long long)c->B * c->T;
     if (c->n == 64) return true;
-    return c->n == 16 ? total >= 50000 || c->T >= 3000 || (c->B == 1 && c->T >= 1536) : total >= 60000 || (total >= 20000 && c->T >= 5000);
+    return c->n == 16 ? total >= 50000 || c->T >= 3000 || (c->B == 1 && c->T >= 1536) : total >= (c->d > 8 ? 30000 : 20000) || c->T >= 4500;
 }
 
 // Steps by chunks at 8 channels: positions per chunk, and whether the Newton step and the gradient go this way.
