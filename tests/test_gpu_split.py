@@ -3,8 +3,9 @@ can go wrong: remainders, weights far from one, activations far from one, zero l
 import numpy as np
 import pytest
 
+import oracle
 from paper_2309_12252_amd import deer, inputs
-from helpers import TOL_ABS
+from helpers import DEV, TOL_ABS, dev, host
 from test_gpu_ode import check, check_grad
 
 pytestmark = pytest.mark.gpu
@@ -74,3 +75,28 @@ def test_field_on_a_coarse_grid(width, nhid):
     w = inputs.mlp_ode_workload("coarse_w%d" % width, 77 + width, B=3, T=12, n=8, width=width, nhid=nhid, t0=0.0, t1=6.0, tol=1e-4)
     w.theta = (w.theta * 2.0).astype(np.float32)
     check(w, deer.DEER_F32)
+
+
+# Reduction by chunks: Jacobians whose entries lie beyond the range of fp16 (the chunk is reduced again with fp32 products), products that leave it within a
+# chunk, ordinary ones, and columns that lose 2^-10 a step.  One step from zero, every position against its own size: fp32 rounding grows by the conditioning of
+# up to eleven products (1e-7 each, some hundred times that where terms cancel).
+@pytest.mark.parametrize("n", [16, 32, 64, 27, 50])
+@pytest.mark.parametrize("scale,T", [(3.0e6, 5), (40.0, 11), (1.0, 300), (2.0 ** -9, 300)])
+@pytest.mark.parametrize("L", ["4", "8"])
+def test_range_of_the_reduction(n, scale, T, L, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", L)
+    d, B = 3, 3
+    w = inputs.gru_workload("range", 640 + n, B=B, T=T, n=n, d=d)
+    U = w.theta[3 * n * d:3 * n * d + 3 * n * n]
+    U *= np.float32(scale)
+    if scale < 1.0:
+        w.theta[3 * n * d + 3 * n * n + n:][:n] = -7.0   # z = 1e-3: nothing but small entries
+    want = oracle.deer_eval(oracle.make_cell(oracle.CELL_GRU, n, d), w.theta, w.x, w.y0, tol=w.tol, max_iter=1, nthreads=8)[0]
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        y = host(ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=1)[0])
+    finally:
+        ctx.close()
+    off = np.abs(y - want).max(axis=-1) / np.maximum(1.0, np.abs(want).max(axis=-1))
+    print(n, scale, L, "%.1e, iterate up to %.1e" % (off.max(), np.abs(want).max()), flush=True)
+    assert off.max() <= 1e-4
