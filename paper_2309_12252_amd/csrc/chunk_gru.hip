@@ -17,7 +17,7 @@
 // product split in two fp16 numbers (split_f16.h): a position costs 12 matrix instructions of 18 cycles and 120 vector instructions of 2.4 at n = 32 (3 and 40 at n =
 // 16) beside its share of the gates (60 fp32 matrix instructions for sixteen positions), in the place of 32 fp32 matrix instructions of 32 cycles and 72 (4 and 20).
 // Two wavefronts a SIMD (registers, LDS) issue in 71 % of the time.  Newton step, reduction alone, fp32 products before / now: n = 32, d = 8, 16 x 100,000
-// positions 1,128 / 737 us; n = 16, d = 6, 32 x 17,984 positions 88 / 72 us (the walk 303 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
+// positions 1,128 / 737 us; n = 16, d = 6, 32 x 17,984 positions 88 / 72 us (the walk 210 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
 // the factor of the next position behind the products of this one: 785 and 74 (20 more vector instructions a position).
 //
 // The split reduction: every column of the product has a power of two of its own, looked at before each sixteen positions (ColumnScale), so that what
