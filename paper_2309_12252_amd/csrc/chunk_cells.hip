@@ -13,10 +13,10 @@
 // (the products with U then contract over 8 entries in two instructions: lane groups 0, 1 supply two of their four
 // units, groups 2, 3 the other two), groups 0, 1 answer for the rows of the first part, 2, 3 for those of the second.
 //
-// Bound: issue (matrix and vector instructions of a SIMD do not overlap).  Above 8 units the reduction has the factors of its
-// products split in two fp16 numbers, as in chunk_gru.hip.  Measured, a Newton step (Jacobian kernel and scan before / both launches now): LSTM u
-// = 8, d = 4, 16 x 50,000 positions 710 / 180 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 290 us (reduction 304 with fp32 products, now 227; dual scan
-// 357 and 293).
+// Bound: issue (matrix and vector instructions of a SIMD do not overlap).  Above 8 units the reduction of a Newton step has the factors of its
+// products split in two fp16 numbers, as in chunk_gru.hip (the dual scan has fp32 products, for the reason given there).  Measured, a Newton step (Jacobian kernel and
+// scan before / both launches now): LSTM u = 8, d = 4, 16 x 50,000 positions 710 / 180 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 290 us (reduction 304 with
+// fp32 products, now 227).
 #include "chunk_common.h"
 #include "split_f16.h"
 
@@ -203,7 +203,7 @@ struct Product16 {
 template <int CELL, int UP, int DS, bool VEC, bool REV, bool FAR>
 __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
     constexpr int N = 2 * UP, NB = N / 16, MS = map_size<N>(), KINDS = Slice<CELL, UP>::kinds;
-    constexpr bool SPLIT = UP == 16 && !FAR;   // (a factor of 16 x 16 a position: the split costs what it saves, LSTM u = 8, 16 x 50,000, 120 us with fp32 products, 133)
+    constexpr bool SPLIT = UP == 16 && !FAR && !REV;   // (a factor of 16 x 16 a position: the split costs what it saves, LSTM u = 8, 16 x 50,000, 120 us with fp32 products, 133)
     __shared__ __align__(16) float sF[4][KINDS * 256];
     if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;

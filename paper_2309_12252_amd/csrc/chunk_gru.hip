@@ -13,19 +13,22 @@
 // Nothing in a launch waits for another workgroup, the number of wavefronts does not depend on the length (the chunk does),
 // and the state that travels between the two launches is one map per chunk.
 //
-// Bound: issue.  The matrix instructions and the vector ALU of a SIMD do not overlap.  The reduction has both factors of a
+// Bound: issue.  The matrix instructions and the vector ALU of a SIMD do not overlap.  The reduction of a Newton step has both factors of a
 // product split in two fp16 numbers (split_f16.h): a position costs 12 matrix instructions of 18 cycles and 120 vector instructions of 2.4 at n = 32 (3 and 40 at n =
 // 16) beside its share of the gates (60 fp32 matrix instructions for sixteen positions), in the place of 32 fp32 matrix instructions of 32 cycles and 72 (4 and 20).
 // Two wavefronts a SIMD (registers, LDS) issue in 71 % of the time.  Newton step, reduction alone, fp32 products before / now: n = 32, d = 8, 16 x 100,000
 // positions 1,128 / 737 us; n = 16, d = 6, 32 x 17,984 positions 88 / 72 us (the walk 210 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
 // the factor of the next position behind the products of this one: 785 and 74 (20 more vector instructions a position).
 //
-// The split reduction: every column of the product has a power of two of its own, looked at before each sixteen positions (ColumnScale), so that what
-// decays keeps its digits; the entries of J are split as they are (what is lost of one is 2^-25 of the largest ones, which z or 1 - z bounds from below, and J's own
-// rounding is as large).  2-norm errors against 64 bits, fp32 / split products (mean of 8 solves):
-// trajectory 1.344e-7 / 1.344e-7 (n = 32), 1.153e-7 / 1.153e-7 (n = 16), dL/dx 2.18e-7 / 2.15e-7, 1.77e-7 / 1.73e-7, dL/dtheta 2.84e-7 / 2.86e-7, 1.98e-7 /
-// 1.98e-7.  Steps from far iterates keep fp32 products.  A product that leaves the range of fp16 leaves infinities or NaN in the map; the
-// wavefront then reduces its chunks again with fp32 products.
+// The split reduction (Newton steps): every column of the product has a power of two of its own, looked at before each sixteen positions (ColumnScale).  The
+// entries of J are split as they are: an absolute error of 2^-25 each, and nothing of one below that; a column that falls by 2^-k between two looks
+// is known to 2^(k-28) of its largest entry at worst.  A step's maps multiply a correction, so what they lose is lost against the correction and the next step
+// takes it up: 2-norm errors of the trajectory against 64 bits, fp32 / split products (mean of 8 solves) 1.344e-7 / 1.344e-7 (n = 32), 1.153e-7 / 1.153e-7
+// (n = 16).  Steps from far iterates keep fp32 products.  A product that leaves the range of fp16 leaves infinities or NaN in the map; the wavefront then
+// reduces its chunks again with fp32 products.
+// The dual scan keeps fp32 products: its maps multiply the cotangent itself, which may have faded by many powers of ten when it reaches the first
+// positions.  With split products dL/dy0 of a loss on the last state had lost 3e-5 to 0.3 of itself behind chunks of 16 positions that keep 0.1 to 0.3 of
+// the state a step, and 1e-6 with fp32 ones.
 //
 // Everything is in correction form: with e = y_new - y the recurrence of a Newton step is e_i = J_i e_{i-1} + (f_i - y_i),
 // e_0 = 0, so neither J h nor a right-hand side is needed and rounding is relative to the correction.
@@ -107,7 +110,7 @@ __device__ __forceinline__ void w_row(float* o, const Weights<N, DS>& w, int gat
 template <int N, int DS, bool REV, bool FAR>
 __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(ChunkParams p) {
     constexpr int NB = N / 16, MS = map_size<N>();
-    constexpr bool SPLIT = !FAR;
+    constexpr bool SPLIT = !FAR && !REV;
     __shared__ __align__(16) Weights<N, DS> sW;
     // forward: [kind: p_z, s_r, s_t, z, residual][position][row]; dual: [position][row][p_z, s_r, s_t, z], then [position][row] of g
     constexpr int PS = REV ? N : N + 4, KS = 16 * PS;   // (forward: sixteen positions' rows of 16 bytes fall on different banks)

@@ -4,10 +4,10 @@
 //     every factor (the rows of J whose gates it has evaluated) into LDS in operand order, double-buffered, one barrier a
 //     position; all four read the whole factor (64 KB of LDS reads against 4 x 2,048 matrix-core cycles).
 //   walk: wavefront w evaluates rows 16 w .. 16 w + 15 of all products; the column vectors cross LDS, one barrier a step.
-// Bound: the reduction has its factors split in two fp16 numbers like that at n = 32 (chunk_gru.hip; wavefronts split the quarter that they
+// Bound: the reduction of a Newton step has its factors split in two fp16 numbers like that at n = 32 (chunk_gru.hip; wavefronts split the quarter that they
 // assemble): 24 matrix instructions of 18 cycles a wavefront and position and about 110 vector instructions of 2.4, then the barrier and the LDS
-// (one workgroup a compute unit at 5 x 9,973 positions: 2,000 cycles a position).  Far iterates: 64 fp32 matrix
-// instructions of 32 cycles.  Reduction at 5 x 9,973 positions, d = 7, with fp32 products / now: Newton step 307 / 177 us, dual scan 302 / 180.
+// (one workgroup a compute unit at 5 x 9,973 positions: 2,000 cycles a position).  Far iterates and the dual scan, for the reason given
+// there: 64 fp32 matrix instructions of 32 cycles.  Reduction at 5 x 9,973 positions, d = 7, with fp32 products / now: Newton step 307 / 177 us.
 #include "chunk_common.h"
 #include "split_f16.h"
 
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     // factor in operand order, [block][lane]; split in two [column blocks / 2][row block][hi, lo][lane], in the same place
     __shared__ __align__(16) Acc sJ[2][NB * NB][64];
     __shared__ unsigned s_again[4];
-    constexpr bool SPLIT = !FAR;
+    constexpr bool SPLIT = !FAR && !REV;
     if (step_closed(p.gate, FAR)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, r = lane & 15;
     const int b = (int)(blockIdx.x % (unsigned)p.B), unit = (int)(blockIdx.x / (unsigned)p.B);
@@ -154,24 +154,14 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
             }
         } else {
             const Acc ff = load4(sFw + (c * 16 + r) * 4);
-            Acc a[NB];
 #pragma unroll
             for (int X = 0; X < NB; ++X) {
+                Acc a;
                 const float diag = X == wave ? 1.f : 0.f;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    a[X][v] = ff[0] * gr.u[1][X][v] + (ff[1] * gr.u[2][X][v] + (ff[2] * gr.u[0][X][v] + diag * dsel[v] * ff[3]));
-            }
-            if (SPLIT && !wide) {
-#pragma unroll
-                for (int K2 = 0; K2 < 2; ++K2) {
-                    const Split8 s = split8(a[2 * K2], a[2 * K2 + 1]);
-                    parts(buf, K2, wave, 0)[lane] = s.hi;
-                    parts(buf, K2, wave, 1)[lane] = s.lo;
-                }
-            } else {
-#pragma unroll
-                for (int X = 0; X < NB; ++X) sJ[buf][wave * NB + X][lane] = a[X];
+                    a[v] = ff[0] * gr.u[1][X][v] + (ff[1] * gr.u[2][X][v] + (ff[2] * gr.u[0][X][v] + diag * dsel[v] * ff[3]));
+                sJ[buf][wave * NB + X][lane] = a;
             }
         }
     };
