@@ -289,8 +289,8 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
             }
         }
         if (wide) break;
-        if (lane == 0) s_again[wave] = 0u;
-        if (again) s_again[wave] = 1u;
+        const bool bad = __ballot(again) != 0ull;
+        if (lane == 0) s_again[wave] = bad;
         __syncthreads();
         if ((s_again[0] | s_again[1] | s_again[2] | s_again[3]) == 0u) break;   // (the same for the four wavefronts)
         wide = true;

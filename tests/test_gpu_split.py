@@ -100,3 +100,26 @@ def test_range_of_the_reduction(n, scale, T, L, monkeypatch):
     off = np.abs(y - want).max(axis=-1) / np.maximum(1.0, np.abs(want).max(axis=-1))
     print(n, scale, L, "%.1e, iterate up to %.1e" % (off.max(), np.abs(want).max()), flush=True)
     assert off.max() <= 1e-4
+
+
+# One column of the running product leaves the range of fp16, in lanes of one wavefront that are not its first: row i of J has entries of some 1e4 and no other row
+# reads channel i.  All chunks are reduced again, those of the other wavefronts (n = 64: a workgroup's four share a unit) too.
+@pytest.mark.parametrize("n,i", [(16, 5), (32, 21), (64, 5), (64, 37), (64, 63)])
+def test_one_column_leaves_the_range(n, i, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", "8")
+    d, B, T = 3, 3, 300
+    w = inputs.gru_workload("one_column", 660 + n + i, B=B, T=T, n=n, d=d)
+    U = w.theta[3 * n * d:3 * n * d + 3 * n * n].reshape(3, n, n)
+    U[:, :, i] = 0.0
+    U[2, i] *= np.float32(3e5)
+    want = oracle.deer_eval(oracle.make_cell(oracle.CELL_GRU, n, d), w.theta, w.x, w.y0, tol=w.tol, max_iter=1, nthreads=8)[0]
+    assert np.abs(want[..., i]).max() > 1e4 and np.abs(np.delete(want, i, axis=-1)).max() < 10.0
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        y = host(ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=1)[0])
+    finally:
+        ctx.close()
+    # channel i is a sum of n terms of 1e4 times rounded ones: entry by entry, against the largest in its place
+    off = np.abs(y - want) / np.maximum(1.0, np.abs(want).max(axis=(0, 1)))
+    print(n, i, "%.1e" % off.max(), flush=True)
+    assert off.max() <= 1e-4
