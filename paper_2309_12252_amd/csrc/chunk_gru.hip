@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 // The walk: one wavefront per group, its sixteen chunks are the columns of every product.
 // ------------------------------------------------------------------------------------------------------------------
 // SPLIT (n = 32, not from far iterates): the products with the state and with the correction have their factors split in two fp16 numbers, a scale
-// to every column from its largest entry; U keeps all its digits for the state (a third part), which the trajectory sees.
+// to every column from its largest entry; U keeps all its digits for the state (a third part), which the trajectory sees, and its small entries theirs next to large ones (Split8Weights).
 // Bound: issue, one or two wavefronts a SIMD: a step takes 12 fp32 matrix instructions (the input's) and 42 of 18 cycles in the place of 108 fp32 ones.  16 x
 // 100,000 positions, d = 8: 318 us with fp32 products, now 210; 2-norm error of the trajectory against 64 bits 1.347e-7, now 1.309e-7.
 template <int N, int DS, bool REV, bool SPLIT>
@@ -458,6 +458,17 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
     const float* __restrict__ th = p.theta;
     const float* __restrict__ U = th + 3 * N * d;
     if (tid < 4 * N) sB[tid] = U[3 * N * N + tid];
+    // sixteen inputs: W waits in LDS, its registers go to the parts of U (with both in registers five spilled: a solve at 16 x 50,000, d = 16, 2,632 us, now 2,534)
+    constexpr bool WLDS = SPLIT && DS == 4;
+    __shared__ __align__(16) Acc sW[WLDS ? 3 * NB : 1][64];
+    auto w_entry = [&](int gate, int I, int l, int s) {
+        const int c = DS * (l >> 4) + s;
+        return c < d ? th[(gate * N + 16 * I + (l & 15)) * d + c] : 0.f;
+    };
+    if constexpr (WLDS)
+        for (int q = tid; q < 3 * NB * 64; q += 256)
+#pragma unroll
+            for (int s = 0; s < DS; ++s) sW[q / 64][q % 64][s] = w_entry(q / 64 / NB, q / 64 % NB, q % 64, s);
     __syncthreads();
 
     const unsigned id = blockIdx.x * 4u + (unsigned)wave;
@@ -507,7 +518,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
         }
 
         Acc u[3][NB][NB];      // U_gate as operand A
-        Half8 uh[3][SPLIT ? NB : 1], ul[3][SPLIT ? NB : 1], um[3][SPLIT ? NB : 1];   // its parts, U 2^eu with entries below 2^8
+        Split8Weights us[3][SPLIT ? NB : 1];   // its parts, U 2^eu with entries below 2^8
         int eu = 0;
         Acc ut[REV ? 3 : 1][REV ? NB : 1][REV ? NB : 1];   // dual: U_gate^T as operand A
         float w[3][NB][DS];
@@ -522,8 +533,9 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
 #pragma unroll
                         for (int v = 0; v < 4; ++v) ut[gate][I][K][v] = U[(gate * N + 16 * K + 4 * g + v) * N + 16 * I + r];
                 }
+                if constexpr (!WLDS)
 #pragma unroll
-                for (int s = 0; s < DS; ++s) w[gate][I][s] = (DS * g + s < d) ? th[(gate * N + 16 * I + r) * d + DS * g + s] : 0.f;
+                    for (int s = 0; s < DS; ++s) w[gate][I][s] = w_entry(gate, I, lane, s);
             }
 
         if constexpr (SPLIT) {
@@ -543,13 +555,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
 #pragma unroll
             for (int gate = 0; gate < 3; ++gate)
 #pragma unroll
-                for (int I = 0; I < NB; ++I) {
-                    const Acc a = u[gate][I][0] * up, b = u[gate][I][NB - 1] * up;
-                    const Split8 s = split8(a, b);
-                    uh[gate][I] = s.hi;
-                    ul[gate][I] = s.lo;
-                    um[gate][I] = split8_rest(a, b, s.hi, s.lo);
-                }
+                for (int I = 0; I < NB; ++I) us[gate][I] = split8_weights(u[gate][I][0] * up, u[gate][I][NB - 1] * up);
         }
 
         Acc e[NB];   // forward: correction of the state in front of the position; dual: lambda at the time after it
@@ -573,6 +579,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
                 Acc y[NB];
                 Acc lr[NB], lz[NB], lc[NB];
                 Split8 hs, es;
+                Half8 small_h, small_e;
                 float down_h = 1.f, down_e = 1.f;
                 if constexpr (SPLIT) {
                     auto split_column = [&](const Acc (&x)[NB], Split8& s) {
@@ -588,6 +595,8 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
                     };
                     down_h = split_column(h, hs);
                     down_e = split_column(e, es);
+                    small_h = split_small(hs.hi);
+                    small_e = split_small(es.hi);
                 }
 #pragma unroll
                 for (int I = 0; I < NB; ++I) {
@@ -596,15 +605,15 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
                     Acc er = zero4(), ez = zero4(), ec = zero4();
                     if constexpr (SPLIT) {
                         auto state = [&](int gate) {
-                            Acc t = mfma16(um[gate][I], hs.hi, zero4());
-                            t = mfma16(ul[gate][I], hs.hi, t);
-                            t = mfma16(uh[gate][I], hs.lo, t);
-                            return mfma16(uh[gate][I], hs.hi, t);
+                            Acc t = mfma16(us[gate][I].rest, small_h, zero4());
+                            t = mfma16(us[gate][I].lo, small_h, t);
+                            t = mfma16(us[gate][I].hi, hs.lo, t);
+                            return mfma16(us[gate][I].hi, hs.hi, t);
                         };
                         auto correction = [&](int gate) {
-                            Acc t = mfma16(ul[gate][I], es.hi, zero4());
-                            t = mfma16(uh[gate][I], es.lo, t);
-                            return mfma16(uh[gate][I], es.hi, t);
+                            Acc t = mfma16(us[gate][I].lo, small_e, zero4());
+                            t = mfma16(us[gate][I].hi, es.lo, t);
+                            return mfma16(us[gate][I].hi, es.hi, t);
                         };
                         const Acc tr = state(0), tz = state(1), tc = state(2);
                         er = correction(0);
@@ -630,6 +639,16 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkP
                                 ec = mfma(u[2][I][K][v], e[K][v], ec);
                             }
                         }
+                    if constexpr (WLDS) {
+                        int at = lane;
+                        asm volatile("" : "+v"(at));   // (or the reads leave the loop)
+#pragma unroll
+                        for (int gate = 0; gate < 3; ++gate) {
+                            const Acc o = sW[gate * NB + I][at];
+#pragma unroll
+                            for (int s = 0; s < DS; ++s) w[gate][I][s] = o[s];
+                        }
+                    }
 #pragma unroll
                     for (int s = 0; s < DS; ++s) {
                         ar = mfma(w[0][I][s], xr[j][s], ar);

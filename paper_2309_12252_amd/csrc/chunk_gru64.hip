@@ -413,7 +413,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
     }
     GateRows<DS> gr;
     load_gate_rows<DS>(gr, p.theta, d, wave, g, r);
-    Half8 uh[SPLIT ? 3 : 1][2], ul[SPLIT ? 3 : 1][2], um[SPLIT ? 3 : 1][2];   // parts of U_gate 2^eu with entries below 2^8
+    Split8Weights us[SPLIT ? 3 : 1][2];   // parts of U_gate 2^eu with entries below 2^8
     int eu = 0;
     if constexpr (SPLIT) {
         float m = 0.f;
@@ -430,13 +430,7 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
 #pragma unroll
         for (int gate = 0; gate < 3; ++gate)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const Acc x = gr.u[gate][2 * q] * up, y = gr.u[gate][2 * q + 1] * up;
-                const Split8 s = split8(x, y);
-                uh[gate][q] = s.hi;
-                ul[gate][q] = s.lo;
-                um[gate][q] = split8_rest(x, y, s.hi, s.lo);
-            }
+            for (int q = 0; q < 2; ++q) us[gate][q] = split8_weights(gr.u[gate][2 * q] * up, gr.u[gate][2 * q + 1] * up);
     }
     Acc ut[REV ? 3 : 1][NB];   // dual: rows 16 w + r of U_gate^T
     if constexpr (REV) {
@@ -591,12 +585,13 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                     Acc t = zero4();
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
-                        t = mfma16(um[gate][q], hh[q], t);
-                        t = mfma16(ul[gate][q], hh[q], t);
-                        t = mfma16(uh[gate][q], hl[q], t);
+                        const Half8 small = split_small(hh[q]);
+                        t = mfma16(us[gate][q].rest, small, t);
+                        t = mfma16(us[gate][q].lo, small, t);
+                        t = mfma16(us[gate][q].hi, hl[q], t);
                     }
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) t = mfma16(uh[gate][q], hh[q], t);
+                    for (int q = 0; q < 2; ++q) t = mfma16(us[gate][q].hi, hh[q], t);
                     a[gate] += t * down_h;
                 }
 #pragma unroll
@@ -621,11 +616,11 @@ __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
                         Acc t = zero4();
 #pragma unroll
                         for (int q = 0; q < 2; ++q) {
-                            t = mfma16(ul[gate][q], eh[q], t);
-                            t = mfma16(uh[gate][q], el[q], t);
+                            t = mfma16(us[gate][q].lo, split_small(eh[q]), t);
+                            t = mfma16(us[gate][q].hi, el[q], t);
                         }
 #pragma unroll
-                        for (int q = 0; q < 2; ++q) t = mfma16(uh[gate][q], eh[q], t);
+                        for (int q = 0; q < 2; ++q) t = mfma16(us[gate][q].hi, eh[q], t);
                         return t * down_e;
                     };
                     er = correction(0);

@@ -45,14 +45,6 @@ __device__ __forceinline__ unsigned split_rest(float a, float b, unsigned hi, un
     return split_hi((a - (float)h[0]) - (float)l[0], (b - (float)h[1]) - (float)l[1]);
 }
 
-// the same of eight entries
-__device__ __forceinline__ Half8 split8_rest(F32x4 a, F32x4 b, Half8 hi, Half8 lo) {
-    F32x8 x = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = (x[i] - (float)hi[i]) - (float)lo[i];
-    return __builtin_convertvector(x, Half8);
-}
-
 // Two accumulators of 16 rows (rows 4g .. 4g + 3 of each in lane group g) as operand B of a contraction over those 32 rows: entry j
 // < 4 of lane group g is row 4g + j of the first, j >= 4 row 4g + j - 4 of the second.  Operand A takes its columns in the same order.
 __device__ __forceinline__ Split8 split8(F32x4 a, F32x4 b) {
@@ -65,6 +57,26 @@ __device__ __forceinline__ Split8 split8(F32x4 a, F32x4 b) {
     s.lo = __builtin_convertvector(r, Half8);
     return s;
 }
+
+// Weights that stay in registers, scaled so that the largest is below 2^8, in three parts.  One that is much smaller keeps its digits all the same: lo and rest are
+// 2^11 times what they stand for (|e| <= 2^-36 for the three, 2^-25 for two unscaled ones) and go with split_small() of the other factor.
+struct Split8Weights {
+    Half8 hi, lo, rest;
+};
+__device__ __forceinline__ Split8Weights split8_weights(F32x4 a, F32x4 b) {
+    const F32x8 x = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    Split8Weights s;
+    s.hi = __builtin_convertvector(x, Half8);
+    F32x8 r;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = (x[i] - (float)s.hi[i]) * 2048.f;
+    s.lo = __builtin_convertvector(r, Half8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] -= (float)s.lo[i];
+    s.rest = __builtin_convertvector(r, Half8);
+    return s;
+}
+__device__ __forceinline__ Half8 split_small(Half8 hi) { return hi * (_Float16)(1.f / 2048.f); }
 
 __device__ __forceinline__ F32x4 mfma16(Half8 a, Half8 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 

@@ -112,14 +112,18 @@ def test_one_column_leaves_the_range(n, i, monkeypatch):
     U = w.theta[3 * n * d:3 * n * d + 3 * n * n].reshape(3, n, n)
     U[:, :, i] = 0.0
     U[2, i] *= np.float32(3e5)
-    want = oracle.deer_eval(oracle.make_cell(oracle.CELL_GRU, n, d), w.theta, w.x, w.y0, tol=w.tol, max_iter=1, nthreads=8)[0]
+    cell = oracle.make_cell(oracle.CELL_GRU, n, d)
+    want = oracle.deer_eval(cell, w.theta, w.x, w.y0, tol=w.tol, max_iter=1, nthreads=8)[0]
     assert np.abs(want[..., i]).max() > 1e4 and np.abs(np.delete(want, i, axis=-1)).max() < 10.0
     ctx = deer.context_for(w, device=DEV)
     try:
-        y = host(ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=1)[0])
+        first, last = [host(ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=m)[0]) for m in (1, 12)]
     finally:
         ctx.close()
-    # channel i is a sum of n terms of 1e4 times rounded ones: entry by entry, against the largest in its place
-    off = np.abs(y - want) / np.maximum(1.0, np.abs(want).max(axis=(0, 1)))
-    print(n, i, "%.1e" % off.max(), flush=True)
-    assert off.max() <= 1e-4
+    # Entry by entry, against the largest in its place, with the weights of row i 1e5 times the others.  A step rounds about eight times (2^-24 each), what is
+    # older than eight steps has faded; four times the root of their sum.  (The solution: without channel i, which is a sign of rounded sums.)
+    bound = 4.0 * np.sqrt(8.0 * 8.0) * 2.0 ** -24
+    off = (np.abs(first - want) / np.maximum(1.0, np.abs(want).max(axis=(0, 1)))).max()
+    rest = np.abs(np.delete(last - oracle.seq_eval(cell, w.theta, w.x, w.y0, nthreads=8), i, axis=-1)).max()
+    print(n, i, "%.1e %.1e of %.1e" % (off, rest, bound), flush=True)
+    assert off <= bound and rest <= bound
