@@ -132,6 +132,7 @@ struct FieldLds {
     float jac[field_threads(WB) / 64][16 * kJacStride];   // per wavefront: Jacobians of sixteen points, rows of 8
     unsigned top[L + 1];  // largest entry of W_1, W_2 .. W_L, W_out (raw bits)
     unsigned row[L];      // largest sum of a row's magnitudes of W_2 .. W_L (raw bits; entry 0 unused)
+    unsigned offset[L];   // largest entry of b_2 .. b_L (raw bits; entry 0 unused)
 };
 
 template <int WB, int L>
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_fu
 
     // ---- weights: scales first, then the parts ----
     if (tid <= L) lds.top[tid] = 0u;
-    if (tid < L) lds.row[tid] = 0u;
+    if (tid < L) lds.row[tid] = lds.offset[tid] = 0u;
     __syncthreads();
     auto raise = [&](unsigned* to, float m) {
 #pragma unroll
@@ -183,13 +184,22 @@ __global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_fu
         }
         raise(&lds.top[l], m);
         raise(&lds.row[l], rows);
-        for (int q = tid; q < W; q += NT) lds.bias[l][q] = src[W * W + q];
+        m = 0.f;
+        for (int q = tid; q < W; q += NT) {
+            lds.bias[l][q] = src[W * W + q];
+            m = fmaxf(m, fabsf(src[W * W + q]));
+        }
+        raise(&lds.offset[l], m);
     }
     __syncthreads();
     // operand A is W 2^ea with entries below 2^8
-    int ea[L + 1];
+    int ea[L + 1], ev_max[L];
 #pragma unroll
     for (int l = 1; l <= L; ++l) ea[l] = min(8 - exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.top[l]))), 100);
+    // A sum starts from the bias times 2^(ev + ea), which stays below 2^120: the activations' scale 2^ev gives way.  That costs digits only where a layer's products
+    // are below 2^-90 of its largest bias (weights near 2^-100 behind softplus units near 2^-23, the smallest that are not zero).
+#pragma unroll
+    for (int l = 1; l < L; ++l) ev_max[l] = 120 - ea[l] - max(exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.offset[l]))), 0);
 #pragma unroll
     for (int l = 1; l < L; ++l) {
         const float* src = th + layer_offset(N, W, l);
@@ -261,12 +271,12 @@ __global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_fu
 #pragma unroll
         for (int l = 1; l < L; ++l) {
             // the activations of a point, scaled: tanh by 2^12, softplus to a largest one of 2^12 to 2^13
-            int ev = 12;
+            int ev = min(12, ev_max[l]);
             if (kind != 0) {
                 float m = 0.f;
 #pragma unroll
                 for (int I = 0; I < WB; ++I) m = fmaxf(fmaxf(fmaxf(a[I][0], a[I][1]), fmaxf(a[I][2], a[I][3])), m);
-                ev = min(13 - exponent(max_groups(m)), 100);
+                ev = min(min(13 - exponent(max_groups(m)), 100), ev_max[l]);
             }
             const float s = __builtin_amdgcn_ldexpf(1.0f, ev), up = __builtin_amdgcn_ldexpf(1.0f, ev + ea[l]);
             const float down = __builtin_amdgcn_ldexpf(1.0f, -ev - ea[l]);

@@ -43,10 +43,20 @@ def zero_layer(w):
     layers(w)[1][0][:] = 0.0
 
 
+def faint_layer(w):
+    # softplus units of about 2^-23 in front of weights of about 2^-100: what such a layer adds is its bias, large or zero
+    l = layers(w)
+    l[0][0][:] *= np.float32(0.1)
+    l[0][1][:] = -15.5
+    l[1][0][:] *= 2.0 ** -100
+    l[1][1][0::3], l[1][1][1::3] = 0.0, 20.0
+
+
 CASES = [(width, nhid, act, plain) for width in (32, 64) for nhid, act in
          ((1, inputs.ACT_SOFTPLUS), (2, inputs.ACT_SOFTPLUS), (3, inputs.ACT_TANH), (4, inputs.ACT_SOFTPLUS), (5, inputs.ACT_TANH))]
 CASES += [(64, 4, inputs.ACT_TANH, far_scales), (32, 3, inputs.ACT_TANH, far_scales), (64, 5, inputs.ACT_SOFTPLUS, large_activations),
-          (32, 2, inputs.ACT_SOFTPLUS, large_activations), (64, 3, inputs.ACT_TANH, zero_layer), (32, 5, inputs.ACT_SOFTPLUS, zero_layer)]
+          (32, 2, inputs.ACT_SOFTPLUS, large_activations), (64, 3, inputs.ACT_TANH, zero_layer), (32, 5, inputs.ACT_SOFTPLUS, zero_layer),
+          (64, 2, inputs.ACT_SOFTPLUS, faint_layer), (64, 5, inputs.ACT_SOFTPLUS, faint_layer), (32, 3, inputs.ACT_SOFTPLUS, faint_layer)]
 
 
 @pytest.mark.parametrize("width,nhid,act,change", CASES)
