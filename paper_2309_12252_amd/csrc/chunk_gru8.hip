@@ -631,7 +631,7 @@ __global__ __launch_bounds__(256, 2) void chunk8_dual_kernel(Chunk8Params p) {
 template <int V, bool BACK>
 __global__ __launch_bounds__(256) void heads_transpose_kernel(const float* __restrict__ src, float* __restrict__ dst, int T, int H, int R) {
     using F = float __attribute__((ext_vector_type(V)));
-    const int words = H * R / V, t0 = blockIdx.x * 32, rows = min(32, T - t0), b = blockIdx.y;
+    const int words = H * R / V, per = (T + 31) / 32, b = (int)(blockIdx.x / (unsigned)per), t0 = 32 * (int)(blockIdx.x % (unsigned)per), rows = min(32, T - t0);
     for (int q = threadIdx.x; q < rows * words; q += 256) {
         const int t = t0 + q / words, w = q % words, h = w / (R / V), r = w % (R / V);
         const long long user = ((long long)b * T + t) * words + w, mine = (((long long)b * H + h) * T + t) * (R / V) + r;
@@ -718,7 +718,7 @@ hipError_t launch_chunk_gru8(const Chunk8Params& p, hipStream_t s) {
 hipError_t launch_heads_transpose(const void* src, void* dst, int B, int T, int H, int R, bool back, hipStream_t s) {
     const float* in = reinterpret_cast<const float*>(src);
     float* out = reinterpret_cast<float*>(dst);
-    const dim3 grid((unsigned)((T + 31) / 32), (unsigned)B);
+    const dim3 grid((unsigned)((long long)B * ((T + 31) / 32)));   // (one dimension: the second one ends at 65,535)
     // (the caller's arrays need no more than their scalars' alignment)
     const bool wide = R % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
     if (wide && back) hipLaunchKernelGGL((heads_transpose_kernel<4, true>), grid, dim3(256), 0, s, in, out, T, H, R);

@@ -10,8 +10,9 @@ from helpers import DEV, dev, host
 pytestmark = pytest.mark.gpu
 
 
-# rows of whole 16-byte pieces and of three scalars, times that are no multiple of a tile, an input that is only scalar-aligned
-@pytest.mark.parametrize("B,T,H,K,d,shift", [(37, 1001, 32, 3, 4, 0), (49, 1001, 32, 4, 3, 0), (37, 1001, 32, 8, 4, 1)])
+# rows of whole 16-byte pieces and of three scalars, times that are no multiple of a tile, an input that is only scalar-aligned, more sequences than a grid's
+# second dimension takes
+@pytest.mark.parametrize("B,T,H,K,d,shift", [(37, 1001, 32, 3, 4, 0), (49, 1001, 32, 4, 3, 0), (37, 1001, 32, 8, 4, 1), (70001, 8, 4, 3, 4, 0)])
 def test_large_layers(B, T, H, K, d, shift):
     n = 8
     w = inputs.mh_gru_workload("head_major", 51 + d, B=B, T=T, n=n, d=d, H=H, K=K)
