@@ -132,7 +132,8 @@ size_t deer_theta_count(const deer_config* cfg);
  * DEER_FUSED / DEER_GRAD_FUSED knobs at 0; LSTM and LEM where they do not step by chunks), the Jacobian stream [B,T,n,n] and the right-hand side, the O(n^2 T)
  * memory of Sec. 3.5.  Where the cell is evaluated inside the scans the workspace is O(n T).  Where steps run by chunks
  * (see deer_eval) every chunk has a map of N^2 + N scalars (N = state size, for LSTM and LEM 2u rounded up to 16 or 32): one for every 4 to 64
- * positions, so short sequences in large numbers take up to (N + 1) / 4 trajectories of it, long ones a fraction of one.
+ * positions, so short sequences in large numbers take up to (N + 1) / 4 trajectories of it, long ones a fraction of one.  Large multi-head
+ * layers of three stride levels and more have copies of x and of a trajectory by heads there, 16 GiB at most.
  * The environment variables listed under "Environment" below are read here and in deer_create(); both calls must
  * see the same values. */
 deer_status deer_workspace_bytes(const deer_config* cfg, size_t* bytes);

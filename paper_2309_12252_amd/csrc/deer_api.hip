@@ -199,8 +199,10 @@ bool supported(const deer_config* c, std::string& why) {
 // d): 1,112 / 898 at 64 x 1,024 x 32, 8, 8; 3,032 / 2,187 at 64 x 2,000 x 32, 4, 8; 530 / 495 at 24 x 1,024 x 32, 8, 8; 1,048 / 1,014 at 64 x 1,024 x 32, 3, 4; 702 /
 // 677 at 64 x 1,500 x 16, 4, 3 (rows of 3 scalars are transposed one by one); but 398 / 391 at 16 x 1,024 x 32, 8, 8, 416 / 417 at 20 x 1,024 x 32, 8, 4, 518 / 527 at 40 x
 // 1,800 x 12, 8, 7, 459 / 478 at 32 x 2,000 x 12, 5, 3, 548 / 552 at 64 x 2,000 x 8, 2, 8, 563 / 587 at 32 x 1,024 x 32, 2, 2.
+// At most 16 GiB of copies: x, y and the workspace's trajectory fill a card first.
 bool head_major_pays(const deer_config* c) {
-    return c->heads > 1 && c->stride_levels >= 3 && (long long)c->B * c->T * c->heads * (c->n + c->d) >= (c->d % 4 == 0 ? 12000000 : 16500000);
+    const long long scalars = (long long)c->B * c->T * c->heads * (c->n + c->d);
+    return c->heads > 1 && c->stride_levels >= 3 && scalars >= (c->d % 4 == 0 ? 12000000 : 16500000) && scalars <= (4LL << 30);
 }
 
 // Multi-head GRU: the tiles of one batch entry, head by head, recurrence by recurrence (first time index r < stride),

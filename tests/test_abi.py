@@ -109,3 +109,13 @@ def test_workspace_of_many_short_sequences(cell, n, d, B, T):
     words = B * -(-T // 64) * (state * state + 2 * state) * 8
     rows = max(2048, B / 4) * deer.theta_count(cfg) * 4
     assert deer.workspace_bytes(cfg) <= 1.02 * (B * T * state * 4 + max(maps + rows, words + rows))
+
+
+def test_workspace_of_a_layer_that_fills_the_card():
+    # 64 x 1,000,000 steps of 32 heads: x, y and the second trajectory are 197 GB together; copies by heads would add 131 more
+    B, T, H, n, d = 64, 1000000, 32, 8, 8
+    y = B * T * H * n * 4
+    assert deer.workspace_bytes(deer.make_config(deer.DEER_CELL_GRU, deer.DEER_F32, B, T, n, d=d, heads=H, stride_levels=8)) < 2.5 * y
+    # smaller ones have them
+    small = deer.make_config(deer.DEER_CELL_GRU, deer.DEER_F32, B, 2000, n, d=d, heads=H, stride_levels=8)
+    assert deer.workspace_bytes(small) > 3 * (B * 2000 * H * n * 4)
