@@ -200,6 +200,10 @@ bool supported(const deer_config* c, std::string& why) {
 // 677 at 64 x 1,500 x 16, 4, 3 (rows of 3 scalars are transposed one by one); but 398 / 391 at 16 x 1,024 x 32, 8, 8, 416 / 417 at 20 x 1,024 x 32, 8, 4, 518 / 527 at 40 x
 // 1,800 x 12, 8, 7, 459 / 478 at 32 x 2,000 x 12, 5, 3, 548 / 552 at 64 x 2,000 x 8, 2, 8, 563 / 587 at 32 x 1,024 x 32, 2, 2.
 // At most 16 GiB of copies: x, y and the workspace's trajectory fill a card first.
+// From a guess one step may do, and three transpositions have to pay with it (steps x heads, levels, d; one step, caller's layout / copies): 1,460 / 1,149 at 64 x
+// 4,000 x 32, 4, 8, 1,156 / 1,032 at 64 x 4,000 x 32, 3, 4, 941 / 829 at 256 x 1,024 x 32, 8, 8, but 591 / 572, 547 / 588 and 448 / 504 at 64 x 2,000 x 32, 4, 3 and 8, 8, and 232 /
+// 266 at 64 x 1,024 x 32, 8, 8: the line is where x and the iterates no longer fit the last-level cache of 256 MB by far.
+constexpr long long kHeadMajorGuess = 90000000;   // scalars of x and of a trajectory
 bool head_major_pays(const deer_config* c) {
     const long long scalars = (long long)c->B * c->T * c->heads * (c->n + c->d);
     return c->heads > 1 && c->stride_levels >= 3 && scalars >= (c->d % 4 == 0 ? 12000000 : 16500000) && scalars <= (4LL << 30);
@@ -580,6 +584,7 @@ struct deer_ctx {
     char* ws;
     unsigned epoch;
     bool far;               // deer_eval: the iterate in front of the next batch may be far from the solution
+    bool by_heads;          // deer_eval: the iterates of this call are copies [B,heads,T,.]
     bool words_dirty;       // the chunks' maps have been written over the published words
     void* h_err;            // pinned: kSlots * 8 bytes of error words, then the status word and a result word
     void* d_h_err;          // the same memory as the device sees it
@@ -720,7 +725,7 @@ hipError_t run_scan(deer_ctx* c, const void* A, const void* bv, const void* y0, 
         q.out = reinterpret_cast<float*>(out);
         q.err = p.err; q.gate = gate;
         q.far = c->far;
-        if (c->plan.head_major) { q.head_rows = q.T; q.time_rows = 1; }
+        if (c->by_heads) { q.head_rows = q.T; q.time_rows = 1; }
         prof_begin(c, KIND_FUSED, iter);
         e = launch_chunk_gru8(q, c->stream);
     } else if (fused_theta && c->plan.mh) {
@@ -909,7 +914,7 @@ deer_status deer_create(const deer_config* cfg, void* d_workspace, size_t worksp
     c->ws = reinterpret_cast<char*>(d_workspace);
     c->epoch = 0;
     c->words_dirty = false;
-    c->far = false;
+    c->far = c->by_heads = false;
     c->h_err = nullptr;
     c->profiling = false;
     c->prof = deer_profile{};
@@ -1021,7 +1026,8 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
     char* buf[2];
     buf[expect & 1] = reinterpret_cast<char*>(d_y);
     buf[(expect + 1) & 1] = c->ws + c->plan.off_ybuf;
-    if (c->plan.head_major) {
+    c->by_heads = c->plan.head_major && (!d_y_guess || (long long)(B * T) * c->plan.mh_H * (g.n + g.d) >= kHeadMajorGuess);
+    if (c->by_heads) {
         buf[expect & 1] = c->ws + c->plan.off_yh;
         HIPCHK(c, launch_heads_transpose(d_x, c->ws + c->plan.off_xh, g.B, g.T, c->plan.mh_H, g.d, false, c->stream));
         d_x = c->ws + c->plan.off_xh;
@@ -1031,7 +1037,7 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
     if (d_y_guess) {
         st = zero_ctl(c);
         if (st != DEER_OK) return st;
-        if (c->plan.head_major)
+        if (c->by_heads)
             HIPCHK(c, launch_heads_transpose(d_y_guess, buf[0], g.B, g.T, c->plan.mh_H, g.n, false, c->stream));
         else if (d_y_guess != buf[0])
             HIPCHK(c, hipMemcpyAsync(buf[0], d_y_guess, ybytes, hipMemcpyDeviceToDevice, c->stream));
@@ -1128,7 +1134,7 @@ static deer_status eval_impl(deer_ctx* c, const void* d_theta, const void* d_x, 
     }
     if (it > 0) c->last_iters = it;
     char* fin = buf[it & 1];
-    if (c->plan.head_major) {
+    if (c->by_heads) {
         HIPCHK(c, launch_heads_transpose(fin, d_y, g.B, g.T, c->plan.mh_H, g.n, true, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
     } else if (fin != reinterpret_cast<char*>(d_y)) {
@@ -1415,7 +1421,7 @@ deer_status deer_linrec_solve_static(int32_t dtype, int32_t B, int32_t T, int32_
     c.stream = reinterpret_cast<hipStream_t>(hip_stream);
     c.ws = reinterpret_cast<char*>(scratch);
     c.words_dirty = false;
-    c.far = false;
+    c.far = c.by_heads = false;
     c.epoch = 1;   // the same tag in every call: everything published by the previous call is cleared below
     c.h_err = nullptr;
     c.d_h_err = nullptr;
