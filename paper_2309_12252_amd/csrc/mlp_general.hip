@@ -88,9 +88,11 @@ __host__ __device__ inline long long gen_theta_len(int n, int w, int L) { return
 // columns of the Jacobians by the weights' largest row sums, so that none can overflow, and once more by their own largest entry after the
 // third layer of four or five.
 // Bound: issue, matrix and vector instructions in turn: a layer of the Jacobians at width 64 takes 8 x 24 matrix instructions of 18 cycles and 8
-// x 48 vector instructions of 2.4 for 16 points.  At five layers of 64 and 160,000 points 464 us with fp32 instructions of 32 cycles, 203 us
-// now; two layers of 32 and 800,000 points 214 us, now 120.  Errors against 64 bits, five layers of 64 (mean of 30 solves, 5,000 points to a sequence): trajectory 2.74e-8 to 2.84e-8, dL/dtheta 9.1e-7 to
-// 8.9e-7, dL/dy0 1.21e-6 to 1.22e-6.
+// x 48 vector instructions of 2.4 for 16 points; the values take 48 and some 100.  At five layers of 64 and 160,000 points 424 us with fp32 instructions of 32 cycles, 185 us
+// now; two layers of 32 and 800,000 points 210 us, now 120.  The values are summed exactly (Split8Grid: 6, 2 and 1 us of these): with hi parts off the grid their small error
+// repeated itself from point to point, and trajectories of softplus fields were 1.03 to 1.13 times as far off as with fp32 sums.  Errors against 64 bits, fp32 / now (mean of 60
+// solves, 5,000 points to a sequence): five softplus layers of 64 trajectory 2.713e-8 / 2.705e-8, dL/dtheta 8.43e-7 / 8.48e-7, dL/dy0 1.200e-6 / 1.203e-6; two of 32 2.841e-8 /
+// 2.819e-8, 8.31e-7 / 8.16e-7, 1.315e-6 / 1.307e-6; five tanh layers of 64 5.905e-8 / 5.891e-8, 8.67e-7 / 8.72e-7, 1.243e-6 / 1.261e-6 (+- 1 % in the gradients).
 typedef float gacc __attribute__((ext_vector_type(4)));
 
 // the LDS slice of a wavefront is written and read by its own lanes only: LDS operations of a wavefront complete in order,
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_fu
         for (int q = tid; q < W * W / 2; q += NT) {
             const int row = q / (W / 2), col = 2 * (q % (W / 2)), k = col % 32;
             const float a = ldexpf(src[2 * q], ea[l]), b = ldexpf(src[2 * q + 1], ea[l]);
-            const unsigned hi = split_hi(a, b), lo = split_lo(a, b, hi), at = split_place(k) / 2;
+            const unsigned hi = split_hi(split_grid_weight(a), split_grid_weight(b)), lo = split_lo(a, b, hi), at = split_place(k) / 2;
             Half8(&to)[3][64] = lds.hidden[l - 1][row / 16][col / 32];
             reinterpret_cast<unsigned*>(&to[0][split_lane(row, k)])[at] = hi;
             reinterpret_cast<unsigned*>(&to[1][split_lane(row, k)])[at] = lo;
@@ -280,24 +282,26 @@ __global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_fu
             }
             const float s = __builtin_amdgcn_ldexpf(1.0f, ev), up = __builtin_amdgcn_ldexpf(1.0f, ev + ea[l]);
             const float down = __builtin_amdgcn_ldexpf(1.0f, -ev - ea[l]);
-            Split8 as[KS];
+            Split8Grid as[KS];
 #pragma unroll
-            for (int k = 0; k < KS; ++k) as[k] = split8(a[2 * k] * s, a[2 * k + 1] * s);
+            for (int k = 0; k < KS; ++k) as[k] = split8_grid(a[2 * k] * s, a[2 * k + 1] * s);
             gacc an[WB];
 #pragma unroll
             for (int I = 0; I < WB; ++I) {
-                // (the bias first: added last it was a third of the error that the layer adds)
-                gacc big = *reinterpret_cast<const gacc*>(&lds.bias[l][16 * I + 4 * g]) * up, small = {0.f, 0.f, 0.f, 0.f};
+                gacc big = {0.f, 0.f, 0.f, 0.f}, small = big;
 #pragma unroll
                 for (int k = 0; k < KS; ++k) {
                     const Half8(&w)[3][64] = lds.hidden[l - 1][I][k];
-                    const Half8 hi = w[0][lane];
+                    const Half8 hi = w[0][lane], lo = w[1][lane];
                     big = mfma16(hi, as[k].hi, big);
                     small = mfma16(w[2][lane], as[k].hi, small);
+                    small = mfma16(hi, as[k].rest, small);
+                    small = mfma16(lo, as[k].lo, small);
+                    small = mfma16(lo, as[k].hi, small);
                     small = mfma16(hi, as[k].lo, small);
-                    small = mfma16(w[1][lane], as[k].hi, small);
                 }
-                an[I] = big + small;
+                // (the bias to the small part, whose digits move from point to point: added to the large one it is rounded the same way at many of them, trajectories 1.2 times as far off)
+                an[I] = big + (*reinterpret_cast<const gacc*>(&lds.bias[l][16 * I + 4 * g]) * up + small);
             }
 #pragma unroll
             for (int I = 0; I < WB; ++I) {

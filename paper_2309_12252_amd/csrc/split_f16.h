@@ -80,6 +80,30 @@ __device__ __forceinline__ Half8 split_small(Half8 hi) { return hi * (_Float16)(
 
 __device__ __forceinline__ F32x4 mfma16(Half8 a, Half8 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
+// Factors whose hi*hi sums are exact.  A matrix instruction drops what lies 24 bits or so below its largest product, and fp16 numbers that change slowly leave out
+// the same there at many points in a row: small (4e-8 of the sum) but the same error again and again, where rounded fp32 sums scatter.  So hi lies on a grid: weights
+// below 2^8 on multiples of 2^-6 (their eleven bits from 2^5 on), the other factor below 2^13 on multiples of 2^5; products are multiples of 1/2, and a sum below 2^23 is exact.
+// What hi leaves out comes in lo and rest: lo*lo and hi*rest count here.
+__device__ __forceinline__ float split_grid_weight(float x) { return (x + 1.5f * (1 << 17)) - 1.5f * (1 << 17); }
+struct Split8Grid {
+    Half8 hi, lo, rest;
+};
+__device__ __forceinline__ Split8Grid split8_grid(F32x4 a, F32x4 b) {
+    F32x8 x = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), h;
+    Split8Grid s;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        h[i] = (x[i] + 1.5f * (1 << 28)) - 1.5f * (1 << 28);
+        x[i] -= h[i];
+    }
+    s.hi = __builtin_convertvector(h, Half8);
+    s.lo = __builtin_convertvector(x, Half8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = split_diff(x[i], s.lo[i]);
+    s.rest = __builtin_convertvector(x, Half8);
+    return s;
+}
+
 // The same for a contraction of 16, i.e. one accumulator, with instructions for 16.  (Two of those for 32 that take (lo | hi) and (hi | lo) of A and (hi | lo) of B cost
 // four moves a factor more.  Never one for 16 after one for 32 on the same accumulator: the compiler puts no wait between two lengths, and
 // what it adds to is not there yet.)

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_2309_12252_amd import deer, inputs
-from helpers import DEV, TOL_ABS, dev, host
+from helpers import DEV, TOL_ABS, dev, host, oracle_eval
 from test_gpu_ode import check, check_grad
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +137,26 @@ def test_one_column_leaves_the_range(n, i, monkeypatch):
     rest = np.abs(np.delete(last - oracle.seq_eval(cell, w.theta, w.x, w.y0, nthreads=8), i, axis=-1)).max()
     print(n, i, "%.1e %.1e of %.1e" % (off, rest, bound), flush=True)
     assert off <= bound and rest <= bound
+
+
+# What the field leaves out at many points in a row adds up along a trajectory, and the rounding of the stored states, twice as large, hides it: so the mean error over the last
+# fifth, 24 solves.  Sums rounded to fp32 term by term leave 1.46e-8 and 1.00e-8 of the states there; a quarter more is the spread of 24 solves
+# (rounding 2^-24 of sums that scatter, on a path of length one).  Sums whose rounding repeats from point to point leave 2.2e-8 and 1.8e-8.
+@pytest.mark.parametrize("nhid,fp32", [(2, 1.46e-8), (3, 1.00e-8)])
+def test_field_does_not_drift(nhid, fp32):
+    off = []
+    for seed in range(24):
+        w = inputs.mlp_ode_workload("drift", 3000 + seed, B=4, T=5000, n=8, width=32, nhid=nhid, t0=0.0, t1=10.0, tol=1e-4, act=inputs.ACT_SOFTPLUS)
+        ctx = deer.context_for(w, device=DEV)
+        try:
+            th, y0 = dev(w.theta, 0), dev(w.y0, 0)
+            y = ctx.eval(th, None, y0, tol=w.tol, max_iter=w.max_iter)[0]
+            y = host(ctx.eval(th, None, y0, y_guess=y, tol=0.0, max_iter=3)[0])
+        finally:
+            ctx.close()
+        want = oracle_eval(w, tol=1e-10, guess=y)[0]
+        e = (y - want)[:, -1000:].mean(axis=1)
+        off.append(np.linalg.norm(e) / np.linalg.norm(np.sqrt((want[:, -1000:] ** 2).mean(axis=1))))
+    rms = np.sqrt(np.mean(np.square(off)))
+    print(nhid, "%.2e of %.2e" % (rms, 1.25 * fp32), flush=True)
+    assert rms <= 1.25 * fp32
