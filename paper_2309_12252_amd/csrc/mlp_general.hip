@@ -88,8 +88,8 @@ __host__ __device__ inline long long gen_theta_len(int n, int w, int L) { return
 // columns of the Jacobians by the weights' largest row sums, so that none can overflow, and once more by their own largest entry after the
 // third layer of four or five.
 // Bound: issue, matrix and vector instructions in turn: a layer of the Jacobians at width 64 takes 8 x 24 matrix instructions of 18 cycles and 8
-// x 48 vector instructions of 2.4 for 16 points; the values take 48 and some 100.  At five layers of 64 and 160,000 points 424 us with fp32 instructions of 32 cycles, 185 us
-// now; two layers of 32 and 800,000 points 210 us, now 120.  The values are summed exactly (Split8Grid: 6, 2 and 1 us of these): with hi parts off the grid their small error
+// x 48 vector instructions of 2.4 for 16 points; the values take 48 and some 100.  At five layers of 64 and 160,000 points 424 us with fp32 instructions of 32 cycles, 172 us
+// now; two layers of 32 and 800,000 points 210 us, now 116.  The values are summed exactly (Split8Grid: 6 and 1.5 us of these): with hi parts off the grid their small error
 // repeated itself from point to point, and trajectories of softplus fields were 1.03 to 1.13 times as far off as with fp32 sums.  Errors against 64 bits, fp32 / now (mean of 60
 // solves, 5,000 points to a sequence): five softplus layers of 64 trajectory 2.713e-8 / 2.705e-8, dL/dtheta 8.43e-7 / 8.48e-7, dL/dy0 1.200e-6 / 1.203e-6; two of 32 2.841e-8 /
 // 2.819e-8, 8.31e-7 / 8.16e-7, 1.315e-6 / 1.307e-6; five tanh layers of 64 5.905e-8 / 5.891e-8, 8.67e-7 / 8.72e-7, 1.243e-6 / 1.261e-6 (+- 1 % in the gradients).
@@ -132,9 +132,6 @@ struct FieldLds {
     float w1[8][W1S];     // W_1 transposed
     float bias[L][W], bias_out[16];
     float jac[field_threads(WB) / 64][16 * kJacStride];   // per wavefront: Jacobians of sixteen points, rows of 8
-    unsigned top[L + 1];  // largest entry of W_1, W_2 .. W_L, W_out (raw bits)
-    unsigned row[L];      // largest sum of a row's magnitudes of W_2 .. W_L (raw bits; entry 0 unused)
-    unsigned offset[L];   // largest entry of b_2 .. b_L (raw bits; entry 0 unused)
 };
 
 template <int WB, int L>
@@ -143,97 +140,106 @@ __global__ __launch_bounds__(field_threads(WB), WB == 2 ? 3 : 2) void mlp_gen_fu
     constexpr int W = 16 * WB, N = 8, KS = WB / 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     FieldLds<WB, L>& lds = *reinterpret_cast<FieldLds<WB, L>*>(smem_raw);
-    const int tid = threadIdx.x, lane = tid & 63, NT = blockDim.x;   // 256 or 512
+    const int tid = threadIdx.x, lane = tid & 63, NT = WB == 2 ? 256 : (int)blockDim.x;   // 256 or 512
     const int g = lane >> 4, c = lane & 15;
     const float* __restrict__ th = reinterpret_cast<const float*>(p.theta);
     const int kind = p.act;
 
-    // ---- weights: scales first, then the parts ----
-    if (tid <= L) lds.top[tid] = 0u;
-    if (tid < L) lds.row[tid] = lds.offset[tid] = 0u;
-    __syncthreads();
-    auto raise = [&](unsigned* to, float m) {
+    // ---- weights: scales first, then the parts.  A launch for few points is this and little more, so every weight is read once and all reads go out together (500
+    // points: two layers of 32 7.2 us, with fp32 products 9.2, one layer 5.4 and 6.4; five of 64 36.5 at 8,000 points, read layer by layer and twice 57) ----
+    constexpr int PH = W * W / 512, HL = L > 1 ? L - 1 : 1;   // pairs of a hidden layer for each of 256 threads
+    float w_in[W * N / 256], w_h[HL][PH][2], w_out[2] = {0.f, 0.f}, bias[L + 1];
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-        if (lane == 0) atomicMax(to, __float_as_uint(m));
-    };
-    {
-        float m = 0.f;
-        for (int q = tid; q < W * N; q += NT) {
-            const float t = th[q];
-            lds.w1[q % N][q / N] = t;
-            m = fmaxf(m, fabsf(t));
-        }
-        raise(&lds.top[0], m);
-        for (int q = tid; q < W; q += NT) lds.bias[0][q] = th[W * N + q];
-        const float* src = th + layer_offset(N, W, L);
-        m = 0.f;
-        for (int q = tid; q < N * W; q += NT) m = fmaxf(m, fabsf(src[q]));
-        raise(&lds.top[L], m);
-        if (tid < 16) lds.bias_out[tid] = (tid < N) ? src[N * W + tid] : 0.0f;
-    }
+    for (int i = 0; i < W * N / 256; ++i) w_in[i] = tid + i * NT < W * N ? th[tid + i * NT] : 0.f;
+#pragma unroll
+    for (int l = 1; l < L; ++l)
+#pragma unroll
+        for (int i = 0; i < PH; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) w_h[l - 1][i][j] = tid + i * NT < W * W / 2 ? th[layer_offset(N, W, l) + 2 * (tid + i * NT) + j] : 0.f;
+    if (tid < N * W / 2)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) w_out[j] = th[layer_offset(N, W, L) + 2 * tid + j];
+#pragma unroll
+    for (int l = 0; l <= L; ++l) bias[l] = tid < (l < L ? W : N) ? th[(l == 0 ? W * N : layer_offset(N, W, l) + (l < L ? W * W : N * W)) + tid] : 0.f;
+#pragma unroll
+    for (int i = 0; i < W * N / 256; ++i)
+        if (tid + i * NT < W * N) lds.w1[(tid + i * NT) % N][(tid + i * NT) / N] = w_in[i];
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+        if (tid < W) lds.bias[l][tid] = bias[l];
+    if (tid < 16) lds.bias_out[tid] = bias[L];
+    // largest entries of W_1 .. W_L, W_out, then of W_2 .. W_L the largest sum of a row's magnitudes and of b_2 .. b_L the largest entry: of a wavefront, then of all
+    constexpr int TOPS = L + 1 + 2 * (L - 1);
+    float top[TOPS];
+    top[0] = 0.f;
+#pragma unroll
+    for (int i = 0; i < W * N / 256; ++i) top[0] = fmaxf(top[0], fabsf(w_in[i]));
+    top[L] = fmaxf(fabsf(w_out[0]), fabsf(w_out[1]));
 #pragma unroll
     for (int l = 1; l < L; ++l) {
-        const float* src = th + layer_offset(N, W, l);
         float m = 0.f, rows = 0.f;
-        for (int q = tid; q < W * W; q += NT) {   // W consecutive threads read a row
-            const float t = fabsf(src[q]);
-            m = fmaxf(m, t);
-            float s = t;
 #pragma unroll
-            for (int o = W / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-            rows = fmaxf(rows, s);
+        for (int i = 0; i < PH; ++i) {   // W / 2 consecutive threads have a row
+            const float x = fabsf(w_h[l - 1][i][0]), y = fabsf(w_h[l - 1][i][1]);
+            m = fmaxf(m, fmaxf(x, y));
+            float sum = x + y;
+#pragma unroll
+            for (int o = W / 4; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+            rows = fmaxf(rows, sum);
         }
-        raise(&lds.top[l], m);
-        raise(&lds.row[l], rows);
-        m = 0.f;
-        for (int q = tid; q < W; q += NT) {
-            lds.bias[l][q] = src[W * W + q];
-            m = fmaxf(m, fabsf(src[W * W + q]));
-        }
-        raise(&lds.offset[l], m);
+        top[l] = m;
+        top[L + l] = rows;
+        top[2 * L - 1 + l] = fabsf(bias[l]);
     }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+        for (int i = 0; i < TOPS; ++i) top[i] = fmaxf(top[i], __shfl_xor(top[i], o));
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < TOPS; ++i) lds.jac[0][16 * (tid >> 6) + i] = top[i];   // (the slices are not in use yet)
     __syncthreads();
+    float mine = 0.f;
+    for (int w = 0; w < NT / 64; ++w) mine = fmaxf(mine, lds.jac[0][16 * w + (lane & 15)]);   // (entries from TOPS on are nobody's)
+    auto largest = [&](int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mine), i)); };
     // operand A is W 2^ea with entries below 2^8
     int ea[L + 1], ev_max[L];
 #pragma unroll
-    for (int l = 1; l <= L; ++l) ea[l] = min(8 - exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.top[l]))), 100);
+    for (int l = 1; l <= L; ++l) ea[l] = min(8 - exponent(largest(l)), 100);
     // A sum starts from the bias times 2^(ev + ea), which stays below 2^120: the activations' scale 2^ev gives way.  That costs digits only where a layer's products
     // are below 2^-90 of its largest bias (weights near 2^-100 behind softplus units near 2^-23, the smallest that are not zero).
 #pragma unroll
-    for (int l = 1; l < L; ++l) ev_max[l] = 120 - ea[l] - max(exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.offset[l]))), 0);
+    for (int l = 1; l < L; ++l) ev_max[l] = 120 - ea[l] - max(exponent(largest(2 * L - 1 + l)), 0);
 #pragma unroll
-    for (int l = 1; l < L; ++l) {
-        const float* src = th + layer_offset(N, W, l);
-        for (int q = tid; q < W * W / 2; q += NT) {
-            const int row = q / (W / 2), col = 2 * (q % (W / 2)), k = col % 32;
-            const float a = ldexpf(src[2 * q], ea[l]), b = ldexpf(src[2 * q + 1], ea[l]);
+    for (int l = 1; l < L; ++l)
+#pragma unroll
+        for (int i = 0; i < PH; ++i) {
+            const int q = tid + i * NT, row = q / (W / 2), col = 2 * (q % (W / 2)), k = col % 32;
+            if (q >= W * W / 2) continue;
+            const float a = ldexpf(w_h[l - 1][i][0], ea[l]), b = ldexpf(w_h[l - 1][i][1], ea[l]);
             const unsigned hi = split_hi(split_grid_weight(a), split_grid_weight(b)), lo = split_lo(a, b, hi), at = split_place(k) / 2;
             Half8(&to)[3][64] = lds.hidden[l - 1][row / 16][col / 32];
             reinterpret_cast<unsigned*>(&to[0][split_lane(row, k)])[at] = hi;
             reinterpret_cast<unsigned*>(&to[1][split_lane(row, k)])[at] = lo;
             reinterpret_cast<unsigned*>(&to[2][split_lane(row, k)])[at] = split_rest(a, b, hi, lo);
         }
-    }
-    {
-        const float* src = th + layer_offset(N, W, L);
-        for (int q = tid; q < N * W / 2; q += NT) {
-            const int row = q / (W / 2), col = 2 * (q % (W / 2)), k = col % 32;
-            const float a = ldexpf(src[2 * q], ea[L]), b = ldexpf(src[2 * q + 1], ea[L]);
-            const unsigned hi = split_hi(a, b), at = split_place(k) / 2;
-            reinterpret_cast<unsigned*>(&lds.out[col / 32][split_lane(row, k)])[at] = hi;
-            reinterpret_cast<unsigned*>(&lds.out[col / 32][split_lane(row + 8, k)])[at] = split_lo(a, b, hi);
-        }
+    if (tid < N * W / 2) {
+        const int row = tid / (W / 2), col = 2 * (tid % (W / 2)), k = col % 32;
+        const float a = ldexpf(w_out[0], ea[L]), b = ldexpf(w_out[1], ea[L]);
+        const unsigned hi = split_hi(a, b), at = split_place(k) / 2;
+        reinterpret_cast<unsigned*>(&lds.out[col / 32][split_lane(row, k)])[at] = hi;
+        reinterpret_cast<unsigned*>(&lds.out[col / 32][split_lane(row + 8, k)])[at] = split_lo(a, b, hi);
     }
     // Scales of the Jacobians' columns: U_1 starts below 2^13, a hidden layer multiplies by at most its largest row sum 2^er (the
     // derivatives are at most 1) and the factor 2^-(ea + er) that goes with D_l keeps it there.
-    const int e1 = min(13 - exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.top[0]))), 100);
+    const int e1 = min(13 - exponent(largest(0)), 100);
     float s_d[L];
     int e_out = e1 + ea[L];   // J carries 2^e_out
     s_d[0] = ldexpf(1.0f, e1);
 #pragma unroll
     for (int l = 1; l < L; ++l) {
-        const int er = exponent(__uint_as_float(__builtin_amdgcn_readfirstlane(lds.row[l])));
+        const int er = exponent(largest(L + l));
         s_d[l] = ldexpf(1.0f, -ea[l] - er);
         e_out -= er;
     }
