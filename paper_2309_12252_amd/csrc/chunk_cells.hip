@@ -218,13 +218,14 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
     float* __restrict__ tot = p.tot + ((long long)b * chunks + first) * MS;
     float* __restrict__ sFw = sF[wave];
     const int q_lo = cpw * wave, q_hi = min(q_lo + cpw, chunks - first);   // chunks of this wavefront (inside the unit)
-    const int lo = (first + q_lo) * Lc, hi = min(T, (first + q_hi) * Lc), blocks = (hi - lo + 15) / 16;
+    const int lo = (first + q_lo) * Lc, hi = min(T, (first + q_hi) * Lc);
+    int top = hi;   // forward: one past the first position that is still to be reduced
     const int j0 = (4 * g) % UP;   // this lane's units
 
     Acc s0, s1, v0, v1;
     float x[DS];
     auto request = [&](int blk) {
-        int pos = (REV ? lo + 16 * blk : hi - 16 * (blk + 1)) + r;
+        int pos = (REV ? lo + 16 * blk : top - 16 * (blk + 1)) + r;
         pos = min(max(pos, lo), hi - 1);
         const float* sp = REV ? yb + (long long)pos * ld : (pos > 0 ? yb + (long long)(pos - 1) * ld : y0b);
         const float* vp = (REV ? gb : yb) + (long long)pos * ld;
@@ -290,27 +291,37 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
                     for (int v = 0; v < 4; ++v) Q[X][C][v] = (X == C) ? dsel[v] * unit_q : 0.f;
             }
         };
-        bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
+        bool wide = !SPLIT, again = false;   // products of fp32 factors; a product of the other kind was not finite
+        int q = REV ? q_lo : q_hi - 1, kept = q;   // chunk being reduced; the same when all was last seen to be finite
         for (;;) {
             reset();
-            int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
-            int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+            int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // the chunk's last position in traversal order
+            const int blocks = (top - lo + 15) / 16;
 
             for (int blk = 0; blk < blocks; ++blk) {
-                const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+                const int base = REV ? lo + 16 * blk : top - 16 * (blk + 1);
                 if (SPLIT && !wide) {
                     // (in front of the gates: nothing waits for it there)
+                    float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
                     for (int C = 0; C < NB; ++C) {
                         float m = 0.f;
 #pragma unroll
                         for (int X = 0; X < NB; ++X)
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(Q[X][C][v]));
+                            for (int v = 0; v < 4; ++v) {
+                                m = fmaxf(m, fabsf(Q[X][C][v]));
+                                sum += 0.f * Q[X][C][v];
+                            }
                         const float f = scale[C].next(max_groups(m));
 #pragma unroll
                         for (int X = 0; X < NB; ++X) Q[X][C] *= f;
                     }
+                    if (__ballot(again || sum != 0.f)) {
+                        again = true;
+                        break;
+                    }
+                    kept = q;
                 }
                 {
                     Factors k[4];
@@ -519,6 +530,8 @@ __global__ __launch_bounds__(256, 2) void cell_totals_kernel(ChunkParams p) {
             if (wide || !__ballot(again)) break;
             wide = true;
             unit_q = 1.f;
+            q = kept;
+            top = min(T, (first + q + 1) * Lc);
             request(0);
         }
     }

@@ -24,8 +24,8 @@
 // entries of J are split as they are: an absolute error of 2^-25 each, and nothing of one below that; a column that falls by 2^-k between two looks
 // is known to 2^(k-28) of its largest entry at worst.  A step's maps multiply a correction, so what they lose is lost against the correction and the next step
 // takes it up: 2-norm errors of the trajectory against 64 bits, fp32 / split products (mean of 8 solves) 1.344e-7 / 1.344e-7 (n = 32), 1.153e-7 / 1.153e-7
-// (n = 16).  Steps from far iterates keep fp32 products.  A product that leaves the range of fp16 leaves infinities or NaN in the map; the wavefront then
-// reduces its chunks again with fp32 products.
+// (n = 16).  Steps from far iterates keep fp32 products.  A product that leaves the range of fp16 leaves infinities or NaN; the wavefront sees them at the next
+// look and goes on with fp32 products from the chunk that it had in work at the look before.
 // The dual scan keeps fp32 products: its maps multiply the cotangent itself, which may have faded by many powers of ten when it reaches the first
 // positions.  With split products dL/dy0 of a loss on the last state had lost 3e-5 to 0.3 of itself behind chunks of 16 positions that keep 0.1 to 0.3 of
 // the state a step, and 1e-6 with fp32 ones.
@@ -133,14 +133,14 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
     const int q_lo = cpw * wave, q_hi = min(q_lo + cpw, chunks - first);   // chunks of this wavefront (inside the unit)
     const int lo = (first + q_lo) * Lc;
     const int hi = min(T, (first + q_hi) * Lc);
-    const int blocks = (hi - lo + 15) / 16;
+    int top = hi;   // forward: one past the first position that is still to be reduced
 
     // operands of one block: state in front of each position (16-byte pieces: operand of the products and the rows of
     // this lane's accumulators), the vector the residual is taken against (forward: the iterate at the position; dual: g), x
     Acc hB[NB], oB[NB];
     float xB[DS];
     auto request = [&](int blk) {
-        int pos = (REV ? lo + 16 * blk : hi - 16 * (blk + 1)) + r;
+        int pos = (REV ? lo + 16 * blk : top - 16 * (blk + 1)) + r;
         pos = min(max(pos, lo), hi - 1);
         const float* hp = REV ? yb + (long long)pos * N : (pos > 0 ? yb + (long long)(pos - 1) * N : y0b);
         const float* op = (REV ? gb : yb) + (long long)pos * N;
@@ -171,7 +171,8 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 #pragma unroll
     for (int v = 0; v < 4; ++v) dsel[v] = (4 * g + v == r) ? 1.f : 0.f;
 
-    bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
+    bool wide = !SPLIT, again = false;   // products of fp32 factors; a product of the other kind was not finite
+    int q = REV ? q_lo : q_hi - 1, kept = q;   // chunk being reduced; the same when all was last seen to be finite
     while (q_lo < q_hi) {
         const float unit_q = wide ? 1.f : (float)(1 << ColumnScale::kStart);
         Acc Q[NB][NB];
@@ -190,24 +191,33 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
         };
         reset();
 
-        int q = REV ? q_lo : q_hi - 1;   // chunk being reduced
-        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // the chunk's last position in traversal order
+        const int blocks = (top - lo + 15) / 16;
 
         for (int blk = 0; blk < blocks; ++blk) {
-            const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            const int base = REV ? lo + 16 * blk : top - 16 * (blk + 1);
             if (SPLIT && !wide) {
                 // (in front of the gates: nothing waits for it there)
+                float sum = 0.f;   // (not a finite number if one of its terms is none)
 #pragma unroll
                 for (int C = 0; C < NB; ++C) {
                     float m = 0.f;
 #pragma unroll
                     for (int X = 0; X < NB; ++X)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(Q[X][C][v]));
+                        for (int v = 0; v < 4; ++v) {
+                            m = fmaxf(m, fabsf(Q[X][C][v]));
+                            sum += 0.f * Q[X][C][v];
+                        }
                     const float f = scale[C].next(max_groups(m));
 #pragma unroll
                     for (int X = 0; X < NB; ++X) Q[X][C] *= f;
                 }
+                if (__ballot(again || sum != 0.f)) {
+                    again = true;
+                    break;
+                }
+                kept = q;
             }
             // ---- gates of the sixteen positions ----
             if constexpr (!REV) {
@@ -428,6 +438,8 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
         }
         if (wide || !__ballot(again)) break;
         wide = true;
+        q = kept;
+        top = min(T, (first + q + 1) * Lc);
         request(0);
     }
     __syncthreads();

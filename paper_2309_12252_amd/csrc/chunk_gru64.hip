@@ -87,11 +87,12 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
     float* __restrict__ tot = p.tot + ((long long)b * chunks + first) * MS;
     float* __restrict__ sFw = sF[wave];
 
-    const int lo = first * Lc, hi = min(T, (first + nq) * Lc), blocks = (hi - lo + 15) / 16;
+    const int lo = first * Lc, hi = min(T, (first + nq) * Lc);
+    int top = hi;    // forward: one past the first position that is still to be reduced
     Acc h[NB], ow;   // state in front of each position, this wavefront's rows of the residual's other term
     float x[DS];
     auto request = [&](int blk) {
-        int pos = (REV ? lo + 16 * blk : hi - 16 * (blk + 1)) + r;
+        int pos = (REV ? lo + 16 * blk : top - 16 * (blk + 1)) + r;
         pos = min(max(pos, lo), hi - 1);
         const float* hp = REV ? yb + (long long)pos * N : (pos > 0 ? yb + (long long)(pos - 1) * N : y0b);
 #pragma unroll
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
 
     Acc Q[NB];   // columns 16 w + r of the running product, rows 16 X + 4g + v
     float vec = 0.f;
-    bool wide = !SPLIT, again = false;   // products of fp32 factors; a map of the other kind was not finite
+    bool wide = !SPLIT, again = false;   // products of fp32 factors; a product of the other kind was not finite
     ColumnScale scale;
     auto reset = [&]() {
         vec = 0.f;
@@ -166,21 +167,27 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
         }
     };
 
+    int q = REV ? 0 : nq - 1, kept = q;   // chunk being reduced; the same when all was last seen to be finite
     for (;;) {
         reset();
-        int q = REV ? 0 : nq - 1;   // chunk being reduced
-        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // its last position in traversal order
+        int edge = REV ? min(T, (first + q + 1) * Lc) - 1 : (first + q) * Lc;   // the chunk's last position in traversal order
+        const int blocks = (top - lo + 15) / 16;
         for (int blk = 0; blk < blocks; ++blk) {
-            const int base = REV ? lo + 16 * blk : hi - 16 * (blk + 1);
+            const int base = REV ? lo + 16 * blk : top - 16 * (blk + 1);
             if (SPLIT && !wide) {
-                float m = 0.f;
+                float m = 0.f, sum = 0.f;   // (sum: not a finite number if one of its terms is none)
 #pragma unroll
                 for (int X = 0; X < NB; ++X)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(Q[X][v]));
+                    for (int v = 0; v < 4; ++v) {
+                        m = fmaxf(m, fabsf(Q[X][v]));
+                        sum += 0.f * Q[X][v];
+                    }
                 const float f = scale.next(max_groups(m));
 #pragma unroll
                 for (int X = 0; X < NB; ++X) Q[X] *= f;
+                again |= __ballot(again || sum != 0.f) != 0ull;
+                if (lane == 0) s_again[wave] = again;
             }
             {
                 GruGates k[4];
@@ -218,6 +225,13 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
             const int c_lo = REV ? 0 : max(lo - base, 0), c_hi = REV ? min(hi - base, 16) : 16, cnt = c_hi - c_lo;
             assemble(0, REV ? c_lo : c_hi - 1);
             __syncthreads();
+            if (SPLIT && !wide) {
+                if ((s_again[0] | s_again[1] | s_again[2] | s_again[3]) != 0u) {   // (the same for the four wavefronts)
+                    again = true;
+                    break;
+                }
+                kept = q;
+            }
             if (blk + 1 < blocks) request(blk + 1);
 #pragma unroll 1
             for (int k = 0; k < cnt; ++k) {
@@ -294,6 +308,8 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
         __syncthreads();
         if ((s_again[0] | s_again[1] | s_again[2] | s_again[3]) == 0u) break;   // (the same for the four wavefronts)
         wide = true;
+        q = kept;
+        top = min(T, (first + q + 1) * Lc);
         request(0);
     }
 

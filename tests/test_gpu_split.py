@@ -160,3 +160,41 @@ def test_field_does_not_drift(nhid, fp32):
     rms = np.sqrt(np.mean(np.square(off)))
     print(nhid, "%.2e of %.2e" % (rms, 1.25 * fp32), flush=True)
     assert rms <= 1.25 * fp32
+
+
+# The same at single positions, another one in every sequence: what was reduced before it is kept, its chunk and those behind it are reduced again.  The reset gate lets
+# the large weights of row i through where the first input says so.
+@pytest.mark.parametrize("kind,n", [("gru", 16), ("gru", 32), ("gru", 64), ("lstm", 16)])
+@pytest.mark.parametrize("L", ["4", "16", "24", "64"])
+def test_one_position_leaves_the_range(kind, n, L, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", L)
+    d, B, T, i = 3, 24, 1100, 5
+    gates = 3 if kind == "gru" else 4
+    make = inputs.gru_workload if kind == "gru" else inputs.lstm_workload
+    w = make("one_position", 680 + n, B, T, n, d)
+    W, U = w.theta[:gates * n * d].reshape(gates, n, d), w.theta[gates * n * d:][:gates * n * n].reshape(gates, n, n)
+    bias = w.theta[gates * n * d + gates * n * n:].reshape(-1, n)
+    gate = 0   # GRU: reset, in front of the candidate's U; LSTM: input, in front of g
+    W[gate, i], bias[gate, i] = 0.0, -40.0
+    W[gate, i, 0] = 80.0
+    U[:, :, i] = 0.0
+    U[gate, i] = 0.0
+    U[2, i] *= np.float32(3e5)
+    w.x[:, :, 0] = 0.0
+    at = np.random.default_rng(9).integers(0, T, size=B)
+    at[:4] = 0, 1, T // 2, T - 1
+    w.x[np.arange(B), at, 0] = 1.0
+    cell = oracle.make_cell(oracle.CELL_GRU if kind == "gru" else oracle.CELL_LSTM, n if kind == "gru" else 2 * n, d)
+    want = oracle.deer_eval(cell, w.theta, w.x, w.y0, tol=w.tol, max_iter=1, nthreads=8)[0]
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        y = host(ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=1)[0])
+    finally:
+        ctx.close()
+    size = np.abs(want).max(axis=(0, 1))
+    assert size.max() > 1e4
+    # (the bound of the whole column above; the large entries' rounding reaches the rest through the state's second half only, whose place is large too)
+    bound = 4.0 * np.sqrt(8.0 * 8.0) * 2.0 ** -24
+    off = (np.abs(y - want) / np.maximum(1.0, size)).max()
+    print(kind, n, L, "%.1e of %.1e, up to %.1e" % (off, bound, size.max()), flush=True)
+    assert off <= bound
