@@ -88,8 +88,8 @@ def test_field_on_a_coarse_grid(width, nhid):
 
 
 # Reduction by chunks: Jacobians whose entries lie beyond the range of fp16 (the chunk is reduced again with fp32 products), products that leave it within a
-# chunk, ordinary ones, and columns that lose 2^-10 a step.  One step from zero, every position against its own size: fp32 rounding grows by the conditioning of
-# up to eleven products (1e-7 each, some hundred times that where terms cancel).
+# chunk, ordinary ones, and ones next to nothing (whose digits the next test looks at).  One step from zero, every position against max(1, its own size): fp32 rounding
+# grows by the conditioning of up to eleven products (1e-7 each, some hundred times that where terms cancel).
 @pytest.mark.parametrize("n", [16, 32, 64, 27, 50])
 @pytest.mark.parametrize("scale,T", [(3.0e6, 5), (40.0, 11), (1.0, 300), (2.0 ** -9, 300)])
 @pytest.mark.parametrize("L", ["4", "8"])
@@ -198,3 +198,35 @@ def test_one_position_leaves_the_range(kind, n, L, monkeypatch):
     off = (np.abs(y - want) / np.maximum(1.0, size)).max()
     print(kind, n, L, "%.1e of %.1e, up to %.1e" % (off, bound, size.max()), flush=True)
     assert off <= bound
+
+
+# Products that fade, against their own size.  Without inputs and biases (but the one that keeps the old state) the cell is zero at zero, so one step from zero carries what y0 leaves at
+# the first position through the chunks' maps alone, and every position is that times a product of Jacobians.
+@pytest.mark.parametrize("kind,n,bias,T", [("gru", n, *b) for n in (16, 27, 32, 50, 64) for b in ((0.0, 150), (-1.0, 64), (-2.0, 40))] +
+                         [("lstm", n, *b) for n in (12, 16) for b in ((1.0, 150), (0.0, 150))])
+@pytest.mark.parametrize("L", ["4", "16", "32", "64"])
+def test_products_that_fade(kind, n, bias, T, L, monkeypatch):
+    monkeypatch.setenv("DEER_CHUNK_L", L)
+    d, B = 3, 3
+    w = (inputs.gru_workload if kind == "gru" else inputs.lstm_workload)("fade", 720 + n + T, B, T, n, d)
+    gates, ch = (3, n) if kind == "gru" else (4, 2 * n)
+    w.theta[:gates * n * d] = 0.0
+    b = w.theta[gates * n * d + gates * n * n:].reshape(-1, n)
+    b[:] = 0.0
+    b[1] = bias
+    w.y0 = (np.random.default_rng(n).standard_normal((B, ch)) * 0.5).astype(np.float32)
+    cell = oracle.make_cell(oracle.CELL_GRU if kind == "gru" else oracle.CELL_LSTM, ch, d)
+    want = oracle.deer_eval(cell, w.theta, w.x, w.y0, tol=w.tol, max_iter=1, nthreads=8)[0]
+    ctx = deer.context_for(w, device=DEV)
+    try:
+        y = host(ctx.eval(dev(w.theta, 0), dev(w.x, 0), dev(w.y0, 0), tol=w.tol, max_iter=1)[0])
+    finally:
+        ctx.close()
+    size = np.linalg.norm(want, axis=-1)
+    off = (np.linalg.norm(y - want, axis=-1) / size).max()
+    # fp32: a step rounds about eight times, as in the gradient's test.  Split: between two looks a column falls by 2^k from at least 2^3, and an entry of it is off by 2^-25; as
+    # many entries as channels, four times that for the products on the way.
+    k = np.log2((size[:, :-16] / size[:, 16:]).max())
+    bound = 4.0 * np.sqrt(8.0 * (T + 1)) * 2.0 ** -24 + 4.0 * np.sqrt(ch) * 2.0 ** (k - 28)
+    print(kind, n, bias, L, "%.1e of %.1e, down to %.1e, 2^%.0f in sixteen positions" % (off, bound, size.min(), -k), flush=True)
+    assert size.min() > 1e-34 and bound < 0.02 and off <= bound
