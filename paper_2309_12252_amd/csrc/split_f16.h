@@ -1,7 +1,9 @@
-// fp32 products on the fp16 matrix cores: every factor as the sum of two fp16 numbers.
+// fp32 products on the fp16 matrix cores: every factor as the sum of two fp16 numbers (Ootomo and Yokota, "Recovering single precision accuracy from
+// Tensor Cores while surpassing the FP32 theoretical peak performance", 2022).
 //
-// x = hi + lo + e with hi = fp16(x), lo = fp16(x - hi), |e| <= 2^-23 |x| while lo is a normal number, i.e. for |x| from 2^-2 to 65504: a
-// factor is scaled there by a power of two first.  A product is lo*hi + hi*lo + hi*hi, added in this order into one fp32
+// x = hi + lo + e with hi = fp16(x), lo = fp16(x - hi), |e| <= 2^-23 |x| while lo is a normal number, i.e. for |x| from 2^-2 to 65504: factors
+// are scaled there by powers of two first, by their largest entry (one 2^-k of that is known to 2^-38 of it at best).  J, the left factor of the reductions, is
+// not scaled: 2^-25 absolute.  A product is lo*hi + hi*lo + hi*hi, added in this order into one fp32
 // accumulator (lo*lo is below 2^-22 of the product).  Measured against 64 bits, 400 products 16 x K by K x 16 of normal and of
 // positive entries (2-norm): K = 32 8.0e-8 to 9.0e-8, K = 64 8.8e-8 to 9.6e-8; the fp32 matrix instructions give 1.03e-7 and
 // 1.43e-7 there (they round the sum after every four terms).  Without the scaling 1.2e-7 to 1.7e-6.
@@ -80,7 +82,7 @@ __device__ __forceinline__ Half8 split_small(Half8 hi) { return hi * (_Float16)(
 
 __device__ __forceinline__ F32x4 mfma16(Half8 a, Half8 b, F32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
-// Factors whose hi*hi sums are exact.  A matrix instruction drops what lies 24 bits or so below its largest product, and fp16 numbers that change slowly leave out
+// Factors whose hi*hi sums are exact (Ozaki, Ogita, Oishi and Rump, "Error-free transformations of matrix multiplication", 2012).  A matrix instruction drops what lies 24 bits or so below its largest product, and fp16 numbers that change slowly leave out
 // the same there at many points in a row: small (4e-8 of the sum) but the same error again and again, where rounded fp32 sums scatter.  So hi lies on a grid: weights
 // below 2^8 on multiples of 2^-6 (their eleven bits from 2^5 on), the other factor below 2^13 on multiples of 2^5; products are multiples of 1/2, and a sum below 2^23 is exact.
 // What hi leaves out comes in lo and rest: lo*lo and hi*rest count here.
