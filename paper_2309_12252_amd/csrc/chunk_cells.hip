@@ -15,8 +15,8 @@
 //
 // Bound: issue (matrix and vector instructions of a SIMD do not overlap).  Above 8 units the reduction of a Newton step has the factors of its
 // products split in two fp16 numbers, as in chunk_gru.hip (the dual scan has fp32 products, for the reason given there).  Measured, a Newton step (Jacobian kernel and
-// scan before / both launches now): LSTM u = 8, d = 4, 16 x 50,000 positions 710 / 180 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 290 us (reduction 304 with
-// fp32 products, now 227).
+// scan before / both launches now): LSTM u = 8, d = 4, 16 x 50,000 positions 710 / 211 us; LEM u = 16, d = 6, 32 x 17,984 positions 2,280 / 359 us (reduction 348 with
+// fp32 products, now 289).
 #include "chunk_common.h"
 #include "split_f16.h"
 

@@ -17,8 +17,8 @@
 // product split in two fp16 numbers (split_f16.h): a position costs 12 matrix instructions of 18 cycles and 120 vector instructions of 2.4 at n = 32 (3 and 40 at n =
 // 16) beside its share of the gates (60 fp32 matrix instructions for sixteen positions), in the place of 32 fp32 matrix instructions of 32 cycles and 72 (4 and 20).
 // Two wavefronts a SIMD (registers, LDS) issue in 71 % of the time.  Newton step, reduction alone, fp32 products before / now: n = 32, d = 8, 16 x 100,000
-// positions 1,128 / 737 us; n = 16, d = 6, 32 x 17,984 positions 88 / 72 us (the walk 210 and 36; the single-pass scan 2,650 and 240 for the whole step).  Assembling
-// the factor of the next position behind the products of this one: 785 and 74 (20 more vector instructions a position).
+// positions 1,150 / 757 us; n = 16, d = 6, 32 x 17,984 positions 101 / 91 us (the walk 212 and 43; the single-pass scan 2,650 and 240 for the whole step).  Assembling
+// the factor of the next position behind the products of this one: 6 and 3 % slower (20 more vector instructions a position).
 //
 // The split reduction (Newton steps): every column of the product has a power of two of its own, looked at before each sixteen positions (ColumnScale).  The
 // entries of J are split as they are: an absolute error of 2^-25 each, and nothing of one below that; a column that falls by 2^-k between two looks
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_totals_kernel(Chun
 // SPLIT (n = 32, not from far iterates): the products with the state and with the correction have their factors split in two fp16 numbers, a scale
 // to every column from its largest entry; U keeps all its digits for the state (a third part), which the trajectory sees, and its small entries theirs next to large ones (Split8Weights).
 // Bound: issue, one or two wavefronts a SIMD: a step takes 12 fp32 matrix instructions (the input's) and 42 of 18 cycles in the place of 108 fp32 ones.  16 x
-// 100,000 positions, d = 8: 318 us with fp32 products, now 210; 2-norm error of the trajectory against 64 bits 1.347e-7, now 1.309e-7.
+// 100,000 positions, d = 8: 314 us with fp32 products, now 212; 2-norm error of the trajectory against 64 bits 1.347e-7, now 1.309e-7.
 template <int N, int DS, bool REV, bool SPLIT>
 __global__ __launch_bounds__(256, N == 16 ? 3 : 2) void chunk_walk_kernel(ChunkParams p) {
     constexpr int NB = N / 16;

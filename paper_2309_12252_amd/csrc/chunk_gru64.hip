@@ -7,7 +7,7 @@
 // Bound: the reduction of a Newton step has its factors split in two fp16 numbers like that at n = 32 (chunk_gru.hip; wavefronts split the quarter that they
 // assemble): 24 matrix instructions of 18 cycles a wavefront and position and about 110 vector instructions of 2.4, then the barrier and the LDS
 // (one workgroup a compute unit at 5 x 9,973 positions: 2,000 cycles a position).  Far iterates and the dual scan, for the reason given
-// there: 64 fp32 matrix instructions of 32 cycles.  Reduction at 5 x 9,973 positions, d = 7, with fp32 products / now: Newton step 307 / 177 us.
+// there: 64 fp32 matrix instructions of 32 cycles.  Reduction at 5 x 9,973 positions, d = 7, with fp32 products / now: Newton step 303 / 185 us.
 #include "chunk_common.h"
 #include "split_f16.h"
 
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(256, 2) void chunk_totals64_kernel(ChunkParams p) {
 // cotangents) from the four wavefronts.
 // SPLIT (not from far iterates): the products with the state and the correction have their factors split in two fp16 numbers, as in the walk at n = 32
 // (chunk_gru.hip).  The wavefronts split their rows and hand the parts round; a column's scale needs the largest entry of all four, which takes
-// a second barrier a step.  5 x 9,973 positions, d = 7: 142 us with fp32 products (102 instructions of 32 cycles a step and wavefront), now 118
+// a second barrier a step.  5 x 9,973 positions, d = 7: 142 us with fp32 products (102 instructions of 32 cycles a step and wavefront), now 120
 // (6 of those and 42 of 18); 2-norm error of the trajectory against 64 bits 1.55e-7, now 1.48e-7 (n = 64).
 template <int DS, bool REV, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void chunk_walk64_kernel(ChunkParams p) {
